@@ -206,9 +206,9 @@ int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const uint16_t *
 
 /* vl_verify_batch for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid it.  Same arguments, same results.
- * Its job table and the list of candidates whose clashing pair is still to be found live in
- * a fixed device array inside the library (8 bytes per candidate, VL_STATIC_MAX_K of them:
- * 512 KB per GPU the library runs on, held until the process ends); the call allocates and
+ * Its job table and the candidates' smallest violations found so far live in
+ * a fixed device array inside the library (4 bytes per candidate, VL_STATIC_MAX_K of them, and a
+ * little more: 260 KB per GPU the library runs on, held until the process ends); the call allocates and
  * frees nothing, on the host or the device, and copies nothing from host memory: it only
  * enqueues kernels on `stream`.  Every call on a GPU uses that GPU's one array: calls that
  * overlap on one GPU (different streams, or threads) race; calls on one stream are ordered.
@@ -224,8 +224,8 @@ int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live, const uin
  * cand/out inside are [device].  Asynchronous on `stream`; calls on different streams may
  * overlap on the device.  Device memory owned by the library: per device and calling
  * stream (up to four streams at a time; a fifth takes over the least recently used slot
- * after waiting for the device) a copy of the job table and a list of the candidates whose
- * clashing pair has to be found.  Both grow on demand, which waits for the stream and
+ * after waiting for the device) a copy of the job table and a word per candidate (its
+ * smallest violation found so far).  Both grow on demand, which waits for the stream and
  * allocates; a call whose jobs are no more, and whose candidates in total are no more, than
  * in an earlier call on that stream allocates nothing, and when its job table is unchanged
  * it only enqueues kernels.  Errors: VL_E_NULL (a pointer missing), VL_E_ARG (a handle that

@@ -56,29 +56,35 @@ struct DevJob {
   vl_result *out;
   uint64_t ld;
   uint32_t K, rows, n_groups, unit_base, n_units, fast, transposed, direct;   // transposed: cand is [occurrence][candidate]
+  uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
   // direct: row-major, aligned, every row holds whole chunks up to its pitch, and a group of rows spans less than
   // 4 GB (its chunks are fetched with 32-bit offsets and no bounds)
 };
 
-__device__ inline uint32_t find_job(const DevJob *jobs, uint32_t n_jobs, uint32_t unit) {
-  uint32_t lo = 0, hi = n_jobs;
-  while (hi - lo > 1) {
-    uint32_t mid = (lo + hi) >> 1;
-    if (jobs[mid].unit_base <= unit) lo = mid; else hi = mid;
+// What the workgroups of one verification share.  Everything is zero before the walk and left
+// zero by it, so that no launch is needed to clear it.
+struct Board {
+  uint32_t *arrived;   // per group of candidate rows: tiles that have reported
+  uint32_t *keys;      // per candidate row: ~(smallest violation key so far), 0 = none
+};
+
+// The job of unit (or group) x, whose first unit (group) is the field `base` of its entry: 64
+// probes at a time, one per lane (two dependent reads for up to 4,096 jobs; a binary search took
+// eight for 256).
+__device__ inline uint32_t find_job(const DevJob *jobs, uint32_t n_jobs, uint32_t x, uint32_t DevJob::*base) {
+  uint32_t lo = 0, len = n_jobs;
+  while (len > 1) {
+    const uint32_t step = (len + 63u) / 64u, off = __lane_id() * step;
+    const uint32_t n = (uint32_t)__popcll(__ballot(off < len && jobs[lo + off].*base <= x));
+    lo += (n - 1u) * step;   // bases ascend, and the first probe never lies above x
+    len = min(step, len - (n - 1u) * step);
   }
   return lo;
 }
 
 // register of occurrence o in candidate k, in either layout
-__device__ inline uint32_t cand_at(const DevJob &J, uint32_t k, uint32_t o) {
+template <class Job> __device__ inline uint32_t cand_at(const Job &J, uint32_t k, uint32_t o) {
   return J.transposed ? J.cand[(uint64_t)o * J.ld + k] : J.cand[(uint64_t)k * J.ld + o];
-}
-
-__global__ void k_init(const DevJob *__restrict__ jobs, uint2 *__restrict__ work) {
-  const DevJob &J = jobs[blockIdx.y];
-  uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < J.K) J.out[k].status = kKeyOk;
-  if ((blockIdx.x | blockIdx.y | threadIdx.x) == 0) work[0].x = 0;   // the list k_finalize fills starts empty
 }
 
 // ---- the candidate walk -----------------------------------------------------------------
@@ -285,15 +291,42 @@ __device__ inline bool unrealizable(const DevMir VL_GLOBAL &m, uint32_t attr, ui
   return bad;
 }
 
+// Turns the winning key of a candidate row (one per lane, `in` for the lanes that have one) into
+// its result record.  Safety results get their pair from k_resolve.
+__device__ inline void finish_row(const DevJob VL_GLOBAL &J, uint32_t k, uint32_t key) {
+  const DevMir VL_GLOBAL &m = *as_global(J.mir);
+  const DevLive VL_GLOBAL &L = *as_global(J.live);
+  vl_result r = {VL_STATUS_OK, 0, 0, 0};
+  if (key != kKeyOk) {
+    const uint32_t pos = key & kKeyPos;
+    switch (key >> 28) {
+      case 0: {
+        const uint32_t v = m.occ_vreg[pos];
+        r = {VL_STATUS_CONSISTENCY, pos, v, L.first[v]};
+        if (m.occ_src) r = {VL_STATUS_CONSISTENCY, m.occ_src[pos], m.val_vreg[v], m.occ_src[L.first[v]]};   // in the caller's numbering
+        break;
+      }
+      case 1: {
+        const uint32_t v = m.occ_vreg[pos];
+        r = {VL_STATUS_REALIZABILITY, pos, v, bad_bits(m, m.vattr[v], cand_at(J, k, pos))};
+        if (m.occ_src) { r.where = m.occ_src[pos]; r.a = m.val_vreg[v]; }
+        break;
+      }
+      default: r = {VL_STATUS_SAFETY, pos, kNone, kNone}; break;
+    }
+  }
+  J.out[k] = r;
+}
+
 template <uint32_t kRingStride, bool kT, bool kDirect>
-__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_walk(const DevJob *__restrict__ jobs, uint32_t n_jobs) {
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_walk(const DevJob *__restrict__ jobs, uint32_t n_jobs, const Board board) {
   // Workgroups go to the eight dies of the device in turn, each die with an L2 of its own.
   // Inside every 16 consecutive workgroup indices, units 2x and 2x + 1 are given to indices
   // x and x + 8: the two candidate groups of one tile (neighbouring units when a job has two
   // groups) then run on the same die and read the tile's stream records through one L2.
   uint32_t unit = blockIdx.x;
   if ((unit | 15u) < gridDim.x) unit = (unit & ~15u) | ((unit & 7u) << 1) | ((unit >> 3) & 1u);
-  const DevJob VL_GLOBAL &J = as_global(jobs)[find_job(jobs, n_jobs, unit)];
+  const DevJob VL_GLOBAL &J = as_global(jobs)[find_job(jobs, n_jobs, unit, &DevJob::unit_base)];
   const DevMir VL_GLOBAL &m = *as_global(J.mir);
   const DevLive VL_GLOBAL &L = *as_global(J.live);
   // arrays of the kernel and of its analysis, as global pointers
@@ -698,48 +731,25 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
   __syncthreads();
   if (active && key != kKeyOk) atomicMin(&vl_lds[w.keys + w.lane], key);
   __syncthreads();
-  if (w.tid < w.nrows && vl_lds[w.keys + w.tid] != kKeyOk) atomicMin(&J.out[row0 + w.tid].status, vl_lds[w.keys + w.tid]);
-}
-
-// Turns the winning key of each candidate into its result record.  Safety results
-// get their pair from k_resolve: their (job, candidate) go onto the list work[1..], whose
-// length is work[0].x (one atomic per wavefront; the order of the list does not matter).
-__global__ void k_finalize(const DevJob *__restrict__ jobs, uint2 *__restrict__ work) {
-  const DevJob &J = jobs[blockIdx.y];
-  uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= J.K) return;
-  const DevMir VL_GLOBAL &m = *as_global(J.mir);
-  const DevLive VL_GLOBAL &L = *as_global(J.live);
-  const uint32_t key = J.out[k].status;
-  vl_result r = {VL_STATUS_OK, 0, 0, 0};
-  if (key != kKeyOk) {
-    const uint32_t pos = key & kKeyPos;
-    switch (key >> 28) {
-      case 0: {
-        const uint32_t v = m.occ_vreg[pos];
-        r = {VL_STATUS_CONSISTENCY, pos, v, L.first[v]};
-        if (m.occ_src) r = {VL_STATUS_CONSISTENCY, m.occ_src[pos], m.val_vreg[v], m.occ_src[L.first[v]]};   // in the caller's numbering
-        break;
-      }
-      case 1: {
-        const uint32_t v = m.occ_vreg[pos];
-        r = {VL_STATUS_REALIZABILITY, pos, v, bad_bits(m, m.vattr[v], cand_at(J, k, pos))};
-        if (m.occ_src) { r.where = m.occ_src[pos]; r.a = m.val_vreg[v]; }
-        break;
-      }
-      default: r = {VL_STATUS_SAFETY, pos, kNone, kNone}; break;
-    }
+  // The tile reports to the group's board; the tile that reports last turns the group's keys into
+  // results (one wavefront, a row per lane).  Keys and counter are only touched by atomics, which
+  // the dies of the device see in one order; the returned values keep a wavefront's own in order.
+  if (w.tid >= 64) return;
+  uint32_t found = w.tid < w.nrows ? vl_lds[w.keys + w.tid] : kKeyOk;
+  const uint32_t T = L.T;
+  if (T > 1) {
+    uint32_t *const my_key = board.keys + J.row_base + row0 + w.tid;
+    uint32_t before = 0;
+    if (found != kKeyOk) before = __hip_atomic_fetch_max(my_key, ~found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(before) : : "memory");
+    uint32_t n_before = 0;
+    uint32_t *const counter = board.arrived + J.group_base + group;
+    if (w.tid == 0) n_before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(n_before) + 1u != T) return;
+    if (w.tid < w.nrows) found = ~__hip_atomic_exchange(my_key, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w.tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  J.out[k] = r;
-  const bool listed = r.status == VL_STATUS_SAFETY;
-  const uint64_t peers = __ballot(listed);
-  if (peers) {
-    const uint32_t lane = __lane_id(), leader = (uint32_t)__ffsll((unsigned long long)peers) - 1u;
-    uint32_t at = 0;
-    if (lane == leader) at = atomicAdd(&work[0].x, (uint32_t)__popcll(peers));
-    at = __shfl(at, leader);
-    if (listed) work[1 + at + __popcll(peers & ((1ull << lane) - 1ull))] = make_uint2(blockIdx.y, k);
-  }
+  if (w.tid < w.nrows) finish_row(J, row0 + w.tid, found);
 }
 
 // For a candidate whose first violation is a register clash at instruction i: the
@@ -747,48 +757,60 @@ __global__ void k_finalize(const DevJob *__restrict__ jobs, uint2 *__restrict__ 
 // with overlapping ranges.  At the first clashing instruction every clashing pair contains a
 // vreg that the instruction defines, so only pairs (definition, anything in P(i)) are
 // examined.  P(i) is rebuilt as a bitset in LDS the way the walk builds occupancy, but over
-// vregs instead of registers (flip_members_of_p).  The workgroups share out the list of
-// such candidates that k_finalize wrote.
-__global__ __launch_bounds__(256) void k_resolve(const DevJob *__restrict__ jobs, const uint2 *__restrict__ work) {
+// vregs instead of registers (flip_members_of_p); its members, some tens, are then listed so that
+// each gets a lane (a lane per vreg of the program took most of the kernel's time: 15,000 vregs
+// are 117 turns of 128 threads).  The workgroups of a group of rows share out the rows that
+// failed on safety.
+constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
+constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
+__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, uint32_t per_group) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
-  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], all_v[kMaxOperands], nd;
-  const uint32_t n_listed = work[0].x;
-  for (uint32_t at = blockIdx.x; at < n_listed; at += gridDim.x) {
-    const uint2 item = work[1 + at];
-    const DevJob &J = jobs[item.x];
-    const uint32_t k = item.y;
+  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], nd, members[kResolveMembers], n_members;
+  const uint32_t global_group = blockIdx.x / per_group, mine_first = blockIdx.x % per_group;
+  const DevJob VL_GLOBAL &J = as_global(jobs)[find_job(jobs, n_jobs, global_group, &DevJob::group_base)];
+  const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
+  const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
+  vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
+  // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
+  const uint64_t failed = __ballot(lane < nrows && out[min(lane, nrows - 1u)].status == VL_STATUS_SAFETY);
+  uint32_t rank = 0;
+  for (uint64_t todo = failed; todo; todo &= todo - 1, ++rank) {
+    if (rank % per_group != mine_first) continue;
+    const uint32_t k = row0 + (uint32_t)__builtin_ctzll(todo);
     const DevMir VL_GLOBAL &m = *as_global(J.mir);
     const DevLive VL_GLOBAL &L = *as_global(J.live);
-    const uint32_t i = J.out[k].where;
-    for (uint32_t x = threadIdx.x; x < m.W; x += blockDim.x) in_p[x] = 0;
+    const uint32_t i = out[k - row0].where;
+    for (uint32_t x = tid; x < m.W; x += kResolveThreads) in_p[x] = 0;
     // the vregs the instruction writes (each once) and their registers: one operand per lane
     const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo;
-    uint32_t my_v = kNone, my_p = 0;
-    if (threadIdx.x < n_ops && (m.occ_flags[o_lo + threadIdx.x] & VL_OCC_DEF)) {
-      my_v = m.occ_vreg[o_lo + threadIdx.x];
-      my_p = cand_at(J, k, L.first[my_v]);
-    }
-    if (threadIdx.x < kMaxOperands) all_v[threadIdx.x] = my_v;
-    if (threadIdx.x == 0) { best = ~0ull; nd = 0; }
-    __syncthreads();
-    if (my_v != kNone) {
-      bool seen = false;
-      for (uint32_t t = 0; t < threadIdx.x; ++t) seen |= all_v[t] == my_v;
-      if (!seen) {
-        const uint32_t slot = atomicAdd(&nd, 1u);
-        dv[slot] = my_v;
-        dp[slot] = my_p;
+    if (tid < 64) {
+      const uint32_t my_v = tid < n_ops && (m.occ_flags[o_lo + tid] & VL_OCC_DEF) ? m.occ_vreg[o_lo + tid] : kNone;
+      bool seen = my_v == kNone;
+      for (uint32_t t = 0; t < n_ops; ++t) {
+        const uint32_t other = __builtin_amdgcn_readlane(my_v, t);   // (every lane takes part)
+        seen |= (t < tid) & (other == my_v);
       }
+      const uint64_t fresh = __ballot(!seen);
+      if (!seen) {
+        const uint32_t slot = (uint32_t)__popcll(fresh & ((1ull << tid) - 1ull));
+        dv[slot] = my_v;
+        dp[slot] = cand_at(J, k, L.first[my_v]);
+      }
+      if (tid == 0) { best = ~0ull; nd = (uint32_t)__popcll(fresh); n_members = 0; }
     }
     __syncthreads();
-    flip_members_of_p(m, L, i, in_p, threadIdx.x, blockDim.x);
+    flip_members_of_p(m, L, i, in_p, tid, kResolveThreads);
+    __syncthreads();
+    for (uint32_t x = tid; x < m.W; x += kResolveThreads) {
+      uint32_t bits = in_p[x];
+      if (!bits) continue;
+      uint32_t at = atomicAdd(&n_members, (uint32_t)__popc(bits));
+      for (; bits && at < kResolveMembers; bits &= bits - 1) members[at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
+    }
     __syncthreads();
     unsigned long long mine = ~0ull;
-    // one vreg per lane (members of P(i) have neighbouring numbers: a lane that walked the
-    // bits of a word would fetch their registers one after the other)
-    for (uint32_t x = threadIdx.x; x < m.V; x += blockDim.x) {
-      if (!((in_p[x >> 5] >> (x & 31)) & 1u)) continue;
+    auto examine = [&](uint32_t x) {
       const uint32_t ax = m.vattr[x], px = cand_at(J, k, L.first[x]), wx = attr_width(ax);
       for (uint32_t t = 0; t < nd; ++t) {
         const uint32_t d = dv[t];
@@ -803,14 +825,20 @@ __global__ __launch_bounds__(256) void k_resolve(const DevJob *__restrict__ jobs
           mine = pr < mine ? pr : mine;
         }
       }
+    };
+    if (n_members <= kResolveMembers) {
+      for (uint32_t x = tid; x < n_members; x += kResolveThreads) examine(members[x]);
+    } else {
+      for (uint32_t x = tid; x < m.V; x += kResolveThreads)
+        if ((in_p[x >> 5] >> (x & 31)) & 1u) examine(x);
     }
     if (mine != ~0ull) atomicMin(&best, mine);
     __syncthreads();
-    if (threadIdx.x == 0) {
-      J.out[k].a = (uint32_t)(best >> 32);
-      J.out[k].b = (uint32_t)best;
+    if (tid == 0) {
+      out[k - row0].a = (uint32_t)(best >> 32);
+      out[k - row0].b = (uint32_t)best;
     }
-    __syncthreads();   // the shared arrays are reused by the next listed candidate
+    __syncthreads();   // the shared arrays are reused by the next row
   }
 }
 
@@ -823,14 +851,14 @@ struct Slot {
   DevJob *dev = nullptr;
   DevJob *host = nullptr;   // pinned
   uint32_t cap = 0, n_valid = 0;
-  uint2 *work = nullptr;    // [0].x = length, then (job, candidate) of the clashes to resolve
-  uint64_t work_cap = 0;    // candidates the list has room for
+  uint32_t *board = nullptr;                 // kHeadWords (the first: Launch::finished), Board::arrived, Board::keys; zero between calls
+  uint64_t groups_cap = 0, rows_cap = 0;     // what the board has room for
   hipEvent_t copied = nullptr;
   uint64_t tick = 0;
 };
 constexpr int kSlots = 4;
-constexpr uint64_t kResolveGroups = 4096;   // workgroups that share out the clashes to resolve
-constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
+constexpr uint32_t kHeadWords = 64;
+constexpr uint64_t kResolveGroups = 4096;   // workgroups that share out the clashes to resolve, about
 struct Scratch {
   std::mutex mu;
   Slot slot[kSlots];
@@ -852,8 +880,9 @@ extern "C" int32_t vl_verify_time_next(void *start, void *stop) {
 namespace {
 struct Launch {
   DevJob *dev = nullptr;
-  uint2 *work = nullptr;
-  uint64_t total_rows = 0;
+  Board board = {};
+  uint32_t *finished = nullptr;   // counter of the reductions, zero between calls
+  uint64_t total_rows = 0, groups = 0;
   uint32_t units = 0, maxK = 0, max_words = 0, max_w = 1, max_rows = 0;
   bool all_direct = true;   // every job can be staged with 32-bit offsets and without bounds (DevJob::direct)
 };
@@ -890,6 +919,10 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   }
   const uint32_t last = u.K - (d.n_groups - 1) * d.rows;
   d.unit_base = out.units;
+  if (out.total_rows + u.K > 0xFFFFFFFFull) return VL_E_SHAPE;
+  d.row_base = (uint32_t)out.total_rows;
+  d.group_base = (uint32_t)out.groups;
+  out.groups += d.n_groups;
   d.n_units = d.n_groups * u.live->h.T;
   out.units += d.n_units;
   out.maxK = std::max(out.maxK, u.K);
@@ -903,6 +936,10 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
 // Validates the jobs, lays out the device job table and makes sure the device copy is
 // current (the copy is skipped when the table is the one the stream's slot already holds).
 // Called with the device's scratch locked.
+__global__ void k_clear_board(uint32_t *p, uint64_t n) {
+  for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (uint64_t)gridDim.x * blockDim.x) p[x] = 0;
+}
+
 int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Scratch &sc, Launch &out, bool transposed = false,
                      bool results_only = false) {
   // the calling stream's slot, else a free one, else the least recently used one (whose
@@ -936,7 +973,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
     for (uint32_t j = 0; j < n_jobs && same; ++j) same = s.host[j].out == jobs[j].out && s.host[j].K == jobs[j].K;
     if (same) {
       out.dev = s.dev;
-      out.work = s.work;
+      out.finished = s.board;
       return VL_OK;
     }
   }
@@ -962,66 +999,81 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
     VL_HIP(hipEventRecord(s.copied, stream));
     s.n_valid = n_jobs;
   }
-  if (s.work_cap < out.total_rows) {
-    VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still read the old list
-    if (s.work) (void)hipFree(s.work);
-    s.work = nullptr; s.work_cap = 0;
-    const uint64_t cap = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2);
-    VL_HIP(hipMalloc((void **)&s.work, (size_t)(cap + 1) * sizeof(uint2)));
-    s.work_cap = cap;
+  if (!s.board || (!results_only && (s.groups_cap < out.groups || s.rows_cap < out.total_rows))) {
+    VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
+    if (s.board) (void)hipFree(s.board);
+    s.board = nullptr; s.groups_cap = s.rows_cap = 0;
+    const uint64_t rows = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2), groups = std::max<uint64_t>(4096, out.groups + out.groups / 2);
+    VL_HIP(hipMalloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
+    k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
+    s.rows_cap = rows; s.groups_cap = groups;
   }
   out.dev = s.dev;
-  out.work = s.work;
+  out.finished = s.board;
+  out.board = Board{s.board + kHeadWords, s.board + kHeadWords + s.groups_cap};
   return VL_OK;
 }
 
 // ---- regeneration-loop reductions ----------------------------------------------------
-// one workgroup per job: histogram of the statuses and the first accepted candidate
-__global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jobs, vl_summary *__restrict__ summaries) {
-  const DevJob &J = jobs[blockIdx.x];
-  __shared__ uint32_t hist[4], first;
-  if (threadIdx.x < 4) hist[threadIdx.x] = 0;
-  if (threadIdx.x == 0) first = J.K;
-  __syncthreads();
-  uint32_t mine[4] = {0, 0, 0, 0}, my_first = J.K;
-  for (uint32_t k = threadIdx.x; k < J.K; k += blockDim.x) {
-    const uint32_t st = J.out[k].status & 3u;
-    mine[0] += st == 0; mine[1] += st == 1; mine[2] += st == 2; mine[3] += st == 3;
-    if (st == VL_STATUS_OK) my_first = min(my_first, k);
+// One wavefront per job: histogram of the statuses and the first accepted candidate.  With
+// `stats`, the workgroup that finishes last also totals the jobs' summaries (every field is
+// written, nothing needs clearing beforehand; `finished` is left zero).  The summaries reach it
+// through stores and loads that all dies see (agent scope).
+__global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jobs, uint32_t n_jobs, vl_summary *__restrict__ summaries,
+                                                   vl_loop_stats *stats, uint32_t *finished) {
+  const uint32_t lane = threadIdx.x & 63u, j = blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (j < n_jobs) {
+    const DevJob &J = jobs[j];
+    uint32_t hist[4] = {0, 0, 0, 0}, first = J.K;
+    for (uint32_t k0 = 0; k0 < J.K; k0 += 64) {
+      const bool in = k0 + lane < J.K;
+      const uint32_t st = in ? J.out[k0 + lane].status & 3u : 4u;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+        const uint64_t with = __ballot(st == t);
+        hist[t] += (uint32_t)__popcll(with);
+        if (t == VL_STATUS_OK && with && first == J.K) first = k0 + (uint32_t)__builtin_ctzll(with);
+      }
+    }
+    const uint32_t word = lane == 0 ? first : lane == 1 ? (first < J.K ? 1u : 0u) : lane == 2 ? hist[0] : lane == 3 ? hist[1] : lane == 4 ? hist[2] : hist[3];
+    static_assert(sizeof(vl_summary) == 24, "six words");
+    if (lane < 6) __hip_atomic_store((uint32_t *)(summaries + j) + lane, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  for (int t = 0; t < 4; ++t)
-    if (mine[t]) atomicAdd(&hist[t], mine[t]);
-  if (my_first != J.K) atomicMin(&first, my_first);
+  if (!stats) return;
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __shared__ uint32_t last;
+  __shared__ unsigned long long part[4][7];   // per wavefront: passed, most tries, sum of tries, histogram
   __syncthreads();
-  if (threadIdx.x == 0)
-    summaries[blockIdx.x] = vl_summary{first, first < J.K ? 1u : 0u, {hist[0], hist[1], hist[2], hist[3]}};
-}
-
-// one workgroup: the totals over the jobs' summaries (every field is written, nothing needs
-// clearing beforehand)
-__global__ __launch_bounds__(256) void k_loop_stats(const DevJob *__restrict__ jobs, uint32_t n_jobs,
-                                                    const vl_summary *__restrict__ summaries, vl_loop_stats *stats) {
-  __shared__ unsigned long long acc[5];   // sum of tries, histogram
-  __shared__ uint32_t n_passed, max_tries;
-  if (threadIdx.x < 5) acc[threadIdx.x] = 0;
-  if (threadIdx.x == 0) { n_passed = 0; max_tries = 0; }
+  if (threadIdx.x == 0) last = __hip_atomic_fetch_add(finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
   __syncthreads();
-  unsigned long long mine[5] = {0, 0, 0, 0, 0};
-  uint32_t my_passed = 0, my_max = 0;
-  for (uint32_t j = threadIdx.x; j < n_jobs; j += blockDim.x) {
-    const vl_summary s = summaries[j];
-    const uint32_t tries = s.passed ? s.first_ok + 1 : jobs[j].K;
-    my_passed += s.passed;
-    my_max = max(my_max, tries);
-    mine[0] += tries;
-    for (int t = 0; t < 4; ++t) mine[1 + t] += s.hist[t];
+  if (!last) return;
+  unsigned long long mine[7] = {0, 0, 0, 0, 0, 0, 0};
+  for (uint32_t x = threadIdx.x; x < n_jobs; x += 256) {
+    uint32_t f[6];
+#pragma unroll
+    for (uint32_t t = 0; t < 6; ++t) f[t] = __hip_atomic_load((uint32_t *)(summaries + x) + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t tries = f[1] ? f[0] + 1u : jobs[x].K;
+    mine[0] += f[1];
+    mine[1] = max(mine[1], (unsigned long long)tries);
+    mine[2] += tries;
+    for (uint32_t t = 0; t < 4; ++t) mine[3 + t] += f[2 + t];
   }
-  for (int t = 0; t < 5; ++t)
-    if (mine[t]) atomicAdd(&acc[t], mine[t]);
-  if (my_passed) atomicAdd(&n_passed, my_passed);
-  if (my_max) atomicMax(&max_tries, my_max);
+  for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+    for (uint32_t t = 0; t < 7; ++t) {
+      const unsigned long long y = __shfl_xor(mine[t], d, 64);
+      mine[t] = t == 1 ? max(mine[t], y) : mine[t] + y;
+    }
+  if (lane == 0)
+    for (uint32_t t = 0; t < 7; ++t) part[threadIdx.x >> 6][t] = mine[t];
   __syncthreads();
-  if (threadIdx.x == 0) *stats = vl_loop_stats{n_passed, max_tries, acc[0], {acc[1], acc[2], acc[3], acc[4]}};
+  if (threadIdx.x == 0) {
+    unsigned long long s[7];
+    for (uint32_t t = 0; t < 7; ++t)
+      s[t] = t == 1 ? max(max(part[0][t], part[1][t]), max(part[2][t], part[3][t])) : part[0][t] + part[1][t] + part[2][t] + part[3][t];
+    *stats = vl_loop_stats{(uint32_t)s[0], (uint32_t)s[1], s[2], {s[3], s[4], s[5], s[6]}};
+    __hip_atomic_store(finished, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 }  // namespace
 
@@ -1038,35 +1090,32 @@ extern "C" int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_su
   Launch L;
   const int32_t rc = prepare_jobs(jobs, n_jobs, stream, s, L, false, true);
   if (rc != VL_OK) return rc;
-  k_summarize<<<n_jobs, 256, 0, stream>>>(L.dev, summaries);
-  if (stats) k_loop_stats<<<1, 256, 0, stream>>>(L.dev, n_jobs, summaries, stats);
+  k_summarize<<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, summaries, stats, L.finished);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
 
 namespace {
-// k_init, the walk, k_finalize and k_resolve over the job table L.dev with the list L.work
+// the walk and the pair search over the job table L.dev with the board L.board
 int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool transposed) {
   const bool narrow = L.max_rows <= kPitchNarrow;   // every group of every job fits the narrow ring
   const size_t lds = (size_t)L.max_words * 64 * 4 + 64 * 4 + 1024 + (size_t)kRing * (narrow ? kPitchNarrow : kPitchWide) * 2;
-  k_init<<<dim3((L.maxK + 255) / 256, n_jobs), 256, 0, stream>>>(L.dev, L.work);
   if (g_time_start) VL_HIP(hipEventRecord(g_time_start, stream));
+  auto walk = [&](auto kernel) { kernel<<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs, L.board); };
   if (transposed) {
-    if (narrow) k_walk<kPitchNarrow, true, false><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
-    else k_walk<kPitchWide, true, false><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
+    if (narrow) walk(k_walk<kPitchNarrow, true, false>);
+    else walk(k_walk<kPitchWide, true, false>);
+  } else if (L.all_direct) {
+    if (narrow) walk(k_walk<kPitchNarrow, false, true>);
+    else walk(k_walk<kPitchWide, false, true>);
   } else {
-    if (L.all_direct) {
-      if (narrow) k_walk<kPitchNarrow, false, true><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
-      else k_walk<kPitchWide, false, true><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
-    } else {
-      if (narrow) k_walk<kPitchNarrow, false, false><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
-      else k_walk<kPitchWide, false, false><<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs);
-    }
+    if (narrow) walk(k_walk<kPitchNarrow, false, false>);
+    else walk(k_walk<kPitchWide, false, false>);
   }
   if (g_time_stop) VL_HIP(hipEventRecord(g_time_stop, stream));
   g_time_start = g_time_stop = nullptr;
-  k_finalize<<<dim3((L.maxK + 255) / 256, n_jobs), 256, 0, stream>>>(L.dev, L.work);
-  k_resolve<<<(uint32_t)std::min<uint64_t>(L.total_rows, kResolveGroups), kResolveThreads, (size_t)L.max_w * 4, stream>>>(L.dev, L.work);
+  const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
+  k_resolve<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(L.dev, n_jobs, per_group);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
@@ -1101,14 +1150,14 @@ extern "C" int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const
 }
 
 // ---- the entry point that allocates nothing ----------------------------------------------
-// Its job table (one job) and its list of candidates to resolve live in a file-scope device
-// array instead of memory the library allocates.  The array's name is only a host-side handle:
+// Its job table (one job) and its board live in a file-scope device array instead of memory the library allocates.  The array's name is only a host-side handle:
 // its device address is looked up once per device and kept.
 namespace {
 constexpr uint32_t kStaticMaxK = VL_STATIC_MAX_K;
-struct StaticScratch {
+struct StaticScratch {   // zero at load time, and between calls
   DevJob job;
-  uint2 work[kStaticMaxK + 1];
+  uint32_t arrived[kStaticMaxK / 64 + 1];
+  uint32_t keys[kStaticMaxK];
 };
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[sizeof(StaticScratch)];
@@ -1143,7 +1192,7 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
     sc = (StaticScratch *)g_static_ptr[device];
   }
   L.dev = &sc->job;
-  L.work = sc->work;
+  L.board = Board{sc->arrived, sc->keys};
   k_put_job<<<1, 1, 0, stream>>>(d, &sc->job);
   return launch_all(L, 1, stream, false);
 }
