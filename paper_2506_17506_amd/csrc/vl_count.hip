@@ -249,7 +249,6 @@ constexpr uint32_t kPairsPerWave = 256, kPairsPerGroup = 4 * kPairsPerWave, kSaf
 constexpr uint32_t kPairsAtOnce = 16;   // the pair list of a program is padded with empty pairs to a multiple of this
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-#define VL_CONSTANT __attribute__((address_space(4)))
 __device__ inline u16x2 both(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
 template <bool kBig>
 __global__ __launch_bounds__(256) void k_cnt_safe(const DevCountJob *__restrict__ jobs) {

@@ -11,6 +11,7 @@
 // Device arrays reached through the structures below are declared as pointers into global
 // memory, so that the compiler emits global / scalar loads for them rather than flat ones.
 #define VL_GLOBAL __attribute__((address_space(1)))
+#define VL_CONSTANT __attribute__((address_space(4)))   // read-only, by scalar loads
 
 namespace vl {
 
@@ -211,14 +212,29 @@ __device__ inline void flip_members_of_p(const DevMir VL_GLOBAL &m, const DevLiv
   auto flip_vreg = [&](uint32_t v) {   // records carry their vreg in x (above the ring slot)
     __hip_atomic_fetch_xor(&in_p[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
-  if (tile > 0)
-    for (uint32_t s = L.seed_off[tile] + tid; s < L.seed_off[tile + 1]; s += n_threads) flip_vreg(L.seeds[s].x >> 8);
   const uint32_t item = i + m.instr_blk[i] + 1;   // boundary items come before their block's instructions
-  const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1];
-  for (uint32_t e = L.tile_range[2 * tile] + tid; e < e_end; e += n_threads) {
+  const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1], e_first = L.tile_range[2 * tile];
+  const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first;
+  // the first word of a record holds the vreg; eight reads in flight per thread (a tile of 512
+  // instructions has some 800 events, which 128 threads then fetch in one round of waiting)
+  auto flip_all = [&](const u32x4 VL_GLOBAL *records, uint32_t from, uint32_t to) {
+    for (uint32_t e0 = from + tid; e0 < to; e0 += 8 * n_threads) {
+      uint32_t x[8];
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u) {
+        const uint32_t e = e0 + u * n_threads;
+        x[u] = e < to ? records[e].x : 0u;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u)
+        if (e0 + u * n_threads < to) flip_vreg(x[u] >> 8);
+    }
+  };
+  flip_all(L.seeds, s_first, s_end);
+  flip_all(L.plan, e_first, e_own);
+  for (uint32_t e = e_own + tid; e < e_end; e += n_threads) {
     const u32x4 r = L.plan[e];
-    if (e >= e_own && (r.w & kEvtPost)) continue;
-    flip_vreg(r.x >> 8);
+    if (!(r.w & kEvtPost)) flip_vreg(r.x >> 8);
   }
 }
 }  // namespace vl

@@ -293,7 +293,7 @@ __device__ inline bool unrealizable(const DevMir VL_GLOBAL &m, uint32_t attr, ui
 
 // Turns the winning key of a candidate row (one per lane, `in` for the lanes that have one) into
 // its result record.  Safety results get their pair from k_resolve.
-__device__ inline void finish_row(const DevJob VL_GLOBAL &J, uint32_t k, uint32_t key) {
+__device__ inline void finish_row(const DevJob &J, uint32_t k, uint32_t key) {
   const DevMir VL_GLOBAL &m = *as_global(J.mir);
   const DevLive VL_GLOBAL &L = *as_global(J.live);
   vl_result r = {VL_STATUS_OK, 0, 0, 0};
@@ -318,15 +318,18 @@ __device__ inline void finish_row(const DevJob VL_GLOBAL &J, uint32_t k, uint32_
   J.out[k] = r;
 }
 
-template <uint32_t kRingStride, bool kT, bool kDirect>
-__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_walk(const DevJob *__restrict__ jobs, uint32_t n_jobs, const Board board) {
+// kOne: the call has one job, which comes as a kernel argument (no table to upload, and a level of
+// dependent reads less at the start of every workgroup).
+template <uint32_t kRingStride, bool kT, bool kDirect, bool kOne>
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_walk(const DevJob one, const DevJob *__restrict__ jobs, uint32_t n_jobs, const Board board) {
   // Workgroups go to the eight dies of the device in turn, each die with an L2 of its own.
   // Inside every 16 consecutive workgroup indices, units 2x and 2x + 1 are given to indices
   // x and x + 8: the two candidate groups of one tile (neighbouring units when a job has two
   // groups) then run on the same die and read the tile's stream records through one L2.
   uint32_t unit = blockIdx.x;
   if ((unit | 15u) < gridDim.x) unit = (unit & ~15u) | ((unit & 7u) << 1) | ((unit >> 3) & 1u);
-  const DevJob VL_GLOBAL &J = as_global(jobs)[find_job(jobs, n_jobs, unit, &DevJob::unit_base)];
+  const uint32_t job = kOne ? 0u : find_job(jobs, n_jobs, unit, &DevJob::unit_base);
+  const DevJob J = kOne ? one : jobs[job];
   const DevMir VL_GLOBAL &m = *as_global(J.mir);
   const DevLive VL_GLOBAL &L = *as_global(J.live);
   // arrays of the kernel and of its analysis, as global pointers
@@ -736,20 +739,25 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
   // the dies of the device see in one order; the returned values keep a wavefront's own in order.
   if (w.tid >= 64) return;
   uint32_t found = w.tid < w.nrows ? vl_lds[w.keys + w.tid] : kKeyOk;
-  const uint32_t T = L.T;
+  // (the job's entry is read again rather than kept in scalar registers through the walk, which
+  // has none to spare; `one` is the first kernel argument)
+  const DevJob VL_CONSTANT *entry = kOne ? (const DevJob VL_CONSTANT *)__builtin_amdgcn_kernarg_segment_ptr() : (const DevJob VL_CONSTANT *)(uintptr_t)jobs;
+  asm volatile("" : "+s"(entry));
+  const DevJob E = *((const DevJob *)entry + job);
+  const uint32_t T = as_global(E.live)->T, row = (unit - E.unit_base) % E.n_groups * E.rows + w.tid;
   if (T > 1) {
-    uint32_t *const my_key = board.keys + J.row_base + row0 + w.tid;
+    uint32_t *const my_key = board.keys + E.row_base + row;
     uint32_t before = 0;
     if (found != kKeyOk) before = __hip_atomic_fetch_max(my_key, ~found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" : "+v"(before) : : "memory");
     uint32_t n_before = 0;
-    uint32_t *const counter = board.arrived + J.group_base + group;
+    uint32_t *const counter = board.arrived + E.group_base + (unit - E.unit_base) % E.n_groups;
     if (w.tid == 0) n_before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane(n_before) + 1u != T) return;
     if (w.tid < w.nrows) found = ~__hip_atomic_exchange(my_key, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (w.tid == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (w.tid < w.nrows) finish_row(J, row0 + w.tid, found);
+  if (w.tid < w.nrows) finish_row(E, row, found);
 }
 
 // For a candidate whose first violation is a register clash at instruction i: the
@@ -763,12 +771,13 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
 // failed on safety.
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
 constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, uint32_t per_group) {
+template <bool kOne>
+__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
   __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], nd, members[kResolveMembers], n_members;
   const uint32_t global_group = blockIdx.x / per_group, mine_first = blockIdx.x % per_group;
-  const DevJob VL_GLOBAL &J = as_global(jobs)[find_job(jobs, n_jobs, global_group, &DevJob::group_base)];
+  const DevJob J = kOne ? one : jobs[find_job(jobs, n_jobs, global_group, &DevJob::group_base)];
   const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
   const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
@@ -845,15 +854,20 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
 // Job tables on the device: per device a few slots, one per stream that has called, so
 // that calls alternating between streams neither wait for each other's table nor overwrite
 // a table that kernels of the other stream still read.
+constexpr uint32_t kStaged = 4;
 struct Slot {
   bool used = false;
   hipStream_t stream = nullptr;
   DevJob *dev = nullptr;
-  DevJob *host = nullptr;   // pinned
+  // the tables on their way to the device: pinned copies used in turn, so that a call with another
+  // table than the last waits only for the upload kStaged calls ago; `host` is the latest one
+  DevJob *staged = nullptr, *host = nullptr;
+  hipEvent_t copied[kStaged] = {};
+  bool in_flight[kStaged] = {};
+  uint32_t turn = 0;
   uint32_t cap = 0, n_valid = 0;
   uint32_t *board = nullptr;                 // kHeadWords (the first: Launch::finished), Board::arrived, Board::keys; zero between calls
   uint64_t groups_cap = 0, rows_cap = 0;     // what the board has room for
-  hipEvent_t copied = nullptr;
   uint64_t tick = 0;
 };
 constexpr int kSlots = 4;
@@ -879,7 +893,8 @@ extern "C" int32_t vl_verify_time_next(void *start, void *stop) {
 
 namespace {
 struct Launch {
-  DevJob *dev = nullptr;
+  DevJob *dev = nullptr;   // the job table on the device; a single job travels as an argument instead
+  DevJob one = {};
   Board board = {};
   uint32_t *finished = nullptr;   // counter of the reductions, zero between calls
   uint64_t total_rows = 0, groups = 0;
@@ -966,7 +981,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
     const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only);
     if (rc != VL_OK) return rc;
   }
-  if (results_only && s.n_valid == n_jobs) {
+  if (results_only && n_jobs > 1 && s.n_valid == n_jobs) {
     // the table a verification call on this stream left behind serves, whatever its candidate
     // layout, when it names the same results
     bool same = true;
@@ -977,27 +992,36 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
       return VL_OK;
     }
   }
-  if (s.cap < n_jobs) {
-    if (s.copied) VL_HIP(hipEventSynchronize(s.copied));
-    VL_HIP(hipStreamSynchronize(stream));
-    if (s.dev) (void)hipFree(s.dev);
-    if (s.host) (void)hipHostFree(s.host);
-    s.dev = nullptr; s.host = nullptr; s.cap = 0; s.n_valid = 0;
-    uint32_t cap = std::max(256u, n_jobs);
-    VL_HIP(hipMalloc((void **)&s.dev, (size_t)cap * sizeof(DevJob)));
-    VL_HIP(hipHostMalloc((void **)&s.host, (size_t)cap * sizeof(DevJob), hipHostMallocDefault));
-    if (!s.copied) VL_HIP(hipEventCreateWithFlags(&s.copied, hipEventDisableTiming));
-    s.cap = cap;
-  }
-  if (s.n_valid != n_jobs || memcmp(s.host, tab.data(), (size_t)n_jobs * sizeof(DevJob)) != 0) {
-    // the previous table may still be on its way to the device
-    if (s.n_valid) VL_HIP(hipEventSynchronize(s.copied));
-    memcpy(s.host, tab.data(), (size_t)n_jobs * sizeof(DevJob));
-    // kernels of an earlier call that still read the old device table run on this same
-    // stream: the copy below is ordered after them
-    VL_HIP(hipMemcpyAsync(s.dev, s.host, (size_t)n_jobs * sizeof(DevJob), hipMemcpyHostToDevice, stream));
-    VL_HIP(hipEventRecord(s.copied, stream));
-    s.n_valid = n_jobs;
+  if (n_jobs == 1) {
+    out.one = tab[0];   // goes to the kernels as an argument
+  } else {
+    if (s.cap < n_jobs) {
+      VL_HIP(hipStreamSynchronize(stream));
+      if (s.dev) (void)hipFree(s.dev);
+      if (s.staged) (void)hipHostFree(s.staged);
+      s.dev = nullptr; s.staged = s.host = nullptr; s.cap = 0; s.n_valid = 0;
+      uint32_t cap = std::max(256u, n_jobs);
+      VL_HIP(hipMalloc((void **)&s.dev, (size_t)cap * sizeof(DevJob)));
+      VL_HIP(hipHostMalloc((void **)&s.staged, (size_t)cap * kStaged * sizeof(DevJob), hipHostMallocDefault));
+      for (uint32_t t = 0; t < kStaged; ++t) {
+        if (!s.copied[t]) VL_HIP(hipEventCreateWithFlags(&s.copied[t], hipEventDisableTiming));
+        s.in_flight[t] = false;
+      }
+      s.cap = cap;
+    }
+    if (s.n_valid != n_jobs || memcmp(s.host, tab.data(), (size_t)n_jobs * sizeof(DevJob)) != 0) {
+      s.turn = (s.turn + 1) % kStaged;
+      if (s.in_flight[s.turn]) VL_HIP(hipEventSynchronize(s.copied[s.turn]));
+      s.host = s.staged + (size_t)s.turn * s.cap;
+      s.n_valid = 0;
+      memcpy(s.host, tab.data(), (size_t)n_jobs * sizeof(DevJob));
+      // kernels of an earlier call that still read the old device table run on this same
+      // stream: the copy below is ordered after them
+      VL_HIP(hipMemcpyAsync(s.dev, s.host, (size_t)n_jobs * sizeof(DevJob), hipMemcpyHostToDevice, stream));
+      VL_HIP(hipEventRecord(s.copied[s.turn], stream));
+      s.in_flight[s.turn] = true;
+      s.n_valid = n_jobs;
+    }
   }
   if (!s.board || (!results_only && (s.groups_cap < out.groups || s.rows_cap < out.total_rows))) {
     VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
@@ -1019,11 +1043,11 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
 // `stats`, the workgroup that finishes last also totals the jobs' summaries (every field is
 // written, nothing needs clearing beforehand; `finished` is left zero).  The summaries reach it
 // through stores and loads that all dies see (agent scope).
-__global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jobs, uint32_t n_jobs, vl_summary *__restrict__ summaries,
+__global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, vl_summary *__restrict__ summaries,
                                                    vl_loop_stats *stats, uint32_t *finished) {
   const uint32_t lane = threadIdx.x & 63u, j = blockIdx.x * 4u + (threadIdx.x >> 6);
   if (j < n_jobs) {
-    const DevJob &J = jobs[j];
+    const DevJob J = n_jobs == 1 ? one : jobs[j];
     uint32_t hist[4] = {0, 0, 0, 0}, first = J.K;
     for (uint32_t k0 = 0; k0 < J.K; k0 += 64) {
       const bool in = k0 + lane < J.K;
@@ -1052,7 +1076,7 @@ __global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jo
     uint32_t f[6];
 #pragma unroll
     for (uint32_t t = 0; t < 6; ++t) f[t] = __hip_atomic_load((uint32_t *)(summaries + x) + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t tries = f[1] ? f[0] + 1u : jobs[x].K;
+    const uint32_t tries = f[1] ? f[0] + 1u : n_jobs == 1 ? one.K : jobs[x].K;
     mine[0] += f[1];
     mine[1] = max(mine[1], (unsigned long long)tries);
     mine[2] += tries;
@@ -1090,7 +1114,7 @@ extern "C" int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_su
   Launch L;
   const int32_t rc = prepare_jobs(jobs, n_jobs, stream, s, L, false, true);
   if (rc != VL_OK) return rc;
-  k_summarize<<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, summaries, stats, L.finished);
+  k_summarize<<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, L.one, summaries, stats, L.finished);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
@@ -1101,21 +1125,26 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   const bool narrow = L.max_rows <= kPitchNarrow;   // every group of every job fits the narrow ring
   const size_t lds = (size_t)L.max_words * 64 * 4 + 64 * 4 + 1024 + (size_t)kRing * (narrow ? kPitchNarrow : kPitchWide) * 2;
   if (g_time_start) VL_HIP(hipEventRecord(g_time_start, stream));
-  auto walk = [&](auto kernel) { kernel<<<L.units, kWalkThreads, lds, stream>>>(L.dev, n_jobs, L.board); };
+  auto walk = [&](auto by_table, auto by_argument) {
+    (n_jobs == 1 ? by_argument : by_table)<<<L.units, kWalkThreads, lds, stream>>>(L.one, L.dev, n_jobs, L.board);
+  };
+#define VL_WALK(...) walk(k_walk<__VA_ARGS__, false>, k_walk<__VA_ARGS__, true>)
   if (transposed) {
-    if (narrow) walk(k_walk<kPitchNarrow, true, false>);
-    else walk(k_walk<kPitchWide, true, false>);
+    if (narrow) VL_WALK(kPitchNarrow, true, false);
+    else VL_WALK(kPitchWide, true, false);
   } else if (L.all_direct) {
-    if (narrow) walk(k_walk<kPitchNarrow, false, true>);
-    else walk(k_walk<kPitchWide, false, true>);
+    if (narrow) VL_WALK(kPitchNarrow, false, true);
+    else VL_WALK(kPitchWide, false, true);
   } else {
-    if (narrow) walk(k_walk<kPitchNarrow, false, false>);
-    else walk(k_walk<kPitchWide, false, false>);
+    if (narrow) VL_WALK(kPitchNarrow, false, false);
+    else VL_WALK(kPitchWide, false, false);
   }
+#undef VL_WALK
   if (g_time_stop) VL_HIP(hipEventRecord(g_time_stop, stream));
   g_time_start = g_time_stop = nullptr;
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
-  k_resolve<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(L.dev, n_jobs, per_group);
+  (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
+      L.dev, n_jobs, L.one, per_group);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
@@ -1150,12 +1179,11 @@ extern "C" int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const
 }
 
 // ---- the entry point that allocates nothing ----------------------------------------------
-// Its job table (one job) and its board live in a file-scope device array instead of memory the library allocates.  The array's name is only a host-side handle:
+// Its board lives in a file-scope device array instead of memory the library allocates.  The array's name is only a host-side handle:
 // its device address is looked up once per device and kept.
 namespace {
 constexpr uint32_t kStaticMaxK = VL_STATIC_MAX_K;
 struct StaticScratch {   // zero at load time, and between calls
-  DevJob job;
   uint32_t arrived[kStaticMaxK / 64 + 1];
   uint32_t keys[kStaticMaxK];
 };
@@ -1164,8 +1192,6 @@ static __device__ __align__(256) unsigned char scratch[sizeof(StaticScratch)];
 namespace {
 std::mutex g_static_mu;
 void *g_static_ptr[16] = {};
-
-__global__ void k_put_job(DevJob job, DevJob *dst) { *dst = job; }
 }  // namespace
 
 extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live, const uint16_t *cand, uint32_t K,
@@ -1191,8 +1217,7 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
     }
     sc = (StaticScratch *)g_static_ptr[device];
   }
-  L.dev = &sc->job;
+  L.one = d;
   L.board = Board{sc->arrived, sc->keys};
-  k_put_job<<<1, 1, 0, stream>>>(d, &sc->job);
   return launch_all(L, 1, stream, false);
 }
