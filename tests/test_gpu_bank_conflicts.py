@@ -61,3 +61,21 @@ def test_argument_errors():
     torch.cuda.synchronize()
     assert (out.cpu().numpy() == 9).all()
     vl.vl_mir_destroy(hm)
+
+
+@pytest.mark.parametrize("n_ops", [0, 1, 3, 4, 5, 16, 64])
+@pytest.mark.parametrize("n_banks", [2, 4, 7])
+def test_operand_counts(n_ops, n_banks):
+    """instructions of n_ops operands among short ones, repeated operands, K around a slab of eight"""
+    rng = np.random.default_rng(n_ops)
+    from vlgen.mir import Mir
+    V = 90
+    width = rng.integers(1, 33, V).astype(np.uint8)
+    instrs = [([v], []) for v in range(V)]
+    for i in range(300):
+        n = n_ops if i % 3 == 0 else int(rng.integers(0, 5))
+        instrs.append(([], [int(x) for x in rng.integers(0, V if n < 10 else 20, n)]))
+    m = Mir.build([instrs], [[]], V, (512,), np.zeros(V, np.uint8), width, np.ones(V, np.uint8), None)
+    for K in (1, 7, 8, 9):
+        rows = rng.integers(0, 512, (K, m.n_occ)).astype(np.uint16)
+        assert (gpu_scores(m, rows, n_banks) == vlo.bank_conflicts(m, rows, n_banks)).all(), K
