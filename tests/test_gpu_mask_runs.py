@@ -1,0 +1,80 @@
+"""Decoding masks where neighbouring queries fold into runs: many rows of one occurrence at equal
+and unequal distances, more runs than travel as a kernel argument (64), shares of several
+queries per wavefront, more than 256 live values; against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2506_17506_amd as vl  # noqa: E402
+from oracle import vlo  # noqa: E402
+from vlgen.mir import Mir  # noqa: E402
+from vlgen.mixed import mixed_mir  # noqa: E402
+from test_gpu_parity import free, gpu_analyze  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    vl.load()
+
+
+def orders(n_rows, occs, rng):
+    """row order and occurrence of every query, as (name, [(row, occ)])"""
+    yield "one run each", [(k, o) for o in occs[:3] for k in range(n_rows)]
+    yield "backwards", [(k, o) for o in occs[:3] for k in range(n_rows - 1, -1, -1)]
+    yield "every other row", [(k, o) for o in occs[:3] for k in range(0, n_rows, 2)]
+    yield "one row again and again", [(1, occs[0])] * 9
+    yield "no two alike", [(int(rng.integers(0, n_rows)), int(o)) for o in rng.choice(occs, 150)]
+    yield "65 short runs", [(k, occs[r % len(occs)]) for r in range(65) for k in range(3)]
+
+
+@pytest.mark.parametrize("ld_extra", [0, 1])
+def test_runs(ld_extra):
+    rng = np.random.default_rng(5)
+    m = mixed_mir(0xA200, n_instr=500, reserved=True)
+    n_rows = 37
+    ld = m.n_occ + ld_extra
+    host = rng.integers(0, 48, (n_rows, ld)).astype(np.uint16)
+    rows = np.ascontiguousarray(host[:, :m.n_occ])
+    dev = torch.from_numpy(host.view(np.int16)).cuda()
+    an = vlo.analyze(m, interference=False, threads=8)
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        occs = [int(o) for o in rng.integers(0, m.n_occ, 40)] + [0, m.n_occ - 1]
+        for name, qs in orders(n_rows, occs, rng):
+            masks = torch.full((len(qs), 16), -1, dtype=torch.int32, device="cuda")
+            vl.vl_free_bases_multi([(hm[0], hl[0], dev[k], o) for k, o in qs], masks)
+            torch.cuda.synchronize()
+            got = masks.cpu().numpy().view(np.uint32)
+            want = np.stack([vlo.free_bases(m, an, rows[k], o) for k, o in qs])
+            bad = np.nonzero((got != want).any(axis=1))[0]
+            assert len(bad) == 0, (name, [qs[j] for j in bad[:5]])
+    finally:
+        free(hm, hl)
+
+
+@pytest.mark.parametrize("n_live,n_queries", [(255, 5), (256, 5), (257, 5), (600, 5), (40, 9000)])
+def test_many_live_values_and_many_queries(n_live, n_queries):
+    V = n_live + 1
+    blocks = [[([v], []) for v in range(V)] + [([], list(range(v, min(V, v + 40)))) for v in range(0, V, 40)]]
+    m = Mir.build(blocks, [[]], V, (512,), np.zeros(V, np.uint8), np.ones(V, np.uint8), np.ones(V, np.uint8), None, name=f"live{n_live}")
+    rng = np.random.default_rng(n_live)
+    rows = np.ascontiguousarray(rng.integers(0, 512, (7, V)).astype(np.uint16)[:, m.occ_vreg])
+    an = vlo.analyze(m, interference=False)
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        dev, ld = vl.rows_to_device(rows)
+        qs = [(j % 7, n_live) for j in range(n_queries)]   # the last value's definition, all others live
+        masks = torch.full((n_queries, 16), -1, dtype=torch.int32, device="cuda")
+        rows_dev = [dev[k] for k in range(7)]
+        vl.vl_free_bases_multi([(hm[0], hl[0], rows_dev[k], o) for k, o in qs], masks)
+        torch.cuda.synchronize()
+        got = masks.cpu().numpy().view(np.uint32)
+        want = np.stack([vlo.free_bases(m, an, rows[k], n_live) for k in range(7)])
+        assert (got == want[[k for k, _ in qs]]).all()
+    finally:
+        free(hm, hl)
