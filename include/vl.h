@@ -275,8 +275,9 @@ int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_summary *summ
  * jobs is [host]; cand and out inside are [device]; out receives K records.  The first call
  * that sees a program enumerates its interfering pairs from `live` (whose analysis must be
  * complete or enqueued on `stream`), synchronising the stream, and keeps them with the
- * vl_mir handle; later calls are asynchronous on `stream` but wait on the host until the
- * previous call's kernels have finished with the library's workspace.
+ * vl_mir handle; later calls are asynchronous on `stream` (the library has four
+ * workspaces per device, used in turn: a call waits on the host until the kernels of the fourth
+ * last call have finished with theirs).
  * Errors: VL_E_NULL, VL_E_ARG (handles of different programs), VL_E_SHAPE (n_jobs == 0 or
  * above 65535, K == 0 or above 65535, ld < n_occ); nothing is launched on error. */
 typedef struct { uint32_t kinds, n_cons, n_real, n_safe, real_bits, reserved[3]; } vl_counts;
@@ -315,8 +316,10 @@ int32_t vl_bank_conflicts(const vl_mir *mir, const uint16_t *cand, uint32_t K, u
  *   the tuple is disjoint from that of every other vreg of the class that is in P(i) and
  *   whose first occurrence lies before `occ`, taken at its first occurrence's register
  *   (Safety; a value that dies at i is not in P(i)).
- * queries is [host]; cand and masks are [device].  Asynchronous on `stream`; the call waits
- * on the host for the previous call's queries to have been consumed.
+ * queries is [host]; cand and masks are [device].  Asynchronous on `stream`; a call whose
+ * queries do not fold into 64 runs or fewer (neighbouring queries of one program at one
+ * occurrence, rows at equal distances) waits on the host until the fourth last such call's
+ * have been consumed.
  * Errors: VL_E_NULL, VL_E_ARG (handles of different programs), VL_E_SHAPE (n == 0, occ past
  * the program's occurrences); nothing is launched on error. */
 typedef struct {

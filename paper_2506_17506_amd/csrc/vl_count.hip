@@ -5,9 +5,7 @@
 //   n_real  mentioned vregs whose T(v) breaks a hardware rule, real_bits the rules broken
 //   n_safe  pairs of one class that are in some P(i) together and whose tuples overlap
 // The pairs (the interference relation) depend on the program only: they are enumerated
-// once per program from the live intervals and kept with the program handle.  Per call the
-// registers T are gathered into a table [vreg][candidate], so that a wavefront that walks
-// the pairs with one candidate per lane reads one line per endpoint.
+// once per program from the live intervals and kept with the program handle.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -32,9 +30,14 @@ __device__ inline bool lists_meet(const uint32_t VL_GLOBAL *seg, uint32_t a0, ui
   return false;
 }
 
+// The pairs (a, b), a < b, are kept as records of eight words, a and up to seven of its partners,
+// each vreg with its width in the upper byte (vreg numbers stay below 2^24: VL_MAX_VREG); unused
+// places hold a vreg of width 0, which overlaps nothing.  (Records instead of pairs: what is
+// looked up for a is looked up once for seven pairs, and a pair takes 4.6 bytes instead of 8.)
+constexpr uint32_t kPartners = 7;
+
 // One wavefront per vreg a, its lanes striding over b > a; blockIdx.y = program.  kFill = false:
-// cnt[a] = number of partners; kFill = true: the pairs are written from off[a] on, in ascending b,
-// each vreg with its width in the upper byte (vreg numbers stay below 2^24: VL_MAX_VREG).
+// cnt[a] = number of records; kFill = true: the records are written from off[a] on, in ascending b.
 // Vregs are taken 64 at a time, and a group whose hulls taken together ([earliest start, latest
 // end), from k_hull_groups) miss a's hull is passed over: vregs are mostly numbered in the
 // order they are first written, so most groups lie entirely before or after a.
@@ -43,7 +46,7 @@ struct PairJob {
   const DevLive *live;
   uint32_t *cnt;         // [V]
   const uint64_t *off;   // [V]
-  uint32_t *pairs;       // [n_pairs rounded up to 32][2]: vreg | width << 24
+  uint32_t *records;     // [n_records][8]: vreg | width << 24
   uint2 *groups;         // [(V + 63) / 64] (earliest start, latest end) of the group's non-empty hulls
 };
 
@@ -64,7 +67,7 @@ __global__ __launch_bounds__(256) void k_hull_groups(const PairJob *__restrict__
   if (lane == 0) J.groups[g] = make_uint2(lo, hi);
 }
 
-// off[a] = number of pairs of the vregs below a, totals[program] = all of them: one workgroup
+// off[a] = number of records of the vregs below a, totals[program] = all of them: one workgroup
 // per program, a contiguous run of vregs per thread
 __global__ __launch_bounds__(1024) void k_pair_offsets(const PairJob *__restrict__ jobs, uint64_t *__restrict__ totals) {
   const PairJob &J = jobs[blockIdx.x];
@@ -100,8 +103,9 @@ __global__ __launch_bounds__(256) void k_pairs(const PairJob *__restrict__ jobs)
   if (a >= m.V) return;   // whole wavefronts leave; nothing below synchronises the workgroup
   const uint32_t h0 = L.hull[2 * (size_t)a], h1 = L.hull[2 * (size_t)a + 1];
   const uint32_t s0 = L.seg_off[a], s1 = L.seg_off[a + 1], cls = attr_class(m.vattr[a]), width_a = attr_width(m.vattr[a]);
-  uint64_t at = kFill ? J.off[a] : 0;
-  uint32_t n = 0;
+  uint32_t VL_GLOBAL *const records = kFill ? as_global_rw(J.records) + 8 * J.off[a] : nullptr;
+  uint32_t n = 0;   // partners so far
+  auto place = [](uint32_t x) { return x / kPartners * 8u + 1u + x % kPartners; };   // of the x-th partner
   const uint32_t n_groups = (m.V + 63u) / 64u;
   for (uint32_t g0 = a / 64; g0 < n_groups; g0 += 64) {   // 64 groups at a time, one per lane
     uint2 span = make_uint2(0xFFFFFFFFu, 0u);
@@ -115,251 +119,242 @@ __global__ __launch_bounds__(256) void k_pairs(const PairJob *__restrict__ jobs)
       if (b > a && b < m.V && attr_class(attr_b) == cls && L.hull[2 * (size_t)b] < h1 && h0 < L.hull[2 * (size_t)b + 1])
         hit = lists_meet(L.seg, s0, s1, L.seg_off[b], L.seg_off[b + 1]);
       const uint64_t hits = __ballot(hit);
-      if (kFill) {
-        if (hit) {
-          const uint64_t pos = at + __popcll(hits & ((1ull << lane) - 1ull));
-          J.pairs[2 * pos] = a | (width_a << 24);
-          J.pairs[2 * pos + 1] = b | (attr_width(attr_b) << 24);
-        }
-        at += __popcll(hits);
-      } else {
-        n += __popcll(hits);
-      }
+      if (kFill && hit) records[place(n + __popcll(hits & ((1ull << lane) - 1ull)))] = b | (attr_width(attr_b) << 24);
+      n += __popcll(hits);
     }
   }
-  if (!kFill && lane == 0) J.cnt[a] = n;
-  // the list ends with pairs of the last vreg with itself, widths 0 (they overlap nothing and
-  // keep a ascending), up to the next multiple of 32 pairs, so that it can be read in pieces
-  // without a tail
-  if (kFill && a == m.V - 1 && (at & 31u) && lane < 32u - (uint32_t)(at & 31u)) {
-    J.pairs[2 * (at + lane)] = a;
-    J.pairs[2 * (at + lane) + 1] = a;
+  const uint32_t n_records = (n + kPartners - 1) / kPartners;
+  if (!kFill && lane == 0) J.cnt[a] = n_records;
+  if (kFill) {
+    for (uint32_t r = lane; r < n_records; r += 64) records[8 * r] = a | (width_a << 24);
+    if (lane < kPartners && n + lane < n_records * kPartners) records[place(n + lane)] = 0;
   }
 }
 
 // ---- per call ----------------------------------------------------------------------------
+// A sample without any violation has all counts zero, and the verifier's walk finds those at a
+// fraction of the cost of counting (it tests a definition against what is occupied, not against
+// every value it interferes with).  So a call runs the walk first, lists each job's failed samples
+// (k_cnt_list) and counts only those (k_cnt_rows).
 struct DevCountJob {
   const DevMir *mir;
   const DevLive *live;
   const uint16_t *cand;
   vl_counts *out;
-  uint16_t *table;         // [V][k_pad] registers of the first occurrences
-  const uint32_t *pairs;   // [n_pairs rounded up to 32][2]: vreg | width << 24, the padding of width 0
-  uint64_t ld, n_pairs;
-  uint32_t K, k_pad, V, pad1;
+  const vl_result *verdicts;   // [K] of the walk; the pairs of safety violations are not in them
+  const uint32_t *records;     // [n_records][8]: the interfering pairs
+  uint64_t ld, n_records;
+  uint32_t K, parts, fail_base, wide;   // fail_base: first entry in the list of failed samples; wide: rows can be read 16 bytes at a time
 };
+struct Unit { uint32_t job, first, n, part; };   // samples failed[first .. first + n) of a job, a share of its work
+struct Head { uint32_t n_units, taken, pad[62]; };   // travels with the job table, zeroed by it
 
-__global__ void k_cnt_clear(const DevCountJob *__restrict__ jobs) {
-  const DevCountJob &J = jobs[blockIdx.y];
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < J.K) J.out[k] = vl_counts{0, 0, 0, 0, 0, {0, 0, 0}};
-}
+constexpr uint32_t kAtOnce = 4;                  // samples per workgroup
+constexpr size_t kTableBytes = 152 * 1024;       // of a compute unit's 160 KB
+constexpr uint64_t kRecordsPerPart = 8192;       // (also keeps a lane's counts far below 2^16)
 
-// table[v][k] = cand[k][first[v]] through a 64 x 64 tile in LDS: reads run along a candidate
-// row (first occurrences mostly ascend with the vreg), writes along the candidates.  The
-// thread that writes a candidate's entries also tests them against the hardware rules
-// (realizability: the vregs that are mentioned, each once).
-__global__ __launch_bounds__(256) void k_cnt_table(const DevCountJob *__restrict__ jobs, uint32_t tiles_k) {
-  const DevCountJob &J = jobs[blockIdx.y];
-  const DevMir VL_GLOBAL &m = *as_global(J.mir);
-  const DevLive VL_GLOBAL &L = *as_global(J.live);
-  const uint32_t v0 = (blockIdx.x / tiles_k) * 64, k0 = (blockIdx.x % tiles_k) * 64;
-  if (v0 >= m.V || k0 >= J.k_pad) return;
-  __shared__ uint16_t tile[64][66];
-  __shared__ uint32_t attrs[64];   // kNone: never mentioned, or past the last vreg
-  const uint32_t tx = threadIdx.x & 63u, ty = threadIdx.x >> 6;
-  const uint32_t v = v0 + tx;
-  const uint32_t fo = v < m.V ? L.first[v] : kNone;
-  if (ty == 0) attrs[tx] = fo != kNone ? m.vattr[v] : kNone;
-  for (uint32_t kk = ty; kk < 64; kk += 4) {
-    const uint32_t k = k0 + kk;
-    tile[kk][tx] = (k < J.K && fo != kNone) ? J.cand[(uint64_t)k * J.ld + fo] : (uint16_t)0;
-  }
-  __syncthreads();
-  uint32_t n = 0, bits = 0;
-  for (uint32_t vv = ty; vv < 64; vv += 4) {
-    if (v0 + vv >= m.V || k0 + tx >= J.k_pad) continue;
-    const uint32_t p = tile[tx][vv];
-    J.table[(size_t)(v0 + vv) * J.k_pad + k0 + tx] = (uint16_t)p;
-    if (attrs[vv] == kNone) continue;
-    const uint32_t bad = bad_bits(m, attrs[vv], p);
-    n += bad != 0;
-    bits |= bad;
-  }
-  if (k0 + tx < J.K && n) {
-    atomicAdd(&J.out[k0 + tx].n_real, n);
-    atomicOr(&J.out[k0 + tx].real_bits, bits);
-  }
-}
-
-// consistency: a workgroup takes 64 candidates (blockIdx.y) and 1024 occurrences.  64
-// occurrences of the 64 rows at a time go through LDS, read along the rows; then a lane is a
-// candidate and compares, occurrence by occurrence, its register with its entry in the
-// table row of the occurrence's vreg (one coalesced read for the 64 candidates).
-__global__ __launch_bounds__(256) void k_cnt_cons(const DevCountJob *__restrict__ jobs) {
-  const DevCountJob &J = jobs[blockIdx.z];
-  const DevMir VL_GLOBAL &m = *as_global(J.mir);
-  const uint32_t k0 = blockIdx.y * 64, o0 = blockIdx.x * 1024;
-  if (k0 >= J.K || o0 >= m.O) return;
-  __shared__ uint16_t tile[64][66];
-  const uint32_t lane = threadIdx.x & 63u, first = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 16u;
-  const uint32_t o_end = min(m.O, o0 + 1024u);
+// One wavefront per job: clears the counts, lists the failed samples and the units of work they make.
+__global__ __launch_bounds__(256) void k_cnt_list(const DevCountJob *__restrict__ jobs, uint32_t n_jobs, Head *head, uint32_t *__restrict__ failed,
+                                                  Unit *__restrict__ units) {
+  const uint32_t lane = threadIdx.x & 63u, j = blockIdx.x * 4u + (threadIdx.x >> 6);
+  if (j >= n_jobs) return;
+  const DevCountJob &J = jobs[j];
   uint32_t n = 0;
-  for (uint32_t oc = o0; oc < o_end; oc += 64) {
-    const bool in = oc + lane < o_end;
-    // this wavefront's 16 rows, all loads in flight together
-    uint16_t mine[16];
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u) {
-      const uint32_t k = k0 + first + u;
-      mine[u] = (in && k < J.K) ? J.cand[(uint64_t)k * J.ld + oc + lane] : (uint16_t)0;
-    }
-    const uint32_t my_v = in ? m.occ_vreg[oc + lane] : 0u;
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u) tile[first + u][lane] = mine[u];
-    __syncthreads();
-    const uint32_t cnt = min(64u, o_end - oc);
-    // this wavefront's quarter of the 64 occurrences; rows past the last candidate hold zeros
-    // in the tile and in the table
-    uint32_t q[16];
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u)
-      q[u] = J.table[(size_t)__builtin_amdgcn_readlane(my_v, first + u) * J.k_pad + k0 + lane];
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u) n += (first + u < cnt && tile[lane][first + u] != q[u]) ? 1u : 0u;
-    __syncthreads();
+  for (uint32_t k0 = 0; k0 < J.K; k0 += 64) {
+    const uint32_t k = k0 + lane;
+    const bool bad = k < J.K && J.verdicts[k].status != VL_STATUS_OK;
+    if (k < J.K) J.out[k] = vl_counts{0, 0, 0, 0, 0, {0, 0, 0}};
+    const uint64_t which = __ballot(bad);
+    if (bad) failed[J.fail_base + n + __popcll(which & ((1ull << lane) - 1ull))] = k;
+    n += (uint32_t)__popcll(which);
   }
-  if (k0 + lane < J.K && n) atomicAdd(&J.out[k0 + lane].n_cons, n);
+  const uint32_t quads = (n + kAtOnce - 1) / kAtOnce, mine = quads * J.parts;
+  uint32_t at = 0;
+  if (lane == 0 && mine) at = __hip_atomic_fetch_add(&head->n_units, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  at = __builtin_amdgcn_readfirstlane(at);
+  for (uint32_t x = lane; x < mine; x += 64) {
+    const uint32_t quad = x / J.parts;
+    units[at + x] = Unit{j, J.fail_base + quad * kAtOnce, min(kAtOnce, n - quad * kAtOnce), x % J.parts};
+  }
 }
 
-// safety: the wavefronts of a program take its pairs in stretches of 256 and walk each once
-// for every group of 128 candidates: a lane holds two neighbouring candidates, whose registers
-// are one 32-bit word of a table row.  Both are tested at once with saturating 16-bit
-// arithmetic, exact for any 16-bit register number: with u = max(pa - pb, 0) and
-// v = max(pb - pa, 0), the tuples overlap iff u < width(b) and v < width(a).  What bounds the
-// kernel is the number of instructions a pair takes, of any kind: seven vector ones for the
-// test; the pairs (with the widths in their upper bytes) arrive through scalar loads, sixteen
-// pairs at a time and the next sixteen fetched ahead, and a table row is addressed by a scalar
-// offset plus the lane's own.  The pairs are stored in ascending (a, b), so the sixteen mostly
-// share a, whose row is then read once.
-// A program has at most 1024 workgroups, whose wavefronts take its stretches in turn.  (Running
-// all workgroups of a program on one of the eight dies, so that its table stays in one L2, cut
-// the memory traffic by ten and made the kernel slower: the dies were then unevenly loaded.)
-constexpr uint32_t kPairsPerWave = 256, kPairsPerGroup = 4 * kPairsPerWave, kSafeGroupsPerProgram = 1024;
-constexpr uint32_t kPairsAtOnce = 16;   // the pair list of a program is padded with empty pairs to a multiple of this
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-__device__ inline u16x2 both(uint32_t x) { return __builtin_bit_cast(u16x2, x); }
-template <bool kBig>
-__global__ __launch_bounds__(256) void k_cnt_safe(const DevCountJob *__restrict__ jobs) {
-  const DevCountJob &J = jobs[blockIdx.y];
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t n_waves = gridDim.x * 4u;
-  const uint32_t wave = blockIdx.x * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if ((uint64_t)wave * kPairsPerWave >= J.n_pairs) return;
-  const uint32_t words = J.k_pad / 2;   // 32-bit words per table row (k_pad is a multiple of 64)
-  const uint32_t row_bytes = words * 4u;
+// A workgroup takes a unit: up to four failed samples of a job and a share of the job's
+// occurrences, vregs and pairs.  The registers T of the four samples' first occurrences are
+// gathered into LDS, 8 bytes per vreg (u16 x 4), and everything is counted against that table, the
+// four samples at once in packed 16-bit arithmetic:
+//   consistency     eight occurrences per lane: their vregs (32 bytes, shared by the samples) and
+//                   registers (16 bytes per sample), one 8-byte LDS read per occurrence
+//   realizability   as the table is filled
+//   safety          a record of seven pairs per lane, eight LDS reads; with u = max(pa - pb, 0) and
+//                   v = max(pb - pa, 0) the tuples overlap iff u < width(b) and v < width(a),
+//                   exact in saturating arithmetic for any 16-bit register
+// What bounds it: the vector instructions of the pairs (18 per pair and four samples) and their
+// LDS reads.  The pairs of a large program (600,000 for 20,000 instructions) are cut into parts of
+// 8,192 records so that a few failed samples still make work for the whole device; each part fills
+// the table anew, about as long as its pairs take.  Units are taken as workgroups get free.
+// A table in memory for all samples, [vreg][sample], with a pass each for table, consistency and
+// safety took 0.42 ms for 64 kernels with 100 samples, whatever they were; with a fifth of them
+// failing, the walk takes 0.13 ms and this kernel 0.09 ms (0.12 ms with pairs instead of records
+// and units dealt out beforehand).
+// kLds = false: the table of a program with more vregs than LDS holds lives in memory (`spill`).
+template <bool kLds>
+__global__ __launch_bounds__(1024) void k_cnt_rows(const DevCountJob *__restrict__ jobs, Head *head, const uint32_t *__restrict__ failed,
+                                                   const Unit *__restrict__ units, uint2 *spill, uint32_t max_v) {
+  extern __shared__ uint2 table_lds[];   // [V]
+  __shared__ uint32_t sums[kAtOnce][4];  // per sample: strays, unrealizable vregs, overlapping pairs, rules broken
+  uint2 *const table = kLds ? table_lds : spill + (size_t)blockIdx.x * max_v;
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  auto both = [](uint32_t x) { return __builtin_bit_cast(u16x2, x); };
   // 1 in both halves, in a form the compiler cannot see through: a minimum with a known 1 is
   // turned into two compares and a merge instead of one packed instruction
   u16x2 one;
   asm volatile("v_mov_b32 %0, 0x10001" : "=v"(one));
-  for (uint32_t w0 = 0; w0 < words; w0 += 64) {
-    // lanes past the row repeat its last word; not counted
-    const uint32_t lane_off = min(w0 + lane, words - 1) * 4u;
-    // A row is fetched with a buffer read: descriptor and row offset in scalar registers, the
-    // lane brings its offset inside the row.  The scalar offset has 32 bits; for a table of
-    // 4 GB or more (kBig) every row gets a descriptor of its own instead.
-    const __amdgpu_buffer_rsrc_t whole = __builtin_amdgcn_make_buffer_rsrc((void *)J.table, 0, kBig ? 0 : (int)(J.V * row_bytes), 0x00020000);
-    auto row = [&](uint32_t packed) __attribute__((always_inline)) {   // this lane's word of the row of vreg (packed & 0xFFFFFF)
-      const uint32_t v = packed & 0xFFFFFFu;
-      if (kBig) {
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((char *)J.table + (uint64_t)v * row_bytes, 0, (int)row_bytes, 0x00020000);
-        return both(__builtin_amdgcn_raw_buffer_load_b32(r, lane_off, 0, 0));
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_units = head->n_units;
+  __shared__ uint32_t taken;
+  for (;;) {
+    if (tid == 0) taken = __hip_atomic_fetch_add(&head->taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint32_t u = __builtin_amdgcn_readfirstlane(taken);
+    if (u >= n_units) break;   // (every workgroup gets here: the counter only grows)
+    const Unit W = units[u];
+    const DevCountJob &J = jobs[W.job];
+    const DevMir VL_GLOBAL &m = *as_global(J.mir);
+    const DevLive VL_GLOBAL &L = *as_global(J.live);
+    const uint16_t VL_GLOBAL *row[kAtOnce];
+#pragma unroll
+    for (uint32_t c = 0; c < kAtOnce; ++c) row[c] = as_global(J.cand) + (uint64_t)failed[W.first + min(c, W.n - 1)] * J.ld;   // (past the last: repeated, not counted)
+    if (tid < kAtOnce * 4) (&sums[0][0])[tid] = 0;
+    uint32_t n_real[kAtOnce] = {0, 0, 0, 0}, rules[kAtOnce] = {0, 0, 0, 0};
+    // the table; this part's share of the vregs is tested against the hardware rules
+    const uint32_t v_lo = (uint32_t)((uint64_t)m.V * W.part / J.parts), v_hi = (uint32_t)((uint64_t)m.V * (W.part + 1) / J.parts);
+    for (uint32_t v0 = tid; v0 < m.V; v0 += 4 * 1024) {
+      uint32_t f[4], p[4][kAtOnce];
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) f[t] = v0 + t * 1024 < m.V ? L.first[v0 + t * 1024] : kNone;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t)
+#pragma unroll
+        for (uint32_t c = 0; c < kAtOnce; ++c) p[t][c] = f[t] != kNone ? row[c][f[t]] : 0u;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+        const uint32_t v = v0 + t * 1024;
+        if (v >= m.V) break;
+        table[v] = make_uint2(p[t][0] | (p[t][1] << 16), p[t][2] | (p[t][3] << 16));
+        if (f[t] == kNone || v < v_lo || v >= v_hi) continue;
+        const uint32_t attr = m.vattr[v];
+#pragma unroll
+        for (uint32_t c = 0; c < kAtOnce; ++c) {
+          const uint32_t bad = bad_bits(m, attr, p[t][c]);
+          n_real[c] += bad != 0;
+          rules[c] |= bad;
+        }
       }
-      return both(__builtin_amdgcn_raw_buffer_load_b32(whole, lane_off, v * row_bytes, 0));
+    }
+    __syncthreads();
+    // consistency
+    u16x2 stray01 = {0, 0}, stray23 = {0, 0};
+    auto stray = [&](uint32_t v, uint32_t p01, uint32_t p23) __attribute__((always_inline)) {
+      const uint2 t = table[v];
+      stray01 += __builtin_elementwise_min(both(p01 ^ t.x), one);
+      stray23 += __builtin_elementwise_min(both(p23 ^ t.y), one);
     };
-    auto width2 = [&](uint32_t packed) __attribute__((always_inline)) {
-      const uint16_t width = (uint16_t)(packed >> 24);
-      return u16x2{width, width};
-    };
-    uint32_t n_lo = 0, n_hi = 0;
-    for (uint64_t e0 = (uint64_t)wave * kPairsPerWave; e0 < J.n_pairs; e0 += (uint64_t)n_waves * kPairsPerWave) {
-      const uint64_t e1 = min(J.n_pairs, e0 + kPairsPerWave);
-      // eight pairs per 64-byte piece; e0 is a multiple of 256
-      const u32x16 VL_CONSTANT *pieces = (const u32x16 VL_CONSTANT *)(uintptr_t)(J.pairs + 2 * e0);
-      u16x2 n = {0, 0};   // at most 256 per half
-      auto count = [&](u16x2 ra, u16x2 rb, u16x2 sa, u16x2 sb) __attribute__((always_inline)) {
-        const u16x2 u = __builtin_elementwise_sub_sat(ra, rb), v = __builtin_elementwise_sub_sat(rb, ra);
-        const u16x2 room = __builtin_elementwise_min(__builtin_elementwise_sub_sat(sb, u), __builtin_elementwise_sub_sat(sa, v));
-        n += __builtin_elementwise_min(room, one);
-      };
-      const uint32_t n_groups = (uint32_t)((e1 - e0 + kPairsAtOnce - 1) / kPairsAtOnce);
-      auto group = [&](const u32x16 lo, const u32x16 hi) __attribute__((always_inline)) {
-        u16x2 rb[kPairsAtOnce];
-        if ((lo[0] & 0xFFFFFFu) == (hi[14] & 0xFFFFFFu)) {
-          // the usual case: one row for a
-          const u16x2 ra = row(lo[0]), sa = width2(lo[0]);
+    {
+      const uint32_t pieces = m.O / 8u;   // whole pieces of eight occurrences; the rest is looked at one by one
+      const uint32_t lo = (uint32_t)((uint64_t)pieces * W.part / J.parts), hi = (uint32_t)((uint64_t)pieces * (W.part + 1) / J.parts);
+      if (J.wide) {
+        for (uint32_t x = lo + tid; x < hi; x += 1024) {
+          u32x4 r[kAtOnce];
 #pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) { rb[t] = row(lo[2 * t + 1]); rb[8 + t] = row(hi[2 * t + 1]); }
-          __builtin_amdgcn_s_waitcnt(0x0F70);   // all rows at once (vmcnt 0) rather than one wait per pair
-#pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) count(ra, rb[t], sa, width2(lo[2 * t + 1]));
-#pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) count(ra, rb[8 + t], sa, width2(hi[2 * t + 1]));
-        } else {
-          u16x2 ra[kPairsAtOnce];
+          for (uint32_t c = 0; c < kAtOnce; ++c) r[c] = *reinterpret_cast<const u32x4 VL_GLOBAL *>(row[c] + 8u * x);
+          const u32x4 va = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x), vb = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x + 4u);
 #pragma unroll
           for (uint32_t t = 0; t < 8; ++t) {
-            ra[t] = row(lo[2 * t]); rb[t] = row(lo[2 * t + 1]);
-            ra[8 + t] = row(hi[2 * t]); rb[8 + t] = row(hi[2 * t + 1]);
+            const uint32_t half = t & 1u ? 0x07060302u : 0x05040100u;   // the t-th register of two samples, side by side
+            stray(t < 4 ? va[t & 3] : vb[t & 3], __builtin_amdgcn_perm(r[1][t / 2], r[0][t / 2], half), __builtin_amdgcn_perm(r[3][t / 2], r[2][t / 2], half));
           }
-          __builtin_amdgcn_s_waitcnt(0x0F70);
-#pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) count(ra[t], rb[t], width2(lo[2 * t]), width2(lo[2 * t + 1]));
-#pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) count(ra[8 + t], rb[8 + t], width2(hi[2 * t]), width2(hi[2 * t + 1]));
         }
+      } else {
+        for (uint32_t o = 8u * lo + tid; o < 8u * hi; o += 1024)
+          stray(m.occ_vreg[o], row[0][o] | ((uint32_t)row[1][o] << 16), row[2][o] | ((uint32_t)row[3][o] << 16));
+      }
+      if (W.part == 0)
+        for (uint32_t o = 8u * pieces + tid; o < m.O; o += 1024)
+          stray(m.occ_vreg[o], row[0][o] | ((uint32_t)row[1][o] << 16), row[2][o] | ((uint32_t)row[3][o] << 16));
+    }
+    // safety
+    u16x2 pair01 = {0, 0}, pair23 = {0, 0};
+    {
+      const uint64_t e_lo = min(J.n_records, W.part * kRecordsPerPart), e_hi = min(J.n_records, e_lo + kRecordsPerPart);
+      const u32x4 VL_GLOBAL *records = (const u32x4 VL_GLOBAL *)(uintptr_t)(J.records) + 2 * e_lo;
+      const uint32_t n = (uint32_t)(e_hi - e_lo);
+      auto at = [&](uint32_t x) { return table[x & 0xFFFFFFu]; };
+      auto width2 = [&](uint32_t x) { return both(__builtin_amdgcn_perm(x, x, 0x0C030C03u)); };   // in both halves
+      auto overlap = [&](u16x2 ra, u16x2 rb, u16x2 wa, u16x2 wb) __attribute__((always_inline)) {
+        const u16x2 x = __builtin_elementwise_sub_sat(ra, rb), y = __builtin_elementwise_sub_sat(rb, ra);
+        return __builtin_elementwise_min(__builtin_elementwise_min(__builtin_elementwise_sub_sat(wb, x), __builtin_elementwise_sub_sat(wa, y)), one);
       };
-      // two groups per turn, each one's pairs fetched while the other is counted
-      u32x16 a_lo = pieces[0], a_hi = pieces[1];
-      for (uint32_t g = 0; g < n_groups; g += 2) {
-        u32x16 b_lo = a_lo, b_hi = a_hi;
-        if (g + 1 < n_groups) { b_lo = pieces[2 * g + 2]; b_hi = pieces[2 * g + 3]; }
-        group(a_lo, a_hi);
-        if (g + 1 < n_groups) {
-          if (g + 2 < n_groups) { a_lo = pieces[2 * g + 4]; a_hi = pieces[2 * g + 5]; }
-          group(b_lo, b_hi);
+      for (uint32_t x = tid; x < n; x += 1024) {
+        const u32x4 lo = records[2 * x], hi = records[2 * x + 1];
+        const uint32_t b[kPartners] = {lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        const uint2 ta = at(lo.x);
+        uint2 tb[kPartners];
+#pragma unroll
+        for (uint32_t t = 0; t < kPartners; ++t) tb[t] = at(b[t]);
+        const u16x2 wa = width2(lo.x);
+#pragma unroll
+        for (uint32_t t = 0; t < kPartners; ++t) {
+          const u16x2 wb = width2(b[t]);
+          pair01 += overlap(both(ta.x), both(tb[t].x), wa, wb);
+          pair23 += overlap(both(ta.y), both(tb[t].y), wa, wb);
         }
       }
-      n_lo += n.x;
-      n_hi += n.y;
     }
-    const uint32_t k = 2 * (w0 + lane);
-    if (w0 + lane < words) {
-      if (k < J.K && n_lo) atomicAdd(&J.out[k].n_safe, n_lo);
-      if (k + 1 < J.K && n_hi) atomicAdd(&J.out[k + 1].n_safe, n_hi);
+    const uint32_t n_stray[kAtOnce] = {stray01.x, stray01.y, stray23.x, stray23.y}, n_pair[kAtOnce] = {pair01.x, pair01.y, pair23.x, pair23.y};
+#pragma unroll
+    for (uint32_t c = 0; c < kAtOnce; ++c) {
+      uint32_t s[3] = {n_stray[c], n_real[c], n_pair[c]}, bits = rules[c];
+      for (int d = 32; d >= 1; d >>= 1) {
+#pragma unroll
+        for (uint32_t t = 0; t < 3; ++t) s[t] += (uint32_t)__shfl_xor((int)s[t], d, 64);
+        bits |= (uint32_t)__shfl_xor((int)bits, d, 64);
+      }
+      if (lane == 0) {
+#pragma unroll
+        for (uint32_t t = 0; t < 3; ++t)
+          if (s[t]) atomicAdd(&sums[c][t], s[t]);
+        if (bits) atomicOr(&sums[c][3], bits);
+      }
     }
+    __syncthreads();
+    if (tid < W.n) {
+      vl_counts VL_GLOBAL *out = as_global_rw(J.out) + failed[W.first + tid];
+      const uint32_t strays = sums[tid][0], unreal = sums[tid][1], overlaps = sums[tid][2];
+      if (strays) atomicAdd(&out->n_cons, strays);
+      if (unreal) { atomicAdd(&out->n_real, unreal); atomicOr(&out->real_bits, sums[tid][3]); }
+      if (overlaps) atomicAdd(&out->n_safe, overlaps);
+      const uint32_t kinds = (strays ? 1u : 0u) | (unreal ? 2u : 0u) | (overlaps ? 4u : 0u);
+      if (kinds) atomicOr(&out->kinds, kinds);
+    }
+    __syncthreads();   // table and sums are reused by the next unit
   }
 }
 
-__global__ void k_cnt_kinds(const DevCountJob *__restrict__ jobs) {
-  const DevCountJob &J = jobs[blockIdx.y];
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= J.K) return;
-  vl_counts &c = J.out[k];
-  c.kinds = (c.n_cons ? 1u : 0u) | (c.n_real ? 2u : 0u) | (c.n_safe ? 4u : 0u);
-}
-
-// per-device workspace: the job table (device + pinned copy) and the register tables
+// Workspaces of a device, used in turn, so that a call waits only for the one kWorkspaces calls ago.
+constexpr uint32_t kWorkspaces = 4;
 struct Work {
-  std::mutex mu;
-  DevCountJob *dev = nullptr, *host = nullptr;
-  uint32_t cap = 0;
-  void *tables = nullptr;
-  size_t tables_cap = 0;
-  hipEvent_t consumed = nullptr;   // recorded after the last kernel of a call
+  char *dev = nullptr, *host = nullptr;   // Head and job table; host: pinned
+  uint32_t cap = 0;                       // jobs
+  char *mem = nullptr;                    // verdicts, failed samples, units, tables that do not fit LDS
+  size_t mem_cap = 0;
+  hipEvent_t consumed = nullptr;          // recorded after the last kernel of a call
+  bool in_flight = false;
 };
-Work g_work[16];
+struct Works {
+  std::mutex mu;
+  Work one[kWorkspaces];
+  uint32_t turn = 0;
+};
+Works g_works[16];
 
 // Enumerates the interference pairs of the programs that do not have them yet, from the
 // intervals of their analyses (which must be complete or enqueued on `stream`): one counting
@@ -415,13 +410,13 @@ int32_t build_pairs(const std::vector<std::pair<vl_mir *, const vl_live *>> &tod
   uint64_t all = 0;
   for (size_t j = 0; j < n; ++j) {
     first_pair[j] = all;
-    all += (totals[j] + 31) & ~(uint64_t)31;   // every program's pairs start on a 256-byte boundary
+    all += (totals[j] + 7) & ~(uint64_t)7;   // every program's records start on a 256-byte boundary
   }
   if (all) {
-    e = hipMalloc(&all_pairs, (size_t)all * 8);
+    e = hipMalloc(&all_pairs, (size_t)all * 32);
     if (e != hipSuccess) return fail(e);
   }
-  for (size_t j = 0; j < n; ++j) jobs[j].pairs = totals[j] ? (uint32_t *)all_pairs + 2 * first_pair[j] : nullptr;
+  for (size_t j = 0; j < n; ++j) jobs[j].records = totals[j] ? (uint32_t *)all_pairs + 8 * first_pair[j] : nullptr;
   e = hipMemcpyAsync(jobs_dev, jobs.data(), n * sizeof(PairJob), hipMemcpyHostToDevice, stream);
   if (e == hipSuccess) {
     k_pairs<true><<<grid, 256, 0, stream>>>(jobs_dev);
@@ -438,7 +433,7 @@ int32_t build_pairs(const std::vector<std::pair<vl_mir *, const vl_live *>> &tod
     if (!block) { (void)hipFree(all_pairs); return VL_E_SHAPE; }
   }
   for (size_t j = 0; j < n; ++j) {
-    todo[j].first->edges = jobs[j].pairs;
+    todo[j].first->edges = jobs[j].records;
     todo[j].first->n_edges = totals[j];
     todo[j].first->edge_block = totals[j] ? block : nullptr;
     todo[j].first->edges_built = true;
@@ -461,8 +456,8 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
   int device = 0;
   VL_HIP(hipGetDevice(&device));
   if (device < 0 || device >= 16) return VL_E_ARG;
-  Work &w = g_work[device];
-  std::lock_guard<std::mutex> lock(w.mu);
+  Works &all = g_works[device];
+  std::lock_guard<std::mutex> lock(all.mu);
   // the pairs of programs seen for the first time (the handle is the cache: not const here)
   {
     std::vector<std::pair<vl_mir *, const vl_live *>> todo;
@@ -478,59 +473,74 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
       if (rc != VL_OK) return rc;
     }
   }
-  // the previous call's kernels must be done with the job table and the register tables
-  if (w.consumed) VL_HIP(hipEventSynchronize(w.consumed));
+  // the kernels of the call that last used this workspace must be done with it
+  Work &w = all.one[all.turn = (all.turn + 1) % kWorkspaces];
+  if (w.in_flight) VL_HIP(hipEventSynchronize(w.consumed));
+  w.in_flight = false;
   if (w.cap < n_jobs) {
     if (w.dev) (void)hipFree(w.dev);
     if (w.host) (void)hipHostFree(w.host);
     w.dev = nullptr; w.host = nullptr; w.cap = 0;
     const uint32_t cap = std::max(256u, n_jobs);
-    VL_HIP(hipMalloc((void **)&w.dev, (size_t)cap * sizeof(DevCountJob)));
-    VL_HIP(hipHostMalloc((void **)&w.host, (size_t)cap * sizeof(DevCountJob), hipHostMallocDefault));
+    VL_HIP(hipMalloc((void **)&w.dev, sizeof(Head) + (size_t)cap * sizeof(DevCountJob)));
+    VL_HIP(hipHostMalloc((void **)&w.host, sizeof(Head) + (size_t)cap * sizeof(DevCountJob), hipHostMallocDefault));
     w.cap = cap;
   }
   if (!w.consumed) VL_HIP(hipEventCreateWithFlags(&w.consumed, hipEventDisableTiming));
-  size_t bytes = 0;
-  std::vector<size_t> at(n_jobs);
-  uint32_t maxK = 0, maxV = 1, maxO = 1, max_kpad = 64;
-  uint64_t max_pairs = 0;
-  bool big_table = false;   // some table has 4 GB or more
+  uint64_t rows = 0, max_units = 0;
+  uint32_t max_v = 1;
   for (uint32_t j = 0; j < n_jobs; ++j) {
-    const uint32_t k_pad = (jobs[j].K + 63u) & ~63u;
-    at[j] = bytes;
-    bytes += (((size_t)jobs[j].mir->h.V * k_pad * 2) + 255) & ~(size_t)255;
-    maxK = std::max(maxK, jobs[j].K); maxV = std::max(maxV, jobs[j].mir->h.V); maxO = std::max(maxO, jobs[j].mir->h.O);
-    max_kpad = std::max(max_kpad, k_pad);
-    max_pairs = std::max(max_pairs, jobs[j].mir->n_edges);
-    big_table |= (uint64_t)jobs[j].mir->h.V * k_pad * 2 >= (1ull << 32);
+    const uint64_t parts = std::max<uint64_t>(1, (jobs[j].mir->n_edges + kRecordsPerPart - 1) / kRecordsPerPart);
+    rows += jobs[j].K;
+    max_units += (jobs[j].K + kAtOnce - 1) / kAtOnce * parts;
+    max_v = std::max(max_v, jobs[j].mir->h.V);
+    if (parts > 0x7FFFFFFFull) return VL_E_SHAPE;
   }
-  if (bytes > w.tables_cap) {
-    if (w.tables) (void)hipFree(w.tables);
-    w.tables = nullptr; w.tables_cap = 0;
-    VL_HIP(hipMalloc(&w.tables, bytes));
-    w.tables_cap = bytes;
+  if (rows > 0x7FFFFFFFull || max_units > 0x7FFFFFFFull) return VL_E_SHAPE;
+  static const bool lds_ok = hipFuncSetAttribute((const void *)k_cnt_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kTableBytes) == hipSuccess;
+  const size_t table_bytes = (size_t)max_v * sizeof(uint2);
+  const bool in_lds = lds_ok && table_bytes <= kTableBytes;
+  // workgroups: as many as fit the 256 compute units at once
+  const uint32_t groups = (uint32_t)std::min<uint64_t>(max_units, in_lds && table_bytes <= kTableBytes / 2 ? 512 : 256);
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t o_failed = up(rows * sizeof(vl_result)), o_units = o_failed + up(rows * 4), o_spill = o_units + up(max_units * sizeof(Unit));
+  const size_t bytes = o_spill + (in_lds ? 0 : groups * table_bytes);
+  if (bytes > w.mem_cap) {
+    if (w.mem) (void)hipFree(w.mem);
+    w.mem = nullptr; w.mem_cap = 0;
+    VL_HIP(hipMalloc((void **)&w.mem, bytes));
+    w.mem_cap = bytes;
   }
+  vl_result *const verdicts = (vl_result *)w.mem;
+  uint32_t *const failed = (uint32_t *)(w.mem + o_failed);
+  Unit *const units = (Unit *)(w.mem + o_units);
+  Head *const head = (Head *)w.dev;
+  const DevCountJob *const dev_jobs = (const DevCountJob *)(w.dev + sizeof(Head));
+  std::vector<vl_job> walk(n_jobs);
+  uint32_t at = 0;
+  memset(w.host, 0, sizeof(Head));
   for (uint32_t j = 0; j < n_jobs; ++j) {
-    DevCountJob &d = w.host[j];
+    const vl_count_job &u = jobs[j];
+    DevCountJob &d = ((DevCountJob *)(w.host + sizeof(Head)))[j];
     memset(&d, 0, sizeof(d));
-    d.mir = jobs[j].mir->dev; d.live = jobs[j].live->dev; d.cand = jobs[j].cand; d.out = jobs[j].out;
-    d.table = (uint16_t *)((char *)w.tables + at[j]);
-    d.pairs = (const uint32_t *)jobs[j].mir->edges; d.n_pairs = jobs[j].mir->n_edges;
-    d.ld = jobs[j].ld; d.K = jobs[j].K; d.k_pad = (jobs[j].K + 63u) & ~63u; d.V = jobs[j].mir->h.V;
+    d.mir = u.mir->dev; d.live = u.live->dev; d.cand = u.cand; d.out = u.out; d.verdicts = verdicts + at;
+    d.records = (const uint32_t *)u.mir->edges; d.n_records = u.mir->n_edges; d.ld = u.ld; d.K = u.K; d.fail_base = at;
+    d.parts = (uint32_t)std::max<uint64_t>(1, (u.mir->n_edges + kRecordsPerPart - 1) / kRecordsPerPart);
+    d.wide = ((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0;
+    walk[j] = vl_job{u.mir, u.live, u.cand, u.K, u.ld, verdicts + at};
+    at += u.K;
   }
-  VL_HIP(hipMemcpyAsync(w.dev, w.host, (size_t)n_jobs * sizeof(DevCountJob), hipMemcpyHostToDevice, stream));
-  const uint32_t tiles_k = max_kpad / 64, tiles_v = (maxV + 63) / 64;
-  const uint32_t stretches = (uint32_t)std::min<uint64_t>(1u << 20, std::max<uint64_t>(1, (max_pairs + kPairsPerGroup - 1) / kPairsPerGroup));
-  k_cnt_clear<<<dim3((maxK + 255) / 256, n_jobs), 256, 0, stream>>>(w.dev);
-  k_cnt_table<<<dim3(tiles_v * tiles_k, n_jobs), 256, 0, stream>>>(w.dev, tiles_k);
-  k_cnt_cons<<<dim3((maxO + 1023) / 1024, tiles_k, n_jobs), 256, 0, stream>>>(w.dev);
-  {
-    const dim3 grid(std::min(stretches, kSafeGroupsPerProgram), n_jobs);
-    if (big_table) k_cnt_safe<true><<<grid, 256, 0, stream>>>(w.dev);
-    else k_cnt_safe<false><<<grid, 256, 0, stream>>>(w.dev);
+  VL_HIP(hipMemcpyAsync(w.dev, w.host, sizeof(Head) + (size_t)n_jobs * sizeof(DevCountJob), hipMemcpyHostToDevice, stream));
+  const int32_t rc = verdicts_only(walk.data(), n_jobs, stream);
+  if (rc != VL_OK) {
+    (void)hipStreamSynchronize(stream);   // the table's upload
+    return rc;
   }
-  k_cnt_kinds<<<dim3((maxK + 255) / 256, n_jobs), 256, 0, stream>>>(w.dev);
+  k_cnt_list<<<(n_jobs + 3) / 4, 256, 0, stream>>>(dev_jobs, n_jobs, head, failed, units);
+  if (in_lds) k_cnt_rows<true><<<groups, 1024, table_bytes, stream>>>(dev_jobs, head, failed, units, nullptr, max_v);
+  else k_cnt_rows<false><<<groups, 1024, 0, stream>>>(dev_jobs, head, failed, units, (uint2 *)(w.mem + o_spill), max_v);
   VL_HIP(hipGetLastError());
   VL_HIP(hipEventRecord(w.consumed, stream));
+  w.in_flight = true;
   return VL_OK;
 }

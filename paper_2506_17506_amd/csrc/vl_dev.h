@@ -194,7 +194,7 @@ __device__ inline uint32_t bad_bits(const DevMir VL_GLOBAL &m, uint32_t attr, ui
   const uint32_t cls = attr_class(attr), width = attr_width(attr), align = attr_align(attr);
   uint32_t bad = 0;
   if (p + width > m.class_size[cls]) bad |= VL_BAD_BOUNDS;
-  if (p % align != 0) bad |= VL_BAD_ALIGN;
+  if ((align & (align - 1u)) ? p % align != 0 : (p & (align - 1u)) != 0) bad |= VL_BAD_ALIGN;
   if (m.has_reserved)
     for (uint32_t r = p; r < p + width; ++r)
       if (r < 512 && ((m.reserved[cls][r >> 5] >> (r & 31)) & 1u)) bad |= VL_BAD_RESERVED;
@@ -256,7 +256,7 @@ struct vl_mir {
   uint64_t magic;
   // interference pairs (a < b, one class, some point in common), built on first use by the
   // all-violations mode and kept for the life of the handle: they depend on the program only
-  void *edges = nullptr;       // device: n_edges pairs of uint32, inside edge_block
+  void *edges = nullptr;       // device: n_edges records of eight words (vl_count.hip), inside edge_block
   uint64_t n_edges = 0;
   bool edges_built = false;
   vl::EdgeBlock *edge_block = nullptr;   // the allocation the pairs sit in, shared with the other programs of that call
@@ -282,6 +282,8 @@ struct vl_live {
 namespace vl {
 constexpr uint64_t kMirMagic = 0x564c4d4952ull, kLiveMagic = 0x564c4c495645ull;
 int32_t hip_fail(hipError_t e);
+// vl_verify_multi without the search for the pair of a safety violation (vl_verify.hip)
+int32_t verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream);
 #define VL_HIP(call)                                   \
   do {                                                 \
     hipError_t e_ = (call);                            \

@@ -1121,7 +1121,7 @@ extern "C" int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_su
 
 namespace {
 // the walk and the pair search over the job table L.dev with the board L.board
-int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool transposed) {
+int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool transposed, bool with_pairs) {
   const bool narrow = L.max_rows <= kPitchNarrow;   // every group of every job fits the narrow ring
   const size_t lds = (size_t)L.max_words * 64 * 4 + 64 * 4 + 1024 + (size_t)kRing * (narrow ? kPitchNarrow : kPitchWide) * 2;
   if (g_time_start) VL_HIP(hipEventRecord(g_time_start, stream));
@@ -1142,6 +1142,8 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
 #undef VL_WALK
   if (g_time_stop) VL_HIP(hipEventRecord(g_time_stop, stream));
   g_time_start = g_time_stop = nullptr;
+  VL_HIP(hipGetLastError());
+  if (!with_pairs) return VL_OK;
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
   (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
       L.dev, n_jobs, L.one, per_group);
@@ -1149,7 +1151,7 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   return VL_OK;
 }
 
-int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, bool transposed) {
+int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, bool transposed, bool with_pairs = true) {
   if (!jobs) return VL_E_NULL;
   if (n_jobs == 0 || n_jobs > 65535) return VL_E_SHAPE;
   int device = 0;
@@ -1160,9 +1162,13 @@ int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, boo
   Launch L;
   const int32_t rc = prepare_jobs(jobs, n_jobs, stream, s, L, transposed);
   if (rc != VL_OK) return rc;
-  return launch_all(L, n_jobs, stream, transposed);
+  return launch_all(L, n_jobs, stream, transposed, with_pairs);
 }
 }  // namespace
+
+int32_t vl::verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream) {
+  return verify_jobs(jobs, n_jobs, stream, false, false);
+}
 
 extern "C" int32_t vl_verify_multi(const vl_job *jobs, uint32_t n_jobs, vl_stream stream) {
   return verify_jobs(jobs, n_jobs, (hipStream_t)stream, false);
@@ -1219,5 +1225,5 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
   }
   L.one = d;
   L.board = Board{sc->arrived, sc->keys};
-  return launch_all(L, 1, stream, false);
+  return launch_all(L, 1, stream, false, true);
 }

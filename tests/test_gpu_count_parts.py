@@ -1,0 +1,68 @@
+"""All-violations counts where the work is cut: 0 to 9 failed samples (units of four), programs
+whose pairs fill several parts, row pitches that allow 16-byte reads or not, a program with more
+vregs than the table in LDS holds (19,456); against the oracle, exactly."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2506_17506_amd as vl  # noqa: E402
+from oracle import vlo  # noqa: E402
+from vlgen import gen  # noqa: E402
+from vlgen.mixed import mixed_mir  # noqa: E402
+from test_gpu_parity import free, gpu_analyze  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    vl.load()
+
+
+def compare(m, row_sets, pitches=(0,)):
+    an = vlo.analyze(m, threads=8)
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        for rows in row_sets:
+            want = vlo.count_violations(m, an, rows, threads=8)
+            K = rows.shape[0]
+            for extra in pitches:
+                ld = (m.n_occ + 7) // 8 * 8 + extra
+                host = np.zeros((K, ld), np.uint16)
+                host[:, :m.n_occ] = rows
+                dev = torch.from_numpy(host.view(np.int16)).cuda()
+                out = torch.full((K, 8), -1, dtype=torch.int32, device="cuda")
+                for _ in range(2):
+                    vl.vl_count_violations_multi([(hm[0], hl[0], dev, K, ld, out)])
+                torch.cuda.synchronize()
+                got = out.cpu().numpy().view(np.uint32)
+                for c, name in enumerate(("kinds", "n_cons", "n_real", "n_safe", "real_bits")):
+                    assert (got[:, c] == want[name]).all(), (m.name, K, extra, name)
+    finally:
+        free(hm, hl)
+
+
+def test_failed_samples_and_parts():
+    k = gen.Kernel(gen.MHA, 0xC0DE, 3001, 2250)
+    rows, log = k.candidates(77, 24, 12, 2)
+    good, bad = rows[log["kind"] == 0], rows[log["kind"] != 0]
+    assert len(good) == 12 and len(bad) == 12
+    rng = np.random.default_rng(3)
+    wild = rng.integers(0, 600, (9, k.mir.n_occ)).astype(np.uint16)   # everything wrong at once
+    sets = [np.ascontiguousarray(np.concatenate([good[:3], bad[:n]])) for n in (0, 1, 3, 4, 5, 8, 9)] + [good[:1], bad[:1], wild]
+    compare(k.mir, sets, pitches=(0, 1, 8))
+
+
+def test_mixed_shapes():
+    m = mixed_mir(0xC300, n_instr=900, reserved=True)
+    rng = np.random.default_rng(4)
+    compare(m, [rng.integers(0, 64, (70, m.n_occ)).astype(np.uint16)], pitches=(0, 3))
+
+
+def test_more_vregs_than_lds():
+    k = gen.Kernel(gen.STRAIGHT, 0xC0DF, 20000, 20000)
+    rows, _ = k.candidates(5, 6, 4, 1)
+    compare(k.mir, [rows])
