@@ -37,9 +37,7 @@ struct DevMir {
   const uint32_t VL_GLOBAL *instr_blk;       // [N] block of each instruction
   const uint32_t VL_GLOBAL *vattr;           // [V] packed attributes, see attr_* below
   const uint8_t VL_GLOBAL *occ_flags;        // [O]
-  const uint64_t VL_GLOBAL *occ_rec;         // [O] vreg | (instruction << 2 | DEF/USE flags) << 32: one read instead of three
-  const uint8_t VL_GLOBAL *instr_keep;       // [N] 1 iff the instruction has an early-clobber definition: what it reads
-                                             // stays occupied through it
+  const uint64_t VL_GLOBAL *occ_rec;         // [O] vreg | kRecKeeps | (instruction << 2 | DEF/USE flags) << 32: one read instead of three
   // a program made by vl_mir_create_lanes (every lane of a partly accessed vreg a value of its own): for
   // each of its occurrences the caller's occurrence, for each of its values the caller's vreg; else null
   const uint32_t VL_GLOBAL *occ_src;         // [O]
@@ -49,6 +47,10 @@ struct DevMir {
   uint16_t class_word[kMaxClass];  // first occupancy word of the class
   uint32_t reserved[kMaxClass][16];
 };
+
+// (in an occurrence's record) its instruction has an early-clobber definition: what it reads stays
+// occupied through it
+constexpr uint32_t kRecKeeps = 1u << 31;
 
 // Packed vreg attributes: class | (width-1) << 3 | (align-1) << 8 | straddle << 13.
 // straddle = a correctly aligned tuple may cross a 32-register word.
@@ -116,6 +118,8 @@ constexpr uint32_t kSeedLinked = 1u << 28; // (tile live-in lists only) the vreg
 // Per-occurrence roles computed by the event kernel.
 constexpr uint8_t kRolePreKill = 1, kRoleTestSet = 2, kRolePostKill = 4, kRoleFirst = 8;
 constexpr uint8_t kRoleKill = 16;   // the occurrence's kill flag, copied to occ_kill in occurrence order later
+constexpr uint32_t kEntBlockStart = 1u << 30;   // the entry's instruction is the first of its block
+constexpr uint32_t kEntVreg = kEntBlockStart - 1;   // the vreg itself
 // Per sorted-entry info bits.
 constexpr uint8_t kEntLiveAfter = 1, kEntHasUse = 2, kEntHasDef = 4, kEntGroupStart = 8,
                   kEntKept = 16;   // read by an instruction with an early-clobber definition: in P(i) whatever follows
@@ -127,9 +131,9 @@ struct DevLive {
   uint32_t VL_GLOBAL *vcur;       // [V] placement cursors
   uint32_t VL_GLOBAL *last_live;  // [V] last block the vreg is live into (0: none after the entry)
   uint32_t VL_GLOBAL *vocc_tmp;   // [O] occurrences grouped by vreg, unordered
-  uint32_t VL_GLOBAL *vocc;       // [O] occurrences grouped by vreg, ascending
-  uint32_t VL_GLOBAL *ent_instr;  // [O] instruction << 2 | occurrence flags of each sorted entry (ascending per vreg)
-  uint32_t VL_GLOBAL *ent_v;      // [O] vreg of each sorted entry
+  uint32_t VL_GLOBAL *vocc;       // [O] the same, ascending per vreg (only where the large-program sort runs)
+  u32x4 VL_GLOBAL *ent;           // [O] the entries, grouped by vreg and ascending: occurrence, instruction << 2 | occurrence
+                                  //     flags, vreg | kRecKeeps | kEntBlockStart, block of the instruction
   uint8_t VL_GLOBAL *ent_info;    // [O] kEnt* bits of each sorted entry
   uint32_t VL_GLOBAL *first;      // [V] first occurrence or kNone
   uint32_t VL_GLOBAL *prev_occ;   // [O] previous occurrence of the same vreg, written only where the 16-bit

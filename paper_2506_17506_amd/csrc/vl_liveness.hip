@@ -26,11 +26,11 @@ namespace {
 
 template <class P> __device__ inline bool bit_get(P row, uint32_t v) { return (row[v >> 5] >> (v & 31)) & 1u; }
 
-// first index in [lo,hi) with a[idx] >= key
-template <class P> __device__ inline uint32_t lower_bound(P a, uint32_t lo, uint32_t hi, uint32_t key) {
+// first of the entries [lo, hi) of a vreg that is at instruction `at` or later
+__device__ inline uint32_t first_entry_at(const DevLive VL_GLOBAL &L, uint32_t lo, uint32_t hi, uint32_t at) {
   while (lo < hi) {
     uint32_t mid = (lo + hi) >> 1;
-    if (a[mid] < key) lo = mid + 1; else hi = mid;
+    if ((L.ent[mid].y >> 2) < at) lo = mid + 1; else hi = mid;
   }
   return lo;
 }
@@ -187,12 +187,7 @@ __device__ inline void f_sort_short(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
   const uint32_t lo = L.vcnt[v], len = L.vcnt[v + 1] - lo;
   if (len == 0) { L.first[v] = kNone; return; }
   if (len > kShortList) return;
-  // (the vreg of each sorted entry is recorded too, for the kernels that walk the entries)
-  auto put = [&](uint32_t at, uint32_t x) {
-    L.vocc[at] = x;
-    L.ent_v[at] = v;
-    if (at == lo) L.first[v] = x;
-  };
+  auto put = [&](uint32_t at, uint32_t x) { L.vocc[at] = x; };
   if (len <= 8) {
     // the common case: all loads issued at once, ranks computed in registers (absent
     // elements are larger than any occurrence index)
@@ -271,8 +266,6 @@ __device__ inline void f_sort_long(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL 
           uint32_t b = __ffs(bits) - 1;
           bits &= bits - 1;
           uint32_t x = wb + w * 32 + b;
-          if (pos == lo) L.first[v] = x;
-          L.ent_v[pos] = v;
           L.vocc[pos++] = x;
         }
       }
@@ -290,134 +283,298 @@ __global__ __launch_bounds__(256) void k_sort(MIRS) {
   else f_sort_short(m, L, blockIdx.x - kLongBlocks, threadIdx.x);
 }
 
-// ---- 2. block summaries ---------------------------------------------------------------
-// def[b]: vregs written in b.  use[b]: vregs whose first mention in b reads them
-// (an instruction reads before it writes).
-// Each workgroup takes a slice of the sorted entries, whose vregs span a narrow range of
-// bitset words.  The bits are collected in an LDS table [block][word of the range] and each
-// non-zero word goes to memory once; when the table would not fit, runs of equal
-// (block, word) are combined by shuffles and every run issues its own atomics.
-constexpr uint32_t kSumSlice = 1024, kSumThreads = 256;   // measured: 4096 / 1024 took 58 us, this 45 us, smaller no less
-constexpr uint32_t kSumWords = kSumSlice / 32 + 1;   // most words a slice can touch
+// The usual way: a workgroup per 16,384 occurrences of a program, all of which count the whole
+// program: the LDS of each then holds, a word per vreg, first the list lengths, then the lists'
+// starts, then the places its own occurrences go to (the starts plus what earlier workgroups place),
+// and nothing is cleared, reserved or prefixed in memory, nor in a launch of its own.  Occurrences
+// are placed 1,024 at a time, with a barrier in between: what is out of order in a list
+// afterwards lies within one such round, and the next kernel puts it right.  It also clears what
+// the later kernels add to.
+// What bounds it: LDS atomics and the placing stores, 64 lines per wavefront, of the largest
+// programs (256 programs of 1,000-20,000 instructions: 50 us; a workgroup per program 58 us;
+// clearing, counting, scanning and placing in launches of their own 86 us).
+constexpr uint32_t kRound = 1024;
+constexpr uint32_t kGroupSlice = 16 * kRound;
+constexpr uint32_t kGroupMaxOcc = 1u << 17;   // with more in some program, counting it all in every workgroup costs too much
+__global__ __launch_bounds__(1024) void k_group(MIRS) {
+  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
+  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  extern __shared__ uint32_t sm[];   // [V]
+  __shared__ uint32_t part[16];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t s0 = blockIdx.x * kGroupSlice, n_slices = max(1u, (m.O + kGroupSlice - 1) / kGroupSlice), s1 = min(m.O, s0 + kGroupSlice);
+  if (blockIdx.x >= n_slices) return;
+  auto add_all = [&](uint32_t end) {   // sm[v] += mentions among the occurrences [0, end)
+    for (uint32_t o = tid * 4; o < end; o += 4 * 4 * 1024) {
+      u32x4 v[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        const uint32_t x = o + u * 4 * 1024;
+        v[u] = kNone;
+        if (x + 4 <= end) v[u] = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + x);
+        else {
+          if (x < end) v[u].x = m.occ_vreg[x];
+          if (x + 1 < end) v[u].y = m.occ_vreg[x + 1];
+          if (x + 2 < end) v[u].z = m.occ_vreg[x + 2];
+        }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u)
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t)
+          if (v[u][t] != kNone) atomicAdd(&sm[v[u][t]], 1u);
+    }
+  };
+  for (uint32_t v = tid; v < m.V; v += 1024) sm[v] = 0;
+  __syncthreads();
+  add_all(m.O);
+  // (the regions are whole vectors long)
+  const uint32_t vecs = (m.B * m.W + 3u) / 4u;
+  const u32x4 none = {0, 0, 0, 0};
+  for (uint32_t x = blockIdx.x * 1024 + tid; x < vecs; x += n_slices * 1024) {
+    reinterpret_cast<u32x4 VL_GLOBAL *>(L.use)[x] = none;
+    reinterpret_cast<u32x4 VL_GLOBAL *>(L.def)[x] = none;
+    reinterpret_cast<u32x4 VL_GLOBAL *>(L.live_in)[x] = none;
+  }
+  if (blockIdx.x == 0 && tid < kCounters) L.counters[tid] = 0;
+  __syncthreads();
+  // exclusive prefix: a contiguous run of vregs per thread
+  const uint32_t per = (m.V + 1023u) / 1024u, lo = min(m.V, tid * per), hi = min(m.V, lo + per);
+  uint32_t sum = 0;
+#pragma unroll 4
+  for (uint32_t v = lo; v < hi; ++v) sum += sm[v];
+  uint32_t incl = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
+    if ((int)lane >= d) incl += y;
+  }
+  if (lane == 63) part[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+  for (uint32_t k = 0; k < wave; ++k) run += part[k];
+#pragma unroll 4
+  for (uint32_t v = lo; v < hi; ++v) {
+    const uint32_t c = sm[v];
+    sm[v] = run;
+    run += c;
+  }
+  __syncthreads();
+  for (uint32_t v = blockIdx.x * 1024 + tid; v < m.V; v += n_slices * 1024) {
+    const uint32_t at = sm[v], next = v + 1 < m.V ? sm[v + 1] : m.O;
+    L.vcnt[v] = at;
+    L.last_live[v] = 0;
+    if (at == next) L.first[v] = kNone;
+  }
+  if (blockIdx.x == 0 && tid == 0) L.vcnt[m.V] = m.O;
+  __syncthreads();
+  add_all(min(s0, m.O));
+  __syncthreads();
+  // the vregs of the next two rounds are in flight
+  auto vreg_of = [&](uint32_t o) { return o < s1 ? m.occ_vreg[o] : 0u; };
+  uint32_t v0 = vreg_of(s0 + tid), v1 = vreg_of(s0 + kRound + tid);
+  for (uint32_t o0 = s0; o0 < s1; o0 += kRound) {
+    const uint32_t v2 = vreg_of(o0 + 2 * kRound + tid), o = o0 + tid;
+    if (o < s1) L.vocc_tmp[atomicAdd(&sm[v0], 1u)] = o;
+    v0 = v1;
+    v1 = v2;
+    // the round's places are taken before the next round takes any (no wait for the stores)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+}
 
-__global__ __launch_bounds__(kSumThreads) void k_summary(MIRS, const uint32_t lds_words) {
+// ---- 2. entries in order, block summaries -------------------------------------------------
+// A workgroup takes a stretch of the grouped occurrences, puts it in order, writes the entry records
+// and collects its share of the block summaries.
+//
+// Order: a list is a row of groups, one per round of 1,024 occurrences in which it was filled;
+// groups follow each other, inside a group the order is open.  An entry's place is its group's
+// first plus the smaller ones in the group (some six entries, read from LDS, where the stretch
+// lies with a margin on both sides; where groups begin is a bit per place).  A group that reaches beyond the margin (a value mentioned more than a hundred times in
+// 1,024 occurrences) is ranked by a bitmap of its round.  kSorted: the lists already ascend (the
+// large-program sort ran).
+//
+// Summaries: def[b]: vregs written in b.  use[b]: vregs whose first mention in b reads them
+// (an instruction reads before it writes).  The stretch's vregs span a narrow range of bitset
+// words; the bits are collected in an LDS table [block][word of the range] and each non-zero word
+// goes to memory once; when the table would not fit, every entry issues its own atomics.
+//
+// (A launch that sorted each list in the registers of a lane and one that summarised the sorted
+// entries took 38 and 45 us where this takes 70, but this needs no sorted list and no cleared counters.)
+constexpr uint32_t kOrdStretch = 1024, kOrdThreads = 256;
+constexpr uint32_t kOrdBack = 72;        // entries before the stretch that are put in order too: one more than an instruction has
+constexpr uint32_t kOrdMargin = 128;
+constexpr uint32_t kOrdWindow = kOrdBack + kOrdStretch + 2 * kOrdMargin;
+constexpr uint32_t kOrdPer = (kOrdWindow + kOrdThreads - 1) / kOrdThreads;
+constexpr uint32_t kOrdWords = kOrdStretch / 32 + 1;   // most words a stretch can touch
+static_assert(kOrdBack > kMaxOperands, "the look-back has to leave an instruction");
+
+template <bool kSorted>
+__global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_words) {
   const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
   DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
   extern __shared__ uint32_t sm[];
-  const uint32_t s0 = blockIdx.x * kSumSlice;
+  // by place in the window; s_o holds the occurrences as they stand, then in order with kRecKeeps
+  __shared__ uint32_t s_o[kOrdWindow], s_v[kOrdWindow], s_ifl[kOrdWindow], s_blk[kOrdWindow];
+  __shared__ uint32_t heads[kOrdPer * kOrdThreads / 32 + 1];   // a bit per place: a group begins here
+  __shared__ uint32_t bits[kRound / 32], n_edge, crossing;
+  const uint32_t s0 = blockIdx.x * kOrdStretch, tid = threadIdx.x;
   if (s0 >= m.O) return;
-  const uint32_t s1 = min(m.O, s0 + kSumSlice);
-  const int lane = threadIdx.x & 63;
-  // (vregs that are never mentioned take no entries but widen the range: a slice whose
-  // table would not fit in the LDS given takes the other path)
-  const uint32_t w_lo = L.ent_v[s0] >> 5, nw = (L.ent_v[s1 - 1] >> 5) - w_lo + 1;
-  const bool lds = (size_t)2 * m.B * nw <= lds_words;
-  if (lds) {
-    for (uint32_t x = threadIdx.x; x < 2 * m.B * nw; x += kSumThreads) sm[x] = 0;
+  const uint32_t s1 = min(m.O, s0 + kOrdStretch);
+  const uint32_t x_lo = s0 - min(s0, kOrdBack);                                           // first entry put in order
+  const uint32_t w_lo = x_lo - min(x_lo, kOrdMargin), w_hi = min(m.O, s1 + kOrdMargin);   // the window
+  const uint32_t n_win = w_hi - w_lo;
+  const uint32_t VL_GLOBAL *const src = kSorted ? L.vocc : L.vocc_tmp;
+  uint32_t o[kOrdPer], v[kOrdPer], ifl[kOrdPer], to[kOrdPer];   // v with kRecKeeps
+  {
+    uint64_t rec[kOrdPer];
+#pragma unroll
+    for (uint32_t u = 0; u < kOrdPer; ++u) {
+      const uint32_t r = u * kOrdThreads + tid;
+      o[u] = r < n_win ? src[w_lo + r] : kNone;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kOrdPer; ++u) rec[u] = o[u] != kNone ? m.occ_rec[o[u]] : 0ull;
+#pragma unroll
+    for (uint32_t u = 0; u < kOrdPer; ++u) {
+      const uint32_t r = u * kOrdThreads + tid;
+      v[u] = (uint32_t)rec[u];
+      ifl[u] = (uint32_t)(rec[u] >> 32);
+      if (r < n_win) { s_o[r] = o[u]; s_v[r] = v[u] & ~kRecKeeps; }
+    }
+  }
+  if (tid == 0) { crossing = 0; n_edge = 0; }
+  if (tid < kRound / 32) bits[tid] = 0;
+  for (uint32_t x = tid; x < min(2 * m.B * kOrdWords, lds_words); x += kOrdThreads) sm[x] = 0;
+  __syncthreads();
+  const uint32_t edge_v[2] = {s_v[0], s_v[n_win - 1]}, edge_round[2] = {s_o[0] / kRound, s_o[n_win - 1] / kRound};
+#pragma unroll
+  for (uint32_t u = 0; u < kOrdPer; ++u) {
+    const uint32_t r = u * kOrdThreads + tid;
+    const bool head = r >= n_win || r == 0 || s_v[r - 1] != (v[u] & ~kRecKeeps) || s_o[r - 1] / kRound != o[u] / kRound;
+    const uint64_t bits64 = __ballot(head);
+    if ((tid & 63u) == 0) { heads[r >> 5] = (uint32_t)bits64; heads[(r >> 5) + 1] = (uint32_t)(bits64 >> 32); }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t u = 0; u < kOrdPer; ++u) {
+    const uint32_t r = u * kOrdThreads + tid;
+    to[u] = r < n_win ? r : kNone;
+    if (kSorted || r >= n_win) continue;
+    // the group [from, end)
+    const uint32_t upto = (2u << (r & 31)) - 1u;   // the bits up to r's
+    uint32_t w = r >> 5, h = heads[w] & upto;
+    while (!h) h = heads[--w];                      // (place 0 is a head)
+    const uint32_t from = w * 32u + 31u - (uint32_t)__clz(h);
+    w = r >> 5;
+    h = heads[w] & ~upto;
+    while (!h && w < kOrdWindow / 32) h = heads[++w];
+    const uint32_t end = min(n_win, h ? w * 32u + (uint32_t)__ffs(h) - 1u : n_win);
+    uint32_t smaller = 0, y = from;
+    for (; y + 4 <= end; y += 4)
+      smaller += (s_o[y] < o[u]) + (s_o[y + 1] < o[u]) + (s_o[y + 2] < o[u]) + (s_o[y + 3] < o[u]);
+    for (; y < end; ++y) smaller += s_o[y] < o[u];
+    to[u] = from + smaller;
+    // (a group that stays in the margin may go on outside: its places are not looked at)
+    const uint32_t crosses = (from == 0 && w_lo > 0 && end > x_lo - w_lo ? 1u : 0u) | (end == n_win && w_hi < m.O && from < s1 - w_lo ? 2u : 0u);
+    if (crosses) atomicOr(&crossing, crosses);
+  }
+  __syncthreads();
+  for (uint32_t side = 0; side < 2; ++side) {
+    if (kSorted || !(crossing & (1u << side))) continue;   // the same for the whole workgroup
+    // the group at this edge of the window goes on outside (it may also just end here)
+    constexpr uint32_t kFar = kRound / kOrdThreads;
+    uint32_t far_o[kFar], far_v[kFar], far_ifl[kFar], n_far = 0, n_near = 0;
+    auto mark = [&](uint32_t x) { atomicOr(&bits[(x % kRound) >> 5], 1u << (x & 31)); };
+    auto member = [&](uint32_t x, uint32_t rec_v) { return x != kNone && x / kRound == edge_round[side] && (rec_v & ~kRecKeeps) == edge_v[side]; };
+#pragma unroll
+    for (uint32_t u = 0; u < kFar; ++u) {
+      const uint32_t d = u * kOrdThreads + tid;
+      const bool in = side == 0 ? d < w_lo : d < m.O - w_hi;
+      far_o[u] = in ? src[side == 0 ? w_lo - 1 - d : w_hi + d] : kNone;
+      const uint64_t rec = in ? m.occ_rec[far_o[u]] : 0ull;
+      far_v[u] = (uint32_t)rec;
+      far_ifl[u] = (uint32_t)(rec >> 32);
+      if (!member(far_o[u], far_v[u])) far_o[u] = kNone;
+      if (far_o[u] != kNone) { ++n_far; mark(far_o[u]); }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kOrdPer; ++u)
+      if (member(o[u], v[u])) { ++n_near; mark(o[u]); }
+    const uint32_t mine = side == 0 ? n_far : n_near;
+    if (mine) atomicAdd(&n_edge, mine);
+    __syncthreads();
+    const uint32_t first = side == 0 ? 0u - n_edge : n_win - n_edge;   // the group's first place (may wrap below zero)
+    auto place = [&](uint32_t x) {
+      const uint32_t word = (x % kRound) >> 5;
+      uint32_t below = __popc(bits[word] & ((1u << (x & 31)) - 1u));
+      for (uint32_t k = 0; k < word; ++k) below += __popc(bits[k]);
+      return first + below;
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < kOrdPer; ++u)
+      if (member(o[u], v[u])) to[u] = place(o[u]);
+#pragma unroll
+    for (uint32_t u = 0; u < kFar; ++u) {
+      const uint32_t at = far_o[u] != kNone ? place(far_o[u]) : kNone;
+      if (at < n_win) { s_o[at] = far_o[u] | (far_v[u] & kRecKeeps); s_ifl[at] = far_ifl[u]; }
+    }
+    __syncthreads();
+    if (tid < kRound / 32) bits[tid] = 0;
+    if (tid == 0) n_edge = 0;
     __syncthreads();
   }
-  uint32_t *def_l = sm, *use_l = sm + m.B * nw;
-  // the lane's entries of the slice, each a chain of three dependent reads (occurrence, its
-  // record, its block): the chains run side by side
-  constexpr uint32_t kPer = kSumSlice / kSumThreads;
-  uint64_t recs[kPer];
-  uint32_t blks[kPer];
-  {
-    uint32_t occ[kPer];
 #pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) {
-      const uint32_t e = s0 + u * kSumThreads + threadIdx.x;
-      occ[u] = e < s1 ? L.vocc[e] : kNone;
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) recs[u] = occ[u] != kNone ? m.occ_rec[occ[u]] : 0ull;
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) blks[u] = occ[u] != kNone ? m.instr_blk[(uint32_t)(recs[u] >> 34)] : kNone;
-  }
-  // the three entries below the wavefront's first one, held by lanes 0..2 (lane l: the entry
-  // l + 1 below), for the lanes whose earlier neighbours are not in this wavefront
-  uint64_t below_rec[kPer];
-  uint32_t below_blk[kPer];
-  {
-    uint32_t occ[kPer];
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) {
-      const uint32_t wave_first = s0 + u * kSumThreads + (threadIdx.x & ~63u);
-      occ[u] = (lane < 3 && wave_first < s1 && wave_first >= (uint32_t)lane + 1u) ? L.vocc[wave_first - 1u - lane] : kNone;
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) below_rec[u] = occ[u] != kNone ? m.occ_rec[occ[u]] : ~0ull;   // none: another vreg
-#pragma unroll
-    for (uint32_t u = 0; u < kPer; ++u) below_blk[u] = occ[u] != kNone ? m.instr_blk[(uint32_t)(below_rec[u] >> 34)] : kNone;
-  }
-#pragma unroll
-  for (uint32_t u = 0; u < kPer; ++u) {
-    const uint32_t e0 = s0 + u * kSumThreads;
-    if (e0 >= s1) break;
-    const uint32_t e = e0 + threadIdx.x;
-    uint32_t b = kNone, w = 0, dbits = 0, ubits = 0, v = kNone, i = kNone, fl = 0;
-    if (e < s1) {
-      // also records instruction and flags of each sorted entry for the kernels that follow
-      const uint64_t rec = recs[u];
-      v = (uint32_t)rec;
-      const uint32_t ifl = (uint32_t)(rec >> 32);
-      L.ent_instr[e] = ifl;
-      i = ifl >> 2;
-      fl = ifl & 3u;
-      b = blks[u];
-      w = v >> 5;
-      if (fl & VL_OCC_DEF) dbits = 1u << (v & 31);
-    }
-    // Is this mention group the first of its vreg in the block?  The nearest earlier entry
-    // with another instruction decides; it usually sits an entry or two below.
-    bool decided = !(fl & VL_OCC_USE), first_in_block = false;
-    const uint32_t bv = (uint32_t)below_rec[u], bi = (uint32_t)(below_rec[u] >> 34), bb = below_blk[u];
-    for (int d = 1; d <= 3; ++d) {
-      uint32_t pv = __shfl_up(v, d, 64), pi = __shfl_up(i, d, 64), pb = __shfl_up(b, d, 64);
-      const int src = (d - 1 - lane) & 63;   // for the lanes below d: the lane that holds their entry d below
-      const uint32_t hv = __shfl(bv, src, 64), hi = __shfl(bi, src, 64), hb = __shfl(bb, src, 64);
-      if (lane < d) { pv = hv; pi = hi; pb = hb; }
-      if (!decided) {
-        if (pv != v) { first_in_block = true; decided = true; }
-        else if (pi != i) { first_in_block = pb != b; decided = true; }
-      }
-    }
-    if (!decided) {   // four or more mentions in one instruction: look the start of the group up
-      const uint32_t lo = L.vcnt[v];
-      uint32_t gs = e;
-      while (gs > lo && (uint32_t)(m.occ_rec[L.vocc[gs - 1]] >> 34) == i) --gs;
-      first_in_block = gs == lo || m.instr_blk[(uint32_t)(m.occ_rec[L.vocc[gs - 1]] >> 34)] != b;
-    }
-    if ((fl & VL_OCC_USE) && first_in_block) ubits = 1u << (v & 31);
-    if (lds) {
-      if (dbits) atomicOr(&def_l[b * nw + (w - w_lo)], dbits);
-      if (ubits) atomicOr(&use_l[b * nw + (w - w_lo)], ubits);
-      continue;
-    }
-    // entries are sorted by vreg, then instruction: neighbours in a wavefront mostly hit
-    // the same word of the same block.  OR them together along runs of equal (block, word)
-    // and let the last lane of each run issue the atomics.
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t pb = __shfl_up(b, d, 64), pw = __shfl_up(w, d, 64);
-      const uint32_t pd = __shfl_up(dbits, d, 64), pu = __shfl_up(ubits, d, 64);
-      // a run of equal keys is contiguous, so equality with the lane d below means the
-      // whole span in between belongs to the run
-      if (lane >= d && pb == b && pw == w) { dbits |= pd; ubits |= pu; }
-    }
-    const uint32_t nb = __shfl_down(b, 1, 64), nxw = __shfl_down(w, 1, 64);
-    const bool last = lane == 63 || nb != b || nxw != w;
-    if (b != kNone && last) {
-      if (dbits) atomicOr(&L.def[(size_t)b * m.W + w], dbits);
-      if (ubits) atomicOr(&L.use[(size_t)b * m.W + w], ubits);
-    }
-  }
-  if (!lds) return;
+  for (uint32_t u = 0; u < kOrdPer; ++u)
+    if (to[u] < n_win) { s_o[to[u]] = o[u] | (v[u] & kRecKeeps); s_ifl[to[u]] = ifl[u]; }
   __syncthreads();
-  // the first and the last word of the range may be shared with the neighbouring slices
-  for (uint32_t x = threadIdx.x; x < m.B * nw; x += kSumThreads) {
-    const uint32_t blk = x / nw, w = w_lo + x % nw;
-    if (def_l[x]) atomicOr(&L.def[(size_t)blk * m.W + w], def_l[x]);
-    if (use_l[x]) atomicOr(&L.use[(size_t)blk * m.W + w], use_l[x]);
+  constexpr uint32_t kOrdered = (kOrdBack + kOrdStretch + kOrdThreads - 1) / kOrdThreads;
+  uint32_t blk[kOrdered];
+  bool starts[kOrdered];
+#pragma unroll
+  for (uint32_t u = 0; u < kOrdered; ++u) {
+    const uint32_t e = x_lo + u * kOrdThreads + tid;
+    blk[u] = e < s1 ? m.instr_blk[s_ifl[e - w_lo] >> 2] : 0u;
+  }
+#pragma unroll
+  for (uint32_t u = 0; u < kOrdered; ++u) {
+    const uint32_t e = x_lo + u * kOrdThreads + tid;
+    if (e < s1) s_blk[e - w_lo] = blk[u];
+    starts[u] = e < s1 && m.blk_start[blk[u]] == s_ifl[e - w_lo] >> 2;
+  }
+  __syncthreads();
+  // (vregs that are never mentioned take no entries but widen the range)
+  const uint32_t word0 = s_v[s0 - w_lo] >> 5, n_words = (s_v[s1 - 1 - w_lo] >> 5) - word0 + 1;
+  const bool table = (size_t)2 * m.B * n_words <= lds_words;
+  uint32_t *const def_l = sm, *const use_l = sm + m.B * n_words;
+#pragma unroll
+  for (uint32_t u = 0; u < kOrdered; ++u) {
+    const uint32_t e = x_lo + u * kOrdThreads + tid, r = e - w_lo;
+    if (e < s0 || e >= s1) continue;
+    const uint32_t ev = s_v[r], eo = s_o[r], ei = s_ifl[r];
+    L.ent[e] = u32x4{eo & ~kRecKeeps, ei, ev | (eo & kRecKeeps) | (starts[u] ? kEntBlockStart : 0u), blk[u]};
+    if (e == 0 || s_v[r - 1] != ev) L.first[ev] = eo & ~kRecKeeps;
+    bool reads_first = false;   // is this mention group the first of its vreg in the block, and does it read?
+    if (ei & VL_OCC_USE) {
+      uint32_t x = r;   // (kOrdBack: the walk leaves the instruction before it leaves what is in order)
+      while (x + w_lo > 0 && s_v[x - 1] == ev && (s_ifl[x - 1] >> 2) == (ei >> 2)) --x;
+      reads_first = x + w_lo == 0 || s_v[x - 1] != ev || s_blk[x - 1] != blk[u];
+    }
+    const uint32_t bit = 1u << (ev & 31), at = blk[u] * n_words + (ev >> 5) - word0;
+    if (table) {
+      if (ei & VL_OCC_DEF) atomicOr(&def_l[at], bit);
+      if (reads_first) atomicOr(&use_l[at], bit);
+    } else {
+      if (ei & VL_OCC_DEF) atomicOr(&L.def[(size_t)blk[u] * m.W + (ev >> 5)], bit);
+      if (reads_first) atomicOr(&L.use[(size_t)blk[u] * m.W + (ev >> 5)], bit);
+    }
+  }
+  if (!table) return;
+  __syncthreads();
+  // the first and the last word of the range may be shared with the neighbouring stretches
+  for (uint32_t x = tid; x < m.B * n_words; x += kOrdThreads) {
+    const size_t at = (size_t)(x / n_words) * m.W + word0 + x % n_words;
+    if (def_l[x]) atomicOr(&L.def[at], def_l[x]);
+    if (use_l[x]) atomicOr(&L.use[at], use_l[x]);
   }
 }
 
@@ -576,30 +733,30 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   // and after it) are looked at many times: the workgroup's stretch of entries plus a halo
   // on both sides is staged in LDS once, and only what lies beyond the halo is read from
   // memory.
-  __shared__ uint32_t s_ifl[kEvtWindow], s_occ[kEvtWindow], s_v[kEvtWindow];
+  __shared__ u32x4 s_ent[kEvtWindow];
   const uint32_t base = where.y * kEvtThreads;
   if (base >= m.O) return;
   const uint32_t win_lo = base - kEvtHalo;   // may wrap below zero: window indices are taken modulo 2^32
   for (uint32_t r = threadIdx.x; r < kEvtWindow; r += kEvtThreads) {
     const uint32_t x = win_lo + r;
     const bool in = x < m.O;   // false for the wrapped indices too
-    s_ifl[r] = in ? L.ent_instr[x] : 0u;
-    s_occ[r] = in ? L.vocc[x] : 0u;
-    s_v[r] = in ? L.ent_v[x] : kNone;
+    s_ent[r] = in ? L.ent[x] : u32x4{0u, 0u, kNone, 0u};
   }
   __syncthreads();
   const uint32_t e = base + threadIdx.x;
   if (e >= m.O) return;
-  auto ent = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ifl[r] : L.ent_instr[x]; };
-  auto occ_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_occ[r] : L.vocc[x]; };
-  const uint32_t o = s_occ[threadIdx.x + kEvtHalo], v = s_v[threadIdx.x + kEvtHalo];
-  const uint32_t ifl = s_ifl[threadIdx.x + kEvtHalo], i = ifl >> 2;
+  auto ent = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ent[r].y : L.ent[x].y; };
+  auto occ_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ent[r].x : L.ent[x].x; };
+  auto kept_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return ((r < kEvtWindow ? s_ent[r].z : L.ent[x].z) & kRecKeeps) != 0; };
+  auto blk_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ent[r].w : L.ent[x].w; };
+  const u32x4 own = s_ent[threadIdx.x + kEvtHalo];
+  const uint32_t o = own.x, v = own.z & kEntVreg, ifl = own.y, i = ifl >> 2;
   // What is read from memory depends on (v, i) first and on the blocks found second: the reads
   // of each level are issued together, with indices clamped where the value may not be needed,
   // so that a lane waits for memory twice instead of once per branch taken.
   const uint32_t lo = L.vcnt[v], hi = L.vcnt[v + 1];
-  const uint32_t b = m.instr_blk[i], blk_before = m.instr_blk[i > 0 ? i - 1 : 0];
-  const bool keeps = m.instr_keep[i] != 0, kept_before = m.instr_keep[i > 0 ? i - 1 : 0] != 0;
+  const uint32_t b = own.w;
+  const bool keeps = (own.z & kRecKeeps) != 0, at_start = (own.z & kEntBlockStart) != 0;
   const uint32_t attr = m.vattr[v], last_live_v = L.last_live[v];
   uint32_t gs = e, ge = e + 1;
   while (gs > lo && (ent(gs - 1) >> 2) == i) --gs;
@@ -614,10 +771,9 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   const uint32_t nxt = ge < hi ? ent(ge) : 0u;
   // second level
   const uint32_t vw = v >> 5, vbit = 1u << (v & 31);
-  const uint32_t blk_next = m.instr_blk[nxt >> 2];
+  const uint32_t blk_next = ge < hi ? blk_at(ge) : 0u;
   const bool out_b = (L.live_out[(size_t)b * m.W + vw] & vbit) != 0;
   const bool out_below = (L.live_out[(size_t)(b > 0 ? b - 1 : 0) * m.W + vw] & vbit) != 0;
-  const bool out_before = (L.live_out[(size_t)blk_before * m.W + vw] & vbit) != 0;
   const uint32_t start_b = m.blk_start[b], start_b1 = m.blk_start[b + 1], start_b2 = m.blk_start[min(b + 2, m.B)];
   const bool in_after = (L.live_in[(size_t)min(b + 1, m.B - 1) * m.W + vw] & vbit) != 0;   // live into the block after b
   const uint32_t F = m.class_size[attr_class(attr)];
@@ -672,14 +828,14 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   bool cur;   // was v occupied just before this stretch?
   if (i == 0) cur = false;
   else if (gs > lo && (ent(gs - 1) >> 2) == i - 1) {
-    bool prev_def = false, prev_use = false;
+    bool prev_def = false, prev_kept_use = false;
     for (uint32_t x = gs; x-- > lo && (ent(x) >> 2) == i - 1;) {
       prev_def |= (ent(x) & VL_OCC_DEF) != 0;
-      prev_use |= (ent(x) & VL_OCC_USE) != 0;
+      prev_kept_use |= (ent(x) & VL_OCC_USE) != 0 && kept_at(x);
     }
-    // live after i - 1: this group is the next mention; in another block the block's live-out decides
-    const bool prev_la = blk_before == b ? has_use : out_before;
-    cur = prev_def || prev_la || (prev_use && kept_before);
+    // live after i - 1: this group is the next mention; in another block (the one below) the
+    // block's live-out decides
+    cur = prev_def || (at_start ? out_below : has_use) || prev_kept_use;
   } else if (i > start_b) cur = has_use;
   else cur = out_below;
   uint8_t sf = cur ? kOpenBefore : 0;
@@ -737,8 +893,8 @@ __device__ inline uint32_t wave_incl_scan(uint32_t x) {
 // nearest occurrence of v before instruction `at`, else the first at or after it
 __device__ inline uint32_t source_occurrence(const DevLive VL_GLOBAL &L, uint32_t v, uint32_t at) {
   const uint32_t lo = L.vcnt[v], hi = L.vcnt[v + 1];
-  uint32_t x = lower_bound(L.ent_instr, lo, hi, at << 2);   // entries hold instruction << 2 | flags
-  return x > lo ? L.vocc[x - 1] : (x < hi ? L.vocc[x] : 0u);
+  const uint32_t x = first_entry_at(L, lo, hi, at);
+  return x > lo ? L.ent[x - 1].x : (x < hi ? L.ent[x].x : 0u);
 }
 
 // The record of one occupancy event (layout in vl_dev.h).  `near`: the occurrence is
@@ -927,7 +1083,7 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
   // stretches (those with changes at block boundaries) are worked out again.
   const uint8_t sf = L.ent_sf[e];
   if (!(sf & (kStartI | kStartI1 | kEndI | kEndI1 | kEndN | kAgain))) return;
-  const uint32_t i = L.ent_instr[e] >> 2;
+  const uint32_t i = L.ent[e].y >> 2;
   // runs that started before this stretch and ended before it: the end index lags the
   // start index by one exactly while a run is open
   size_t n_start = L.ent_seg[e];
@@ -941,7 +1097,7 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
     return;
   }
   const uint8_t info = L.ent_info[e];
-  const uint32_t v = L.ent_v[e];
+  const uint32_t v = L.ent[e].z & kEntVreg;
   const uint32_t hi = L.vcnt[v + 1], b = m.instr_blk[i];
   bool cur = (sf & kOpenBefore) != 0;
   auto span = [&](uint32_t s, uint32_t t, bool member) {
@@ -951,10 +1107,10 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
     cur = member;
   };
   uint32_t ge = e + 1;
-  while (ge < hi && (L.ent_instr[ge] >> 2) == i) ++ge;
+  while (ge < hi && (L.ent[ge].y >> 2) == i) ++ge;
   const bool la = (info & kEntLiveAfter) != 0;
   span(i, i + 1, (info & (kEntHasDef | kEntKept)) || la);
-  const uint32_t i2 = ge < hi ? L.ent_instr[ge] >> 2 : m.N;
+  const uint32_t i2 = ge < hi ? L.ent[ge].y >> 2 : m.N;
   const uint32_t b2 = ge < hi ? m.instr_blk[i2] : m.B;
   if (b2 == b) {
     span(i + 1, i2, la);
@@ -1091,11 +1247,11 @@ __device__ inline void f_seed_src(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
   const uint32_t v = raw.x, t = raw.y;
   // the register is always gathered from memory: the ring offset stays unused
   const uint32_t at = t * L.tile_len, lo = L.vcnt[v], hi = L.vcnt[v + 1];
-  const uint32_t x = lower_bound(L.ent_instr, lo, hi, at << 2);   // first mention at or after the tile's start
-  u32x4 r = event_record(m, x > lo ? L.vocc[x - 1] : (x < hi ? L.vocc[x] : 0u), v, false, true);
+  const uint32_t x = first_entry_at(L, lo, hi, at);   // first mention at or after the tile's start
+  u32x4 r = event_record(m, x > lo ? L.ent[x - 1].x : (x < hi ? L.ent[x].x : 0u), v, false, true);
   r.x &= ~0xFFu;   // only the vreg: the register is always gathered from memory
   // the verifier keeps the gathered registers at hand for the link of that first mention
-  if (x > lo && x < hi && (L.ent_instr[x] >> 2) < min(m.N, at + L.tile_len)) r.w |= kSeedLinked;
+  if (x > lo && x < hi && (L.ent[x].y >> 2) < min(m.N, at + L.tile_len)) r.w |= kSeedLinked;
   L.seeds[k] = r;
 }
 
@@ -1378,7 +1534,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
 
   // ---- arena 1 layout: [zeroed zone | counters | rest | device tables] ----
   std::vector<DevLive> h(n);
-  struct Off1 { size_t last_live, vcnt, vcur, use, def, in, seed_off, seed_cur, out, tmp, vocc, ent_instr, ent_v, ent_info, first, prev,
+  struct Off1 { size_t last_live, vcnt, vcur, use, def, in, seed_off, seed_cur, out, tmp, vocc, ent, ent_info, first, prev,
                 role, kill, item, seg_off, hull, queue, bitmap, ent_seg, ent_sf, chk, evt_cut, tile_live; };
   std::vector<Off1> off(n);
   Bump bump;
@@ -1404,8 +1560,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     const DevMir &m = mirs[k]->h;
     const size_t O1 = std::max(1u, m.O), bw = (size_t)m.B * std::max(1u, m.W) * 4;
     off[k].out = bump.take(bw);
-    off[k].tmp = bump.take(O1 * 4); off[k].vocc = bump.take(O1 * 4); off[k].ent_instr = bump.take(O1 * 4);
-    off[k].ent_v = bump.take(O1 * 4);
+    off[k].tmp = bump.take(O1 * 4); off[k].vocc = bump.take(O1 * 4); off[k].ent = bump.take(O1 * sizeof(u32x4));
     off[k].ent_info = bump.take(O1); off[k].first = bump.take((size_t)(m.V + 1) * 4); off[k].prev = bump.take(O1 * 4);
     off[k].role = bump.take(O1); off[k].kill = bump.take(O1);
     off[k].seg_off = bump.take((size_t)(m.V + 1) * 4); off[k].hull = bump.take((size_t)(m.V + 1) * 8);
@@ -1442,8 +1597,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.use = (uint32_t VL_GLOBAL *)(a1 + off[k].use); L.def = (uint32_t VL_GLOBAL *)(a1 + off[k].def);
     L.live_in = (uint32_t VL_GLOBAL *)(a1 + off[k].in); L.live_out = (uint32_t VL_GLOBAL *)(a1 + off[k].out);
     L.seed_off = (uint32_t VL_GLOBAL *)(a1 + off[k].seed_off); L.seed_cur = (uint32_t VL_GLOBAL *)(a1 + off[k].seed_cur);
-    L.vocc_tmp = (uint32_t VL_GLOBAL *)(a1 + off[k].tmp); L.ent_v = (uint32_t VL_GLOBAL *)(a1 + off[k].ent_v); L.vocc = (uint32_t VL_GLOBAL *)(a1 + off[k].vocc);
-    L.ent_instr = (uint32_t VL_GLOBAL *)(a1 + off[k].ent_instr); L.ent_info = (uint8_t VL_GLOBAL *)(a1 + off[k].ent_info);
+    L.vocc_tmp = (uint32_t VL_GLOBAL *)(a1 + off[k].tmp); L.vocc = (uint32_t VL_GLOBAL *)(a1 + off[k].vocc);
+    L.ent = (u32x4 VL_GLOBAL *)(a1 + off[k].ent); L.ent_info = (uint8_t VL_GLOBAL *)(a1 + off[k].ent_info);
     L.first = (uint32_t VL_GLOBAL *)(a1 + off[k].first); L.prev_occ = (uint32_t VL_GLOBAL *)(a1 + off[k].prev);
     L.occ_role = (uint8_t VL_GLOBAL *)(a1 + off[k].role); L.occ_kill = (uint8_t VL_GLOBAL *)(a1 + off[k].kill);
     L.item_off = (uint32_t VL_GLOBAL *)(a1 + off[k].item); L.seg_off = (uint32_t VL_GLOBAL *)(a1 + off[k].seg_off);
@@ -1508,7 +1663,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
 
   // pinned staging: stage_a / stage_mirs are read by the copies below; when the sizes are not
   // known yet the host waits further down and stage_b carries the second upload after that
-  zero_async(a1, zero_bytes, stream);
   hipError_t e = hipSuccess;
   // with known sizes the tables on the device are usually the ones this call would upload
   const bool tables_current = known && batch->uploaded.size() == (size_t)n * sizeof(DevLive) &&
@@ -1541,23 +1695,30 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   const DevMir *const *dm = batch->dev_mirs;
   DevLive *dl = batch->dev_lives;
   const uint32_t TB = 256;
-  // LDS histograms over the vregs when they fit (4 bytes per vreg to count, 8 to place)
+  // LDS histograms over the vregs when they fit
   static const bool lds_ok = [] {
-    hipError_t a = hipFuncSetAttribute((const void *)k_count<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    hipError_t b = hipFuncSetAttribute((const void *)k_place<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    return a == hipSuccess && b == hipSuccess;
+    bool ok = true;
+    for (const void *f : {(const void *)k_group, (const void *)k_count<true>, (const void *)k_place<true>})
+      ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) == hipSuccess;
+    return ok;
   }();
   const bool hist_lds = lds_ok && (size_t)maxV * 4 <= 128 * 1024;
-  const dim3 slices((maxO + kSlice - 1) / kSlice, n);
-  if (hist_lds) k_count<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
-  else k_count<false><<<slices, 1024, 0, stream>>>(dm, dl);
-  k_scan<kScanVreg><<<n, 1024, 0, stream>>>(dm, dl);
-  if (hist_lds) k_place<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
-  else k_place<false><<<slices, 1024, 0, stream>>>(dm, dl);
-  k_sort<<<dim3(kLongBlocks + (maxV + 255) / 256, n), 256, 0, stream>>>(dm, dl);
+  const bool small = hist_lds && maxO <= kGroupMaxOcc;
+  if (small) {
+    k_group<<<dim3((maxO + kGroupSlice - 1) / kGroupSlice, n), 1024, (size_t)maxV * 4, stream>>>(dm, dl);
+  } else {
+    zero_async(a1, zero_bytes, stream);
+    const dim3 slices((maxO + kSlice - 1) / kSlice, n);
+    if (hist_lds) k_count<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
+    else k_count<false><<<slices, 1024, 0, stream>>>(dm, dl);
+    k_scan<kScanVreg><<<n, 1024, 0, stream>>>(dm, dl);
+    if (hist_lds) k_place<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
+    else k_place<false><<<slices, 1024, 0, stream>>>(dm, dl);
+    k_sort<<<dim3(kLongBlocks + (maxV + 255) / 256, n), 256, 0, stream>>>(dm, dl);
+  }
   {
-    const size_t lds = std::min<size_t>((size_t)maxB * std::min(maxW, kSumWords) * 8, 48 * 1024);
-    k_summary<<<grid1(maxO, kSumSlice, n), kSumThreads, lds, stream>>>(dm, dl, (uint32_t)(lds / 4));
+    const size_t lds = std::min<size_t>((size_t)maxB * std::min(maxW, kOrdWords) * 8, 40 * 1024);
+    (small ? k_order<false> : k_order<true>)<<<grid1(maxO, kOrdStretch, n), kOrdThreads, lds, stream>>>(dm, dl, (uint32_t)(lds / 4));
   }
   {
     const size_t lds = ((size_t)maxB * 3 + 1) * 64 * 4 + ((size_t)maxB * 3 + 1 + maxE) * 4;

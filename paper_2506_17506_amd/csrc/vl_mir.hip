@@ -109,12 +109,13 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
     for (uint32_t o = d->instr_occ_off[i]; o < d->instr_occ_off[i + 1]; ++o) occ_instr[o] = i;
   for (uint32_t b = 0; b < B; ++b)
     for (uint32_t i = d->blk_start[b]; i < d->blk_start[b + 1]; ++i) instr_blk[i] = b;
-  std::vector<uint64_t> occ_rec(O ? O : 1);
-  for (uint32_t o = 0; o < O; ++o)
-    occ_rec[o] = (uint64_t)d->occ_vreg[o] | ((uint64_t)((occ_instr[o] << 2) | (d->occ_flags[o] & 3u)) << 32);
   std::vector<uint8_t> instr_keep(N, 0);
   for (uint32_t o = 0; o < O; ++o)
     if (d->occ_flags[o] & VL_OCC_EARLY) instr_keep[occ_instr[o]] = 1;
+  std::vector<uint64_t> occ_rec(O ? O : 1);
+  for (uint32_t o = 0; o < O; ++o)
+    occ_rec[o] = (uint64_t)(d->occ_vreg[o] | (instr_keep[occ_instr[o]] ? vl::kRecKeeps : 0u)) |
+                 ((uint64_t)((occ_instr[o] << 2) | (d->occ_flags[o] & 3u)) << 32);
 
   // the device header's class tables come first: the packed attributes carry the class's mask word
   vl::DevMir hh;
@@ -148,7 +149,6 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   size_t o_oi = bump.take((size_t)(O ? O : 1) * 4), o_ib = bump.take((size_t)N * 4);
   size_t o_va = bump.take((size_t)(V ? V : 1) * 4), o_of = bump.take((size_t)(O ? O : 1));
   size_t o_rec = bump.take((size_t)(O ? O : 1) * 8);
-  size_t o_keep = bump.take((size_t)N);
   size_t o_src = 0, o_add = 0, o_vv = 0, o_vl = 0;
   if (maps) {
     o_src = bump.take((size_t)(O ? O : 1) * 4); o_add = bump.take((size_t)(O ? O : 1));
@@ -180,7 +180,6 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   up(o_va, vattr.data(), (size_t)V * 4);
   up(o_of, d->occ_flags, (size_t)O);
   up(o_rec, occ_rec.data(), (size_t)O * 8);
-  up(o_keep, instr_keep.data(), (size_t)N);
   if (maps) {
     up(o_src, maps->occ_src, (size_t)O * 4); up(o_add, maps->occ_add, (size_t)O);
     up(o_vv, maps->val_vreg, (size_t)V * 4); up(o_vl, maps->val_lane, (size_t)V);
@@ -198,7 +197,6 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   h.vattr = (const uint32_t VL_GLOBAL *)(base + o_va);
   h.occ_flags = (const uint8_t VL_GLOBAL *)(base + o_of);
   h.occ_rec = (const uint64_t VL_GLOBAL *)(base + o_rec);
-  h.instr_keep = (const uint8_t VL_GLOBAL *)(base + o_keep);
   if (maps) {
     h.occ_src = (const uint32_t VL_GLOBAL *)(base + o_src);
     h.val_vreg = (const uint32_t VL_GLOBAL *)(base + o_vv);
