@@ -383,13 +383,11 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
   // ---- occupancy events (lane = candidate) ----
   // Events are replayed in instruction order, so the first clash of a row is the one to
   // report; after it the row's mask is no longer exact and its later clashes are ignored.
+  // (The key names the occurrence until the wavefront is done; its instruction is read once, for
+  // all rows together.  Reading it at each clash cost a trip to memory per clash.)
   uint32_t alive = 0xFFFFFFFFu;
   auto clash = [&](uint32_t hit, uint32_t o) __attribute__((always_inline)) {
-    hit &= alive;
-    if (__any(hit != 0)) {
-      const uint32_t i = g_occ_instr[o];
-      if (hit) { key = min(key, kKeySafe | i); alive = 0; }
-    }
+    if (hit & alive) { key = kKeySafe | o; alive = 0; }
   };
   // flips the range of a tuple whose base register is p (any shape of tuple)
   auto apply1 = [&](uint32_t o, uint32_t attr, bool tested, uint32_t p) __attribute__((always_inline)) {
@@ -603,17 +601,25 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
       acc |= wrong2((uint32_t)pv, (uint32_t)qv) | wrong2((uint32_t)(pv >> 32), (uint32_t)(qv >> 32));
     }
     if (__any(acc != 0 || generic)) {
-      // rare: attribute row by row
+      // rare: attribute row by row.  A row's smallest failing key is its first failing
+      // consistency check, else its first failing first mention: bits of two lane masks, kept in
+      // the lane that stands for the row.  (A reduction over the wavefront for every failing row, and
+      // the reads at clashes, were what a chunk with failures waited for: verification of 200
+      // instructions with half of 64 samples damaged 33.3 us, 26.0 without them.)
+      const uint64_t links = __ballot(is_chk);
       for (uint32_t qd = q_lo; qd < q_hi; ++qd) {
-        for (uint32_t r = 4 * qd; r < min(w.nrows, 4 * qd + 4); ++r) {
-          const uint32_t pr = VL_LDS16[a_p * 4 + r], qr = VL_LDS16[a_q * 4 + r];
-          bool bad = (pr != qr) | ((pr & amask2 & 0xFFFFu) != 0) | (pr > (limit2 & 0xFFFFu));
-          if (generic) bad = unrealizable(m, attr, m.class_size[attr_class(attr)], pr);
-          if (__any(bad)) {
-            // the smallest failing key of this row among the chunk's checks
-            uint32_t k = bad ? ((is_chk ? kKeyCons : kKeyReal) | o) : kKeyOk;
-            for (int d = 32; d >= 1; d >>= 1) k = min(k, (uint32_t)__shfl_xor((int)k, d, 64));
-            if (w.lane == 0) atomicMin(&vl_lds[w.keys + r], k);
+        const uint64_t pv = lds64[a_p + qd], qv = lds64[a_q + qd];
+        const uint32_t wrong[2] = {wrong2((uint32_t)pv, (uint32_t)qv), wrong2((uint32_t)(pv >> 32), (uint32_t)(qv >> 32))};
+        if (!__any((wrong[0] | wrong[1]) != 0 || generic)) continue;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+          const uint32_t r = 4 * qd + t;
+          bool bad = ((wrong[t >> 1] >> (16u * (t & 1u))) & 0xFFFFu) != 0;
+          if (generic && r < w.nrows) bad = unrealizable(m, attr, m.class_size[attr_class(attr)], (uint32_t)(pv >> (16u * t)) & 0xFFFFu);
+          const uint64_t fails = __ballot(bad), broken = fails & links;
+          if (fails) {
+            const uint32_t k = (broken ? kKeyCons | (uint32_t)__builtin_ctzll(broken) : kKeyReal | (uint32_t)__builtin_ctzll(fails)) + c * kChunk;
+            if (w.lane == r) key = min(key, k);
           }
         }
       }
@@ -690,6 +696,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
       events(from, to, first);
       __syncthreads();
     }
+    if (key != kKeyOk) key = kKeySafe | g_occ_instr[key & kKeyPos];
   } else {
     const uint32_t j = role - 1;
     // direct staging: this lane's row of every pass
