@@ -207,8 +207,8 @@ int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const uint16_t *
 /* vl_verify_batch for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid it.  Same arguments, same results.
  * Its job table and the candidates' smallest violations found so far live in
- * a fixed device array inside the library (4 bytes per candidate, VL_STATIC_MAX_K of them, and a
- * little more: 260 KB per GPU the library runs on, held until the process ends); the call allocates and
+ * a fixed device array inside the library (8 bytes per candidate, VL_STATIC_MAX_K of them:
+ * 512 KB per GPU the library runs on, held until the process ends); the call allocates and
  * frees nothing, on the host or the device, and copies nothing from host memory: it only
  * enqueues kernels on `stream`.  Every call on a GPU uses that GPU's one array: calls that
  * overlap on one GPU (different streams, or threads) race; calls on one stream are ordered.

@@ -55,10 +55,9 @@ struct DevJob {
   const uint16_t *cand;
   vl_result *out;
   uint64_t ld;
-  uint32_t K, rows, n_groups, unit_base, n_units, fast, transposed, direct;   // transposed: cand is [occurrence][candidate]
+  uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
   uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
-  // direct: row-major, aligned, every row holds whole chunks up to its pitch, and a group of rows spans less than
-  // 4 GB (its chunks are fetched with 32-bit offsets and no bounds)
+  // direct: row-major, aligned, and every row holds whole chunks up to its pitch (fetched without bounds)
 };
 
 // What the workgroups of one verification share.  Everything is zero before the walk and left
@@ -115,9 +114,9 @@ struct Walk {
   uint64_t ld;
   uint32_t keys, ring16;  // LDS indices
   // readable occurrences: [max(lo, hi - kWalkReach), hi); hi is the end of the chunk being processed
-  uint32_t tid, lane, row, nrows, n_occ, lo, hi, fast;
-  uint32_t pre[kStagePasses][4];     // check wavefronts: their share of the chunk being fetched
-  // direct staging: per pass, this lane's byte offset into the group's rows and its uint16 index into
+  uint32_t tid, lane, row, nrows, n_occ, lo, hi;
+  uint32_t pre[kStagePasses][5];     // check wavefronts: their share of the chunk being fetched (the fifth word: ragged staging)
+  // row-major staging: per pass, this lane's byte offset into the group's rows and its uint16 index into
   // ring slot 0 (kNone in from_row: the pass has no row for this lane)
   uint32_t from_row[kStagePasses], to_ring[kStagePasses];
 };
@@ -135,69 +134,38 @@ __device__ inline uint32_t staged_row(uint32_t lane, uint32_t q) {
   return (q & 1u) + 2u * rr + 16u * ((k >> 2) ^ (q >> 2)) + 32u * ((q >> 1) & 1u);
 }
 
-// kT: the candidates are stored occurrence-major, cand[occurrence][candidate] with pitch ld.
-// A chunk is then 64 occurrences x 8 pieces of 16 bytes (8 candidates) that already have the
+// Occurrence-major candidates, cand[occurrence][candidate] with pitch ld:
+// a chunk is then 64 occurrences x 8 pieces of 16 bytes (8 candidates) that already have the
 // ring's layout: lane (occurrence o8, piece k) of pass q copies piece k of occurrence
 // 8 q + o8, eight lanes reading one 128-byte line.
-template <bool kT>
-__device__ inline void load_chunk(Walk &w, uint32_t c0, uint32_t j) {
-  const uint32_t c = c0 + (w.lane & 7u) * 8u;
+__device__ inline void load_chunk_occ(Walk &w, uint32_t c0, uint32_t j) {
 #pragma unroll
   for (int h = 0; h < kStagePasses; ++h) {
     const uint32_t q = j + kCheckWaves * h;
     w.pre[h][0] = w.pre[h][1] = w.pre[h][2] = w.pre[h][3] = 0;
     if (q >= 8u) continue;
-    if (kT) {
-      const uint32_t o = c0 + q * 8u + (w.lane >> 3), piece = w.lane & 7u;
-      if (piece * 8u < w.nrows && o < w.n_occ) {   // the 16 bytes lie inside the occurrence's pitch (a multiple of 8)
-        const u32x4 x = *reinterpret_cast<const u32x4 VL_GLOBAL *>(w.rows + (uint64_t)o * w.ld + piece * 8u);
-        w.pre[h][0] = x.x; w.pre[h][1] = x.y; w.pre[h][2] = x.z; w.pre[h][3] = x.w;
-      }
-      continue;
-    }
-    const uint32_t r = staged_row(w.lane, q);
-    if (r < w.nrows && c < w.n_occ) {
-      const uint16_t VL_GLOBAL *src = w.rows + (uint64_t)r * w.ld + c;
-      if (w.fast && c + 8u <= w.n_occ) {
-        const u32x4 x = *reinterpret_cast<const u32x4 VL_GLOBAL *>(src);
-        w.pre[h][0] = x.x; w.pre[h][1] = x.y; w.pre[h][2] = x.z; w.pre[h][3] = x.w;
-      } else {
-        for (int t = 0; t < 4; ++t) {
-          uint32_t a = (c + 2 * t < w.n_occ) ? src[2 * t] : 0u;
-          uint32_t b = (c + 2 * t + 1 < w.n_occ) ? src[2 * t + 1] : 0u;
-          w.pre[h][t] = a | (b << 16);
-        }
-      }
+    const uint32_t o = c0 + q * 8u + (w.lane >> 3), piece = w.lane & 7u;
+    if (piece * 8u < w.nrows && o < w.n_occ) {   // the 16 bytes lie inside the occurrence's pitch (a multiple of 8)
+      const u32x4 x = *reinterpret_cast<const u32x4 VL_GLOBAL *>(w.rows + (uint64_t)o * w.ld + piece * 8u);
+      w.pre[h][0] = x.x; w.pre[h][1] = x.y; w.pre[h][2] = x.z; w.pre[h][3] = x.w;
     }
   }
 }
 
 // writes the chunk held in registers into the ring as chunk [c0, c0 + 64)
-template <uint32_t kRingStride, bool kT>
-__device__ inline void store_chunk(const Walk &w, uint32_t c0, uint32_t j) {
-  const uint32_t c = c0 + (w.lane & 7u) * 8u;
+template <uint32_t kRingStride>
+__device__ inline void store_chunk_occ(const Walk &w, uint32_t c0, uint32_t j) {
 #pragma unroll
   for (int h = 0; h < kStagePasses; ++h) {
     const uint32_t q = j + kCheckWaves * h;
     if (q >= 8u) continue;
-    if (kT) {
-      // 8 candidates of one occurrence: two 8-byte stores (ring slots start on 8-byte
-      // boundaries); what would fall beyond the slot's pitch is left out
-      const uint32_t o = c0 + q * 8u + (w.lane >> 3), piece = w.lane & 7u;
-      const uint32_t dst = (w.ring16 + (o % kRing) * kRingStride + piece * 8u) >> 2;   // in 8-byte units
-      uint64_t *lds64 = reinterpret_cast<uint64_t *>(vl_lds);
-      if (piece * 8u + 4u <= kRingStride) lds64[dst] = (uint64_t)w.pre[h][0] | ((uint64_t)w.pre[h][1] << 32);
-      if (piece * 8u + 8u <= kRingStride) lds64[dst + 1] = (uint64_t)w.pre[h][2] | ((uint64_t)w.pre[h][3] << 32);
-      continue;
-    }
-    const uint32_t r = staged_row(w.lane, q);
-    if (kRingStride < 64u && r >= kRingStride) continue;   // rows the narrow ring has no room for (none of them is in use)
-    const uint32_t dst = w.ring16 + (c % kRing) * kRingStride + r;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      VL_LDS16[dst + (2 * t) * kRingStride] = (uint16_t)w.pre[h][t];
-      VL_LDS16[dst + (2 * t + 1) * kRingStride] = (uint16_t)(w.pre[h][t] >> 16);
-    }
+    // 8 candidates of one occurrence: two 8-byte stores (ring slots start on 8-byte
+    // boundaries); what would fall beyond the slot's pitch is left out
+    const uint32_t o = c0 + q * 8u + (w.lane >> 3), piece = w.lane & 7u;
+    const uint32_t dst = (w.ring16 + (o % kRing) * kRingStride + piece * 8u) >> 2;   // in 8-byte units
+    uint64_t *lds64 = reinterpret_cast<uint64_t *>(vl_lds);
+    if (piece * 8u + 4u <= kRingStride) lds64[dst] = (uint64_t)w.pre[h][0] | ((uint64_t)w.pre[h][1] << 32);
+    if (piece * 8u + 8u <= kRingStride) lds64[dst + 1] = (uint64_t)w.pre[h][2] | ((uint64_t)w.pre[h][3] << 32);
   }
 }
 
@@ -228,6 +196,47 @@ __device__ inline void store_chunk_direct(const Walk &w, uint32_t c0) {
     for (int t = 0; t < 4; ++t) {
       VL_LDS16[dst + (2 * t) * kRingStride] = (uint16_t)w.pre[h][t];
       VL_LDS16[dst + (2 * t + 1) * kRingStride] = (uint16_t)(w.pre[h][t] >> 16);
+    }
+  }
+}
+
+// Ragged staging: rows of any pitch and alignment.  A piece of 8 registers lies in the four or,
+// when it starts in the middle of one (bit 0 of from_row), five aligned words around it, which are
+// read whole and shifted into place when they are stored.  Each of these words holds part of the
+// piece, so nothing beyond the memory's last word is touched as long as the piece is the
+// program's; in the chunk that the program ends in, words past the row's last are replaced by that
+// one.  (Reading every chunk with 2 bytes per register, verification of 24 programs of
+// 1,000-12,000 instructions with 37 packed rows took 81 us, 12 of them before the first chunk; 62 this
+// way, 67 with the registers of six wavefronts per SIMD, eleven of which then lie in memory.)
+__device__ inline void load_chunk_ragged(Walk &w, uint32_t c0, __amdgpu_buffer_rsrc_t rows, bool shifted) {
+#pragma unroll
+  for (int h = 0; h < kStagePasses; ++h) {
+    if (w.from_row[h] == kNone) continue;
+    const uint32_t odd = w.from_row[h] & 1u, at = w.from_row[h] - odd;
+    if (c0 + kChunk <= w.n_occ) {
+      const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, at, c0 * 2u, 0));
+      w.pre[h][0] = x.x; w.pre[h][1] = x.y; w.pre[h][2] = x.z; w.pre[h][3] = x.w;
+      if (shifted) w.pre[h][4] = __builtin_amdgcn_raw_buffer_load_b32(rows, at + 12u + 4u * odd, c0 * 2u, 0);
+    } else {
+      const uint32_t last = (at - (w.lane & 7u) * 16u + 2u * (odd + w.n_occ - 1u)) & ~3u;
+#pragma unroll
+      for (uint32_t t = 0; t < 5; ++t) w.pre[h][t] = __builtin_amdgcn_raw_buffer_load_b32(rows, min(at + c0 * 2u + 4u * t, last), 0, 0);
+    }
+  }
+}
+
+template <uint32_t kRingStride>
+__device__ inline void store_chunk_ragged(const Walk &w, uint32_t c0) {
+  const uint32_t slot = (c0 % kRing) * kRingStride;
+#pragma unroll
+  for (int h = 0; h < kStagePasses; ++h) {
+    if (w.from_row[h] == kNone) continue;
+    const uint32_t dst = w.to_ring[h] + slot, shift = 16u * (w.from_row[h] & 1u);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t x = __builtin_amdgcn_alignbit(w.pre[h][t + 1], w.pre[h][t], shift);
+      VL_LDS16[dst + (2 * t) * kRingStride] = (uint16_t)x;
+      VL_LDS16[dst + (2 * t + 1) * kRingStride] = (uint16_t)(x >> 16);
     }
   }
 }
@@ -321,7 +330,7 @@ __device__ inline void finish_row(const DevJob &J, uint32_t k, uint32_t key) {
 // kOne: the call has one job, which comes as a kernel argument (no table to upload, and a level of
 // dependent reads less at the start of every workgroup).
 template <uint32_t kRingStride, bool kT, bool kDirect, bool kOne>
-__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_walk(const DevJob one, const DevJob *__restrict__ jobs, uint32_t n_jobs, const Board board) {
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT || kDirect ? 6 : 5))) void k_walk(const DevJob one, const DevJob *__restrict__ jobs, uint32_t n_jobs, const Board board) {
   // Workgroups go to the eight dies of the device in turn, each die with an L2 of its own.
   // Inside every 16 consecutive workgroup indices, units 2x and 2x + 1 are given to indices
   // x and x + 8: the two candidate groups of one tile (neighbouring units when a job has two
@@ -354,13 +363,12 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
   w.rows = as_global(J.cand) + (kT ? (uint64_t)row0 : (uint64_t)row0 * J.ld);
   w.ld = J.ld;
   w.n_occ = m.O;
-  w.fast = J.fast;
   w.keys = m.occ_words * 64;
   const uint32_t evb = (w.keys + 64) * 4;   // byte offset of the occupancy wavefront's event buffer: 64 records of 16 bytes
   w.ring16 = (w.keys + 64 + 256) * 2;
   for (uint32_t x = w.tid; x < m.occ_words * 64; x += kWalkThreads) vl_lds[x] = 0;
   if (w.tid < 64) vl_lds[w.keys + w.tid] = kKeyOk;
-  if (kDirect) {
+  if (!kT) {
     // ring entries of the rows past the group's last: zero, and never written again
     const uint32_t spare = kRingStride - w.nrows;
     for (uint32_t x = w.tid; x < spare * kRing; x += kWalkThreads) VL_LDS16[w.ring16 + (x / spare) * kRingStride + w.nrows + x % spare] = 0;
@@ -699,22 +707,28 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(6)
     if (key != kKeyOk) key = kKeySafe | g_occ_instr[key & kKeyPos];
   } else {
     const uint32_t j = role - 1;
-    // direct staging: this lane's row of every pass
-    const __amdgpu_buffer_rsrc_t rows_desc = __builtin_amdgcn_make_buffer_rsrc((void *)w.rows, 0, -1, 0x00020000);
+    // row-major staging: this lane's row of every pass, from the word the group's rows begin in
+    const uint32_t in_word = (uint32_t)(uintptr_t)w.rows & 2u;
+    const __amdgpu_buffer_rsrc_t rows_desc = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)w.rows - in_word), 0, -1, 0x00020000);
+    const bool shifted = !kDirect && (in_word || (w.ld & 1u));   // some rows begin in the middle of a word
 #pragma unroll
     for (int h = 0; h < kStagePasses; ++h) {
       const uint32_t q = j + kCheckWaves * h, r = staged_row(w.lane, q);
-      const bool has_row = kDirect && q < 8u && r < w.nrows;
-      w.from_row[h] = has_row ? (uint32_t)((r * w.ld + (w.lane & 7u) * 8u) * 2u) : kNone;
+      const bool has_row = !kT && q < 8u && r < w.nrows;
+      const uint32_t from = (uint32_t)((r * w.ld + (w.lane & 7u) * 8u) * 2u) + in_word;
+      w.from_row[h] = has_row ? (kDirect ? from : (from & ~3u) | ((from >> 1) & 1u)) : kNone;
+      if (!kT && !kDirect) w.pre[h][4] = 0;
       w.to_ring[h] = w.ring16 + (w.lane & 7u) * 8u * kRingStride + r;
     }
     auto stage_load = [&](uint32_t c0) __attribute__((always_inline)) {
       if (kDirect) load_chunk_direct(w, c0, rows_desc);
-      else load_chunk<kT>(w, c0, j);
+      else if (kT) load_chunk_occ(w, c0, j);
+      else load_chunk_ragged(w, c0, rows_desc, shifted);
     };
     auto stage_store = [&](uint32_t c0) __attribute__((always_inline)) {
       if (kDirect) store_chunk_direct<kRingStride>(w, c0);
-      else store_chunk<kRingStride, kT>(w, c0, j);
+      else if (kT) store_chunk_occ<kRingStride>(w, c0, j);
+      else store_chunk_ragged<kRingStride>(w, c0);
     };
     for (uint32_t c = c_first; c <= ca && c < c_end; ++c) {   // history chunk and the tile's first chunk
       stage_load(c * kChunk);
@@ -918,20 +932,22 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   if (u.K == 0 || (!results_only && u.ld < (transposed ? u.K : u.mir->h.O))) return VL_E_SHAPE;
   memset(&d, 0, sizeof(d));
   d.mir = u.mir->dev; d.live = u.live->dev; d.cand = u.cand; d.out = u.out; d.ld = u.ld; d.K = u.K;
-  d.fast = (((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0) ? 1u : 0u;
+  const bool aligned = ((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0;
   d.transposed = transposed ? 1u : 0u;
-  // whole chunks can be read from every row: the pitch covers the last chunk, and a group spans less than 4 GB
-  d.direct = (d.fast && !transposed && u.ld >= (((uint64_t)u.mir->h.O + kChunk - 1) / kChunk) * kChunk &&
-              64ull * u.ld * 2 + 4096 < (1ull << 32)) ? 1u : 0u;
+  // whole chunks can be read from every row: the pitch covers the last chunk
+  d.direct = (aligned && !transposed && u.ld >= (((uint64_t)u.mir->h.O + kChunk - 1) / kChunk) * kChunk) ? 1u : 0u;
   out.all_direct = out.all_direct && d.direct;
-  // groups of up to 64 candidates; every group but the last has d.rows of them
-  d.n_groups = (u.K + 63) / 64;
+  // groups of up to 64 candidates; every group but the last has d.rows of them.  Row-major groups span
+  // less than 4 GB, so that 32-bit offsets reach every register (a row alone needs less than 32 MB of it)
+  const uint64_t reach = ((1ull << 32) - (1ull << 26)) / (2 * std::max<uint64_t>(1, u.ld));
+  const uint32_t most = transposed || results_only ? 64u : (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, reach));
+  d.n_groups = (u.K + most - 1) / most;
   d.rows = (u.K + d.n_groups - 1) / d.n_groups;
   if (transposed) {
     // occurrence-major: a group is copied in 16-byte pieces of 8 candidates, so groups
     // start at multiples of 8; rounding the group size down keeps the groups small
     // (100 candidates: 48 + 52) unless the last one then outgrows a wavefront
-    if (!d.fast) return VL_E_SHAPE;
+    if (!aligned) return VL_E_SHAPE;
     uint32_t base = (u.K / d.n_groups) & ~7u;
     if (base == 0 || u.K - (d.n_groups - 1) * base > 64) {
       base = ((u.K + d.n_groups - 1) / d.n_groups + 7u) & ~7u;
@@ -1197,7 +1213,7 @@ extern "C" int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const
 namespace {
 constexpr uint32_t kStaticMaxK = VL_STATIC_MAX_K;
 struct StaticScratch {   // zero at load time, and between calls
-  uint32_t arrived[kStaticMaxK / 64 + 1];
+  uint32_t arrived[kStaticMaxK];   // (a group may be a single row)
   uint32_t keys[kStaticMaxK];
 };
 }  // namespace
