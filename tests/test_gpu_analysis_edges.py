@@ -1,0 +1,92 @@
+"""The analysis where its parts change shape: up to 32 blocks the fixed point keeps its rows in
+registers, beyond that in LDS; counts are prefixed by stretches of 256 entries and instructions; the
+tiles' live-ins are counted in windows of 2,048 tiles, by one workgroup for up to 1,024 words of vregs.
+Everything against the oracle, exactly."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2506_17506_amd as vl  # noqa: E402
+from oracle import vlo  # noqa: E402
+from vlgen.mir import Mir  # noqa: E402
+from test_gpu_parity import assert_liveness_equal, assert_results_equal, free, gpu_analyze, gpu_verify  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    vl.load()
+
+
+def flow_program(seed, n_block, n_vreg, per_block):
+    """n_vreg values written in the entry block, then random reads and writes in blocks joined by random
+    edges, forwards and backwards, none to four more out of each"""
+    rng = np.random.default_rng(seed)
+    entry = [(list(range(v, min(n_vreg, v + 30))), []) for v in range(0, n_vreg, 30)]
+    blocks = [entry + [([], [int(rng.integers(n_vreg))])]]
+    for _ in range(n_block - 1):
+        blocks.append([(rng.integers(0, n_vreg, rng.integers(0, 3)).tolist(), np.unique(rng.integers(0, n_vreg, 1 + rng.integers(0, 3))).tolist())
+                       for _ in range(1 + int(rng.integers(per_block)))])
+    for blk in blocks:
+        for x, (d, u) in enumerate(blk):
+            blk[x] = (sorted(set(d)), u)
+    succ = []
+    for b in range(n_block):
+        more = rng.integers(0, n_block, rng.integers(0, 5)) if rng.random() < 0.6 else np.zeros(0, int)
+        succ.append(sorted({*([b + 1] if b + 1 < n_block else []), *[int(x) for x in more]}))
+    return Mir.build(blocks, succ, n_vreg, (512,), name=f"flow{n_block}x{n_vreg}")
+
+
+def check(mirs, tile_len=0, dense=True):
+    hm, hl, got, _ = gpu_analyze(mirs, tile_len, dense)
+    try:
+        rows_list, wants = [], []
+        rng = np.random.default_rng(3)
+        for m, g in zip(mirs, got):
+            an = vlo.analyze(m, threads=8)
+            assert an.contract == 0
+            assert_liveness_equal(m, an, g, m.name)
+            rows = rng.integers(0, 512, (3, m.n_vreg)).astype(np.uint16)[:, m.occ_vreg]
+            rows_list.append(np.ascontiguousarray(rows))
+            wants.append(vlo.verify(m, an, rows_list[-1], threads=8))
+        for m, w, r in zip(mirs, wants, gpu_verify(hm, hl, rows_list)):
+            assert_results_equal(w, r, m.name)
+    finally:
+        free(hm, hl)
+
+
+@pytest.mark.parametrize("n_block", [1, 2, 3, 31, 32, 33, 40])
+@pytest.mark.parametrize("n_vreg", [1, 33, 2048, 2100])
+def test_blocks_around_the_registers(n_block, n_vreg):
+    check([flow_program(n_block * 10000 + n_vreg, n_block, n_vreg, 8)])
+
+
+def test_batch_on_both_sides():
+    """a batch takes the way of its largest program; small ones beside it end early"""
+    check([flow_program(s, b, v, 6) for s, b, v in ((1, 32, 700), (2, 1, 5), (3, 7, 64), (4, 20, 3000))])
+    check([flow_program(s, b, v, 6) for s, b, v in ((1, 45, 300), (2, 1, 5), (3, 32, 64))])
+
+
+@pytest.mark.parametrize("n", [255, 256, 257, 511, 513])
+def test_stretches(n):
+    """n instructions of one operand each, then of two"""
+    for width in (1, 2):
+        blk = [([0, 1][:width], [])] + [([], [0, 1][:width]) for _ in range(n - 1)]
+        cut = n // 2
+        check([Mir.build([blk[:cut], blk[cut:]], [[1], []], 2, (512,), name=f"n{n}x{width}")])
+
+
+@pytest.mark.parametrize("tile_len", [1, 3])
+def test_many_tiles(tile_len):
+    """more tiles than a window counts (2,048)"""
+    check([flow_program(77, 12, 90, 900)], tile_len, dense=False)
+
+
+@pytest.mark.parametrize("n_vreg", [32 * 1024, 32 * 1024 + 1, 70000])
+def test_wide_rows(n_vreg):
+    """around the 1,024 words that one workgroup takes"""
+    check([flow_program(5, 4, n_vreg, 40), flow_program(6, 9, 50, 30)], dense=False)
