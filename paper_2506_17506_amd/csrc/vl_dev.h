@@ -149,7 +149,10 @@ struct DevLive {
   uint32_t VL_GLOBAL *seg_off;    // [V+1]
   u32x4 VL_GLOBAL *chk;           // [O] check records
   uint32_t VL_GLOBAL *evt_cut;    // [ceil(O/64)+1] first event replayable once chunk c is staged
-  uint32_t VL_GLOBAL *ent_seg;    // [O+1] runs starting in each mention group's stretch -> prefix sums
+  uint32_t VL_GLOBAL *ent_seg;    // [O] runs that start in the entries before this one in its stretch of 256
+  uint32_t VL_GLOBAL *seg_base;   // [O/256 + 1] runs of each stretch of 256 entries -> prefix sums
+  uint32_t VL_GLOBAL *item_base;  // [N/256 + 1] events of each stretch of 256 instructions -> prefix sums
+  uint32_t VL_GLOBAL *bound_off;  // [B+1] events of each block boundary -> prefix sums
   uint8_t VL_GLOBAL *ent_sf;      // [O] where membership changes in the stretch, for the interval filling pass
   uint32_t VL_GLOBAL *hull;       // [V][2]
   uint32_t VL_GLOBAL *seed_off;   // [T+1]

@@ -63,15 +63,31 @@ __global__ __launch_bounds__(1024) void k_count(MIRS) {
 
 constexpr uint32_t kShortList = 16;   // longer occurrence lists go to the bitmap sort
 
-enum { kScanVreg = 0, kScanItems = 1, kScanSeg = 2, kScanSeed = 3 };   // kScanSeg: per-entry run counts
+// inclusive prefix over the wavefront, in the vector unit (rows of 16 lanes, then across rows)
+__device__ inline uint32_t wave_prefix(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+constexpr uint32_t kStretch = 256;    // entries or instructions whose counts are prefixed by the kernel that counts them
+__host__ __device__ inline uint32_t stretches(uint32_t n) { return (n + kStretch - 1) / kStretch; }
+
+enum { kScanVreg = 0, kScanItems = 1, kScanSeg = 2, kScanSeed = 3, kScanBound = 4 };   // kScanItems, kScanSeg: totals of stretches
 
 // In-place exclusive scan of p[0..n), total to p[n]; one 1024-thread block per kernel.
 // (The array is chosen at compile time: a run-time switch over the four arrays was
 // seen to pick the wrong pointer in its default branch.)
 template <int kWhich>
 __device__ inline void f_scan(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L) {
-  uint32_t VL_GLOBAL *p = kWhich == kScanVreg ? L.vcnt : kWhich == kScanItems ? L.item_off : kWhich == kScanSeg ? L.ent_seg : L.seed_off;
-  const uint32_t n = kWhich == kScanVreg ? m.V : kWhich == kScanItems ? m.N + m.B : kWhich == kScanSeg ? m.O : L.T;
+  uint32_t VL_GLOBAL *p = kWhich == kScanVreg ? L.vcnt : kWhich == kScanItems ? L.item_base : kWhich == kScanSeg ? L.seg_base :
+                          kWhich == kScanBound ? L.bound_off : L.seed_off;
+  const uint32_t n = kWhich == kScanVreg ? m.V : kWhich == kScanItems ? stretches(m.N) : kWhich == kScanSeg ? stretches(m.O) :
+                     kWhich == kScanBound ? m.B : L.T;
   // Each of the 16 wavefronts owns a contiguous sixteenth of the array and walks it 256
   // elements at a time (four consecutive elements per lane, one 16-byte access): first to
   // total its part, then, once the parts' totals are prefixed, to write the exclusive sums.
@@ -802,6 +818,32 @@ __global__ __launch_bounds__(64) void k_fixpoint_regs(MIRS) {
 // one-byte summary of where membership in P(.) changes inside a mention group's stretch
 constexpr uint8_t kStartI = 1, kStartI1 = 2, kEndI = 4, kEndI1 = 8, kEndN = 16, kAgain = 32, kOpenBefore = 64;
 
+// exclusive prefixes over a workgroup of kStretch threads, of n values per thread at once: x[k] of all threads,
+// the total of which goes to sums[k] (those from n_sums on are dropped)
+template <uint32_t n>
+__device__ inline void stretch_prefix(uint32_t (&x)[n], uint32_t VL_GLOBAL *sums, uint32_t n_sums) {
+  __shared__ uint32_t part[n][kStretch / 64];
+  const uint32_t wave = threadIdx.x >> 6;
+  uint32_t incl[n];
+#pragma unroll
+  for (uint32_t k = 0; k < n; ++k) {
+    incl[k] = wave_prefix(x[k]);
+    if ((threadIdx.x & 63u) == 63u) part[k][wave] = incl[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t k = 0; k < n; ++k) {
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (uint32_t y = 0; y < kStretch / 64; ++y) {
+      before += y < wave ? part[k][y] : 0u;
+      total += part[k][y];
+    }
+    if (threadIdx.x == k && k < n_sums) sums[k] = total;
+    x[k] = before + incl[k] - x[k];
+  }
+}
+
 // ---- 4. per-occurrence liveness, kill flags and event roles ---------------------------
 // For the mentions of v at instruction i (its "group"): v is live after i iff the next
 // mention of v in the same block reads it, or, with no later mention in the block, v is
@@ -829,7 +871,9 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   }
   __syncthreads();
   const uint32_t e = base + threadIdx.x;
-  if (e >= m.O) return;
+  // (the part below leaves early where an entry has nothing to count)
+  auto count_runs = [&]() __attribute__((always_inline)) -> uint32_t {
+  if (e >= m.O) return 0;
   auto ent = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ent[r].y : L.ent[x].y; };
   auto occ_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return r < kEvtWindow ? s_ent[r].x : L.ent[x].x; };
   auto kept_at = [&](uint32_t x) { const uint32_t r = x - win_lo; return ((r < kEvtWindow ? s_ent[r].z : L.ent[x].z) & kRecKeeps) != 0; };
@@ -909,7 +953,7 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   // The first entry of each mention group owns the stretch from i up to the next mention of v
   // and counts the run starts in it; what the neighbouring groups contribute is worked out
   // from their flags here, since their own threads may not have run yet.
-  if (e != gs) { L.ent_seg[e] = 0; L.ent_sf[e] = 0; return; }
+  if (e != gs) { L.ent_sf[e] = 0; return 0; }
   bool cur;   // was v occupied just before this stretch?
   if (i == 0) cur = false;
   else if (gs > lo && (ent(gs - 1) >> 2) == i - 1) {
@@ -960,9 +1004,20 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
   }
   if (ge >= hi && cur) sf |= kEndN;
   if (n_start > 1) sf |= kAgain;   // two starts in one stretch cannot be told apart by the summary
-  L.ent_seg[e] = n_start;
   L.ent_sf[e] = sf;
+  return n_start;
+  };
+  // where the runs of each entry go, from the stretch's first
+  uint32_t runs[1] = {count_runs()};
+  stretch_prefix(runs, L.seg_base + where.y, 1);
+  if (e < m.O) L.ent_seg[e] = runs[0];
 }
+
+// The grids are sized for the largest kernel of the batch, so most blocks belong to smaller
+// kernels and exit at once.  A block of the part that counts each instruction's events (light
+// work) takes this many stretches of 256 instructions, which keeps their number down; the
+// heavier parts are faster with one stretch per block.
+constexpr uint32_t kStageReps = 4;
 
 // ---- 5a. event stream -----------------------------------------------------------------
 __device__ inline uint32_t item_of_instr(const DevMir VL_GLOBAL &m, uint32_t i) { return i + m.instr_blk[i] + 1; }
@@ -1008,7 +1063,7 @@ __device__ inline void f_boundary(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
   if (b >= m.B) return;
   const uint32_t item = m.blk_start[b] + b;
   if (b == 0) {
-    if (!kFill && lane == 0) L.item_off[item] = 0;
+    if (!kFill && lane == 0) L.bound_off[0] = 0;
     return;
   }
   const uint32_t W = m.W, at = m.blk_start[b];
@@ -1031,7 +1086,7 @@ __device__ inline void f_boundary(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
     uint32_t mine = 0;
     for (uint32_t w = lane; w < W; w += 64) mine += __popc(out_prev[w] ^ in_cur[w]);
     for (int d = 32; d >= 1; d >>= 1) mine += (uint32_t)__shfl_xor((int)mine, d, 64);
-    if (lane == 0) L.item_off[item] = mine;
+    if (lane == 0) L.bound_off[b] = mine;
     return;
   }
   for (int pass = 0; pass < 2; ++pass) {  // 0: leaving, 1: entering
@@ -1061,7 +1116,6 @@ __device__ inline void f_boundary(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
       total += n_here;
     }
   }
-  if (!kFill && lane == 0) L.item_off[item] = total;
 }
 
 // Occupancy events of each instruction, in the order they take effect: releases of
@@ -1071,8 +1125,23 @@ __device__ inline void f_plan_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL 
                                    const uint32_t bdim) {
   uint32_t i = bx * bdim + tx;
   if (i >= m.N) return;
-  const uint32_t base = L.item_off[item_of_instr(m, i)];
+  // the instruction's first event: those of earlier stretches, of earlier instructions in its own, and of block boundaries
+  const uint32_t blk = m.instr_blk[i], item = i + blk + 1, in_order = L.item_base[bx] + L.item_off[item];
+  const uint32_t base = in_order + L.bound_off[blk + 1];
+  L.item_off[item] = base;
+  uint32_t first = base;   // a block boundary's events go with the block's first instruction
+  if (m.blk_start[blk] == i) L.item_off[item - 1] = first = in_order + L.bound_off[blk];
   const uint32_t o0 = m.occ_off[i], o1 = m.occ_off[i + 1];
+  // evt_cut[c]: the first event of the instruction that occurrence 64 c belongs to (its events may be
+  // replayed once the occurrences before 64 (c + 1) are staged); no instruction has more than 64
+  static_assert(kMaxOperands <= kWalkChunk, "an instruction holds the first occurrence of one chunk at most");
+  const uint32_t chunk = (o0 + kWalkChunk - 1) / kWalkChunk;
+  if (chunk * kWalkChunk < o1) L.evt_cut[chunk] = first;
+  if (i + 1 == m.N) {
+    const uint32_t all = L.item_base[stretches(m.N)] + L.bound_off[m.B];
+    L.item_off[item + 1] = all;
+    L.evt_cut[(m.O + kWalkChunk - 1) / kWalkChunk] = all;
+  }
   uint32_t n_pre = 0, n_set = 0;
   if (o1 - o0 <= 4) {
     // the common case: roles and vregs of all operands are read together, then their
@@ -1121,34 +1190,37 @@ __device__ inline void f_plan_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL 
   }
 }
 
-// number of events of each instruction: the roles of its operands (the counterpart of the
-// filling pass above)
-__device__ inline void f_item_count(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
-                                    const uint32_t bdim) {
-  const uint32_t i = bx * bdim + tx;
-  if (i >= m.N) return;
-  uint32_t n_evt = 0;
-  for (uint32_t o = m.occ_off[i]; o < m.occ_off[i + 1]; ++o)
-    n_evt += __popc(L.occ_role[o] & (kRolePreKill | kRoleTestSet | kRolePostKill));
-  L.item_off[item_of_instr(m, i)] = n_evt;
-}
-
-// evt_cut[c] = index of the first event of the first item whose operands end in chunk c or
-// later (an item's events may be replayed once occurrences [0, 64 (c + 1)) are staged).
-__device__ inline void f_evt_cut(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
-                                 const uint32_t bdim) {
-  const uint32_t c = bx * bdim + tx;
-  const uint32_t n_chunk = (m.O + 63) / 64;
-  if (c > n_chunk) return;
-  // first instruction i with occ_off[i + 1] > 64 c: the one that occurrence 64 c belongs to
-  const uint32_t lo = 64 * c < m.O ? m.occ_instr[64 * c] : m.N;
-  uint32_t cut;
-  if (lo >= m.N || c == n_chunk) cut = L.item_off[m.N + m.B];
-  else {
-    const uint32_t b = m.instr_blk[lo];
-    cut = L.item_off[m.blk_start[b] == lo ? lo + b : lo + b + 1];   // boundary events go with their block's first instruction
+// Number of events of each instruction (the roles of its operands, as the filling pass above has
+// them), prefixed over its stretch; kStageReps stretches at a time, side by side.
+__device__ inline void f_item_count(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx) {
+  const uint32_t s0 = bx * kStageReps, n_stretch = stretches(m.N);
+  if (s0 >= n_stretch) return;
+  uint32_t o0[kStageReps], n_op[kStageReps], blk[kStageReps], n_evt[kStageReps], role[kStageReps][4];
+#pragma unroll
+  for (uint32_t r = 0; r < kStageReps; ++r) {
+    const uint32_t i = (s0 + r) * kStretch + tx;
+    o0[r] = i < m.N ? m.occ_off[i] : 0u;
+    n_op[r] = i < m.N ? m.occ_off[i + 1] - o0[r] : 0u;
+    blk[r] = i < m.N ? m.instr_blk[i] : 0u;
   }
-  L.evt_cut[c] = cut;
+#pragma unroll
+  for (uint32_t r = 0; r < kStageReps; ++r)
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) role[r][u] = u < n_op[r] ? (uint32_t)L.occ_role[o0[r] + u] : 0u;
+  constexpr uint32_t kEvents = kRolePreKill | kRoleTestSet | kRolePostKill;
+#pragma unroll
+  for (uint32_t r = 0; r < kStageReps; ++r) {
+    n_evt[r] = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) n_evt[r] += __popc(role[r][u] & kEvents);
+    for (uint32_t u = 4; u < n_op[r]; ++u) n_evt[r] += __popc(L.occ_role[o0[r] + u] & kEvents);
+  }
+  stretch_prefix(n_evt, L.item_base + s0, n_stretch - s0);
+#pragma unroll
+  for (uint32_t r = 0; r < kStageReps; ++r) {
+    const uint32_t i = (s0 + r) * kStretch + tx;
+    if (i < m.N) L.item_off[i + blk[r] + 1] = n_evt[r];
+  }
 }
 
 // ---- 5b. live intervals ---------------------------------------------------------------
@@ -1171,7 +1243,7 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
   const uint32_t i = L.ent[e].y >> 2;
   // runs that started before this stretch and ended before it: the end index lags the
   // start index by one exactly while a run is open
-  size_t n_start = L.ent_seg[e];
+  size_t n_start = L.seg_base[bx] + L.ent_seg[e];
   size_t n_end = n_start - ((sf & kOpenBefore) ? 1u : 0u);
   if (!(sf & kAgain)) {
     if (sf & kStartI) L.seg[2 * n_start] = i;
@@ -1210,20 +1282,16 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
   if (ge >= hi && cur) L.seg[2 * n_end + 1] = m.N;
 }
 
-// seg_off per vreg from the per-entry prefix sums
-__device__ inline void f_seg_off(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
-                                 const uint32_t bdim) {
-  const uint32_t v = bx * bdim + tx;
-  if (v > m.V) return;
-  L.seg_off[v] = L.ent_seg[v < m.V ? L.vcnt[v] : m.O];
-}
-
-// hull of each vreg from its (ascending) runs: [first start, last end), or [0,0) without runs
+// where each vreg's (ascending) runs begin, and its hull: [first start, last end), or [0,0) without runs
 __device__ inline void f_hull(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
                               const uint32_t bdim) {
   const uint32_t v = bx * bdim + tx;
-  if (v >= m.V) return;
-  const uint32_t s0 = L.seg_off[v], s1 = L.seg_off[v + 1];
+  if (v > m.V) return;
+  auto runs_before = [&](uint32_t e) { return e < m.O ? L.seg_base[e / kStretch] + L.ent_seg[e] : L.seg_base[stretches(m.O)]; };
+  const uint32_t s0 = runs_before(L.vcnt[v]);
+  L.seg_off[v] = s0;
+  if (v == m.V) return;
+  const uint32_t s1 = runs_before(L.vcnt[v + 1]);
   L.hull[2 * v] = s1 > s0 ? L.seg[2 * (size_t)s0] : 0u;
   L.hull[2 * v + 1] = s1 > s0 ? L.seg[2 * (size_t)s1 - 1] : 0u;
 }
@@ -1269,22 +1337,81 @@ __device__ inline void f_tile_delta(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
   for (uint32_t w = tx; w < W; w += 256) L.tile_live[(size_t)t * W + w] = row[w];
 }
 
-// exclusive prefix-XOR over the tiles, one bitset word per lane
-__device__ inline void f_tile_prefix(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
-                                     const uint32_t bdim) {
-  const uint32_t w = bx * bdim + tx;
-  if (w >= m.W) return;
+// Exclusive prefix-XOR over the tiles: a lane per bitset word, and a wavefront per run of tiles where
+// the words leave some of the workgroup's sixteen free (a program of 8,000 instructions has 188 words
+// and 63 tiles: five runs of 13, read at once).  members: counts the members of each tile's row
+// (nothing is live into the first).
+constexpr uint32_t kTileWords = 1024;    // words of a workgroup
+constexpr uint32_t kTileCounts = 2048;   // most tiles whose members are counted
+__device__ inline void f_tile_prefix(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, uint32_t *members) {
+  __shared__ uint32_t run_xor[16][64];
+  const uint32_t W = m.W, T = L.T, w0 = bx * kTileWords, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  if (w0 >= W) return;
+  const uint32_t groups = (min(W - w0, kTileWords) + 63u) / 64u, runs = 16u / groups, run = wave / groups;
+  const uint32_t w = w0 + wave % groups * 64 + lane, len = (T + runs - 1) / runs;
+  const uint32_t t_lo = run < runs ? min(T, run * len) : T, t_hi = run < runs ? min(T, t_lo + len) : T;
+  uint32_t d[16], x = 0;
+  auto fetch = [&](uint32_t t0) __attribute__((always_inline)) {
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u) d[u] = t0 + u < t_hi && w < W ? L.tile_live[(size_t)(t0 + u) * W + w] : 0u;
+  };
+  for (uint32_t t0 = t_lo; t0 < t_hi; t0 += 16) {
+    fetch(t0);
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u) x ^= d[u];
+  }
+  run_xor[wave][lane] = x;
+  __syncthreads();
   uint32_t acc = 0;
-  for (uint32_t t0 = 0; t0 < L.T; t0 += 8) {   // eight tiles' words in flight
-    uint32_t d[8];
+  for (uint32_t k = wave % groups; k < run * groups && run < runs; k += groups) acc ^= run_xor[k][lane];
+  for (uint32_t t0 = t_lo; t0 < t_hi; t0 += 16) {
+    if (len > 16) fetch(t0);   // (otherwise they are still there)
+    uint32_t two = 0;          // the counts of two tiles: a wavefront's are at most 2,048 each
 #pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) d[u] = t0 + u < L.T ? L.tile_live[(size_t)(t0 + u) * m.W + w] : 0u;
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) {
-      if (t0 + u < L.T) L.tile_live[(size_t)(t0 + u) * m.W + w] = acc;
+    for (uint32_t u = 0; u < 16; ++u) {
+      if (t0 + u < t_hi && w < W) L.tile_live[(size_t)(t0 + u) * W + w] = acc;
+      if (members) {
+        two |= (uint32_t)__popc(acc) << (16u * (u & 1u));
+        if (u & 1u) {
+          two = wave_prefix(two);
+          if (lane == 63u && t0 + u - 1 < t_hi) atomicAdd(&members[t0 + u - 1], two & 0xFFFFu);
+          if (lane == 63u && t0 + u < t_hi) atomicAdd(&members[t0 + u], two >> 16);
+          two = 0;
+        }
+      }
       acc ^= d[u];
     }
   }
+}
+
+// In-place exclusive scan of p[0..n), total to p[n], by one wavefront: four elements per lane, four
+// rounds of reads in flight.
+__device__ inline void wave_scan(uint32_t VL_GLOBAL *p, const uint32_t n) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t base = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += 4 * 256) {
+    u32x4 x[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + u * 256 + lane * 4;
+      x[u] = 0;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t)
+        if (i + t < n) x[u][t] = p[i + t];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + u * 256 + lane * 4, sum = x[u].x + x[u].y + x[u].z + x[u].w, incl = wave_prefix(sum);
+      uint32_t at = base + incl - sum;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+        if (i + t < n) p[i + t] = at;
+        at += x[u][t];
+      }
+      base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+  }
+  if (lane == 0) p[n] = base;
 }
 
 // One wavefront per tile lists the members of its seed row as occupy-without-test entries
@@ -1360,8 +1487,8 @@ __global__ void k_collect(MIRS, uint32_t n) {
   if (k >= n) return;
   const DevMir VL_GLOBAL &m = *as_global(mirs[k]);
   DevLive VL_GLOBAL &L = *as_global_rw(&lives[k]);
-  L.counters[kCtrPlanLen] = L.item_off[m.N + m.B];
-  L.counters[kCtrSeg] = L.ent_seg[m.O];
+  L.counters[kCtrPlanLen] = L.item_base[stretches(m.N)] + L.bound_off[m.B];
+  L.counters[kCtrSeg] = L.seg_base[stretches(m.O)];
   L.counters[kCtrSeed] = L.seed_off[L.T];
 }
 
@@ -1383,18 +1510,17 @@ __device__ inline void f_tile_range(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
 }
 
 // ---- stages ---------------------------------------------------------------------------
-// After the per-occurrence pass three chains are independent: the event stream (boundary
-// counts, scan, chunk cuts, fill), the intervals (count, scan, offsets, fill) and the tile
-// live-ins (flips, prefix, count, scan, fill, sources).  Each stage below runs one step of
-// every chain in one launch, the block index selecting the part, so that the short serial
-// steps of one chain (scans, prefixes) overlap the bandwidth-heavy steps of another.  A
-// part made of one wavefront per item gets four items per 256-thread block.
+// After the per-occurrence pass three chains are independent: the event stream (counts, prefix,
+// fill, chunk cuts), the intervals (counts, prefix, fill, offsets) and the tile live-ins (flips,
+// prefix, counts, fill, sources).  Each stage below runs one step of every chain in one launch, the
+// block index selecting the part, so that the short serial steps of one chain (prefixes) overlap the
+// bandwidth-heavy steps of another.  A part made of one wavefront per item gets four items per
+// 256-thread block.  Counts are prefixed per stretch of 256 where they are counted, so that only the
+// stretches' totals have to be scanned in between, and a stretch's first place is a look-up for the
+// kernels that fill.  (Scanning every entry and every instruction, and offsets, counts of the
+// live-ins and their scan in two launches of their own: 38 us for 256 programs of 1,000-20,000
+// instructions and 22 for one of 8,000, where the one launch takes 11.5 and 7.5.)
 struct StageGrid { uint32_t a, b, c; };   // blocks of the three parts, in launch order
-// The grids are sized for the largest kernel of the batch, so most blocks belong to smaller
-// kernels and exit at once.  A block of the part that counts each instruction's events (light
-// work) takes this many stretches of 256 instructions, which keeps their number down; the
-// heavier parts are faster with one stretch per block.
-constexpr uint32_t kStageReps = 4;
 
 __global__ __launch_bounds__(256) void k_stage_count(MIRS, StageGrid g) {
   const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
@@ -1402,26 +1528,53 @@ __global__ __launch_bounds__(256) void k_stage_count(MIRS, StageGrid g) {
   const uint32_t bx = blockIdx.x, tx = threadIdx.x;
   if (bx < g.a) f_tile_delta(m, L, bx, tx, 256);
   else if (bx < g.a + g.b) f_boundary<false>(m, L, (bx - g.a) * 4 + (tx >> 6), tx & 63u, 64);
-  else
-    for (uint32_t r = 0; r < kStageReps; ++r) f_item_count(m, L, (bx - g.a - g.b) * kStageReps + r, tx, 256);
+  else f_item_count(m, L, bx - g.a - g.b, tx);
 }
 
-__global__ __launch_bounds__(1024) void k_stage_scan(MIRS, StageGrid g) {
+// kCount: a workgroup per kernel does everything, its wavefronts side by side; otherwise the tiles'
+// rows are prefixed by workgroups of their own.
+constexpr uint32_t kWaveScan = 4096;   // longer arrays are scanned by the whole workgroup
+template <bool kCount>
+__global__ __launch_bounds__(1024) void k_stage_scan(MIRS) {
   const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
   DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
-  const uint32_t bx = blockIdx.x;
-  if (bx == 0) f_scan<kScanSeg>(m, L);
-  else if (bx == 1) f_scan<kScanItems>(m, L);
-  else f_tile_prefix(m, L, bx - 2, threadIdx.x, 1024);
+  if (!kCount && blockIdx.x > 0) {
+    f_tile_prefix(m, L, blockIdx.x - 1, nullptr);
+    return;
+  }
+  __shared__ uint32_t members[kCount ? kTileCounts : 1];
+  if (kCount) {
+    for (uint32_t t = threadIdx.x; t < L.T; t += 1024) members[t] = 0;
+    __syncthreads();
+    f_tile_prefix(m, L, 0, members);
+    __syncthreads();
+  }
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  if (kCount && wave == 3) {
+    uint32_t base = 0;
+    for (uint32_t t0 = 0; t0 < L.T; t0 += 64) {
+      const uint32_t t = t0 + lane, x = t < L.T ? members[t] : 0u, incl = wave_prefix(x);
+      if (t < L.T) L.seed_off[t] = base + incl - x;
+      base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+    if (lane == 0) L.seed_off[L.T] = base;
+  }
+  if (max(max(m.O, m.N) / kStretch, m.B) < kWaveScan) {
+    if (wave == 0) wave_scan(L.seg_base, stretches(m.O));
+    if (wave == 1) wave_scan(L.item_base, stretches(m.N));
+    if (wave == 2) wave_scan(L.bound_off, m.B);
+  } else {
+    f_scan<kScanSeg>(m, L);
+    __syncthreads();
+    f_scan<kScanItems>(m, L);
+    __syncthreads();
+    f_scan<kScanBound>(m, L);
+  }
 }
 
-__global__ __launch_bounds__(256) void k_stage_offsets(MIRS, StageGrid g) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
-  const uint32_t bx = blockIdx.x, tx = threadIdx.x;
-  if (bx < g.a) f_seed<false>(m, L, bx * 4 + (tx >> 6), tx & 63u, 64);
-  else if (bx < g.a + g.b) f_evt_cut(m, L, bx - g.a, tx, 256);
-  else f_seg_off(m, L, bx - g.a - g.b, tx, 256);
+// the counts of the tiles' live-ins where a row takes several workgroups of the launch above
+__global__ __launch_bounds__(256) void k_seed_count(MIRS) {
+  f_seed<false>(*as_global(mirs[blockIdx.y]), *as_global_rw(&lives[blockIdx.y]), blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63u, 64);
 }
 
 // One-dimensional grid.  Part a: per_a workgroups for every kernel; parts b and c: one
@@ -1620,7 +1773,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   // ---- arena 1 layout: [zeroed zone | counters | rest | device tables] ----
   std::vector<DevLive> h(n);
   struct Off1 { size_t last_live, vcnt, vcur, use, def, in, seed_off, seed_cur, out, tmp, vocc, ent, ent_info, first, prev,
-                role, kill, item, seg_off, hull, queue, bitmap, ent_seg, ent_sf, chk, evt_cut, tile_live; };
+                role, kill, item, seg_off, hull, queue, bitmap, ent_seg, ent_sf, chk, evt_cut, tile_live, seg_base, item_base, bound_off; };
   std::vector<Off1> off(n);
   Bump bump;
   uint32_t maxO = 1, maxV = 1, maxN = 1, maxB = 1, maxW = 1, maxT = 1, maxE = 0;
@@ -1655,6 +1808,9 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     off[k].chk = bump.take(O1 * sizeof(u32x4));
     off[k].tile_live = bump.take((size_t)h[k].T * std::max(1u, m.W) * 4);
     off[k].evt_cut = bump.take(((size_t)(m.O + 63) / 64 + 2) * 4);
+    off[k].seg_base = bump.take(((size_t)stretches(m.O) + 1) * 4);
+    off[k].item_base = bump.take(((size_t)stretches(m.N) + 1) * 4);
+    off[k].bound_off = bump.take(((size_t)m.B + 1) * 4);
     off[k].bitmap = 0;
   }
   const size_t o_mirs = bump.take((size_t)n * sizeof(DevMir *));
@@ -1691,6 +1847,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.ent_seg = (uint32_t VL_GLOBAL *)(a1 + off[k].ent_seg);
     L.ent_sf = (uint8_t VL_GLOBAL *)(a1 + off[k].ent_sf);
     L.chk = (u32x4 VL_GLOBAL *)(a1 + off[k].chk); L.tile_live = (uint32_t VL_GLOBAL *)(a1 + off[k].tile_live); L.evt_cut = (uint32_t VL_GLOBAL *)(a1 + off[k].evt_cut);
+    L.seg_base = (uint32_t VL_GLOBAL *)(a1 + off[k].seg_base); L.item_base = (uint32_t VL_GLOBAL *)(a1 + off[k].item_base);
+    L.bound_off = (uint32_t VL_GLOBAL *)(a1 + off[k].bound_off);
     L.bitmap = (uint32_t VL_GLOBAL *)nullptr;
     L.counters = (uint32_t VL_GLOBAL *)(a1 + o_counters) + (size_t)k * kCounters;
     mir_ptrs[k] = mirs[k]->dev;
@@ -1811,16 +1969,18 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     else if (lds <= 64 * 1024) k_fixpoint<true><<<grid1(maxW, 64, n), 64, lds, stream>>>(dm, dl);
     else k_fixpoint<false><<<grid1(maxW, 64, n), 64, 0, stream>>>(dm, dl);
   }
-  static_assert(kEvtThreads == 256, "the block map counts stretches of 256 entries");
+  static_assert(kEvtThreads == kStretch && kStretch == 256, "the block map counts stretches of 256 entries");
   if (blocks_occ) k_events<<<(uint32_t)blocks_occ, kEvtThreads, 0, stream>>>(dm, dl, map_occ);
   auto blocks = [](uint32_t items, uint32_t per) { return std::max(1u, (items + per - 1) / per); };
   const StageGrid g_count = {maxT, blocks(maxB, 4), blocks(maxN, TB * kStageReps)};
-  const StageGrid g_scan = {1, 1, blocks(maxW, 1024)};
-  const StageGrid g_off = {blocks(maxT, 4), blocks(maxO / 64 + 2, TB), blocks(maxV + 1, TB)};
   k_stage_count<<<dim3(g_count.a + g_count.b + g_count.c, n), 256, (size_t)maxW * 4, stream>>>(dm, dl, g_count);
-  k_stage_scan<<<dim3(g_scan.a + g_scan.b + g_scan.c, n), 1024, 0, stream>>>(dm, dl, g_scan);
-  k_stage_offsets<<<dim3(g_off.a + g_off.b + g_off.c, n), 256, 0, stream>>>(dm, dl, g_off);
-  k_scan<kScanSeed><<<n, 1024, 0, stream>>>(dm, dl);
+  if (maxW <= kTileWords && maxT <= kTileCounts) {
+    k_stage_scan<true><<<dim3(1, n), 1024, 0, stream>>>(dm, dl);
+  } else {
+    k_stage_scan<false><<<dim3(1 + blocks(maxW, kTileWords), n), 1024, 0, stream>>>(dm, dl);
+    k_seed_count<<<dim3(blocks(maxT, 4), n), 256, 0, stream>>>(dm, dl);
+    k_scan<kScanSeed><<<n, 1024, 0, stream>>>(dm, dl);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return fail(hip_fail(e));
   if (!known) {
@@ -1845,7 +2005,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   const StageGrid g_fill = {per_a * n, (uint32_t)blocks_instr, (uint32_t)blocks_occ};
   const StageGrid g_fin = {blocks(maxB, 4), blocks(maxT, TB), blocks(max_seed, TB)};
   k_stage_fill<<<g_fill.a + g_fill.b + g_fill.c, 256, 0, stream>>>(dm, dl, g_fill, per_a, map_instr, map_occ);
-  k_stage_finish<<<dim3(g_fin.a + g_fin.b + g_fin.c + blocks(maxV, TB), n), 256, 0, stream>>>(dm, dl, g_fin);
+  k_stage_finish<<<dim3(g_fin.a + g_fin.b + g_fin.c + blocks(maxV + 1, TB), n), 256, 0, stream>>>(dm, dl, g_fin);
   if (dense) {
     k_dense<<<dim3((maxW + 63) / 64, maxT, n), 256, 0, stream>>>(dm, dl);
   }
