@@ -13,6 +13,8 @@
 // condition (Section 3.4) needs to know which lifetimes overlap.
 #include <algorithm>
 #include <cstring>
+#include <initializer_list>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -1684,9 +1686,11 @@ struct vl_batch {
   size_t cap1 = 0, cap2 = 0;
   const DevMir **dev_mirs = nullptr;  // device array [n]
   DevLive *dev_lives = nullptr;       // device array [n]
-  uint32_t *host_counters = nullptr;  // pinned [n][kCounters]
-  const DevMir **stage_mirs = nullptr;  // pinned [n]
-  DevLive *stage_a = nullptr, *stage_b = nullptr;  // pinned [n] each: first and second upload
+  void *pinned = nullptr;             // one allocation that holds the five arrays below
+  uint32_t *host_counters = nullptr;  // [n][kCounters]
+  const DevMir **stage_mirs = nullptr;  // [n]
+  DevLive *stage_a = nullptr, *stage_b = nullptr;  // [n] each: first and second upload
+  uint2 *stage_map = nullptr;         // the block maps (kernel, stretch of 256) of the per-instruction and per-entry launches
   std::vector<vl_live *> lives;
   // result sizes of the last successful call (the analysis of the same kernels with the same
   // options is deterministic, so a recycling call need not read them back)
@@ -1694,18 +1698,99 @@ struct vl_batch {
   uint32_t sized_tile_len = 0;
   std::vector<uint32_t> sizes;   // [n][3]: events, interval segments, tile live-ins
   std::vector<char> uploaded;    // the DevLive table as it stands on the device after the last successful call
-  uint2 *stage_map = nullptr;    // pinned: the block maps (kernel, stretch of 256) of the per-instruction and per-entry launches
-  size_t map_cap = 0;
 };
 
+// Device memory of analyses on its way from one to the next.  Kernels that arrive with their first
+// samples are analysed into new handles and dropped, and mapping and unmapping tens of megabytes
+// took longer than the analysis (32 MB: hipMalloc 24 us, hipFree 180 us).  A few blocks of middling
+// size per device are kept when an analysis is destroyed; a block that several takers in turn had no
+// use for goes back to the system, and all of them when memory runs short.  As with hipFree, whoever
+// gives memory back waits for the device, so what a taker gets is idle on every stream.
+namespace {
+struct Arena {
+  void *mem;
+  size_t cap;
+};
+constexpr int kPoolBlocks = 6;
+constexpr size_t kPoolMin = 1u << 20, kPoolMax = 64u << 20;   // bytes of a block that is kept
+constexpr uint32_t kPoolIdle = 32;                            // takers that pass a block by before it is freed
+struct Pool {
+  std::mutex mu;
+  Arena block[kPoolBlocks] = {};
+  uint32_t passed[kPoolBlocks] = {};
+};
+Pool g_pool[16];
+
+hipError_t arena_take(int device, size_t bytes, void **mem, size_t *cap) {
+  Arena got = {nullptr, 0}, stale[kPoolBlocks] = {};
+  Pool *pool = device >= 0 && device < 16 ? &g_pool[device] : nullptr;
+  if (pool) {
+    std::lock_guard<std::mutex> lock(pool->mu);
+    int best = -1;
+    for (int k = 0; k < kPoolBlocks; ++k)
+      if (pool->block[k].mem && pool->block[k].cap >= bytes && pool->block[k].cap / 4 <= bytes && (best < 0 || pool->block[k].cap < pool->block[best].cap)) best = k;
+    for (int k = 0; k < kPoolBlocks; ++k) {
+      if (k == best) got = pool->block[k];
+      else if (pool->block[k].mem && ++pool->passed[k] > kPoolIdle) stale[k] = pool->block[k];
+      else continue;
+      pool->block[k] = {nullptr, 0};
+    }
+  }
+  for (const Arena &a : stale)
+    if (a.mem) (void)hipFree(a.mem);
+  hipError_t e = hipSuccess;
+  if (!got.mem) {
+    got.cap = bytes;
+    e = hipMalloc(&got.mem, bytes);
+    if (e == hipErrorOutOfMemory && pool) {
+      (void)hipGetLastError();
+      Arena all[kPoolBlocks];
+      {
+        std::lock_guard<std::mutex> lock(pool->mu);
+        for (int k = 0; k < kPoolBlocks; ++k) { all[k] = pool->block[k]; pool->block[k] = {nullptr, 0}; }
+      }
+      for (const Arena &a : all)
+        if (a.mem) (void)hipFree(a.mem);
+      e = hipMalloc(&got.mem, bytes);
+    }
+    if (e != hipSuccess) got = {nullptr, 0};
+  }
+  *mem = got.mem;
+  *cap = got.cap;
+  return e;
+}
+
+void arenas_give(int device, std::initializer_list<Arena> arenas) {
+  bool worth = false;
+  for (const Arena &a : arenas) worth |= a.mem && a.cap >= kPoolMin && a.cap <= kPoolMax;
+  Pool *pool = device >= 0 && device < 16 && worth ? &g_pool[device] : nullptr;
+  if (pool) {
+    int before = device;
+    bool idle = hipGetDevice(&before) == hipSuccess && (before == device || hipSetDevice(device) == hipSuccess);
+    idle = idle && hipDeviceSynchronize() == hipSuccess;
+    if (before != device) (void)hipSetDevice(before);
+    if (!idle) pool = nullptr;   // (hipFree below waits, or says what is wrong)
+  }
+  for (const Arena &a : arenas) {
+    if (!a.mem) continue;
+    bool kept = false;
+    if (pool && a.cap >= kPoolMin && a.cap <= kPoolMax) {
+      std::lock_guard<std::mutex> lock(pool->mu);
+      for (int k = 0; k < kPoolBlocks && !kept; ++k)
+        if (!pool->block[k].mem) {
+          pool->block[k] = a;
+          pool->passed[k] = 0;
+          kept = true;
+        }
+    }
+    if (!kept) (void)hipFree(a.mem);
+  }
+}
+}  // namespace
+
 static void batch_free(vl_batch *b) {
-  if (b->arena1) (void)hipFree(b->arena1);
-  if (b->arena2) (void)hipFree(b->arena2);
-  if (b->host_counters) (void)hipHostFree(b->host_counters);
-  if (b->stage_mirs) (void)hipHostFree(b->stage_mirs);
-  if (b->stage_a) (void)hipHostFree(b->stage_a);
-  if (b->stage_b) (void)hipHostFree(b->stage_b);
-  if (b->stage_map) (void)hipHostFree(b->stage_map);
+  arenas_give(b->device, {{b->arena1, b->cap1}, {b->arena2, b->cap2}});
+  if (b->pinned) (void)hipHostFree(b->pinned);
   delete b;
 }
 
@@ -1741,6 +1826,14 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   }
   const bool dense = (flags & VL_DENSE_POINTS) != 0;
 
+  // block maps: one entry per stretch of 256 instructions, then one per stretch of 256 entries
+  size_t blocks_instr = 0, blocks_occ = 0;
+  for (uint32_t k = 0; k < n; ++k) {
+    blocks_instr += stretches(mirs[k]->h.N);
+    blocks_occ += stretches(mirs[k]->h.O);
+  }
+  const bool too_many = blocks_instr + blocks_occ > 0x7FFFFFFFull;
+
   // recycle or create the batch
   vl_batch *batch = nullptr;
   bool fresh = false;
@@ -1758,11 +1851,20 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     if (!batch) return VL_E_SHAPE;
     batch->n = n;
     fresh = true;
+    if (too_many) { delete batch; return VL_E_RANGE; }
     hipError_t e = hipGetDevice(&batch->device);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&batch->host_counters, (size_t)n * kCounters * 4, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&batch->stage_mirs, (size_t)n * sizeof(DevMir *), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&batch->stage_a, (size_t)n * sizeof(DevLive), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&batch->stage_b, (size_t)n * sizeof(DevLive), hipHostMallocDefault);
+    Bump pin;
+    const size_t o_cnt = pin.take((size_t)n * kCounters * 4), o_mir = pin.take((size_t)n * sizeof(DevMir *));
+    const size_t o_a = pin.take((size_t)n * sizeof(DevLive)), o_b = pin.take((size_t)n * sizeof(DevLive));
+    const size_t o_map = pin.take((blocks_instr + blocks_occ + 1) * sizeof(uint2));
+    if (e == hipSuccess) e = hipHostMalloc(&batch->pinned, pin.off, hipHostMallocDefault);
+    if (e == hipSuccess) {
+      char *at = (char *)batch->pinned;
+      batch->host_counters = (uint32_t *)(at + o_cnt);
+      batch->stage_mirs = (const DevMir **)(at + o_mir);
+      batch->stage_a = (DevLive *)(at + o_a); batch->stage_b = (DevLive *)(at + o_b);
+      batch->stage_map = (uint2 *)(at + o_map);
+    }
     if (e != hipSuccess) { batch_free(batch); return hip_fail(e); }
   }
   auto fail = [&](int32_t rc) {
@@ -1815,19 +1917,11 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   }
   const size_t o_mirs = bump.take((size_t)n * sizeof(DevMir *));
   const size_t o_lives = bump.take((size_t)n * sizeof(DevLive));
-  // block maps: one entry per stretch of 256 instructions, then one per stretch of 256 entries
-  size_t blocks_instr = 0, blocks_occ = 0;
-  for (uint32_t k = 0; k < n; ++k) {
-    blocks_instr += (mirs[k]->h.N + 255u) / 256u;
-    blocks_occ += (mirs[k]->h.O + 255u) / 256u;
-  }
-  if (blocks_instr + blocks_occ > 0x7FFFFFFFull) return fail(VL_E_RANGE);
   const size_t o_map = bump.take((blocks_instr + blocks_occ + 1) * sizeof(uint2));
   if (bump.off > batch->cap1) {
     if (batch->arena1) { VL_HIP(hipStreamSynchronize(stream)); (void)hipFree(batch->arena1); batch->arena1 = nullptr; batch->cap1 = 0; }
-    hipError_t e = hipMalloc(&batch->arena1, bump.off);
+    hipError_t e = arena_take(batch->device, bump.off, &batch->arena1, &batch->cap1);
     if (e != hipSuccess) return fail(hip_fail(e));
-    batch->cap1 = bump.off;
   }
   char *a1 = (char *)batch->arena1;
   const DevMir **mir_ptrs = batch->stage_mirs;
@@ -1886,9 +1980,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     }
     if (b2.off > batch->cap2) {
       if (batch->arena2) { (void)hipFree(batch->arena2); batch->arena2 = nullptr; batch->cap2 = 0; }
-      hipError_t ae = hipMalloc(&batch->arena2, b2.off);
+      hipError_t ae = arena_take(batch->device, b2.off, &batch->arena2, &batch->cap2);
       if (ae != hipSuccess) return hip_fail(ae);
-      batch->cap2 = b2.off;
     }
     char *a2 = (char *)batch->arena2;
     for (uint32_t k = 0; k < n; ++k) {
@@ -1915,14 +2008,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     memcpy(batch->stage_a, h.data(), (size_t)n * sizeof(DevLive));
     if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_mirs, mir_ptrs, (size_t)n * sizeof(DevMir *), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_lives, batch->stage_a, (size_t)n * sizeof(DevLive), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && batch->map_cap < blocks_instr + blocks_occ + 1) {
-      // (an earlier copy out of the old buffer is complete: growing means other kernels, and
-      // then the sizes were not known and that call waited for the stream)
-      if (batch->stage_map) (void)hipHostFree(batch->stage_map);
-      batch->stage_map = nullptr; batch->map_cap = 0;
-      e = hipHostMalloc((void **)&batch->stage_map, (blocks_instr + blocks_occ + 1) * sizeof(uint2), hipHostMallocDefault);
-      if (e == hipSuccess) batch->map_cap = blocks_instr + blocks_occ + 1;
-    }
     if (e == hipSuccess) {
       uint2 *at = batch->stage_map;
       for (uint32_t k = 0; k < n; ++k)

@@ -56,9 +56,14 @@ static int32_t validate(const vl_mir_desc *d, bool mentions) {
     if (d->instr_occ_off[i + 1] < d->instr_occ_off[i]) return VL_E_SHAPE;
     if (d->instr_occ_off[i + 1] - d->instr_occ_off[i] > vl::kMaxOperands) return VL_E_RANGE;
   }
-  for (uint32_t o = 0; o < d->n_occ; ++o) {
-    if (d->occ_vreg[o] >= d->n_vreg) return VL_E_RANGE;
-    const uint8_t f = d->occ_flags[o];
+  // (one answer for all occurrences, without a branch for each)
+  uint32_t far_vreg = 0;
+  for (uint32_t o = 0; o < d->n_occ; ++o) far_vreg |= d->occ_vreg[o] >= d->n_vreg ? 1u : 0u;
+  uint8_t seen[256] = {};
+  for (uint32_t o = 0; o < d->n_occ; ++o) seen[d->occ_flags[o]] = 1;
+  if (far_vreg) return VL_E_RANGE;
+  for (uint32_t f = 0; f < 256; ++f) {
+    if (!seen[f]) continue;
     if (((f & (VL_OCC_DEF | VL_OCC_USE)) == 0 && !mentions) || (f & ~(VL_OCC_DEF | VL_OCC_USE | VL_OCC_EARLY))) return VL_E_RANGE;
     if ((f & VL_OCC_EARLY) && !(f & VL_OCC_DEF)) return VL_E_RANGE;
   }
@@ -98,25 +103,43 @@ struct LaneMaps {
   uint32_t src_occ, src_vreg;
 };
 
+// The arrays that follow from the description (expansions of the CSR offsets, packed attributes and
+// records) are written by the device: an instruction and a vreg per thread.  They are three quarters
+// of a program's bytes, and putting them together and sending them from the host was most of what
+// vl_mir_create took (16 programs of 1,000-16,000 instructions: 1,900 us, 950 this way).
+__global__ __launch_bounds__(256) void k_derive(const vl::DevMir *__restrict__ prog, const uint8_t *__restrict__ vclass,
+                                                const uint8_t *__restrict__ vwidth, const uint8_t *__restrict__ valign,
+                                                uint32_t *__restrict__ occ_instr, uint32_t *__restrict__ instr_blk,
+                                                uint32_t *__restrict__ vattr, uint64_t *__restrict__ occ_rec) {
+  const uint32_t x = blockIdx.x * 256 + threadIdx.x;
+  const vl::DevMir &m = *prog;
+  if (x < m.V) vattr[x] = vl::attr_pack(vclass[x], vwidth[x], valign[x]) | ((uint32_t)m.class_word[vclass[x]] << 16);
+  if (x >= m.N) return;
+  uint32_t lo = 0, hi = m.B;   // the last block that starts at x or earlier
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (m.blk_start[mid] <= x) lo = mid; else hi = mid;
+  }
+  instr_blk[x] = lo;
+  const uint32_t o0 = m.occ_off[x], o1 = m.occ_off[x + 1];
+  uint32_t all = 0;
+  for (uint32_t o = o0; o < o1; ++o) all |= m.occ_flags[o];
+  const uint32_t keeps = all & VL_OCC_EARLY ? vl::kRecKeeps : 0u;
+  for (uint32_t o = o0; o < o1; ++o) {
+    occ_instr[o] = x;
+    occ_rec[o] = (uint64_t)(m.occ_vreg[o] | keeps) | ((uint64_t)((x << 2) | (m.occ_flags[o] & 3u)) << 32);
+  }
+}
+
+// What a program sends is put together here: kept by the thread for its next program, up to a bound.
+constexpr size_t kImageKeep = 4u << 20;
+thread_local std::vector<char> t_image;
+
 int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   if (!d || !out) return VL_E_NULL;
   int32_t rc = validate(d, maps != nullptr);
   if (rc != VL_OK) return rc;
   const uint32_t N = d->n_instr, V = d->n_vreg, B = d->n_block, O = d->n_occ, E = d->n_edge;
-  // derived index arrays (plain expansions of the CSR offsets) and packed attributes
-  std::vector<uint32_t> occ_instr(O ? O : 1), instr_blk(N), vattr(V ? V : 1);
-  for (uint32_t i = 0; i < N; ++i)
-    for (uint32_t o = d->instr_occ_off[i]; o < d->instr_occ_off[i + 1]; ++o) occ_instr[o] = i;
-  for (uint32_t b = 0; b < B; ++b)
-    for (uint32_t i = d->blk_start[b]; i < d->blk_start[b + 1]; ++i) instr_blk[i] = b;
-  std::vector<uint8_t> instr_keep(N, 0);
-  for (uint32_t o = 0; o < O; ++o)
-    if (d->occ_flags[o] & VL_OCC_EARLY) instr_keep[occ_instr[o]] = 1;
-  std::vector<uint64_t> occ_rec(O ? O : 1);
-  for (uint32_t o = 0; o < O; ++o)
-    occ_rec[o] = (uint64_t)(d->occ_vreg[o] | (instr_keep[occ_instr[o]] ? vl::kRecKeeps : 0u)) |
-                 ((uint64_t)((occ_instr[o] << 2) | (d->occ_flags[o] & 3u)) << 32);
-
   // the device header's class tables come first: the packed attributes carry the class's mask word
   vl::DevMir hh;
   memset(&hh, 0, sizeof(hh));
@@ -140,21 +163,20 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
         if (hh.reserved[c][w]) hh.has_reserved = 1;
       }
   }
-  for (uint32_t v = 0; v < V; ++v)
-    vattr[v] = vl::attr_pack(d->vreg_class[v], d->vreg_width[v], d->vreg_align[v]) | ((uint32_t)hh.class_word[d->vreg_class[v]] << 16);
-
+  // what is sent comes first in the arena, what the device derives from it last
   Bump bump;
   size_t o_blk = bump.take((B + 1) * 4), o_soff = bump.take((B + 1) * 4), o_succ = bump.take((size_t)(E ? E : 1) * 4);
   size_t o_ooff = bump.take((size_t)(N + 1) * 4), o_ov = bump.take((size_t)(O ? O : 1) * 4);
-  size_t o_oi = bump.take((size_t)(O ? O : 1) * 4), o_ib = bump.take((size_t)N * 4);
-  size_t o_va = bump.take((size_t)(V ? V : 1) * 4), o_of = bump.take((size_t)(O ? O : 1));
-  size_t o_rec = bump.take((size_t)(O ? O : 1) * 8);
+  size_t o_of = bump.take((size_t)(O ? O : 1)), o_vc = bump.take(V), o_vw = bump.take(V), o_val = bump.take(V);
   size_t o_src = 0, o_add = 0, o_vv = 0, o_vl = 0;
   if (maps) {
     o_src = bump.take((size_t)(O ? O : 1) * 4); o_add = bump.take((size_t)(O ? O : 1));
     o_vv = bump.take((size_t)(V ? V : 1) * 4); o_vl = bump.take((size_t)(V ? V : 1));
   }
   size_t o_dev = bump.take(sizeof(vl::DevMir));
+  const size_t sent = bump.off;
+  size_t o_oi = bump.take((size_t)(O ? O : 1) * 4), o_ib = bump.take((size_t)N * 4);
+  size_t o_va = bump.take((size_t)(V ? V : 1) * 4), o_rec = bump.take((size_t)(O ? O : 1) * 8);
 
   vl_mir *m = new (std::nothrow) vl_mir;
   if (!m) return VL_E_SHAPE;
@@ -165,8 +187,8 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   if (e == hipSuccess) e = hipMalloc(&m->arena, bump.off);
   if (e != hipSuccess) { delete m; return vl::hip_fail(e); }
   char *base = (char *)m->arena;
-  // the arena is put together on the host and sent in one copy
-  std::vector<char> image(bump.off, 0);
+  std::vector<char> &image = t_image;
+  image.resize(sent);
   auto up = [&](size_t off, const void *src, size_t bytes) {
     if (bytes) memcpy(image.data() + off, src, bytes);
   };
@@ -175,11 +197,8 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   up(o_succ, d->succ, (size_t)E * 4);
   up(o_ooff, d->instr_occ_off, (size_t)(N + 1) * 4);
   up(o_ov, d->occ_vreg, (size_t)O * 4);
-  up(o_oi, occ_instr.data(), (size_t)O * 4);
-  up(o_ib, instr_blk.data(), (size_t)N * 4);
-  up(o_va, vattr.data(), (size_t)V * 4);
   up(o_of, d->occ_flags, (size_t)O);
-  up(o_rec, occ_rec.data(), (size_t)O * 8);
+  up(o_vc, d->vreg_class, V); up(o_vw, d->vreg_width, V); up(o_val, d->vreg_align, V);
   if (maps) {
     up(o_src, maps->occ_src, (size_t)O * 4); up(o_add, maps->occ_add, (size_t)O);
     up(o_vv, maps->val_vreg, (size_t)V * 4); up(o_vl, maps->val_lane, (size_t)V);
@@ -207,7 +226,16 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   }
   m->dev = (vl::DevMir *)(base + o_dev);
   up(o_dev, &h, sizeof(h));
-  e = hipMemcpy(base, image.data(), bump.off, hipMemcpyHostToDevice);
+  e = hipMemcpyAsync(base, image.data(), sent, hipMemcpyHostToDevice, nullptr);
+  if (e == hipSuccess) {
+    k_derive<<<(std::max(N, V) + 255) / 256, 256, 0, nullptr>>>(m->dev, (const uint8_t *)(base + o_vc), (const uint8_t *)(base + o_vw),
+                                                                (const uint8_t *)(base + o_val), (uint32_t *)(base + o_oi),
+                                                                (uint32_t *)(base + o_ib), (uint32_t *)(base + o_va), (uint64_t *)(base + o_rec));
+    e = hipGetLastError();
+    const hipError_t done = hipStreamSynchronize(nullptr);   // the image is reused, and any stream may use the program
+    if (e == hipSuccess) e = done;
+  }
+  if (image.capacity() > kImageKeep) std::vector<char>().swap(image);
   if (e != hipSuccess) {
     (void)hipFree(m->arena);
     delete m;
