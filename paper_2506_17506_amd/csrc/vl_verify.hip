@@ -470,8 +470,10 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
     struct Ev { uint32_t y, zb, t, p; };
     auto fetch_group = [&](uint32_t g0, Ev (&e)[H]) __attribute__((always_inline)) {
       u32x4 x[H];
+      uint32_t a_group = a_ev + g0 * 16u;
+      asm volatile("" : "+v"(a_group));   // the reads differ by constant offsets from it, not by an addition each
 #pragma unroll
-      for (int t = 0; t < H; ++t) x[t] = *(lds_u32x4 *)(size_t)(a_ev + (g0 + t) * 16u);
+      for (int t = 0; t < H; ++t) x[t] = *(lds_u32x4 *)(size_t)(a_group + t * 16u);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < H; ++t) {
@@ -483,11 +485,13 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
     auto apply_group = [&](uint32_t g0, Ev (&e)[H], uint32_t (&hit)[H]) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < H; ++t) {
-        const uint32_t msk = e[t].y << (e[t].p & 31u);
-        const uint32_t old = __hip_atomic_fetch_xor((lds_u32 *)(size_t)(((e[t].p << 3) & 0xF00u) + e[t].zb + a_occ), msk,
-                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        hit[t] = old & msk & e[t].t;
+        e[t].y <<= e[t].p & 31u;
+        e[t].p = __hip_atomic_fetch_xor((lds_u32 *)(size_t)(((e[t].p << 3) & 0xF00u) + e[t].zb + a_occ), e[t].y,
+                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < H; ++t) hit[t] = e[t].p & e[t].y & e[t].t;
     };
     auto settle = [&](uint32_t g0, uint32_t (&hit)[H]) __attribute__((always_inline)) {
       uint32_t any_hit = 0;
