@@ -206,7 +206,7 @@ int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const uint16_t *
 
 /* vl_verify_batch for callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid it.  Same arguments, same results.
- * Its job table and the candidates' smallest violations found so far live in
+ * The candidates' smallest violations found so far and the counters of its workgroups live in
  * a fixed device array inside the library (8 bytes per candidate, VL_STATIC_MAX_K of them:
  * 512 KB per GPU the library runs on, held until the process ends); the call allocates and
  * frees nothing, on the host or the device, and copies nothing from host memory: it only

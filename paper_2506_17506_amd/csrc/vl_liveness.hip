@@ -1,12 +1,12 @@
 // Liveness analysis on the GPU, batched over kernels (one grid slice per kernel).
 //
 // Pipeline (every step is a kernel below; the host only sizes buffers):
-//   1. group operand occurrences by vreg, ascending (count / scan / place / sort)
-//   2. per-block use and def bitsets from the first mention of each vreg in a block
+//   1. group operand occurrences by vreg (large programs: count / scan / place / sort)
+//   2. put them in order; per-block use and def bitsets from the first mention of each vreg in a block
 //   3. backward dataflow to the least fixed point, one bitset word per lane
 //   4. per occurrence: liveness after its instruction, kill flag, and its role in
 //      the verifier's event stream
-//   5. count, scan and write the event stream, the live intervals and the
+//   5. count, prefix and write the event stream, the live intervals and the
 //      per-tile live-in lists; optionally the dense per-point bitsets
 // The paper defers this to "following the control and data dependency"
 // (Section 4.6); the dataflow equations are the textbook ones its Safety

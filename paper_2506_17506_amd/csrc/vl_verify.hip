@@ -14,8 +14,8 @@
 //                 [word][lane]; a definition tests its range against the
 //                 mask, then sets it; kills clear it.  Tiles start from the
 //                 live-in list of their first instruction.
-// Each lane keeps the smallest violation key it has seen; tiles combine with
-// an atomic minimum in the result slot.  (Section 3.4 of the paper states the
+// Each lane keeps the smallest violation key it has seen; tiles combine on a
+// board in memory, and the last one to report writes the results.  (Section 3.4 of the paper states the
 // three conditions; Section 1 items (1) and (2) define a correct allocation.)
 #include <cstring>
 #include <mutex>
@@ -97,7 +97,7 @@ template <class Job> __device__ inline uint32_t cand_at(const Job &J, uint32_t k
 //     check per lane, looping over their share of the rows: what is uniform per check
 //     (ring offsets, class limits) is then computed once per lane instead of once per
 //     check and candidate.
-// Violations go to a per-row key in LDS (smallest wins) and from there to the result slot.
+// Violations go to a per-row key in LDS (smallest wins) and from there to the board.
 // LDS layout (indices into the dynamic shared array, kept as integers so that every
 // access is a DS instruction rather than a flat one):
 //   [0, occ_words * 64)            occupancy masks [word][lane]
@@ -245,7 +245,6 @@ __device__ inline bool in_ring(const Walk &w, uint32_t o) {
   return o < w.hi && o + kWalkReach >= w.hi && o >= w.lo;
 }
 
-// value of occurrence o (uniform) in this lane's row
 // value of occurrence o in this lane's row, from memory
 template <bool kT>
 __device__ inline uint32_t from_memory(const Walk &w, uint32_t o) {
