@@ -153,7 +153,7 @@ int32_t vl_lanes_expand(const vl_mir *mir, const uint16_t *cand, uint32_t K, uin
  * On error no handle is created; recycled handles stay allocated but their
  * contents are undefined until the next successful call.
  * tile_len: instructions per verification tile, 0 = library default (512, less for batches of
- * fewer than half a million instructions in total, down to 128).
+ * fewer than half a million instructions in total, down to 128, and to 32 below 6,144).
  * Errors: VL_E_NOT_STRICT / VL_E_LAYOUT refer to the first offending kernel. */
 int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint32_t flags, uint32_t tile_len,
                           vl_stream stream, vl_live **live);
