@@ -423,7 +423,7 @@ constexpr uint32_t kOrdBack = 72;        // entries before the stretch that are 
 constexpr uint32_t kOrdMargin = 128;
 constexpr uint32_t kOrdWindow = kOrdBack + kOrdStretch + 2 * kOrdMargin;
 constexpr uint32_t kOrdPer = (kOrdWindow + kOrdThreads - 1) / kOrdThreads;
-constexpr uint32_t kOrdWords = kOrdStretch / 32 + 1;   // most words a stretch can touch
+constexpr uint32_t kOrdWords = kOrdStretch / 32 + 1;   // most words a stretch touches when every vreg is mentioned
 static_assert(kOrdBack > kMaxOperands, "the look-back has to leave an instruction");
 
 template <bool kSorted>
@@ -462,8 +462,13 @@ __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_
   }
   if (tid == 0) { crossing = 0; n_edge = 0; }
   if (tid < kRound / 32) bits[tid] = 0;
-  for (uint32_t x = tid; x < min(2 * m.B * kOrdWords, lds_words); x += kOrdThreads) sm[x] = 0;
   __syncthreads();
+  // the range of bitset words is known once the vregs are staged (putting a list in order leaves each
+  // place its vreg): the table is cleared exactly as far as it will be used.  Vregs that are never mentioned
+  // take no entries but widen the range, and the launch's LDS is sized by its largest program
+  const uint32_t word0 = s_v[s0 - w_lo] >> 5, n_words = (s_v[s1 - 1 - w_lo] >> 5) - word0 + 1;
+  const bool table = (size_t)2 * m.B * n_words <= lds_words;
+  for (uint32_t x = tid; table && x < 2 * m.B * n_words; x += kOrdThreads) sm[x] = 0;
   const uint32_t edge_v[2] = {s_v[0], s_v[n_win - 1]}, edge_round[2] = {s_o[0] / kRound, s_o[n_win - 1] / kRound};
 #pragma unroll
   for (uint32_t u = 0; u < kOrdPer; ++u) {
@@ -560,9 +565,6 @@ __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_
     starts[u] = e < s1 && m.blk_start[blk[u]] == s_ifl[e - w_lo] >> 2;
   }
   __syncthreads();
-  // (vregs that are never mentioned take no entries but widen the range)
-  const uint32_t word0 = s_v[s0 - w_lo] >> 5, n_words = (s_v[s1 - 1 - w_lo] >> 5) - word0 + 1;
-  const bool table = (size_t)2 * m.B * n_words <= lds_words;
   uint32_t *const def_l = sm, *const use_l = sm + m.B * n_words;
 #pragma unroll
   for (uint32_t u = 0; u < kOrdered; ++u) {

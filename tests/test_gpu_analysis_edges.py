@@ -90,3 +90,40 @@ def test_many_tiles(tile_len):
 def test_wide_rows(n_vreg):
     """around the 1,024 words that one workgroup takes"""
     check([flow_program(5, 4, n_vreg, 40), flow_program(6, 9, 50, 30)], dense=False)
+
+
+def with_gaps(m, step):
+    """the program with its vregs numbered `step` apart: those in between are never mentioned"""
+    V = m.n_vreg * step
+    return Mir(m.blk_start, m.succ_off, m.succ, m.instr_occ_off, m.occ_vreg * np.uint32(step), m.occ_flags,
+               np.zeros(V, np.uint8), np.ones(V, np.uint8), np.ones(V, np.uint8), m.class_size, None, name=f"{m.name}_by{step}")
+
+
+@pytest.mark.parametrize("n_block,step", [(1, 4), (2, 16), (3, 64)])
+def test_gaps_in_the_numbering_beside_a_program_of_many_blocks(n_block, step):
+    """1,024 entries of the small program span more bitset words than they could without gaps, and the
+    other program's blocks make room for a table of that many: the block sets are collected there, in new
+    handles and in recycled ones (whose sizes are not read back)"""
+    rng = np.random.default_rng(step)
+    V = 700
+    defs = [([v], []) for v in range(V)]
+    reads = [([], sorted(set(rng.integers(0, V, 2).tolist()))) for _ in range(V)]
+    cut = np.linspace(0, len(reads), n_block + 1).astype(int)
+    blocks = [(defs if b == 0 else []) + reads[cut[b]:cut[b + 1]] for b in range(n_block)]
+    succ = [[b + 1] if b + 1 < n_block else [] for b in range(n_block)]
+    small = with_gaps(Mir.build(blocks, succ, V, (512,), name=f"gaps{n_block}"), step)
+    mirs = [flow_program(1, 22, 34 * 32, 8), small, flow_program(2, 22, 40 * 32, 8)]
+    ans = [vlo.analyze(m, threads=8) for m in mirs]
+    assert all(an.contract == 0 for an in ans)
+    hm, hl, got, _ = gpu_analyze(mirs)
+    try:
+        for _ in range(2):
+            for m, an, g in zip(mirs, ans, got):
+                assert_liveness_equal(m, an, g, m.name)
+            hl = vl.vl_liveness_multi(hm, vl.VL_DENSE_POINTS, live=hl)
+            torch.cuda.synchronize()
+            got = [vl.view_to_numpy(vl.vl_live_get(h)) for h in hl]
+        for m, an, g in zip(mirs, ans, got):
+            assert_liveness_equal(m, an, g, m.name)
+    finally:
+        free(hm, hl)
