@@ -164,7 +164,7 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
   const uint16_t *next = nullptr;
   for (uint32_t j = 0; j < n; ++j) {
     const vl_mask_query &u = queries[j];
-    const bool same = u.mir == mir && u.live == live;
+    const bool same = j > 0 && u.mir == mir && u.live == live;   // (checked with the query before)
     if (!same || !u.cand) {
       if (!u.mir || !u.live || !u.cand) return VL_E_NULL;
       if (u.mir->magic != kMirMagic || u.live->magic != kLiveMagic || u.live->mir != u.mir || u.mir->lowered) return VL_E_ARG;

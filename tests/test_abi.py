@@ -118,3 +118,20 @@ def test_null_arguments():
     assert lib.vl_live_get(None, None) == -1
     lib.vl_mir_destroy(None)
     lib.vl_live_destroy(None)
+
+
+def test_mask_queries_with_null_pointers():
+    """refused before anything is read through them (the pointers that are given are never read)"""
+    lib = vl.load()
+    mir, live, cand, masks = (C.create_string_buffer(4096) for _ in range(4))
+    for has_mir in (False, True):
+        for has_live in (False, True):
+            for has_cand in (False, True):
+                if has_mir and has_live and has_cand:
+                    continue
+                q = (binding._MaskQuery * 2)()
+                for x in q:
+                    x.mir = C.addressof(mir) if has_mir else None
+                    x.live = C.addressof(live) if has_live else None
+                    x.cand = C.addressof(cand) if has_cand else None
+                assert lib.vl_free_bases_multi(q, 2, masks, None) == -1, (has_mir, has_live, has_cand)

@@ -10,6 +10,7 @@ torch = pytest.importorskip("torch")
 
 import paper_2506_17506_amd as vl  # noqa: E402
 from oracle import vlo  # noqa: E402
+from vlgen import gen  # noqa: E402
 from vlgen.mir import Mir  # noqa: E402
 from vlgen.mixed import mixed_mir  # noqa: E402
 from test_gpu_parity import free, gpu_analyze  # noqa: E402
@@ -78,3 +79,22 @@ def test_many_live_values_and_many_queries(n_live, n_queries):
         assert (got == want[[k for k, _ in qs]]).all()
     finally:
         free(hm, hl)
+
+
+@pytest.mark.parametrize("missing", ["mir", "live", "cand"])
+def test_null_pointers_in_a_later_query(missing):
+    k = gen.Kernel(gen.STRAIGHT, 3, 60, 60)
+    hm = vl.vl_mir_create(k.mir)
+    hl = vl.vl_liveness(hm)
+    rows = torch.zeros((1, vl.pad_ld(k.mir.n_occ)), dtype=torch.int16, device="cuda")
+    masks = torch.zeros((3, 16), dtype=torch.int32, device="cuda")
+    try:
+        queries = vl.make_mask_queries([(hm, hl, rows, 0)] * 3)
+        setattr(queries[2], missing, None)
+        with pytest.raises(vl.VlError) as e:
+            vl.vl_free_bases_multi(queries, masks)
+        assert e.value.code == -1
+    finally:
+        torch.cuda.synchronize()
+        vl.vl_live_destroy(hl)
+        vl.vl_mir_destroy(hm)
