@@ -1041,7 +1041,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
     const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only);
     if (rc != VL_OK) return rc;
   }
-  if (results_only && n_jobs > 1 && s.n_valid == n_jobs) {
+  if (results_only && n_jobs > 1 && s.n_valid == n_jobs && s.board) {
     // the table a verification call on this stream left behind serves, whatever its candidate
     // layout, when it names the same results
     bool same = true;
@@ -1051,6 +1051,15 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
       out.finished = s.board;
       return VL_OK;
     }
+  }
+  if (!s.board || (!results_only && (s.groups_cap < out.groups || s.rows_cap < out.total_rows))) {
+    VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
+    if (s.board) (void)hipFree(s.board);
+    s.board = nullptr; s.groups_cap = s.rows_cap = 0;
+    const uint64_t rows = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2), groups = std::max<uint64_t>(4096, out.groups + out.groups / 2);
+    VL_HIP(hipMalloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
+    k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
+    s.rows_cap = rows; s.groups_cap = groups;
   }
   if (n_jobs == 1) {
     out.one = tab[0];   // goes to the kernels as an argument
@@ -1082,15 +1091,6 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
       s.in_flight[s.turn] = true;
       s.n_valid = n_jobs;
     }
-  }
-  if (!s.board || (!results_only && (s.groups_cap < out.groups || s.rows_cap < out.total_rows))) {
-    VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
-    if (s.board) (void)hipFree(s.board);
-    s.board = nullptr; s.groups_cap = s.rows_cap = 0;
-    const uint64_t rows = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2), groups = std::max<uint64_t>(4096, out.groups + out.groups / 2);
-    VL_HIP(hipMalloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
-    k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
-    s.rows_cap = rows; s.groups_cap = groups;
   }
   out.dev = s.dev;
   out.finished = s.board;

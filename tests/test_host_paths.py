@@ -1,0 +1,72 @@
+"""The library's host code on a stand-in runtime: what it allocates, uploads and launches, and what it
+does when memory runs out."""
+import ctypes as C
+
+import numpy as np
+
+from stand_in import in_own_process
+from vlgen.mir import Mir
+
+S1 = 0x1000   # a stream, to the library a handle like any other
+
+
+def program(n=8):
+    return Mir.build([[((v,), ()) for v in range(n)] + [((), (v,)) for v in range(n)]], [[]], n, [64])
+
+
+def analysed(s, how_many):
+    hm = [s.vl.vl_mir_create(program(8 + k)) for k in range(how_many)]
+    hl = s.vl.vl_liveness_multi(hm, stream=S1)
+    return hm, hl
+
+
+class Buffer:
+    """host memory that stands for a device buffer"""
+    def __init__(self, n_bytes):
+        self.mem = np.zeros(n_bytes + 64, np.uint8)
+
+    def data_ptr(self):
+        return (self.mem.ctypes.data + 63) & ~63
+
+
+def jobs_of(s, hm, hl, K, record=16):
+    bufs = [(Buffer(K * 128), Buffer(K * record)) for _ in hm]
+    return [(m, l, c, K, 64, o) for m, l, (c, o) in zip(hm, hl, bufs)], bufs
+
+
+@in_own_process
+def test_reductions_after_a_verification_that_ran_out_of_memory(s):
+    """whichever allocation of the verification fails: the reductions that follow have their counter"""
+    hm, hl = analysed(s, 2)
+    jobs, keep = jobs_of(s, hm, hl, 8)
+    arr = s.vl.make_jobs(jobs)
+    sums, stats = Buffer(48), Buffer(48)
+    failed = 0
+    for stream, fail in ((S1, 0), (S1 + 1, 1)):   # a stream's first call allocates its table and its board
+        s.fail_allocation(fail)
+        try:
+            s.vl.vl_verify_multi(arr, stream=stream)
+        except s.vl.VlError as e:
+            assert e.code == -6
+            failed += 1
+        s.launches.clear()
+        s.vl.vl_summarize_multi(arr, sums, stats, stream=stream)
+        (launch,) = [x for x in s.launches if "k_summarize" in x[0]]
+        assert launch[5][1] != 0, "no counter"
+    assert failed == 2
+    # a board that was given up for a larger one that could not be had
+    many, keep2 = jobs_of(s, hm, hl, 8)
+    big = s.vl.make_jobs(many)
+    for j in big:
+        j.K = 1 << 20   # (nothing is read: the kernels are not run)
+    s.vl.vl_verify_multi(arr, stream=S1)
+    s.fail_allocation(0)
+    try:
+        s.vl.vl_verify_multi(big, stream=S1)
+        raise AssertionError("the allocation did not fail")
+    except s.vl.VlError as e:
+        assert e.code == -6
+    for which in (arr, big):
+        s.launches.clear()
+        s.vl.vl_summarize_multi(which, sums, stats, stream=S1)
+        assert [x[5][1] != 0 for x in s.launches if "k_summarize" in x[0]] == [True]
