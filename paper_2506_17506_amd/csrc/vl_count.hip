@@ -346,6 +346,7 @@ struct Work {
   uint32_t cap = 0;                       // jobs
   char *mem = nullptr;                    // verdicts, failed samples, units, tables that do not fit LDS
   size_t mem_cap = 0;
+  WalkSpace walk;                         // job table and board of the walk: a stream's own stay as its verifications left them
   hipEvent_t consumed = nullptr;          // recorded after the last kernel of a call
   bool in_flight = false;
 };
@@ -531,7 +532,7 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
     at += u.K;
   }
   VL_HIP(hipMemcpyAsync(w.dev, w.host, sizeof(Head) + (size_t)n_jobs * sizeof(DevCountJob), hipMemcpyHostToDevice, stream));
-  const int32_t rc = verdicts_only(walk.data(), n_jobs, stream);
+  const int32_t rc = verdicts_only(walk.data(), n_jobs, stream, w.walk);
   if (rc != VL_OK) {
     (void)hipStreamSynchronize(stream);   // the table's upload
     return rc;

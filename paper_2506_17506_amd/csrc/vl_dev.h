@@ -289,8 +289,24 @@ struct vl_live {
 namespace vl {
 constexpr uint64_t kMirMagic = 0x564c4d4952ull, kLiveMagic = 0x564c4c495645ull;
 int32_t hip_fail(hipError_t e);
+// What a verification's launches work in beside the caller's memory.  Each calling stream has one, and
+// each workspace of the all-violations mode its own: calls that share one run one after the other.
+struct DevJob;   // vl_verify.hip
+constexpr uint32_t kStaged = 4;
+struct WalkSpace {
+  DevJob *dev = nullptr;
+  // the tables on their way to the device: pinned copies used in turn, so that a call with another
+  // table than the last waits only for the upload kStaged calls ago; `host` is the latest one
+  DevJob *staged = nullptr, *host = nullptr;
+  hipEvent_t copied[kStaged] = {};
+  bool in_flight[kStaged] = {};
+  uint32_t turn = 0;
+  uint32_t cap = 0, n_valid = 0;
+  uint32_t *board = nullptr;                 // zero between calls
+  uint64_t groups_cap = 0, rows_cap = 0;     // what the board has room for
+};
 // vl_verify_multi without the search for the pair of a safety violation (vl_verify.hip)
-int32_t verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream);
+int32_t verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &space);
 #define VL_HIP(call)                                   \
   do {                                                 \
     hipError_t e_ = (call);                            \

@@ -29,6 +29,19 @@
 
 using namespace vl;
 
+namespace vl {
+struct DevJob {
+  const DevMir *mir;
+  const DevLive *live;
+  const uint16_t *cand;
+  vl_result *out;
+  uint64_t ld;
+  uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
+  uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
+  // direct: row-major, aligned, and every row holds whole chunks up to its pitch (fetched without bounds)
+};
+}  // namespace vl
+
 namespace {
 
 // Occurrences kept per candidate in LDS: three chunks.  A ring slot holds one uint16 per
@@ -48,17 +61,6 @@ constexpr int kStagePasses = (8 + kCheckWaves - 1) / kCheckWaves;
 constexpr uint32_t kChunk = kWalkChunk;                 // occurrences staged per step (128 B per row)
 constexpr uint32_t kKeyOk = 0xFFFFFFFFu;
 constexpr uint32_t kKeyCons = 0u << 28, kKeyReal = 1u << 28, kKeySafe = 2u << 28, kKeyPos = (1u << 28) - 1;
-
-struct DevJob {
-  const DevMir *mir;
-  const DevLive *live;
-  const uint16_t *cand;
-  vl_result *out;
-  uint64_t ld;
-  uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
-  uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
-  // direct: row-major, aligned, and every row holds whole chunks up to its pitch (fetched without bounds)
-};
 
 // What the workgroups of one verification share.  Everything is zero before the walk and left
 // zero by it, so that no launch is needed to clear it.
@@ -912,24 +914,14 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
 // Job tables on the device: per device a few slots, one per stream that has called, so
 // that calls alternating between streams neither wait for each other's table nor overwrite
 // a table that kernels of the other stream still read.
-constexpr uint32_t kStaged = 4;
 struct Slot {
   bool used = false;
   hipStream_t stream = nullptr;
-  DevJob *dev = nullptr;
-  // the tables on their way to the device: pinned copies used in turn, so that a call with another
-  // table than the last waits only for the upload kStaged calls ago; `host` is the latest one
-  DevJob *staged = nullptr, *host = nullptr;
-  hipEvent_t copied[kStaged] = {};
-  bool in_flight[kStaged] = {};
-  uint32_t turn = 0;
-  uint32_t cap = 0, n_valid = 0;
-  uint32_t *board = nullptr;                 // kHeadWords (the first: Launch::finished), Board::arrived, Board::keys; zero between calls
-  uint64_t groups_cap = 0, rows_cap = 0;     // what the board has room for
+  WalkSpace space;
   uint64_t tick = 0;
 };
 constexpr int kSlots = 4;
-constexpr uint32_t kHeadWords = 64;
+constexpr uint32_t kHeadWords = 64;   // of a board: the first is Launch::finished, then Board::arrived, Board::keys
 constexpr uint64_t kResolveGroups = 4096;   // workgroups that share out the clashes to resolve, about
 struct Scratch {
   std::mutex mu;
@@ -1008,17 +1000,14 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   return VL_OK;
 }
 
-// Validates the jobs, lays out the device job table and makes sure the device copy is
-// current (the copy is skipped when the table is the one the stream's slot already holds).
-// Called with the device's scratch locked.
 __global__ void k_clear_board(uint32_t *p, uint64_t n) {
   for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (uint64_t)gridDim.x * blockDim.x) p[x] = 0;
 }
 
-int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Scratch &sc, Launch &out, bool transposed = false,
-                     bool results_only = false) {
-  // the calling stream's slot, else a free one, else the least recently used one (whose
-  // earlier kernels may be anywhere: the device is drained before the slot changes hands)
+// The calling stream's slot, else a free one, else the least recently used one (whose
+// earlier kernels may be anywhere: the device is drained before the slot changes hands).
+// Called with the device's scratch locked.
+int32_t space_of(Scratch &sc, hipStream_t stream, WalkSpace *&out) {
   Slot *found = nullptr;
   for (Slot &c : sc.slot)
     if (c.used && c.stream == stream) found = &c;
@@ -1030,12 +1019,20 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Sc
     for (Slot &c : sc.slot)
       if (c.tick < found->tick) found = &c;
     VL_HIP(hipDeviceSynchronize());
-    found->n_valid = 0;
+    found->space.n_valid = 0;
   }
-  Slot &s = *found;
-  s.used = true;
-  s.stream = stream;
-  s.tick = ++sc.clock;
+  found->used = true;
+  found->stream = stream;
+  found->tick = ++sc.clock;
+  out = &found->space;
+  return VL_OK;
+}
+
+// Validates the jobs, lays out the device job table and makes sure the device copy is
+// current (the copy is skipped when the table is the one the space already holds).  The space is the
+// caller's for the duration of the call, and its earlier kernels run on `stream` or have ended.
+int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &s, Launch &out, bool transposed = false,
+                     bool results_only = false) {
   std::vector<DevJob> tab(n_jobs);
   for (uint32_t j = 0; j < n_jobs; ++j) {
     const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only);
@@ -1171,8 +1168,10 @@ extern "C" int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_su
   if (device < 0 || device >= 16) return VL_E_ARG;
   Scratch &s = g_scratch[device];
   std::lock_guard<std::mutex> lock(s.mu);
+  WalkSpace *space = nullptr;
   Launch L;
-  const int32_t rc = prepare_jobs(jobs, n_jobs, stream, s, L, false, true);
+  int32_t rc = space_of(s, stream, space);
+  if (rc == VL_OK) rc = prepare_jobs(jobs, n_jobs, stream, *space, L, false, true);
   if (rc != VL_OK) return rc;
   k_summarize<<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, L.one, summaries, stats, L.finished);
   VL_HIP(hipGetLastError());
@@ -1184,7 +1183,7 @@ namespace {
 int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool transposed, bool with_pairs) {
   const bool narrow = L.max_rows <= kPitchNarrow;   // every group of every job fits the narrow ring
   const size_t lds = (size_t)L.max_words * 64 * 4 + 64 * 4 + 1024 + (size_t)kRing * (narrow ? kPitchNarrow : kPitchWide) * 2;
-  if (g_time_start) VL_HIP(hipEventRecord(g_time_start, stream));
+  if (with_pairs && g_time_start) VL_HIP(hipEventRecord(g_time_start, stream));   // (the hook is for the verification calls)
   auto walk = [&](auto by_table, auto by_argument) {
     (n_jobs == 1 ? by_argument : by_table)<<<L.units, kWalkThreads, lds, stream>>>(L.one, L.dev, n_jobs, L.board);
   };
@@ -1200,10 +1199,13 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
     else VL_WALK(kPitchWide, false, false);
   }
 #undef VL_WALK
+  if (!with_pairs) {
+    VL_HIP(hipGetLastError());
+    return VL_OK;
+  }
   if (g_time_stop) VL_HIP(hipEventRecord(g_time_stop, stream));
   g_time_start = g_time_stop = nullptr;
   VL_HIP(hipGetLastError());
-  if (!with_pairs) return VL_OK;
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
   (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
       L.dev, n_jobs, L.one, per_group);
@@ -1211,7 +1213,7 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   return VL_OK;
 }
 
-int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, bool transposed, bool with_pairs = true) {
+int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, bool transposed) {
   if (!jobs) return VL_E_NULL;
   if (n_jobs == 0 || n_jobs > 65535) return VL_E_SHAPE;
   int device = 0;
@@ -1219,15 +1221,20 @@ int32_t verify_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, boo
   if (device < 0 || device >= 16) return VL_E_ARG;
   Scratch &s = g_scratch[device];
   std::lock_guard<std::mutex> lock(s.mu);
+  WalkSpace *space = nullptr;
   Launch L;
-  const int32_t rc = prepare_jobs(jobs, n_jobs, stream, s, L, transposed);
+  int32_t rc = space_of(s, stream, space);
+  if (rc == VL_OK) rc = prepare_jobs(jobs, n_jobs, stream, *space, L, transposed);
   if (rc != VL_OK) return rc;
-  return launch_all(L, n_jobs, stream, transposed, with_pairs);
+  return launch_all(L, n_jobs, stream, transposed, true);
 }
 }  // namespace
 
-int32_t vl::verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream) {
-  return verify_jobs(jobs, n_jobs, stream, false, false);
+int32_t vl::verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &space) {
+  Launch L;
+  const int32_t rc = prepare_jobs(jobs, n_jobs, stream, space, L);
+  if (rc != VL_OK) return rc;
+  return launch_all(L, n_jobs, stream, false, false);
 }
 
 extern "C" int32_t vl_verify_multi(const vl_job *jobs, uint32_t n_jobs, vl_stream stream) {

@@ -32,6 +32,8 @@ class StandIn:
         words = []
         if "k_summarize" in name:   # its fourth and sixth arguments
             words = [C.cast(args[k], C.POINTER(C.c_uint64))[0] for k in (3, 5)]
+        elif "k_walk" in name:       # its job table
+            words = [C.cast(args[1], C.POINTER(C.c_uint64))[0]]
         self.launches.append((name, grid, block, lds, stream, words))
 
     def fail_allocation(self, after, more=0):

@@ -117,3 +117,48 @@ def test_graph_replays_match_eager_and_oracle():
         else:
             for m in hm:
                 vl.vl_mir_destroy(m)
+
+
+def test_replays_with_counting_calls_in_between():
+    """the all-violations mode verifies too, with a table of its own: a pass of several jobs recorded on
+    the same stream still writes its own results"""
+    w = gen.config(5, n_kernels=3)
+    mirs = [k.mir for k in w.kernels]
+    ans = [vlo.analyze(m, threads=16) for m in mirs]
+    want = [vlo.verify(m, an, rows, threads=16) for m, an, rows in zip(mirs, ans, w.rows)]
+    hm = [vl.vl_mir_create(m) for m in mirs]
+    side = torch.cuda.Stream()
+    hl = None
+    try:
+        with torch.cuda.stream(side):
+            hl = vl.vl_liveness_multi(hm, 0, 0)
+            devs = [vl.rows_to_device(rows) for rows in w.rows]
+            outs = [torch.full((rows.shape[0], 4), -1, dtype=torch.int32, device="cuda") for rows in w.rows]
+            cnts = [torch.full((rows.shape[0], 8), -1, dtype=torch.int32, device="cuda") for rows in w.rows]
+            jobs = vl.make_jobs([(m, l, d, d.shape[0], ld, o) for m, l, (d, ld), o in zip(hm, hl, devs, outs)])
+            counting = [(m, l, d, d.shape[0], ld, o) for m, l, (d, ld), o in zip(hm, hl, devs, cnts)]
+            vl.vl_verify_multi(jobs)
+            vl.vl_count_violations_multi(counting)
+            vl.vl_verify_multi(jobs)
+            side.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                vl.vl_verify_multi(jobs)
+            for _ in range(3):
+                vl.vl_count_violations_multi(counting[::-1])
+                for o in outs:
+                    o.fill_(-1)
+                side.synchronize()
+                graph.replay()
+                side.synchronize()
+                for k in range(len(mirs)):
+                    assert_results_equal(want[k], results(outs)[k], f"kernel {k}")
+                    kinds = cnts[k].cpu().numpy()[:, 0]
+                    assert ((kinds != 0) == (want[k]["status"] != 0)).all()
+    finally:
+        torch.cuda.synchronize()
+        if hl is not None:
+            free(hm, hl)
+        else:
+            for m in hm:
+                vl.vl_mir_destroy(m)

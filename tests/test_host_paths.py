@@ -70,3 +70,40 @@ def test_reductions_after_a_verification_that_ran_out_of_memory(s):
         s.launches.clear()
         s.vl.vl_summarize_multi(which, sums, stats, stream=S1)
         assert [x[5][1] != 0 for x in s.launches if "k_summarize" in x[0]] == [True]
+
+
+@in_own_process
+def test_counting_leaves_the_streams_verification_as_it_was(s):
+    """a recorded verification replays over the table it was recorded with, and a loop of verifying and
+    counting uploads nothing once it has settled"""
+    hm, hl = analysed(s, 3)
+    jobs, keep = jobs_of(s, hm, hl, 8)
+    counts, keep2 = jobs_of(s, hm, hl, 8, record=32)
+    arr = s.vl.make_jobs(jobs)
+    s.vl.vl_verify_multi(arr, stream=S1)
+    (table,) = [x[5][0] for x in s.launches if "k_walk" in x[0]]
+    before = C.string_at(table, 3 * 32)
+    for _ in range(9):   # more than there are workspaces and staged tables
+        s.launches.clear()
+        s.vl.vl_count_violations_multi(counts, stream=S1)
+        assert [x[5][0] != table for x in s.launches if "k_walk" in x[0]] == [True]
+        assert C.string_at(table, 3 * 32) == before
+        uploads = s.counts()["uploads"]
+        s.vl.vl_verify_multi(arr, stream=S1)
+        assert s.counts()["uploads"] == uploads, "the table was uploaded again"
+
+
+@in_own_process
+def test_counting_takes_no_streams_place(s):
+    """four streams verify without waiting for the device, whatever other streams count"""
+    hm, hl = analysed(s, 2)
+    jobs, keep = jobs_of(s, hm, hl, 8)
+    counts, keep2 = jobs_of(s, hm, hl, 8, record=32)
+    arr = s.vl.make_jobs(jobs)
+    for k in range(8):
+        s.vl.vl_count_violations_multi(counts, stream=S1 + 100 + k)
+    for _ in range(2):
+        for k in range(4):
+            s.vl.vl_verify_multi(arr, stream=S1 + k)
+            s.vl.vl_count_violations_multi(counts, stream=S1 + 200)
+    assert s.counts()["device_waits"] == 0
