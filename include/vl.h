@@ -196,10 +196,9 @@ enum { VL_BAD_BOUNDS = 1, VL_BAD_ALIGN = 2, VL_BAD_RESERVED = 4 };
 /* Checks K candidates of one kernel (Section 3.4; Section 3.4's regeneration
  * loop supplies the K samples).  cand [device]: K rows of uint16, row k at
  * cand + k*ld, one physical base register per operand occurrence; ld >= n_occ.
- * Rows are read fastest when cand is 16-byte aligned and ld is a multiple of 8; when ld is
- * also at least n_occ rounded up to a multiple of 64, rows are fetched in whole 128-byte
- * lines up to that bound, so all K x ld elements must then belong to the buffer (what the
- * padding holds is ignored).
+ * Rows are read fastest when cand is 16-byte aligned, ld is a multiple of 8 and at least
+ * n_occ rounded up to a multiple of 64.  Of a row nothing is read past its registers but the
+ * rest of the 16 bytes (rows on 16-byte boundaries) or the 4 bytes that its last one lies in.
  * out [device]: K results.  Asynchronous on `stream`. */
 int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const uint16_t *cand, uint32_t K,
                         uint64_t ld, vl_result *out, vl_stream stream);
@@ -275,7 +274,8 @@ int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_summary *summ
  * jobs is [host]; cand and out inside are [device]; out receives K records.  The first call
  * that sees a program enumerates its interfering pairs from `live` (whose analysis must be
  * complete or enqueued on `stream`), synchronising the stream, and keeps them with the
- * vl_mir handle; later calls are asynchronous on `stream` (the library has four
+ * vl_mir handle; later calls are asynchronous on `stream` (rows are read
+ * as vl_verify_batch reads them; the library has four
  * workspaces per device, used in turn: a call waits on the host until the kernels of the fourth
  * last call have finished with theirs).
  * Errors: VL_E_NULL, VL_E_ARG (handles of different programs), VL_E_SHAPE (n_jobs == 0 or

@@ -38,7 +38,7 @@ struct DevJob {
   uint64_t ld;
   uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
   uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
-  // direct: row-major, aligned, and every row holds whole chunks up to its pitch (fetched without bounds)
+  // direct: row-major, aligned, and every row has room for whole chunks up to its pitch
 };
 }  // namespace vl
 
@@ -121,6 +121,7 @@ struct Walk {
   // row-major staging: per pass, this lane's byte offset into the group's rows and its uint16 index into
   // ring slot 0 (kNone in from_row: the pass has no row for this lane)
   uint32_t from_row[kStagePasses], to_ring[kStagePasses];
+  int32_t last_piece;   // direct staging: from this lane's piece of a row's first chunk to the last piece with registers, in bytes
 };
 
 // Staging is done by the three check wavefronts.  A chunk is 64 rows x 8 pieces of 16 bytes
@@ -172,17 +173,19 @@ __device__ inline void store_chunk_occ(const Walk &w, uint32_t c0, uint32_t j) {
 }
 
 // Direct staging, when every job of the launch allows it (DevJob::direct): without the
-// per-lane bounds of the general path, a buffer read per pass (descriptor of the group's rows
-// and the chunk's byte offset in scalar registers, the lane's row offset from set-up) and
-// eight 2-byte stores from an address that only needs the chunk's slot added.  Rows past the
-// group's last are never written; their ring entries are cleared once at the start.  What a
-// row holds beyond the program's last occurrence (up to its pitch) lands in the ring and is
-// never looked at.
+// per-lane branches of the general path, a buffer read per pass (descriptor of the group's rows
+// in scalar registers, the lane's row offset from set-up) and eight 2-byte stores from an address
+// that only needs the chunk's slot added.  Rows past the group's last are never written; their ring
+// entries are cleared once at the start.  Beyond the program's last occurrence nothing is read but
+// the rest of the 16 bytes it lies in: lanes whose piece lies further repeat that one (a minimum per
+// chunk and an addition per pass, which cost nothing that could be measured), and what lands in the
+// ring there is never looked at.
 __device__ inline void load_chunk_direct(Walk &w, uint32_t c0, __amdgpu_buffer_rsrc_t rows) {
+  const int32_t at = min((int32_t)(c0 * 2u), w.last_piece);
 #pragma unroll
   for (int h = 0; h < kStagePasses; ++h) {
     if (w.from_row[h] == kNone) continue;
-    const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, w.from_row[h], c0 * 2u, 0));
+    const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, w.from_row[h] + (uint32_t)at, 0, 0));
     w.pre[h][0] = x.x; w.pre[h][1] = x.y; w.pre[h][2] = x.z; w.pre[h][3] = x.w;
   }
 }
@@ -749,6 +752,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
     // row-major staging: this lane's row of every pass, from the word the group's rows begin in
     const uint32_t in_word = (uint32_t)(uintptr_t)w.rows & 2u;
     const __amdgpu_buffer_rsrc_t rows_desc = __builtin_amdgcn_make_buffer_rsrc((void *)((uintptr_t)w.rows - in_word), 0, -1, 0x00020000);
+    w.last_piece = (int32_t)((w.n_occ - 1u) / 8u * 16u) - (int32_t)(w.lane & 7u) * 16;
     const bool shifted = !kDirect && (in_word || (w.ld & 1u));   // some rows begin in the middle of a word
 #pragma unroll
     for (int h = 0; h < kStagePasses; ++h) {
@@ -963,7 +967,7 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   d.mir = u.mir->dev; d.live = u.live->dev; d.cand = u.cand; d.out = u.out; d.ld = u.ld; d.K = u.K;
   const bool aligned = ((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0;
   d.transposed = transposed ? 1u : 0u;
-  // whole chunks can be read from every row: the pitch covers the last chunk
+  // every row has room for whole chunks: the pitch covers the last one
   d.direct = (aligned && !transposed && u.ld >= (((uint64_t)u.mir->h.O + kChunk - 1) / kChunk) * kChunk) ? 1u : 0u;
   out.all_direct = out.all_direct && d.direct;
   // groups of up to 64 candidates; every group but the last has d.rows of them.  Row-major groups span

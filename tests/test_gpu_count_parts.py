@@ -1,6 +1,8 @@
 """All-violations counts where the work is cut: 0 to 9 failed samples (units of four), programs
 whose pairs fill several parts, row pitches that allow 16-byte reads or not, a program with more
 vregs than the table in LDS holds (19,456); against the oracle, exactly."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -66,3 +68,37 @@ def test_more_vregs_than_lds():
     k = gen.Kernel(gen.STRAIGHT, 0xC0DF, 20000, 20000)
     rows, _ = k.candidates(5, 6, 4, 1)
     compare(k.mir, [rows])
+
+
+@pytest.mark.parametrize("n_instr", [61, 64, 200])
+@pytest.mark.parametrize("K", [1, 70])
+def test_rows_that_end_with_their_memory(n_instr, K):
+    """nothing is asked of a row beyond its registers: the last one ends where the allocation does (the
+    16 bytes, or the word, its last register lies in), whatever the pitch"""
+    k = gen.Kernel(gen.STRAIGHT, 0xC0E0 + n_instr, n_instr, n_instr)
+    m = k.mir
+    rows, _ = k.candidates(9, K, K // 2, 1)
+    an = vlo.analyze(m, threads=8)
+    want = vlo.count_violations(m, an, rows, threads=8)
+    hip = vl.binding.hip_runtime()
+    size = 4 << 20
+    mem = C.c_void_p()
+    assert hip.hipMalloc(C.byref(mem), C.c_size_t(size)) == 0
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        for ld, unit in ((vl.pad_ld(m.n_occ), 16), ((m.n_occ + 7) // 8 * 8, 16), (m.n_occ | 1, 4), (m.n_occ + 1 & ~1, 4)):
+            used = (K - 1) * ld * 2 + m.n_occ * 2
+            start = (size - used) // unit * unit
+            host = np.zeros((size - start) // 2, np.uint16)
+            for r in range(K):
+                host[r * ld:r * ld + m.n_occ] = rows[r]
+            assert hip.hipMemcpy(C.c_void_p(mem.value + start), host.ctypes.data_as(C.c_void_p), C.c_size_t(host.nbytes), 1) == 0
+            out = torch.full((K, 8), -1, dtype=torch.int32, device="cuda")
+            vl.vl_count_violations_multi([(hm[0], hl[0], mem.value + start, K, ld, out)])
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().view(np.uint32)
+            for c, name in enumerate(("kinds", "n_cons", "n_real", "n_safe", "real_bits")):
+                assert (got[:, c] == want[name]).all(), (ld, name)
+    finally:
+        free(hm, hl)
+        assert hip.hipFree(mem) == 0
