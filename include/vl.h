@@ -210,7 +210,8 @@ int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const uint16_t *
  * 512 KB per GPU the library runs on, held until the process ends); the call allocates and
  * frees nothing, on the host or the device, and copies nothing from host memory: it only
  * enqueues kernels on `stream`.  Every call on a GPU uses that GPU's one array: calls that
- * overlap on one GPU (different streams, or threads) race; calls on one stream are ordered.
+ * overlap on one GPU (different streams, or threads) race, and their results are undefined;
+ * calls on one stream are ordered.  Later calls are not affected once those have ended.
  * Errors: as vl_verify_batch, and VL_E_LIMIT for K above VL_STATIC_MAX_K (nothing is
  * launched then). */
 #define VL_STATIC_MAX_K 65536u
@@ -227,7 +228,10 @@ int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live, const uin
  * smallest violation found so far).  Both grow on demand, which waits for the stream and
  * allocates; a call whose jobs are no more, and whose candidates in total are no more, than
  * in an earlier call on that stream allocates nothing, and when its job table is unchanged
- * it only enqueues kernels.  Errors: VL_E_NULL (a pointer missing), VL_E_ARG (a handle that
+ * it only enqueues kernels.  A recorded pass keeps the memory of the stream it was recorded on:
+ * replays that overlap with calls on that stream, or with each other, race as the calls of
+ * vl_verify_batch_static do, and leave later passes (a verification, then its reductions)
+ * as unaffected.  Errors: VL_E_NULL (a pointer missing), VL_E_ARG (a handle that
  * is not a live handle of its program, or more than 16 devices), VL_E_SHAPE (n_jobs = 0 or
  * above 65,535, K = 0, ld below n_occ), VL_E_HIP. */
 typedef struct {

@@ -63,7 +63,10 @@ constexpr uint32_t kKeyOk = 0xFFFFFFFFu;
 constexpr uint32_t kKeyCons = 0u << 28, kKeyReal = 1u << 28, kKeySafe = 2u << 28, kKeyPos = (1u << 28) - 1;
 
 // What the workgroups of one verification share.  Everything is zero before the walk and left
-// zero by it, so that no launch is needed to clear it.
+// zero by it, so that no launch is needed to clear it.  The pair search, which follows every walk but
+// those of the all-violations mode, writes the zeros again: calls that overlapped against the rules (their counts mixed)
+// spoil each other, and without it every later call too.  Of such calls, the one whose walk ends last clears
+// what it has in common with the others after all of them.
 struct Board {
   uint32_t *arrived;   // per group of candidate rows: tiles that have reported
   uint32_t *keys;      // per candidate row: ~(smallest violation key so far), 0 = none
@@ -832,11 +835,12 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
 // vregs instead of registers (flip_members_of_p); its members, some tens, are then listed so that
 // each gets a lane (a lane per vreg of the program took most of the kernel's time: 15,000 vregs
 // are 117 turns of 128 threads).  The workgroups of a group of rows share out the rows that
-// failed on safety.
+// failed on safety; the first of them leaves the group's part of the board zero (Board).
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
 constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
 template <bool kOne>
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group) {
+__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group,
+                                                             const Board board, uint32_t *finished) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
   __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], nd, members[kResolveMembers], n_members;
@@ -845,6 +849,12 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
   const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
   const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
+  if (mine_first == 0) {
+    auto clear = [](uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (tid < nrows) clear(board.keys + J.row_base + row0 + tid);
+    if (tid == 64) clear(board.arrived + J.group_base + group);
+    if (tid == 65 && global_group == 0 && finished) clear(finished);
+  }
   // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
   const uint64_t failed = __ballot(lane < nrows && out[min(lane, nrows - 1u)].status == VL_STATUS_SAFETY);
   uint32_t rank = 0;
@@ -854,6 +864,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
     const DevMir VL_GLOBAL &m = *as_global(J.mir);
     const DevLive VL_GLOBAL &L = *as_global(J.live);
     const uint32_t i = out[k - row0].where;
+    if (i >= m.N) continue;   // (not a result of this call: calls overlapped against the rules)
     for (uint32_t x = tid; x < m.W; x += kResolveThreads) in_p[x] = 0;
     // the vregs the instruction writes (each once) and their registers: one operand per lane
     const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo;
@@ -950,7 +961,7 @@ struct Launch {
   DevJob *dev = nullptr;   // the job table on the device; a single job travels as an argument instead
   DevJob one = {};
   Board board = {};
-  uint32_t *finished = nullptr;   // counter of the reductions, zero between calls
+  uint32_t *finished = nullptr;   // counter of the stream's reductions, zero between calls
   uint64_t total_rows = 0, groups = 0;
   uint32_t units = 0, maxK = 0, max_words = 0, max_w = 1, max_rows = 0;
   bool all_direct = true;   // every job can be staged with 32-bit offsets and without bounds (DevJob::direct)
@@ -1212,7 +1223,7 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   VL_HIP(hipGetLastError());
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
   (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
-      L.dev, n_jobs, L.one, per_group);
+      L.dev, n_jobs, L.one, per_group, L.board, L.finished);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
