@@ -1111,40 +1111,69 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Wa
 }
 
 // ---- regeneration-loop reductions ----------------------------------------------------
-// One wavefront per job: histogram of the statuses and the first accepted candidate.  With
+// Per job the histogram of the statuses and the first accepted candidate.  With
 // `stats`, the workgroup that finishes last also totals the jobs' summaries (every field is
 // written, nothing needs clearing beforehand; `finished` is left zero).  The summaries reach it
 // through stores and loads that all dies see (agent scope).
-__global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, vl_summary *__restrict__ summaries,
+// What bounds it: waiting for the statuses, 16 bytes apart.  A wavefront reads 256 (many samples: 512)
+// at a time.  Jobs of up to kFewSamples get a wavefront each, four to a workgroup; with more in some job,
+// every job gets a workgroup of sixteen.  (A wavefront and a
+// workgroup per job, 64 jobs: 1,000 samples 7.8 and 10.0 us, 2,000 10.4 and 10.0, 4,000 16.6 and 10.1; one
+// job of 65,536: 198 and 24, 54 with a workgroup of four that reads 256 at a time.)
+constexpr uint32_t kFewSamples = 2048;
+template <bool kMany>
+__global__ __launch_bounds__(kMany ? 1024 : 256) void k_summarize(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, vl_summary *__restrict__ summaries,
                                                    vl_loop_stats *stats, uint32_t *finished) {
-  const uint32_t lane = threadIdx.x & 63u, j = blockIdx.x * 4u + (threadIdx.x >> 6);
+  constexpr uint32_t kWaves = kMany ? 16 : 4, kThreads = 64 * kWaves, kAtOnce = kMany ? 8 : 4;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, j = kMany ? blockIdx.x : blockIdx.x * kWaves + wave;
+  __shared__ uint32_t sums[kMany ? 5 : 1];   // (many) histogram, first accepted
+  if (kMany) {
+    if (threadIdx.x < 5) sums[threadIdx.x] = threadIdx.x < 4 ? 0u : kNone;
+    __syncthreads();
+  }
   if (j < n_jobs) {
     const DevJob J = n_jobs == 1 ? one : jobs[j];
-    uint32_t hist[4] = {0, 0, 0, 0}, first = J.K;
-    for (uint32_t k0 = 0; k0 < J.K; k0 += 64) {
-      const bool in = k0 + lane < J.K;
-      const uint32_t st = in ? J.out[k0 + lane].status & 3u : 4u;
+    uint32_t hist[4] = {0, 0, 0, 0}, first = kNone;
+    // (64 bits: the last step may pass 2^32)
+    for (uint64_t k0 = kMany ? wave * 64u * kAtOnce : 0u; k0 < J.K; k0 += 64u * kAtOnce * (kMany ? kWaves : 1u)) {
+      uint32_t st[kAtOnce];
 #pragma unroll
-      for (uint32_t t = 0; t < 4; ++t) {
-        const uint64_t with = __ballot(st == t);
-        hist[t] += (uint32_t)__popcll(with);
-        if (t == VL_STATUS_OK && with && first == J.K) first = k0 + (uint32_t)__builtin_ctzll(with);
+      for (uint32_t u = 0; u < kAtOnce; ++u) {
+        const uint64_t k = k0 + u * 64u + lane;
+        st[u] = k < J.K ? J.out[k].status & 3u : 4u;
       }
+#pragma unroll
+      for (uint32_t u = 0; u < kAtOnce; ++u)
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+          const uint64_t with = __ballot(st[u] == t);
+          hist[t] += (uint32_t)__popcll(with);
+          if (t == VL_STATUS_OK && with && first == kNone) first = (uint32_t)k0 + u * 64u + (uint32_t)__builtin_ctzll(with);
+        }
     }
+    if (kMany) {
+      if (lane < 4) atomicAdd(&sums[lane], lane == 0 ? hist[0] : lane == 1 ? hist[1] : lane == 2 ? hist[2] : hist[3]);
+      if (lane == 4) atomicMin(&sums[4], first);
+      __syncthreads();   // (a whole workgroup has the same job)
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) hist[t] = sums[t];
+      first = sums[4];
+    }
+    first = min(first, J.K);
     const uint32_t word = lane == 0 ? first : lane == 1 ? (first < J.K ? 1u : 0u) : lane == 2 ? hist[0] : lane == 3 ? hist[1] : lane == 4 ? hist[2] : hist[3];
     static_assert(sizeof(vl_summary) == 24, "six words");
-    if (lane < 6) __hip_atomic_store((uint32_t *)(summaries + j) + lane, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < 6 && (!kMany || wave == 0)) __hip_atomic_store((uint32_t *)(summaries + j) + lane, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (!stats) return;
   asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   __shared__ uint32_t last;
-  __shared__ unsigned long long part[4][7];   // per wavefront: passed, most tries, sum of tries, histogram
+  __shared__ unsigned long long part[kWaves][7];   // per wavefront: passed, most tries, sum of tries, histogram
   __syncthreads();
   if (threadIdx.x == 0) last = __hip_atomic_fetch_add(finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
   __syncthreads();
   if (!last) return;
   unsigned long long mine[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (uint32_t x = threadIdx.x; x < n_jobs; x += 256) {
+  for (uint32_t x = threadIdx.x; x < n_jobs; x += kThreads) {
     uint32_t f[6];
 #pragma unroll
     for (uint32_t t = 0; t < 6; ++t) f[t] = __hip_atomic_load((uint32_t *)(summaries + x) + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1161,12 +1190,14 @@ __global__ __launch_bounds__(256) void k_summarize(const DevJob *__restrict__ jo
       mine[t] = t == 1 ? max(mine[t], y) : mine[t] + y;
     }
   if (lane == 0)
-    for (uint32_t t = 0; t < 7; ++t) part[threadIdx.x >> 6][t] = mine[t];
+    for (uint32_t t = 0; t < 7; ++t) part[wave][t] = mine[t];
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned long long s[7];
-    for (uint32_t t = 0; t < 7; ++t)
-      s[t] = t == 1 ? max(max(part[0][t], part[1][t]), max(part[2][t], part[3][t])) : part[0][t] + part[1][t] + part[2][t] + part[3][t];
+    for (uint32_t t = 0; t < 7; ++t) {
+      s[t] = part[0][t];
+      for (uint32_t k = 1; k < kWaves; ++k) s[t] = t == 1 ? max(s[t], part[k][t]) : s[t] + part[k][t];
+    }
     *stats = vl_loop_stats{(uint32_t)s[0], (uint32_t)s[1], s[2], {s[3], s[4], s[5], s[6]}};
     __hip_atomic_store(finished, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -1188,7 +1219,8 @@ extern "C" int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_su
   int32_t rc = space_of(s, stream, space);
   if (rc == VL_OK) rc = prepare_jobs(jobs, n_jobs, stream, *space, L, false, true);
   if (rc != VL_OK) return rc;
-  k_summarize<<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, L.one, summaries, stats, L.finished);
+  if (L.maxK > kFewSamples) k_summarize<true><<<n_jobs, 1024, 0, stream>>>(L.dev, n_jobs, L.one, summaries, stats, L.finished);
+  else k_summarize<false><<<(n_jobs + 3) / 4, 256, 0, stream>>>(L.dev, n_jobs, L.one, summaries, stats, L.finished);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }

@@ -82,3 +82,44 @@ def test_exhausted_attempts_are_reported():
     want_s, want_l = run(w.kernels, rows_list)
     assert want_s["passed"][1] == 0 and want_s["first_ok"][1] == bad.shape[0]
     assert want_l["n_passed"] == 2 and want_l["max_tries"] == bad.shape[0]
+
+
+@pytest.mark.parametrize("K", [1, 255, 257, 2048, 2049, 8192, 8193, 70001])
+@pytest.mark.parametrize("n", [1, 3, 5])
+def test_sample_counts(K, n):
+    """around the samples that are read at a time and the line between a wavefront and a workgroup per
+    job; the first accepted sample nowhere, first, last and in between; jobs of different sizes"""
+    k = gen.Kernel(gen.STRAIGHT, 0x5A0, 60, 60)
+    hm, hl, _, _ = gpu_analyze([k.mir], dense=False)
+    rng = np.random.default_rng(K * 10 + n)
+    try:
+        sizes = [K if j % 2 == 0 else max(1, K // 2) for j in range(n)]
+        status = [rng.integers(1, 4, x) for x in sizes]
+        for j, s in enumerate(status):
+            if j % 4 != 1:
+                s[[0, -1, len(s) // 2][j % 3]] = 0
+        outs = []
+        for s in status:
+            o = np.full((len(s), 4), 7, np.int32)
+            o[:, 0] = s
+            outs.append(torch.from_numpy(o).cuda())
+        row = torch.zeros(k.mir.n_occ, dtype=torch.int16, device="cuda")   # not read
+        jobs = vl.make_jobs([(hm[0], hl[0], row, len(s), k.mir.n_occ, o) for s, o in zip(status, outs)])
+        summaries = torch.full((n, 6), -1, dtype=torch.int32, device="cuda")
+        stats = torch.full((6,), -1, dtype=torch.int64, device="cuda")
+        for _ in range(2):
+            vl.vl_summarize_multi(jobs, summaries, stats)
+        torch.cuda.synchronize()
+        got_s = summaries.cpu().numpy().view(np.uint32).reshape(-1).view(vl.SUMMARY_DTYPE)
+        got_l = stats.cpu().numpy().view(np.uint8).view(vl.LOOP_DTYPE)[0]
+        tries, passed = [], 0
+        for s, g in zip(status, got_s):
+            ok = np.nonzero(s == 0)[0]
+            assert g["first_ok"] == (ok[0] if len(ok) else len(s)) and g["passed"] == (len(ok) > 0)
+            assert (g["hist"] == np.bincount(s, minlength=4)).all()
+            tries.append(int(ok[0]) + 1 if len(ok) else len(s))
+            passed += len(ok) > 0
+        assert got_l["n_passed"] == passed and got_l["max_tries"] == max(tries) and got_l["sum_tries"] == sum(tries)
+        assert (got_l["hist"] == sum(np.bincount(s, minlength=4) for s in status)).all()
+    finally:
+        free(hm, hl)
