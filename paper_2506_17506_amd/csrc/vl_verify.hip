@@ -983,8 +983,9 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   out.all_direct = out.all_direct && d.direct;
   // groups of up to 64 candidates; every group but the last has d.rows of them.  Row-major groups span
   // less than 4 GB, so that 32-bit offsets reach every register (a row alone needs less than 32 MB of it)
-  const uint64_t reach = ((1ull << 32) - (1ull << 26)) / (2 * std::max<uint64_t>(1, u.ld));
-  const uint32_t most = transposed || results_only ? 64u : (uint32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, reach));
+  constexpr uint64_t kReach = ((1ull << 32) - (1ull << 26)) / 2;
+  uint32_t most = 64;
+  if (!transposed && !results_only && u.ld > kReach / 64) most = (uint32_t)std::max<uint64_t>(1, kReach / u.ld);
   d.n_groups = (u.K + most - 1) / most;
   d.rows = (u.K + d.n_groups - 1) / d.n_groups;
   if (transposed) {
