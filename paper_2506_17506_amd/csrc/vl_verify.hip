@@ -1002,7 +1002,7 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   }
   const uint32_t last = u.K - (d.n_groups - 1) * d.rows;
   d.unit_base = out.units;
-  if (out.total_rows + u.K > 0xFFFFFFFFull) return VL_E_SHAPE;
+  if (!results_only && out.total_rows + u.K > 0xFFFFFFFFull) return VL_E_SHAPE;   // (the board has an entry per row)
   d.row_base = (uint32_t)out.total_rows;
   d.group_base = (uint32_t)out.groups;
   out.groups += d.n_groups;
@@ -1069,7 +1069,8 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Wa
     VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
     if (s.board) (void)hipFree(s.board);
     s.board = nullptr; s.groups_cap = s.rows_cap = 0;
-    const uint64_t rows = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2), groups = std::max<uint64_t>(4096, out.groups + out.groups / 2);
+    const uint64_t of_rows = results_only ? 0 : out.total_rows, of_groups = results_only ? 0 : out.groups;   // (reductions use the head alone)
+    const uint64_t rows = std::max<uint64_t>(65536, of_rows + of_rows / 2), groups = std::max<uint64_t>(4096, of_groups + of_groups / 2);
     VL_HIP(hipMalloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
     k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
     s.rows_cap = rows; s.groups_cap = groups;

@@ -15,13 +15,13 @@ static int g_n;
 static launch_fn g_on_launch;
 static int g_fail = -1;         /* allocations until one fails, -1: none does */
 static int g_fail_more;         /* and how many after it */
-static uint64_t g_mallocs, g_frees, g_uploads, g_stream_syncs, g_device_syncs;
+static uint64_t g_mallocs, g_frees, g_uploads, g_stream_syncs, g_device_syncs, g_largest;
 static struct { dim3_t grid, block; size_t lds; void *stream; } g_call;
 
 void stand_in_on_launch(launch_fn f) { g_on_launch = f; }
 void stand_in_fail(int after, int more) { g_fail = after; g_fail_more = more; }
-void stand_in_counts(uint64_t *out) {   /* allocations, frees, uploads, waits for a stream, waits for the device */
-  out[0] = g_mallocs; out[1] = g_frees; out[2] = g_uploads; out[3] = g_stream_syncs; out[4] = g_device_syncs;
+void stand_in_counts(uint64_t *out) {   /* allocations, frees, uploads, waits for a stream, waits for the device, largest allocation */
+  out[0] = g_mallocs; out[1] = g_frees; out[2] = g_uploads; out[3] = g_stream_syncs; out[4] = g_device_syncs; out[5] = g_largest;
 }
 
 static int fails(void) {
@@ -54,7 +54,7 @@ int hipLaunchKernel(const void *func, dim3_t grid, dim3_t block, void **args, si
   if (g_on_launch) g_on_launch(name, grid.x, grid.y, grid.z, block.x, lds, stream, args);
   return 0;
 }
-int hipMalloc(void **p, size_t n) { ++g_mallocs; if (fails()) { *p = 0; return kOutOfMemory; } *p = calloc(1, n + 256); return *p ? 0 : kOutOfMemory; }
+int hipMalloc(void **p, size_t n) { ++g_mallocs; if (n > g_largest) g_largest = n; if (fails()) { *p = 0; return kOutOfMemory; } *p = calloc(1, n + 256); return *p ? 0 : kOutOfMemory; }
 int hipFree(void *p) { ++g_frees; free(p); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; *p = calloc(1, n + 1); return 0; }
 int hipHostFree(void *p) { free(p); return 0; }

@@ -40,9 +40,9 @@ class StandIn:
         self.lib.stand_in_fail(after, more)
 
     def counts(self):
-        out = (C.c_uint64 * 5)()
+        out = (C.c_uint64 * 6)()
         self.lib.stand_in_counts(out)
-        return dict(zip(("mallocs", "frees", "uploads", "stream_waits", "device_waits"), out))
+        return dict(zip(("mallocs", "frees", "uploads", "stream_waits", "device_waits", "largest"), out))
 
 
 def in_own_process(test):

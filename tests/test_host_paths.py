@@ -107,3 +107,17 @@ def test_counting_takes_no_streams_place(s):
             s.vl.vl_verify_multi(arr, stream=S1 + k)
             s.vl.vl_count_violations_multi(counts, stream=S1 + 200)
     assert s.counts()["device_waits"] == 0
+
+
+@in_own_process
+def test_reductions_over_more_samples_than_a_verification_takes(s):
+    """no memory per sample is needed, so their number is bounded per job alone"""
+    hm, hl = analysed(s, 1)
+    jobs, keep = jobs_of(s, hm * 3, hl * 3, 8)
+    arr = s.vl.make_jobs(jobs)
+    for j in arr:
+        j.K = 1 << 31   # (nothing is read: the kernels are not run)
+    sums, stats = Buffer(72), Buffer(48)
+    s.vl.vl_summarize_multi(arr, sums, stats, stream=S1)
+    assert sum("k_summarize" in x[0] for x in s.launches) == 1
+    assert s.counts()["largest"] < 64 << 20
