@@ -283,6 +283,7 @@ struct vl_live {
   const vl_mir *mir;
   vl::DevLive h;       // host mirror
   vl::DevLive *dev;    // element of the batch's device array
+  uint32_t span;       // tiles that a verification of many samples may take at once
   uint64_t magic;
 };
 

@@ -1816,6 +1816,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   for (uint32_t k = 0; k < n; ++k)
     if (!mirs[k] || mirs[k]->magic != kMirMagic) return VL_E_NULL;
   hipStream_t stream = (hipStream_t)stream_;
+  uint32_t span = 1;   // tiles a verification may join: up to 128 instructions, where the length is not the caller's
   if (tile_len == 0) {
     // Default: 512 instructions per tile when that gives the verifier a thousand tiles or more
     // over the batch; a small batch gets shorter tiles (down to 128), so that its candidate
@@ -1825,12 +1826,11 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     for (uint32_t k = 0; k < n; ++k) total += mirs[k]->h.N;
     tile_len = kDefaultTile;
     while (tile_len > 128 && total / tile_len < 1024) tile_len /= 2;
-    // What makes fewer than 48 of those leaves most of the device without work whatever the number
-    // of samples, and is cut down to 32 (200 instructions with 64 samples: 24.9 us a call with tiles
-    // of 128, 18.3 with 32; 4,000 with 100 samples: 51, and 40 with 64).  The line lies below 8,000
-    // instructions, 62 tiles, where a thousand samples fill the device with tiles of 128 already:
-    // a step 119 us, 133 with 64.
-    while (tile_len > 32 && total / tile_len < 48) tile_len /= 2;
+    // What makes fewer than 48 of those leaves most of the device without work, and is cut down to 32
+    // (200 instructions with 64 samples: 24.9 us a call with tiles of 128, 18.3 with 32; 4,000 with 100
+    // samples: 51, and 40 with 64).  Where there are enough samples to fill the device with longer tiles, a
+    // verification joins them again, up to 128 instructions.
+    while (tile_len > 32 && total / tile_len < 48) { tile_len /= 2; span *= 2; }
   }
   const bool dense = (flags & VL_DENSE_POINTS) != 0;
 
@@ -2124,6 +2124,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     vl_live *l = batch->lives[k];
     l->h = h[k];
     l->dev = batch->dev_lives + k;
+    l->span = span;
     live[k] = l;
   }
   batch->uploaded.assign((const char *)h.data(), (const char *)h.data() + (size_t)n * sizeof(DevLive));

@@ -38,6 +38,7 @@ struct DevJob {
   uint64_t ld;
   uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
   uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
+  uint32_t span, n_spans;          // analysis tiles that a workgroup takes at once, and how often that is
   // direct: row-major, aligned, and every row has room for whole chunks up to its pitch
 };
 }  // namespace vl
@@ -361,7 +362,9 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
   const u32x4 VL_GLOBAL *g_chk = L.chk, *g_seeds = L.seeds;
   const u32x4 VL_GLOBAL *g_plan = L.plan;
   const uint32_t local = unit - J.unit_base;
-  const uint32_t tile = local / J.n_groups, group = local % J.n_groups;
+  // this workgroup's tile: J.span neighbouring tiles of the analysis, walked as one (the events of a
+  // range of tiles follow each other, and what is live into the first starts it)
+  const uint32_t tile = local / J.n_groups * J.span, group = local % J.n_groups;
   const uint32_t row0 = group * J.rows;
   Walk w;
   w.tid = threadIdx.x;
@@ -389,9 +392,9 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
   const uint32_t cls_tab_v = w.lane < m.C ? ((uint32_t)m.class_size[w.lane] | ((uint32_t)m.class_word[w.lane] << 16)) : 0u;
   uint32_t key = kKeyOk;   // event role and far checks: this lane's row
 
-  const uint32_t i0 = tile * L.tile_len, i1 = min(m.N, i0 + L.tile_len);
+  const uint32_t i0 = tile * L.tile_len, i1 = min(m.N, i0 + J.span * L.tile_len);
   const uint32_t oa = g_occ_off[i0], ob = g_occ_off[i1];      // the tile's occurrences
-  const uint32_t ea = g_tile_range[2 * tile], eb = g_tile_range[2 * tile + 1];   // its events
+  const uint32_t ea = g_tile_range[2 * tile], eb = g_tile_range[2 * min(tile + J.span, L.T) - 1];   // its events
   const uint32_t ca = oa / kChunk;
   const uint32_t c_end = ob > oa ? (ob - 1) / kChunk + 1 : ca;   // chunks [ca, c_end)
   // the ring starts one chunk before the tile's first occurrence, so that nearby history is in LDS
@@ -811,7 +814,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
   const DevJob VL_CONSTANT *entry = kOne ? (const DevJob VL_CONSTANT *)__builtin_amdgcn_kernarg_segment_ptr() : (const DevJob VL_CONSTANT *)(uintptr_t)jobs;
   asm volatile("" : "+s"(entry));
   const DevJob E = *((const DevJob *)entry + job);
-  const uint32_t T = as_global(E.live)->T, row = (unit - E.unit_base) % E.n_groups * E.rows + w.tid;
+  const uint32_t T = E.n_spans, row = (unit - E.unit_base) % E.n_groups * E.rows + w.tid;
   if (T > 1) {
     uint32_t *const my_key = board.keys + E.row_base + row;
     uint32_t before = 0;
@@ -963,14 +966,15 @@ struct Launch {
   Board board = {};
   uint32_t *finished = nullptr;   // counter of the stream's reductions, zero between calls
   uint64_t total_rows = 0, groups = 0;
+  uint32_t most_span = 1;         // of the analyses
   uint32_t units = 0, maxK = 0, max_words = 0, max_w = 1, max_rows = 0;
   bool all_direct = true;   // every job can be staged with 32-bit offsets and without bounds (DevJob::direct)
 };
 
 // Validates one job, lays out its entry of the device job table and adds it to the launch.
 // results_only: for the kernels that read nothing but the jobs' results (cand and ld are
-// neither checked nor used).
-int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool results_only = false) {
+// neither checked nor used).  span: analysis tiles taken at once, where the analysis allows it.
+int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool results_only, uint32_t span) {
   if (!u.mir || !u.live || !u.out || (!u.cand && !results_only)) return VL_E_NULL;
   if (u.mir->magic != kMirMagic || u.live->magic != kLiveMagic || u.live->mir != u.mir) return VL_E_ARG;
   if (u.K == 0 || (!results_only && u.ld < (transposed ? u.K : u.mir->h.O))) return VL_E_SHAPE;
@@ -1006,7 +1010,10 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   d.row_base = (uint32_t)out.total_rows;
   d.group_base = (uint32_t)out.groups;
   out.groups += d.n_groups;
-  d.n_units = d.n_groups * u.live->h.T;
+  d.span = std::min(span, u.live->span);
+  d.n_spans = (u.live->h.T + d.span - 1) / d.span;
+  d.n_units = d.n_groups * d.n_spans;
+  out.most_span = std::max(out.most_span, u.live->span);
   out.units += d.n_units;
   out.maxK = std::max(out.maxK, u.K);
   out.total_rows += u.K;
@@ -1014,6 +1021,24 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   out.max_words = std::max(out.max_words, u.mir->h.occ_words);
   out.max_w = std::max(out.max_w, u.mir->h.W);
   return VL_OK;
+}
+
+// The jobs of a call.  Short tiles are cut for programs of few instructions, whatever the number of samples, so that
+// few samples keep the device busy; once there are some 900 workgroups (it holds 1,280 to 1,536), halving their
+// number costs nothing and saves every second tile's set-up and live-in list.  (Tiles of 32, 64 and 128,
+// us per call.  4,000 instructions x 1,000 samples, 2,000 / 1,000 / 500 workgroups: 46, 33, 32;
+// 2,000 x 1,000, 1,008 / 504 / 252: 29, 26, 30; 2,000 x 4,000, 3,969 / 1,984 / 992: 70, 54, 47;
+// 1,000 x 1,000, 512 / 256 / 128: 23, 24, 28; 400 straight x 4,000, 819 / 441 / 252: 23, 24, 30.)
+constexpr uint32_t kEnoughUnits = 900;
+int32_t fill_jobs(const vl_job *jobs, uint32_t n_jobs, bool transposed, DevJob *tab, Launch &out, bool results_only) {
+  for (uint32_t span = 1;; span *= 2) {
+    out = Launch();
+    for (uint32_t j = 0; j < n_jobs; ++j) {
+      const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only, span);
+      if (rc != VL_OK) return rc;
+    }
+    if (results_only || out.units <= kEnoughUnits || span >= out.most_span) return VL_OK;
+  }
 }
 
 __global__ void k_clear_board(uint32_t *p, uint64_t n) {
@@ -1050,10 +1075,8 @@ int32_t space_of(Scratch &sc, hipStream_t stream, WalkSpace *&out) {
 int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &s, Launch &out, bool transposed = false,
                      bool results_only = false) {
   std::vector<DevJob> tab(n_jobs);
-  for (uint32_t j = 0; j < n_jobs; ++j) {
-    const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only);
-    if (rc != VL_OK) return rc;
-  }
+  const int32_t rc = fill_jobs(jobs, n_jobs, transposed, tab.data(), out, results_only);
+  if (rc != VL_OK) return rc;
   if (results_only && n_jobs > 1 && s.n_valid == n_jobs && s.board) {
     // the table a verification call on this stream left behind serves, whatever its candidate
     // layout, when it names the same results
@@ -1322,7 +1345,7 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
   const vl_job u = {mir, live, cand, K, ld, out};
   DevJob d;
   Launch L;
-  const int32_t rc = fill_job(u, false, d, L);
+  const int32_t rc = fill_jobs(&u, 1, false, &d, L, false);
   if (rc != VL_OK) return rc;
   hipStream_t stream = (hipStream_t)stream_;
   int device = 0;
