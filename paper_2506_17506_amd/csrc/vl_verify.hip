@@ -852,14 +852,15 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
   const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
   const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
+  // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
+  const uint32_t status = out[min(lane, nrows - 1u)].status;   // (before the stores: reads wait for the stores before them)
   if (mine_first == 0) {
     auto clear = [](uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     if (tid < nrows) clear(board.keys + J.row_base + row0 + tid);
     if (tid == 64) clear(board.arrived + J.group_base + group);
     if (tid == 65 && global_group == 0 && finished) clear(finished);
   }
-  // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
-  const uint64_t failed = __ballot(lane < nrows && out[min(lane, nrows - 1u)].status == VL_STATUS_SAFETY);
+  const uint64_t failed = __ballot(lane < nrows && status == VL_STATUS_SAFETY);
   uint32_t rank = 0;
   for (uint64_t todo = failed; todo; todo &= todo - 1, ++rank) {
     if (rank % per_group != mine_first) continue;
