@@ -144,37 +144,69 @@ struct DevCountJob {
   const vl_result *verdicts;   // [K] of the walk; the pairs of safety violations are not in them
   const uint32_t *records;     // [n_records][8]: the interfering pairs
   uint64_t ld, n_records;
-  uint32_t K, parts, fail_base, wide;   // fail_base: first entry in the list of failed samples; wide: rows can be read 16 bytes at a time
+  uint32_t K, fail_base, wide, table;   // fail_base: first entry in the list of failed samples; wide: rows can be read 16 bytes
+                                        // at a time; table: where the table of registers fits (kTableFour and on)
+  float records_per_few;                // of a part, for every few samples that failed (parts_of)
 };
-struct Unit { uint32_t job, first, n, part; };   // samples failed[first .. first + n) of a job, a share of its work
-struct Head { uint32_t n_units, taken, pad[62]; };   // travels with the job table, zeroed by it
+struct Unit { uint32_t job_n, first, part, parts; };   // samples failed[first .. first + n) of a job (job | n << 16), a share of its work
+struct Head { uint32_t n_units, taken, pad[62]; };     // of a launch; travel with the job table, zeroed by it
+// Tables of the registers of four samples, 8 bytes per vreg, in LDS; of two samples, 4 bytes, in LDS; of four samples in
+// memory.  (17 programs, one of them of 22,500 vregs, 100 samples each, all failing: 252 us with that one's tables in memory, 192
+// with two samples in LDS; alone 132 and 80.)
+enum { kTableFour = 0, kTableTwo = 1, kTableMemory = 2 };
+__host__ __device__ constexpr uint32_t at_once(uint32_t table) { return table == kTableTwo ? 2u : 4u; }   // samples per workgroup
+__host__ __device__ constexpr uint32_t launch_of(uint32_t table) { return table == kTableMemory ? 1u : 0u; }
+constexpr uint32_t kLaunches = 2;   // with tables in LDS, and in memory
+struct UnitLists { Unit *of[kLaunches]; };
 
-constexpr uint32_t kAtOnce = 4;                  // samples per workgroup
 constexpr size_t kTableBytes = 152 * 1024;       // of a compute unit's 160 KB
-constexpr uint64_t kRecordsPerPart = 8192;       // (also keeps a lane's counts far below 2^16)
+constexpr uint32_t kLeastRecords = 8192;         // of a part: with fewer, filling the table takes longer than the pairs
+constexpr uint32_t kMostRecords = 1u << 22;      // keeps a lane's counts (7 pairs of a record, twice that many, 1,024 lanes) below 2^16
+constexpr uint32_t kRounds = 3;                  // units per workgroup, about, so that workgroups end together (one job: all alike, one)
+
+// How many parts a program's pairs are cut into when `fews` fours (twos) of its samples failed.  Every part fills the table
+// anew, so there are as many as give every workgroup of the launch work, and no more: a job takes its share of
+// the launch (its share of all records, once per four samples), and the fewer samples failed the more parts it is.
+__device__ inline uint32_t parts_of(const DevCountJob &J, uint32_t fews) {
+  const float share = min(J.records_per_few * (float)fews, (float)kMostRecords);
+  if (share < (float)kLeastRecords) return (uint32_t)max((J.n_records + kLeastRecords - 1) / kLeastRecords, (uint64_t)1);
+  return (uint32_t)max(J.n_records / (uint64_t)share, (uint64_t)1);   // (rounded down: a last round for a few units costs more)
+}
 
 // One wavefront per job: clears the counts, lists the failed samples and the units of work they make.
-__global__ __launch_bounds__(256) void k_cnt_list(const DevCountJob *__restrict__ jobs, uint32_t n_jobs, Head *head, uint32_t *__restrict__ failed,
-                                                  Unit *__restrict__ units) {
+__global__ __launch_bounds__(256) void k_cnt_list(const DevCountJob *__restrict__ jobs, uint32_t n_jobs, Head *heads, uint32_t *__restrict__ failed,
+                                                  const UnitLists units) {
   const uint32_t lane = threadIdx.x & 63u, j = blockIdx.x * 4u + (threadIdx.x >> 6);
   if (j >= n_jobs) return;
   const DevCountJob &J = jobs[j];
   uint32_t n = 0;
-  for (uint32_t k0 = 0; k0 < J.K; k0 += 64) {
-    const uint32_t k = k0 + lane;
-    const bool bad = k < J.K && J.verdicts[k].status != VL_STATUS_OK;
-    if (k < J.K) J.out[k] = vl_counts{0, 0, 0, 0, 0, {0, 0, 0}};
-    const uint64_t which = __ballot(bad);
-    if (bad) failed[J.fail_base + n + __popcll(which & ((1ull << lane) - 1ull))] = k;
-    n += (uint32_t)__popcll(which);
+  constexpr uint32_t kAhead = 4;   // reads of verdicts in flight
+  for (uint32_t k0 = 0; k0 < J.K; k0 += 64 * kAhead) {
+    uint32_t status[kAhead];
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint32_t k = k0 + u * 64 + lane;
+      status[u] = k < J.K ? J.verdicts[k].status : (uint32_t)VL_STATUS_OK;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+      const uint32_t k = k0 + u * 64 + lane;
+      const bool bad = status[u] != VL_STATUS_OK;
+      if (k < J.K) J.out[k] = vl_counts{0, 0, 0, 0, 0, {0, 0, 0}};
+      const uint64_t which = __ballot(bad);
+      if (bad) failed[J.fail_base + n + __popcll(which & ((1ull << lane) - 1ull))] = k;
+      n += (uint32_t)__popcll(which);
+    }
   }
-  const uint32_t quads = (n + kAtOnce - 1) / kAtOnce, mine = quads * J.parts;
+  if (!n) return;
+  const uint32_t per = at_once(J.table), fews = (n + per - 1) / per, parts = parts_of(J, fews), mine = fews * parts;
   uint32_t at = 0;
-  if (lane == 0 && mine) at = __hip_atomic_fetch_add(&head->n_units, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) at = __hip_atomic_fetch_add(&heads[launch_of(J.table)].n_units, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   at = __builtin_amdgcn_readfirstlane(at);
+  Unit *const list = launch_of(J.table) ? units.of[1] : units.of[0];
   for (uint32_t x = lane; x < mine; x += 64) {
-    const uint32_t quad = x / J.parts;
-    units[at + x] = Unit{j, J.fail_base + quad * kAtOnce, min(kAtOnce, n - quad * kAtOnce), x % J.parts};
+    const uint32_t few = x / parts;
+    list[at + x] = Unit{j | (min(per, n - few * per) << 16), J.fail_base + few * per, x % parts, parts};
   }
 }
 
@@ -189,158 +221,176 @@ __global__ __launch_bounds__(256) void k_cnt_list(const DevCountJob *__restrict_
 //                   v = max(pb - pa, 0) the tuples overlap iff u < width(b) and v < width(a),
 //                   exact in saturating arithmetic for any 16-bit register
 // What bounds it: the vector instructions of the pairs (18 per pair and four samples) and their
-// LDS reads.  The pairs of a large program (600,000 for 20,000 instructions) are cut into parts of
-// 8,192 records so that a few failed samples still make work for the whole device; each part fills
-// the table anew, about as long as its pairs take.  Units are taken as workgroups get free.
-// A table in memory for all samples, [vreg][sample], with a pass each for table, consistency and
-// safety took 0.42 ms for 64 kernels with 100 samples, whatever they were; with a fifth of them
-// failing, the walk takes 0.13 ms and this kernel 0.09 ms (0.12 ms with pairs instead of records
-// and units dealt out beforehand).
-// kLds = false: the table of a program with more vregs than LDS holds lives in memory (`spill`).
-template <bool kLds>
-__global__ __launch_bounds__(1024) void k_cnt_rows(const DevCountJob *__restrict__ jobs, Head *head, const uint32_t *__restrict__ failed,
-                                                   const Unit *__restrict__ units, uint2 *spill, uint32_t max_v) {
-  extern __shared__ uint2 table_lds[];   // [V]
-  __shared__ uint32_t sums[kAtOnce][4];  // per sample: strays, unrealizable vregs, overlapping pairs, rules broken
-  uint2 *const table = kLds ? table_lds : spill + (size_t)blockIdx.x * max_v;
+// LDS reads.  The pairs of a large program (600,000 for 20,000 instructions) are cut into parts, so
+// that a few failed samples still make work for the whole device; each part fills
+// the table anew, which costs as much as some 8,192 records, so there are no more than needed (parts_of).
+// Units are taken as workgroups get free.  (64 programs x 100 samples, us per call; parts of 8,192 records
+// whatever failed: a fifth fails 224, half 338, all 507; as here 214, 299, 415.  A table in memory for all
+// samples, [vreg][sample], with a pass each for table, consistency and safety, took 428 whatever failed.)
+template <uint32_t kTable>
+__device__ __attribute__((always_inline)) inline void count_unit(const Unit &W, const DevCountJob &J, const uint32_t *failed, uint2 *table_at, uint32_t (&sums)[4][4]) {
+  constexpr uint32_t kAtOnce = at_once(kTable), kHalf = kAtOnce / 2;
+  struct alignas(4 * kHalf) Regs { uint32_t two[kHalf]; };   // of a vreg, two samples in a word
+  Regs *const table = (Regs *)table_at;
   typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
   auto both = [](uint32_t x) { return __builtin_bit_cast(u16x2, x); };
   // 1 in both halves, in a form the compiler cannot see through: a minimum with a known 1 is
   // turned into two compares and a merge instead of one packed instruction
   u16x2 one;
   asm volatile("v_mov_b32 %0, 0x10001" : "=v"(one));
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_units = head->n_units;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_samples = W.job_n >> 16;
+  const DevMir VL_GLOBAL &m = *as_global(J.mir);
+  const DevLive VL_GLOBAL &L = *as_global(J.live);
+  const uint16_t VL_GLOBAL *row[kAtOnce];
+#pragma unroll
+  for (uint32_t c = 0; c < kAtOnce; ++c) row[c] = as_global(J.cand) + (uint64_t)failed[W.first + min(c, n_samples - 1)] * J.ld;   // (past the last: repeated, not counted)
+  if (tid < kAtOnce * 4) (&sums[0][0])[tid] = 0;
+  uint32_t n_real[kAtOnce] = {}, rules[kAtOnce] = {};
+  // the table; this part's share of the vregs is tested against the hardware rules
+  const uint32_t v_lo = (uint32_t)((uint64_t)m.V * W.part / W.parts), v_hi = (uint32_t)((uint64_t)m.V * (W.part + 1) / W.parts);
+  for (uint32_t v0 = tid; v0 < m.V; v0 += 4 * 1024) {
+    uint32_t f[4], p[4][kAtOnce];
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) f[t] = v0 + t * 1024 < m.V ? L.first[v0 + t * 1024] : kNone;
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t)
+#pragma unroll
+      for (uint32_t c = 0; c < kAtOnce; ++c) p[t][c] = f[t] != kNone ? row[c][f[t]] : 0u;
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+      const uint32_t v = v0 + t * 1024;
+      if (v >= m.V) break;
+      Regs r;
+#pragma unroll
+      for (uint32_t h = 0; h < kHalf; ++h) r.two[h] = p[t][2 * h] | (p[t][2 * h + 1] << 16);
+      table[v] = r;
+      if (f[t] == kNone || v < v_lo || v >= v_hi) continue;
+      const uint32_t attr = m.vattr[v];
+#pragma unroll
+      for (uint32_t c = 0; c < kAtOnce; ++c) {
+        const uint32_t bad = bad_bits(m, attr, p[t][c]);
+        n_real[c] += bad != 0;
+        rules[c] |= bad;
+      }
+    }
+  }
+  __syncthreads();
+  // consistency
+  u16x2 n_stray2[kHalf] = {}, n_pair2[kHalf] = {};
+  auto stray = [&](uint32_t v, const uint32_t (&p)[kHalf]) __attribute__((always_inline)) {
+    const Regs t = table[v];
+#pragma unroll
+    for (uint32_t h = 0; h < kHalf; ++h) n_stray2[h] += __builtin_elementwise_min(both(p[h] ^ t.two[h]), one);
+  };
+  auto stray_at = [&](uint32_t o) __attribute__((always_inline)) {
+    uint32_t p[kHalf];
+#pragma unroll
+    for (uint32_t h = 0; h < kHalf; ++h) p[h] = row[2 * h][o] | ((uint32_t)row[2 * h + 1][o] << 16);
+    stray(m.occ_vreg[o], p);
+  };
+  {
+    const uint32_t pieces = m.O / 8u;   // whole pieces of eight occurrences; the rest is looked at one by one
+    const uint32_t lo = (uint32_t)((uint64_t)pieces * W.part / W.parts), hi = (uint32_t)((uint64_t)pieces * (W.part + 1) / W.parts);
+    if (J.wide) {
+      for (uint32_t x = lo + tid; x < hi; x += 1024) {
+        u32x4 r[kAtOnce];
+#pragma unroll
+        for (uint32_t c = 0; c < kAtOnce; ++c) r[c] = *reinterpret_cast<const u32x4 VL_GLOBAL *>(row[c] + 8u * x);
+        const u32x4 va = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x), vb = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x + 4u);
+#pragma unroll
+        for (uint32_t t = 0; t < 8; ++t) {
+          const uint32_t half = t & 1u ? 0x07060302u : 0x05040100u;   // the t-th register of two samples, side by side
+          uint32_t p[kHalf];
+#pragma unroll
+          for (uint32_t h = 0; h < kHalf; ++h) p[h] = __builtin_amdgcn_perm(r[2 * h + 1][t / 2], r[2 * h][t / 2], half);
+          stray(t < 4 ? va[t & 3] : vb[t & 3], p);
+        }
+      }
+    } else {
+      for (uint32_t o = 8u * lo + tid; o < 8u * hi; o += 1024) stray_at(o);
+    }
+    if (W.part == 0)
+      for (uint32_t o = 8u * pieces + tid; o < m.O; o += 1024) stray_at(o);
+  }
+  // safety
+  {
+    const uint64_t e_lo = J.n_records * W.part / W.parts, e_hi = J.n_records * (W.part + 1) / W.parts;
+    const u32x4 VL_GLOBAL *records = (const u32x4 VL_GLOBAL *)(uintptr_t)(J.records) + 2 * e_lo;
+    const uint32_t n = (uint32_t)(e_hi - e_lo);
+    auto at = [&](uint32_t x) { return table[x & 0xFFFFFFu]; };
+    auto width2 = [&](uint32_t x) { return both(__builtin_amdgcn_perm(x, x, 0x0C030C03u)); };   // in both halves
+    auto overlap = [&](u16x2 ra, u16x2 rb, u16x2 wa, u16x2 wb) __attribute__((always_inline)) {
+      const u16x2 x = __builtin_elementwise_sub_sat(ra, rb), y = __builtin_elementwise_sub_sat(rb, ra);
+      return __builtin_elementwise_min(__builtin_elementwise_min(__builtin_elementwise_sub_sat(wb, x), __builtin_elementwise_sub_sat(wa, y)), one);
+    };
+    for (uint32_t x = tid; x < n; x += 1024) {
+      const u32x4 lo = records[2 * x], hi = records[2 * x + 1];
+      const uint32_t b[kPartners] = {lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      const Regs ta = at(lo.x);
+      Regs tb[kPartners];
+#pragma unroll
+      for (uint32_t t = 0; t < kPartners; ++t) tb[t] = at(b[t]);
+      const u16x2 wa = width2(lo.x);
+#pragma unroll
+      for (uint32_t t = 0; t < kPartners; ++t) {
+        const u16x2 wb = width2(b[t]);
+#pragma unroll
+        for (uint32_t h = 0; h < kHalf; ++h) n_pair2[h] += overlap(both(ta.two[h]), both(tb[t].two[h]), wa, wb);
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t c = 0; c < kAtOnce; ++c) {
+    uint32_t s[3] = {n_stray2[c / 2][c % 2], n_real[c], n_pair2[c / 2][c % 2]}, bits = rules[c];
+    for (int d = 32; d >= 1; d >>= 1) {
+#pragma unroll
+      for (uint32_t t = 0; t < 3; ++t) s[t] += (uint32_t)__shfl_xor((int)s[t], d, 64);
+      bits |= (uint32_t)__shfl_xor((int)bits, d, 64);
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (uint32_t t = 0; t < 3; ++t)
+        if (s[t]) atomicAdd(&sums[c][t], s[t]);
+      if (bits) atomicOr(&sums[c][3], bits);
+    }
+  }
+  __syncthreads();
+  if (tid < n_samples) {
+    vl_counts VL_GLOBAL *out = as_global_rw(J.out) + failed[W.first + tid];
+    const uint32_t strays = sums[tid][0], unreal = sums[tid][1], overlaps = sums[tid][2];
+    if (strays) atomicAdd(&out->n_cons, strays);
+    if (unreal) { atomicAdd(&out->n_real, unreal); atomicOr(&out->real_bits, sums[tid][3]); }
+    if (overlaps) atomicAdd(&out->n_safe, overlaps);
+    const uint32_t kinds = (strays ? 1u : 0u) | (unreal ? 2u : 0u) | (overlaps ? 4u : 0u);
+    if (kinds) atomicOr(&out->kinds, kinds);
+  }
+}
+
+// kLds = false: the tables lie in memory, `max_v` vregs of four samples for each workgroup
+template <bool kLds>
+__global__ __launch_bounds__(1024) void k_cnt_rows(const DevCountJob *__restrict__ jobs, Head *head, const uint32_t *__restrict__ failed,
+                                                   const Unit *__restrict__ units, uint2 *tables, uint32_t max_v) {
+  extern __shared__ uint2 table_lds[];   // [V]
+  __shared__ uint32_t sums[4][4];        // per sample: strays, unrealizable vregs, overlapping pairs, rules broken
   __shared__ uint32_t taken;
+  const uint32_t n_units = head->n_units;
   for (;;) {
-    if (tid == 0) taken = __hip_atomic_fetch_add(&head->taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) taken = __hip_atomic_fetch_add(&head->taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const uint32_t u = __builtin_amdgcn_readfirstlane(taken);
     if (u >= n_units) break;   // (every workgroup gets here: the counter only grows)
     const Unit W = units[u];
-    const DevCountJob &J = jobs[W.job];
-    const DevMir VL_GLOBAL &m = *as_global(J.mir);
-    const DevLive VL_GLOBAL &L = *as_global(J.live);
-    const uint16_t VL_GLOBAL *row[kAtOnce];
-#pragma unroll
-    for (uint32_t c = 0; c < kAtOnce; ++c) row[c] = as_global(J.cand) + (uint64_t)failed[W.first + min(c, W.n - 1)] * J.ld;   // (past the last: repeated, not counted)
-    if (tid < kAtOnce * 4) (&sums[0][0])[tid] = 0;
-    uint32_t n_real[kAtOnce] = {0, 0, 0, 0}, rules[kAtOnce] = {0, 0, 0, 0};
-    // the table; this part's share of the vregs is tested against the hardware rules
-    const uint32_t v_lo = (uint32_t)((uint64_t)m.V * W.part / J.parts), v_hi = (uint32_t)((uint64_t)m.V * (W.part + 1) / J.parts);
-    for (uint32_t v0 = tid; v0 < m.V; v0 += 4 * 1024) {
-      uint32_t f[4], p[4][kAtOnce];
-#pragma unroll
-      for (uint32_t t = 0; t < 4; ++t) f[t] = v0 + t * 1024 < m.V ? L.first[v0 + t * 1024] : kNone;
-#pragma unroll
-      for (uint32_t t = 0; t < 4; ++t)
-#pragma unroll
-        for (uint32_t c = 0; c < kAtOnce; ++c) p[t][c] = f[t] != kNone ? row[c][f[t]] : 0u;
-#pragma unroll
-      for (uint32_t t = 0; t < 4; ++t) {
-        const uint32_t v = v0 + t * 1024;
-        if (v >= m.V) break;
-        table[v] = make_uint2(p[t][0] | (p[t][1] << 16), p[t][2] | (p[t][3] << 16));
-        if (f[t] == kNone || v < v_lo || v >= v_hi) continue;
-        const uint32_t attr = m.vattr[v];
-#pragma unroll
-        for (uint32_t c = 0; c < kAtOnce; ++c) {
-          const uint32_t bad = bad_bits(m, attr, p[t][c]);
-          n_real[c] += bad != 0;
-          rules[c] |= bad;
-        }
-      }
-    }
-    __syncthreads();
-    // consistency
-    u16x2 stray01 = {0, 0}, stray23 = {0, 0};
-    auto stray = [&](uint32_t v, uint32_t p01, uint32_t p23) __attribute__((always_inline)) {
-      const uint2 t = table[v];
-      stray01 += __builtin_elementwise_min(both(p01 ^ t.x), one);
-      stray23 += __builtin_elementwise_min(both(p23 ^ t.y), one);
-    };
-    {
-      const uint32_t pieces = m.O / 8u;   // whole pieces of eight occurrences; the rest is looked at one by one
-      const uint32_t lo = (uint32_t)((uint64_t)pieces * W.part / J.parts), hi = (uint32_t)((uint64_t)pieces * (W.part + 1) / J.parts);
-      if (J.wide) {
-        for (uint32_t x = lo + tid; x < hi; x += 1024) {
-          u32x4 r[kAtOnce];
-#pragma unroll
-          for (uint32_t c = 0; c < kAtOnce; ++c) r[c] = *reinterpret_cast<const u32x4 VL_GLOBAL *>(row[c] + 8u * x);
-          const u32x4 va = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x), vb = *reinterpret_cast<const u32x4 VL_GLOBAL *>(m.occ_vreg + 8u * x + 4u);
-#pragma unroll
-          for (uint32_t t = 0; t < 8; ++t) {
-            const uint32_t half = t & 1u ? 0x07060302u : 0x05040100u;   // the t-th register of two samples, side by side
-            stray(t < 4 ? va[t & 3] : vb[t & 3], __builtin_amdgcn_perm(r[1][t / 2], r[0][t / 2], half), __builtin_amdgcn_perm(r[3][t / 2], r[2][t / 2], half));
-          }
-        }
-      } else {
-        for (uint32_t o = 8u * lo + tid; o < 8u * hi; o += 1024)
-          stray(m.occ_vreg[o], row[0][o] | ((uint32_t)row[1][o] << 16), row[2][o] | ((uint32_t)row[3][o] << 16));
-      }
-      if (W.part == 0)
-        for (uint32_t o = 8u * pieces + tid; o < m.O; o += 1024)
-          stray(m.occ_vreg[o], row[0][o] | ((uint32_t)row[1][o] << 16), row[2][o] | ((uint32_t)row[3][o] << 16));
-    }
-    // safety
-    u16x2 pair01 = {0, 0}, pair23 = {0, 0};
-    {
-      const uint64_t e_lo = min(J.n_records, W.part * kRecordsPerPart), e_hi = min(J.n_records, e_lo + kRecordsPerPart);
-      const u32x4 VL_GLOBAL *records = (const u32x4 VL_GLOBAL *)(uintptr_t)(J.records) + 2 * e_lo;
-      const uint32_t n = (uint32_t)(e_hi - e_lo);
-      auto at = [&](uint32_t x) { return table[x & 0xFFFFFFu]; };
-      auto width2 = [&](uint32_t x) { return both(__builtin_amdgcn_perm(x, x, 0x0C030C03u)); };   // in both halves
-      auto overlap = [&](u16x2 ra, u16x2 rb, u16x2 wa, u16x2 wb) __attribute__((always_inline)) {
-        const u16x2 x = __builtin_elementwise_sub_sat(ra, rb), y = __builtin_elementwise_sub_sat(rb, ra);
-        return __builtin_elementwise_min(__builtin_elementwise_min(__builtin_elementwise_sub_sat(wb, x), __builtin_elementwise_sub_sat(wa, y)), one);
-      };
-      for (uint32_t x = tid; x < n; x += 1024) {
-        const u32x4 lo = records[2 * x], hi = records[2 * x + 1];
-        const uint32_t b[kPartners] = {lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        const uint2 ta = at(lo.x);
-        uint2 tb[kPartners];
-#pragma unroll
-        for (uint32_t t = 0; t < kPartners; ++t) tb[t] = at(b[t]);
-        const u16x2 wa = width2(lo.x);
-#pragma unroll
-        for (uint32_t t = 0; t < kPartners; ++t) {
-          const u16x2 wb = width2(b[t]);
-          pair01 += overlap(both(ta.x), both(tb[t].x), wa, wb);
-          pair23 += overlap(both(ta.y), both(tb[t].y), wa, wb);
-        }
-      }
-    }
-    const uint32_t n_stray[kAtOnce] = {stray01.x, stray01.y, stray23.x, stray23.y}, n_pair[kAtOnce] = {pair01.x, pair01.y, pair23.x, pair23.y};
-#pragma unroll
-    for (uint32_t c = 0; c < kAtOnce; ++c) {
-      uint32_t s[3] = {n_stray[c], n_real[c], n_pair[c]}, bits = rules[c];
-      for (int d = 32; d >= 1; d >>= 1) {
-#pragma unroll
-        for (uint32_t t = 0; t < 3; ++t) s[t] += (uint32_t)__shfl_xor((int)s[t], d, 64);
-        bits |= (uint32_t)__shfl_xor((int)bits, d, 64);
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (uint32_t t = 0; t < 3; ++t)
-          if (s[t]) atomicAdd(&sums[c][t], s[t]);
-        if (bits) atomicOr(&sums[c][3], bits);
-      }
-    }
-    __syncthreads();
-    if (tid < W.n) {
-      vl_counts VL_GLOBAL *out = as_global_rw(J.out) + failed[W.first + tid];
-      const uint32_t strays = sums[tid][0], unreal = sums[tid][1], overlaps = sums[tid][2];
-      if (strays) atomicAdd(&out->n_cons, strays);
-      if (unreal) { atomicAdd(&out->n_real, unreal); atomicOr(&out->real_bits, sums[tid][3]); }
-      if (overlaps) atomicAdd(&out->n_safe, overlaps);
-      const uint32_t kinds = (strays ? 1u : 0u) | (unreal ? 2u : 0u) | (overlaps ? 4u : 0u);
-      if (kinds) atomicOr(&out->kinds, kinds);
-    }
+    const DevCountJob &J = jobs[W.job_n & 0xFFFFu];
+    if (!kLds) count_unit<kTableMemory>(W, J, failed, tables + (size_t)blockIdx.x * max_v, sums);
+    else if (J.table == kTableTwo) count_unit<kTableTwo>(W, J, failed, table_lds, sums);
+    else count_unit<kTableFour>(W, J, failed, table_lds, sums);
     __syncthreads();   // table and sums are reused by the next unit
   }
 }
 
 // Workspaces of a device, used in turn, so that a call waits only for the one kWorkspaces calls ago.
 constexpr uint32_t kWorkspaces = 4;
+constexpr size_t kHeads = kLaunches * sizeof(Head);
 struct Work {
   char *dev = nullptr, *host = nullptr;   // Head and job table; host: pinned
   uint32_t cap = 0;                       // jobs
@@ -483,29 +533,44 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
     if (w.host) (void)hipHostFree(w.host);
     w.dev = nullptr; w.host = nullptr; w.cap = 0;
     const uint32_t cap = std::max(256u, n_jobs);
-    VL_HIP(hipMalloc((void **)&w.dev, sizeof(Head) + (size_t)cap * sizeof(DevCountJob)));
-    VL_HIP(hipHostMalloc((void **)&w.host, sizeof(Head) + (size_t)cap * sizeof(DevCountJob), hipHostMallocDefault));
+    VL_HIP(hipMalloc((void **)&w.dev, kHeads + (size_t)cap * sizeof(DevCountJob)));
+    VL_HIP(hipHostMalloc((void **)&w.host, kHeads + (size_t)cap * sizeof(DevCountJob), hipHostMallocDefault));
     w.cap = cap;
   }
   if (!w.consumed) VL_HIP(hipEventCreateWithFlags(&w.consumed, hipEventDisableTiming));
-  uint64_t rows = 0, max_units = 0;
-  uint32_t max_v = 1;
-  for (uint32_t j = 0; j < n_jobs; ++j) {
-    const uint64_t parts = std::max<uint64_t>(1, (jobs[j].mir->n_edges + kRecordsPerPart - 1) / kRecordsPerPart);
-    rows += jobs[j].K;
-    max_units += (jobs[j].K + kAtOnce - 1) / kAtOnce * parts;
-    max_v = std::max(max_v, jobs[j].mir->h.V);
-    if (parts > 0x7FFFFFFFull) return VL_E_SHAPE;
-  }
-  if (rows > 0x7FFFFFFFull || max_units > 0x7FFFFFFFull) return VL_E_SHAPE;
   static const bool lds_ok = hipFuncSetAttribute((const void *)k_cnt_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kTableBytes) == hipSuccess;
-  const size_t table_bytes = (size_t)max_v * sizeof(uint2);
-  const bool in_lds = lds_ok && table_bytes <= kTableBytes;
-  // workgroups: as many as fit the 256 compute units at once
-  const uint32_t groups = (uint32_t)std::min<uint64_t>(max_units, in_lds && table_bytes <= kTableBytes / 2 ? 512 : 256);
+  auto table_of = [&](const vl_mir *m) -> uint32_t {
+    return !lds_ok || m->h.V * sizeof(uint32_t) > kTableBytes ? kTableMemory : m->h.V * sizeof(uint2) > kTableBytes ? kTableTwo : kTableFour;
+  };
+  // of each launch: the largest table, all records once per few samples, and how many units there can be
+  struct Part {
+    uint64_t most = 0, least = 0;   // units, with parts as short as they get; with one part for every few samples
+    double work = 0;
+    size_t table_bytes = 0;
+    uint32_t groups = 0;
+  } launches[kLaunches];
+  uint64_t rows = 0, total_units = 0;
+  const uint32_t rounds = n_jobs == 1 ? 1 : kRounds;
+  for (uint32_t j = 0; j < n_jobs; ++j) {
+    const uint32_t t = table_of(jobs[j].mir);
+    Part &p = launches[launch_of(t)];
+    const uint64_t fews = (jobs[j].K + at_once(t) - 1) / at_once(t), records = jobs[j].mir->n_edges;
+    rows += jobs[j].K;
+    p.table_bytes = std::max(p.table_bytes, std::max<size_t>(1, jobs[j].mir->h.V) * 2 * at_once(t));
+    p.work += (double)fews * (double)records;
+    p.most += fews * std::max<uint64_t>(1, (records + kLeastRecords - 1) / kLeastRecords);
+    p.least += fews * (1 + records / kMostRecords) + 1;
+  }
+  for (uint32_t x = 0; x < kLaunches; ++x) {
+    Part &p = launches[x];
+    p.groups = x == 0 && p.table_bytes <= kTableBytes / 2 ? 512 : 256;   // workgroups: as many as fit the 256 compute units at once
+    p.most = std::min(p.most, p.least + p.groups * rounds);              // (parts_of)
+    total_units += p.most;
+  }
+  if (rows > 0x7FFFFFFFull || total_units > 0x7FFFFFFFull) return VL_E_SHAPE;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t o_failed = up(rows * sizeof(vl_result)), o_units = o_failed + up(rows * 4), o_spill = o_units + up(max_units * sizeof(Unit));
-  const size_t bytes = o_spill + (in_lds ? 0 : groups * table_bytes);
+  const size_t o_failed = up(rows * sizeof(vl_result)), o_units = o_failed + up(rows * 4), o_tables = o_units + up(total_units * sizeof(Unit));
+  const size_t bytes = o_tables + (launches[1].most ? launches[1].groups * launches[1].table_bytes : 0);
   if (bytes > w.mem_cap) {
     if (w.mem) (void)hipFree(w.mem);
     w.mem = nullptr; w.mem_cap = 0;
@@ -515,31 +580,39 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
   vl_result *const verdicts = (vl_result *)w.mem;
   uint32_t *const failed = (uint32_t *)(w.mem + o_failed);
   Unit *const units = (Unit *)(w.mem + o_units);
-  Head *const head = (Head *)w.dev;
-  const DevCountJob *const dev_jobs = (const DevCountJob *)(w.dev + sizeof(Head));
+  const UnitLists lists = {{units, units + launches[0].most}};
+  Head *const heads = (Head *)w.dev;
+  const DevCountJob *const dev_jobs = (const DevCountJob *)(w.dev + kHeads);
   std::vector<vl_job> walk(n_jobs);
   uint32_t at = 0;
-  memset(w.host, 0, sizeof(Head));
+  memset(w.host, 0, kHeads);
   for (uint32_t j = 0; j < n_jobs; ++j) {
     const vl_count_job &u = jobs[j];
-    DevCountJob &d = ((DevCountJob *)(w.host + sizeof(Head)))[j];
+    DevCountJob &d = ((DevCountJob *)(w.host + kHeads))[j];
     memset(&d, 0, sizeof(d));
     d.mir = u.mir->dev; d.live = u.live->dev; d.cand = u.cand; d.out = u.out; d.verdicts = verdicts + at;
     d.records = (const uint32_t *)u.mir->edges; d.n_records = u.mir->n_edges; d.ld = u.ld; d.K = u.K; d.fail_base = at;
-    d.parts = (uint32_t)std::max<uint64_t>(1, (u.mir->n_edges + kRecordsPerPart - 1) / kRecordsPerPart);
+    d.table = table_of(u.mir);
+    const Part &p = launches[launch_of(d.table)];
+    // (a little more, so that rounding never asks for more units than there is room for)
+    d.records_per_few = (float)(1.001 * p.work / ((double)((u.K + at_once(d.table) - 1) / at_once(d.table)) * p.groups * rounds));
     d.wide = ((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0;
     walk[j] = vl_job{u.mir, u.live, u.cand, u.K, u.ld, verdicts + at};
     at += u.K;
   }
-  VL_HIP(hipMemcpyAsync(w.dev, w.host, sizeof(Head) + (size_t)n_jobs * sizeof(DevCountJob), hipMemcpyHostToDevice, stream));
+  VL_HIP(hipMemcpyAsync(w.dev, w.host, kHeads + (size_t)n_jobs * sizeof(DevCountJob), hipMemcpyHostToDevice, stream));
   const int32_t rc = verdicts_only(walk.data(), n_jobs, stream, w.walk);
   if (rc != VL_OK) {
     (void)hipStreamSynchronize(stream);   // the table's upload
     return rc;
   }
-  k_cnt_list<<<(n_jobs + 3) / 4, 256, 0, stream>>>(dev_jobs, n_jobs, head, failed, units);
-  if (in_lds) k_cnt_rows<true><<<groups, 1024, table_bytes, stream>>>(dev_jobs, head, failed, units, nullptr, max_v);
-  else k_cnt_rows<false><<<groups, 1024, 0, stream>>>(dev_jobs, head, failed, units, (uint2 *)(w.mem + o_spill), max_v);
+  k_cnt_list<<<(n_jobs + 3) / 4, 256, 0, stream>>>(dev_jobs, n_jobs, heads, failed, lists);
+  if (launches[0].most)
+    k_cnt_rows<true><<<(uint32_t)std::min<uint64_t>(launches[0].most, launches[0].groups), 1024, launches[0].table_bytes, stream>>>(
+        dev_jobs, heads, failed, lists.of[0], nullptr, 0);
+  if (launches[1].most)
+    k_cnt_rows<false><<<(uint32_t)std::min<uint64_t>(launches[1].most, launches[1].groups), 1024, 0, stream>>>(
+        dev_jobs, heads + 1, failed, lists.of[1], (uint2 *)(w.mem + o_tables), (uint32_t)(launches[1].table_bytes / sizeof(uint2)));
   VL_HIP(hipGetLastError());
   VL_HIP(hipEventRecord(w.consumed, stream));
   w.in_flight = true;

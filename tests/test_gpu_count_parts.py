@@ -102,3 +102,39 @@ def test_rows_that_end_with_their_memory(n_instr, K):
     finally:
         free(hm, hl)
         assert hip.hipFree(mem) == 0
+
+
+def test_tables_of_every_kind_in_one_call():
+    """programs whose registers fit LDS for four samples, for two, and not at all; nearly every sample, one
+    of them and none failing, so that the pairs are cut into few parts and into many"""
+    sets = []
+    for j, (n, seed) in enumerate(((300, 1), (20000, 2), (39500, 3), (5000, 4))):
+        k = gen.Kernel(gen.STRAIGHT, 0xC0F0 + seed, n, n)
+        rows, log = k.candidates(5, 11, 9, 1)
+        rows[9] = np.random.default_rng(j).integers(0, 512, k.mir.n_occ)
+        sets.append((k.mir, rows, log["kind"] == 0))
+    assert [m.n_vreg > x for (m, _, _), x in zip(sets[1:3], (19456, 38912))] == [True, True]
+    ans = [vlo.analyze(m, threads=8) for m, _, _ in sets]
+    hm, hl, _, _ = gpu_analyze([m for m, _, _ in sets], dense=False)
+    try:
+        for pick in (lambda good, n: np.arange(n), lambda good, n: np.r_[np.nonzero(good)[0], 0], lambda good, n: np.nonzero(good)[0]):
+            jobs, wants = [], []
+            for m, l, (mir, rows, good), an in zip(hm, hl, sets, ans):
+                rows = np.ascontiguousarray(rows[pick(good, len(rows))])
+                dev, ld = vl.rows_to_device(rows)
+                out = torch.full((len(rows), 8), -1, dtype=torch.int32, device="cuda")
+                jobs.append((m, l, dev, len(rows), ld, out))
+                wants.append(vlo.count_violations(mir, an, rows, threads=8))
+            for order in (jobs, jobs[::-1], jobs[1:2], jobs[2:3]):
+                for j in order:
+                    j[5].fill_(-1)
+                vl.vl_count_violations_multi(order)
+                torch.cuda.synchronize()
+                for j, want in zip(jobs, wants):
+                    if not any(j is x for x in order):
+                        continue
+                    got = j[5].cpu().numpy().view(np.uint32)
+                    for c, name in enumerate(("kinds", "n_cons", "n_real", "n_safe", "real_bits")):
+                        assert (got[:, c] == want[name]).all(), name
+    finally:
+        free(hm, hl)
