@@ -13,7 +13,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
-#include <vector>
+#include <type_traits>
 
 #include "vl_dev.h"
 
@@ -28,15 +28,18 @@ struct Run {
   int64_t stride;
   uint32_t occ, count, first_query, first_block;
 };
-constexpr uint32_t kArgRuns = 64;   // runs that travel as a kernel argument (3 KB); more go through a table
+constexpr uint32_t kArgRuns = 64;   // runs that travel as a kernel argument (3 KB); more go through a table, whose upload costs 7 us
+                                   // (runs of 20 queries: 64 take 12.3 us, 65 19.2)
 struct RunArgs { Run run[kArgRuns]; };
 constexpr uint32_t kMaskThreads = 256, kMaskWaves = kMaskThreads / 64;
 constexpr uint32_t kMaskMembers = 256;   // members of P(i) that are listed; with more, every vreg gets a turn
 
 template <bool kByArgument>
-__global__ __launch_bounds__(kMaskThreads) void k_free_bases(const RunArgs args, const Run *__restrict__ table, uint32_t n_runs,
+__global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditional_t<kByArgument, RunArgs, const Run *> args, uint32_t n_runs,
                                                              uint32_t per_block, uint32_t *__restrict__ masks) {
-  const Run *const runs = kByArgument ? args.run : table;
+  const Run *runs;
+  if constexpr (kByArgument) runs = args.run;
+  else runs = args;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   // the run of this block: 64 probes at a time, one per lane
   uint32_t at = 0, len = n_runs;
@@ -124,6 +127,73 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const RunArgs args,
   }
 }
 
+// Runs of a query or two, a workgroup each: nothing to share out, so two wavefronts do everything
+// together.  The members of P(i) are first listed, which takes no reads from memory, and then looked up a lane
+// each.  (us per call, a workgroup of four wavefronts for each of them / this: 1,000 scattered queries of a program of
+// 8,000 instructions 31 / 25, 4,000 42 / 30, 16,000 121 / 53; of first mentions 31 / 25, 55 / 32, 153 / 66;
+// 29, 35, 63 and 30, 38, 81 with a workgroup of two that looked every vreg up.)
+constexpr uint32_t kAloneThreads = 128, kAloneMembers = 512;   // (members that are listed; with more, every vreg gets a turn)
+__global__ __launch_bounds__(kAloneThreads) void k_free_bases_alone(const Run *__restrict__ runs, uint32_t *__restrict__ masks) {
+  const Run R = runs[blockIdx.x];
+  const DevMir VL_GLOBAL &m = *as_global(R.mir);
+  const DevLive VL_GLOBAL &L = *as_global(R.live);
+  extern __shared__ uint32_t in_p[];      // [W] members of P(i)
+  __shared__ uint32_t members[kAloneMembers], n_members;
+  __shared__ uint32_t blocked[17];        // registers that are taken or reserved (word 16: always zero)
+  const uint32_t tid = threadIdx.x, q = R.occ, v = m.occ_vreg[q], i = m.occ_instr[q];
+  const uint32_t attr = m.vattr[v], cls = attr_class(attr), width = attr_width(attr), align = attr_align(attr);
+  const uint32_t F = m.class_size[cls], first_v = L.first[v];
+  const bool fresh = first_v >= q;   // the first mention of v: everything in P(i) that already has a register is in the way
+  if (fresh) {
+    for (uint32_t x = tid; x < m.W; x += kAloneThreads) in_p[x] = 0;
+    if (tid == 0) n_members = 0;
+    __syncthreads();
+    flip_members_of_p(m, L, i, in_p, tid, kAloneThreads);
+    __syncthreads();
+    for (uint32_t x = tid; x < m.W; x += kAloneThreads) {
+      uint32_t bits = in_p[x];
+      if (!bits) continue;
+      uint32_t at = atomicAdd(&n_members, (uint32_t)__popc(bits));
+      for (; bits && at < kAloneMembers; bits &= bits - 1) members[at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
+    }
+  }
+  const uint32_t wm = width == 32 ? 0xFFFFFFFFu : ((1u << width) - 1u);
+  for (uint32_t x = 0; x < R.count; ++x) {
+    const uint16_t VL_GLOBAL *row = as_global(R.cand) + (int64_t)x * R.stride;
+    if (tid < 17) blocked[tid] = (tid < 16 && m.has_reserved) ? m.reserved[cls][tid] : 0u;
+    __syncthreads();
+    auto take = [&](uint32_t b) {
+      const uint32_t ab = m.vattr[b], fb = L.first[b];
+      if (b == v || attr_class(ab) != cls || fb >= q) return;
+      const uint32_t p = row[fb], end = p + attr_width(ab);
+      for (uint32_t r = p; r < end && r < 512u; r = (r | 31u) + 1u) {   // one word after the other
+        const uint32_t n = min(end - r, 32u - (r & 31u));
+        atomicOr(&blocked[r >> 5], (n == 32u ? 0xFFFFFFFFu : ((1u << n) - 1u)) << (r & 31u));
+      }
+    };
+    if (fresh) {
+      if (n_members <= kAloneMembers) {
+        for (uint32_t y = tid; y < n_members; y += kAloneThreads) take(members[y]);
+      } else {
+        for (uint32_t b = tid; b < m.V; b += kAloneThreads)
+          if ((in_p[b >> 5] >> (b & 31)) & 1u) take(b);
+      }
+      __syncthreads();
+    }
+    const uint32_t forced = fresh ? kNone : (uint32_t)row[first_v];   // a later mention: only its own register
+    uint32_t *const out = masks + (size_t)(R.first_query + x) * 16;
+#pragma unroll
+    for (uint32_t p = tid; p < 512u; p += kAloneThreads) {
+      const uint64_t window = ((uint64_t)blocked[p >> 5] | ((uint64_t)blocked[(p >> 5) + 1] << 32)) >> (p & 31);
+      bool ok = p % align == 0 && p + width <= F && ((uint32_t)window & wm) == 0;
+      if (forced != kNone && p != forced) ok = false;
+      const uint64_t ballot = __ballot(ok);   // a wavefront covers 64 consecutive bases: two words of the mask
+      if ((tid & 63u) < 2u) out[(p >> 6) * 2u + (tid & 1u)] = (tid & 1u) ? (uint32_t)(ballot >> 32) : (uint32_t)ballot;
+    }
+    __syncthreads();   // the words are rewritten by the next query
+  }
+}
+
 // tables of runs on the device, one set per device, for calls with more runs than fit the kernel's
 // argument; used in turn, so that a call waits only for the one kTables calls ago
 constexpr uint32_t kTables = 4;
@@ -147,18 +217,39 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
   uint32_t max_w = 1;
   // neighbouring queries of one program at one occurrence whose rows lie at equal distances are one run
   RunArgs args;
-  std::vector<Run> more;
+  Run *runs = args.run;
   uint32_t n_runs = 0;
-  Run run = {};
-  auto close = [&]() {
-    if (!run.count) return;
-    if (n_runs < kArgRuns) args.run[n_runs] = run;
-    else {
-      if (more.empty()) more.assign(args.run, args.run + kArgRuns);
-      more.push_back(run);
+  // the first run too many for the argument takes a table, and the runs are put together there
+  std::unique_lock<std::mutex> lock;
+  Tables::One *t = nullptr;
+  auto take_table = [&]() -> int32_t {
+    int device = 0;
+    VL_HIP(hipGetDevice(&device));
+    if (device < 0 || device >= 16) return VL_E_ARG;
+    Tables &all = g_tables[device];
+    lock = std::unique_lock<std::mutex>(all.mu);
+    t = &all.one[all.turn = (all.turn + 1) % kTables];
+    // the kernel that last read this table must be done with it before it is overwritten
+    if (t->in_flight) VL_HIP(hipEventSynchronize(t->consumed));
+    t->in_flight = false;
+    if (t->cap < n) {
+      if (t->dev) (void)hipFree(t->dev);
+      if (t->host) (void)hipHostFree(t->host);
+      t->dev = nullptr; t->host = nullptr; t->cap = 0;
+      const uint32_t cap = std::max(1024u, n);
+      VL_HIP(hipMalloc((void **)&t->dev, (size_t)cap * sizeof(Run)));
+      VL_HIP(hipHostMalloc((void **)&t->host, (size_t)cap * sizeof(Run), hipHostMallocDefault));
+      if (!t->consumed) VL_HIP(hipEventCreateWithFlags(&t->consumed, hipEventDisableTiming));
+      t->cap = cap;
     }
-    ++n_runs;
+    memcpy(t->host, args.run, sizeof(args.run));
+    runs = t->host;
+    return VL_OK;
   };
+  // a workgroup per four queries (one per wavefront) up to a thousand workgroups, then longer shares
+  const uint32_t per_block = kMaskWaves * std::max(1u, std::min(16u, n / (kMaskWaves * 1024u)));
+  uint32_t blocks = 0;
+  Run run = {};
   const vl_mir *mir = nullptr;
   const vl_live *live = nullptr;
   const uint16_t *next = nullptr;
@@ -181,48 +272,34 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
         continue;
       }
     }
-    close();
-    run = Run{mir->dev, live->dev, u.cand, 0, u.occ, 1, j, 0};
+    if (run.count) {   // the run before is complete
+      if (n_runs == kArgRuns) {
+        const int32_t rc = take_table();
+        if (rc != VL_OK) return rc;
+      }
+      runs[n_runs++] = run;
+      blocks += run.count <= per_block ? 1u : (run.count + per_block - 1) / per_block;
+    }
+    run = Run{mir->dev, live->dev, u.cand, 0, u.occ, 1, j, blocks};
   }
-  close();
-  Run *const runs = n_runs <= kArgRuns ? args.run : more.data();
-  // a workgroup per four queries (one per wavefront) up to a thousand workgroups, then longer shares
-  const uint32_t per_block = kMaskWaves * std::max(1u, std::min(16u, n / (kMaskWaves * 1024u)));
-  uint32_t blocks = 0;
-  for (uint32_t r = 0; r < n_runs; ++r) {
-    runs[r].first_block = blocks;
-    blocks += (runs[r].count + per_block - 1) / per_block;
+  if (n_runs == kArgRuns) {
+    const int32_t rc = take_table();
+    if (rc != VL_OK) return rc;
   }
+  runs[n_runs++] = run;
+  blocks += run.count <= per_block ? 1u : (run.count + per_block - 1) / per_block;
   hipStream_t stream = (hipStream_t)stream_;
-  int device = 0;
-  VL_HIP(hipGetDevice(&device));
-  if (device < 0 || device >= 16) return VL_E_ARG;
-  if (n_runs <= kArgRuns) {
-    k_free_bases<true><<<blocks, kMaskThreads, (size_t)max_w * 4, stream>>>(args, nullptr, n_runs, per_block, masks);
+  const size_t lds = (size_t)max_w * 4;
+  if (!t) {
+    k_free_bases<true><<<blocks, kMaskThreads, lds, stream>>>(args, n_runs, per_block, masks);
     VL_HIP(hipGetLastError());
     return VL_OK;
   }
-  Tables &all = g_tables[device];
-  std::lock_guard<std::mutex> lock(all.mu);
-  Tables::One &t = all.one[all.turn = (all.turn + 1) % kTables];
-  // the kernel that last read this table must be done with it before it is overwritten
-  if (t.in_flight) VL_HIP(hipEventSynchronize(t.consumed));
-  t.in_flight = false;
-  if (t.cap < n_runs) {
-    if (t.dev) (void)hipFree(t.dev);
-    if (t.host) (void)hipHostFree(t.host);
-    t.dev = nullptr; t.host = nullptr; t.cap = 0;
-    const uint32_t cap = std::max(1024u, n_runs);
-    VL_HIP(hipMalloc((void **)&t.dev, (size_t)cap * sizeof(Run)));
-    VL_HIP(hipHostMalloc((void **)&t.host, (size_t)cap * sizeof(Run), hipHostMallocDefault));
-    if (!t.consumed) VL_HIP(hipEventCreateWithFlags(&t.consumed, hipEventDisableTiming));
-    t.cap = cap;
-  }
-  memcpy(t.host, runs, (size_t)n_runs * sizeof(Run));
-  VL_HIP(hipMemcpyAsync(t.dev, t.host, (size_t)n_runs * sizeof(Run), hipMemcpyHostToDevice, stream));
-  k_free_bases<false><<<blocks, kMaskThreads, (size_t)max_w * 4, stream>>>(RunArgs{}, t.dev, n_runs, per_block, masks);
+  VL_HIP(hipMemcpyAsync(t->dev, t->host, (size_t)n_runs * sizeof(Run), hipMemcpyHostToDevice, stream));
+  if (blocks == n_runs && n <= 2ull * n_runs) k_free_bases_alone<<<blocks, kAloneThreads, lds, stream>>>(t->dev, masks);
+  else k_free_bases<false><<<blocks, kMaskThreads, lds, stream>>>(t->dev, n_runs, per_block, masks);
   VL_HIP(hipGetLastError());
-  VL_HIP(hipEventRecord(t.consumed, stream));
-  t.in_flight = true;
+  VL_HIP(hipEventRecord(t->consumed, stream));
+  t->in_flight = true;
   return VL_OK;
 }

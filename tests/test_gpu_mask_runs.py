@@ -98,3 +98,31 @@ def test_null_pointers_in_a_later_query(missing):
         torch.cuda.synchronize()
         vl.vl_live_destroy(hl)
         vl.vl_mir_destroy(hm)
+
+
+@pytest.mark.parametrize("n_live", [511, 512, 700])
+@pytest.mark.parametrize("together", [1, 2])
+def test_queries_that_stand_alone(n_live, together):
+    """more runs than travel as an argument, of one query or two: first and later mentions, in P(i) as many
+    values as are listed, one more and many more"""
+    V = n_live + 1
+    blocks = [[([v], []) for v in range(V)] + [([], list(range(v, min(V, v + 40)))) for v in range(0, V, 40)]]
+    rng = np.random.default_rng(n_live + together)
+    reserved = np.zeros((1, 16), np.uint32)
+    reserved[0, 3] = 0xF0
+    m = Mir.build(blocks, [[]], V, (512,), np.zeros(V, np.uint8), rng.choice([1, 2, 32], V, p=[0.8, 0.15, 0.05]), np.ones(V, np.uint8),
+                  reserved, name=f"alone{n_live}")
+    rows = np.ascontiguousarray(rng.integers(0, 640, (9, V)).astype(np.uint16)[:, m.occ_vreg])
+    an = vlo.analyze(m, interference=False)
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        dev, ld = vl.rows_to_device(rows)
+        qs = [(0, n_live), (4, n_live)] + [(int(rng.integers(8)), int(o)) for o in rng.choice(m.n_occ, 150)]
+        qs = [(k + t, o) for k, o in qs for t in range(together)]
+        masks = torch.full((len(qs), 16), -1, dtype=torch.int32, device="cuda")
+        vl.vl_free_bases_multi([(hm[0], hl[0], dev[k], o) for k, o in qs], masks)
+        torch.cuda.synchronize()
+        want = np.stack([vlo.free_bases(m, an, rows[k], o) for k, o in qs])
+        assert (masks.cpu().numpy().view(np.uint32) == want).all()
+    finally:
+        free(hm, hl)
