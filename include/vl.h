@@ -159,6 +159,10 @@ int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint32_t flags,
                           vl_stream stream, vl_live **live);
 /* The same for one kernel. */
 int32_t vl_liveness(const vl_mir *mir, uint32_t flags, vl_stream stream, vl_live **live);
+/* Waits for the device when it is the last handle of its call.  Of the analysis' device memory,
+ * blocks of 1 to 64 MB are kept for later analyses, at most six per device (so 384 MB at
+ * most): one that 32 analyses in turn had no use for is returned to the system, and all of them
+ * when an allocation of the library fails for want of memory. */
 void vl_live_destroy(vl_live *live);
 
 /* Device views of one analysis; every pointer is [device], owned by the

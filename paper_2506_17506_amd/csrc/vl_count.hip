@@ -439,11 +439,11 @@ int32_t build_pairs(const std::vector<std::pair<vl_mir *, const vl_live *>> &tod
     return hip_fail(err);
   };
   // (a kernel's groups start at base / 64 + its index: at most one entry per kernel is left unused)
-  hipError_t e = hipMalloc((void **)&cnt, total_v * 4);
-  if (e == hipSuccess) e = hipMalloc((void **)&off, total_v * 8);
-  if (e == hipSuccess) e = hipMalloc((void **)&groups, (total_v / 64 + n + 1) * sizeof(uint2));
-  if (e == hipSuccess) e = hipMalloc((void **)&totals_dev, n * 8);
-  if (e == hipSuccess) e = hipMalloc((void **)&jobs_dev, n * sizeof(PairJob));
+  hipError_t e = device_alloc((void **)&cnt, total_v * 4);
+  if (e == hipSuccess) e = device_alloc((void **)&off, total_v * 8);
+  if (e == hipSuccess) e = device_alloc((void **)&groups, (total_v / 64 + n + 1) * sizeof(uint2));
+  if (e == hipSuccess) e = device_alloc((void **)&totals_dev, n * 8);
+  if (e == hipSuccess) e = device_alloc((void **)&jobs_dev, n * sizeof(PairJob));
   if (e != hipSuccess) return fail(e);
   std::vector<PairJob> jobs(n);
   for (size_t j = 0; j < n; ++j)
@@ -464,7 +464,7 @@ int32_t build_pairs(const std::vector<std::pair<vl_mir *, const vl_live *>> &tod
     all += (totals[j] + 7) & ~(uint64_t)7;   // every program's records start on a 256-byte boundary
   }
   if (all) {
-    e = hipMalloc(&all_pairs, (size_t)all * 32);
+    e = device_alloc(&all_pairs, (size_t)all * 32);
     if (e != hipSuccess) return fail(e);
   }
   for (size_t j = 0; j < n; ++j) jobs[j].records = totals[j] ? (uint32_t *)all_pairs + 8 * first_pair[j] : nullptr;
@@ -533,7 +533,7 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
     if (w.host) (void)hipHostFree(w.host);
     w.dev = nullptr; w.host = nullptr; w.cap = 0;
     const uint32_t cap = std::max(256u, n_jobs);
-    VL_HIP(hipMalloc((void **)&w.dev, kHeads + (size_t)cap * sizeof(DevCountJob)));
+    VL_HIP(device_alloc((void **)&w.dev, kHeads + (size_t)cap * sizeof(DevCountJob)));
     VL_HIP(hipHostMalloc((void **)&w.host, kHeads + (size_t)cap * sizeof(DevCountJob), hipHostMallocDefault));
     w.cap = cap;
   }
@@ -574,7 +574,7 @@ extern "C" int32_t vl_count_violations_multi(const vl_count_job *jobs, uint32_t 
   if (bytes > w.mem_cap) {
     if (w.mem) (void)hipFree(w.mem);
     w.mem = nullptr; w.mem_cap = 0;
-    VL_HIP(hipMalloc((void **)&w.mem, bytes));
+    VL_HIP(device_alloc((void **)&w.mem, bytes));
     w.mem_cap = bytes;
   }
   vl_result *const verdicts = (vl_result *)w.mem;

@@ -308,6 +308,9 @@ struct WalkSpace {
 };
 // vl_verify_multi without the search for the pair of a safety violation (vl_verify.hip)
 int32_t verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &space);
+// hipMalloc for the library's own memory: when it runs short, the memory kept from destroyed analyses on the
+// current device goes back first (vl_liveness.hip)
+hipError_t device_alloc(void **mem, size_t bytes);
 #define VL_HIP(call)                                   \
   do {                                                 \
     hipError_t e_ = (call);                            \

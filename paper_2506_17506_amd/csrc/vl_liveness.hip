@@ -1706,7 +1706,7 @@ struct vl_batch {
 // samples are analysed into new handles and dropped, and mapping and unmapping tens of megabytes
 // took longer than the analysis (32 MB: hipMalloc 24 us, hipFree 180 us).  A few blocks of middling
 // size per device are kept when an analysis is destroyed; a block that several takers in turn had no
-// use for goes back to the system, and all of them when memory runs short.  As with hipFree, whoever
+// use for goes back to the system, and all of them when any allocation of the library finds memory short.  As with hipFree, whoever
 // gives memory back waits for the device, so what a taker gets is idle on every stream.
 namespace {
 struct Arena {
@@ -1723,6 +1723,31 @@ struct Pool {
 };
 Pool g_pool[16];
 
+// gives back everything that is kept; whether that was anything
+bool pool_empty(int device) {
+  if (device < 0 || device >= 16) return false;
+  Arena all[kPoolBlocks];
+  {
+    std::lock_guard<std::mutex> lock(g_pool[device].mu);
+    for (int k = 0; k < kPoolBlocks; ++k) { all[k] = g_pool[device].block[k]; g_pool[device].block[k] = {nullptr, 0}; }
+  }
+  bool any = false;
+  for (const Arena &a : all)
+    if (a.mem) { (void)hipFree(a.mem); any = true; }
+  return any;
+}
+}  // namespace
+
+hipError_t vl::device_alloc(void **mem, size_t bytes) {
+  hipError_t e = hipMalloc(mem, bytes);
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess || !pool_empty(device)) return e;
+  return hipMalloc(mem, bytes);
+}
+
+namespace {
 hipError_t arena_take(int device, size_t bytes, void **mem, size_t *cap) {
   Arena got = {nullptr, 0}, stale[kPoolBlocks] = {};
   Pool *pool = device >= 0 && device < 16 ? &g_pool[device] : nullptr;
@@ -1743,18 +1768,7 @@ hipError_t arena_take(int device, size_t bytes, void **mem, size_t *cap) {
   hipError_t e = hipSuccess;
   if (!got.mem) {
     got.cap = bytes;
-    e = hipMalloc(&got.mem, bytes);
-    if (e == hipErrorOutOfMemory && pool) {
-      (void)hipGetLastError();
-      Arena all[kPoolBlocks];
-      {
-        std::lock_guard<std::mutex> lock(pool->mu);
-        for (int k = 0; k < kPoolBlocks; ++k) { all[k] = pool->block[k]; pool->block[k] = {nullptr, 0}; }
-      }
-      for (const Arena &a : all)
-        if (a.mem) (void)hipFree(a.mem);
-      e = hipMalloc(&got.mem, bytes);
-    }
+    e = device_alloc(&got.mem, bytes);
     if (e != hipSuccess) got = {nullptr, 0};
   }
   *mem = got.mem;

@@ -237,7 +237,7 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
       if (t->host) (void)hipHostFree(t->host);
       t->dev = nullptr; t->host = nullptr; t->cap = 0;
       const uint32_t cap = std::max(1024u, n);
-      VL_HIP(hipMalloc((void **)&t->dev, (size_t)cap * sizeof(Run)));
+      VL_HIP(device_alloc((void **)&t->dev, (size_t)cap * sizeof(Run)));
       VL_HIP(hipHostMalloc((void **)&t->host, (size_t)cap * sizeof(Run), hipHostMallocDefault));
       if (!t->consumed) VL_HIP(hipEventCreateWithFlags(&t->consumed, hipEventDisableTiming));
       t->cap = cap;

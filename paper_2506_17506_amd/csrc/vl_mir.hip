@@ -184,7 +184,7 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   m->arena = nullptr;
   m->magic = vl::kMirMagic;
   hipError_t e = hipGetDevice(&m->device);
-  if (e == hipSuccess) e = hipMalloc(&m->arena, bump.off);
+  if (e == hipSuccess) e = vl::device_alloc(&m->arena, bump.off);
   if (e != hipSuccess) { delete m; return vl::hip_fail(e); }
   char *base = (char *)m->arena;
   std::vector<char> &image = t_image;

@@ -1095,7 +1095,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Wa
     s.board = nullptr; s.groups_cap = s.rows_cap = 0;
     const uint64_t of_rows = results_only ? 0 : out.total_rows, of_groups = results_only ? 0 : out.groups;   // (reductions use the head alone)
     const uint64_t rows = std::max<uint64_t>(65536, of_rows + of_rows / 2), groups = std::max<uint64_t>(4096, of_groups + of_groups / 2);
-    VL_HIP(hipMalloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
+    VL_HIP(device_alloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
     k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
     s.rows_cap = rows; s.groups_cap = groups;
   }
@@ -1108,7 +1108,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Wa
       if (s.staged) (void)hipHostFree(s.staged);
       s.dev = nullptr; s.staged = s.host = nullptr; s.cap = 0; s.n_valid = 0;
       uint32_t cap = std::max(256u, n_jobs);
-      VL_HIP(hipMalloc((void **)&s.dev, (size_t)cap * sizeof(DevJob)));
+      VL_HIP(device_alloc((void **)&s.dev, (size_t)cap * sizeof(DevJob)));
       VL_HIP(hipHostMalloc((void **)&s.staged, (size_t)cap * kStaged * sizeof(DevJob), hipHostMallocDefault));
       for (uint32_t t = 0; t < kStaged; ++t) {
         if (!s.copied[t]) VL_HIP(hipEventCreateWithFlags(&s.copied[t], hipEventDisableTiming));

@@ -20,6 +20,7 @@ static struct { dim3_t grid, block; size_t lds; void *stream; } g_call;
 
 void stand_in_on_launch(launch_fn f) { g_on_launch = f; }
 void stand_in_fail(int after, int more) { g_fail = after; g_fail_more = more; }
+int stand_in_failing(void) { return g_fail >= 0; }   /* the allocation that is to fail has not come yet */
 void stand_in_counts(uint64_t *out) {   /* allocations, frees, uploads, waits for a stream, waits for the device, largest allocation */
   out[0] = g_mallocs; out[1] = g_frees; out[2] = g_uploads; out[3] = g_stream_syncs; out[4] = g_device_syncs; out[5] = g_largest;
 }

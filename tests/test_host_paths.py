@@ -121,3 +121,47 @@ def test_reductions_over_more_samples_than_a_verification_takes(s):
     s.vl.vl_summarize_multi(arr, sums, stats, stream=S1)
     assert sum("k_summarize" in x[0] for x in s.launches) == 1
     assert s.counts()["largest"] < 64 << 20
+
+
+@in_own_process
+def test_kept_memory_is_given_back_when_memory_runs_short(s):
+    """whichever allocation of whichever call finds no memory: what destroyed analyses left is returned first"""
+    n = 20000
+    large = s.vl.vl_mir_create(Mir.build([[((v,), ()) for v in range(n)] + [((), (v,)) for v in range(n)]], [[]], n, [64]))
+    hm, hl = analysed(s, 2)
+
+    def keep_some():
+        for h in s.vl.vl_liveness_multi([large], stream=S1):
+            s.vl.vl_live_destroy(h)
+
+    def fails_once_and_recovers(what, after):
+        keep_some()
+        frees = s.counts()["frees"]
+        s.fail_allocation(after)
+        what()
+        left = s.lib.stand_in_failing()
+        s.fail_allocation(-1)
+        if left:
+            return False   # fewer allocations than that
+        assert s.counts()["frees"] > frees
+        return True
+
+    made = []
+    streams = iter(range(S1 + 1000, S1 + 2000))
+    jobs, keep = jobs_of(s, hm, hl, 8)
+    queries = s.vl.make_mask_queries([(hm[0], hl[0], keep[0][0], o % 8) for o in range(3000)])
+    masks = Buffer(3000 * 64)
+
+    def count():
+        fresh, lives = analysed(s, 2)
+        cj, k2 = jobs_of(s, fresh, lives, 8, record=32)
+        s.vl.vl_count_violations_multi(cj, stream=S1)
+    calls = {"create": lambda: made.append(s.vl.vl_mir_create(program())),
+             "verify": lambda: s.vl.vl_verify_multi(jobs, stream=next(streams)),
+             "count": count,
+             "mask": lambda: s.vl.vl_free_bases_multi(queries, masks, stream=S1)}
+    tried = {name: 0 for name in calls}
+    for name, call in calls.items():
+        while tried[name] < 20 and fails_once_and_recovers(call, tried[name]):
+            tried[name] += 1
+    assert tried["create"] >= 1 and tried["verify"] >= 2 and tried["count"] >= 8 and tried["mask"] >= 1, tried
