@@ -2053,7 +2053,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     return ok;
   }();
   const bool hist_lds = lds_ok && (size_t)maxV * 4 <= 128 * 1024;
-  const bool small = hist_lds && maxO <= kGroupMaxOcc;
+  // (k_group clears block sets by 32-bit indices)
+  const bool small = hist_lds && maxO <= kGroupMaxOcc && (uint64_t)maxB * maxW < (1ull << 32) - 4;
   if (small) {
     k_group<<<dim3((maxO + kGroupSlice - 1) / kGroupSlice, n), 1024, (size_t)maxV * 4, stream>>>(dm, dl);
   } else {

@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
 typedef void (*launch_fn)(const char *name, uint32_t gx, uint32_t gy, uint32_t gz, uint32_t bx, size_t lds, void *stream, void **args);
@@ -55,8 +56,23 @@ int hipLaunchKernel(const void *func, dim3_t grid, dim3_t block, void **args, si
   if (g_on_launch) g_on_launch(name, grid.x, grid.y, grid.z, block.x, lds, stream, args);
   return 0;
 }
-int hipMalloc(void **p, size_t n) { ++g_mallocs; if (n > g_largest) g_largest = n; if (fails()) { *p = 0; return kOutOfMemory; } *p = calloc(1, n + 256); return *p ? 0 : kOutOfMemory; }
-int hipFree(void *p) { ++g_frees; free(p); return 0; }
+/* cleared memory that takes no room until it is written (a device has more than this host); its size in front of it */
+int hipMalloc(void **p, size_t n) {
+  ++g_mallocs;
+  if (n > g_largest) g_largest = n;
+  *p = 0;
+  if (fails()) return kOutOfMemory;
+  size_t *m = mmap(0, n + 4096, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  if (m == MAP_FAILED) return kOutOfMemory;
+  *m = n + 4096;
+  *p = (char *)m + 4096;
+  return 0;
+}
+int hipFree(void *p) {
+  ++g_frees;
+  if (p) munmap((char *)p - 4096, *(size_t *)((char *)p - 4096));
+  return 0;
+}
 int hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; *p = calloc(1, n + 1); return 0; }
 int hipHostFree(void *p) { free(p); return 0; }
 int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream) { (void)stream; g_uploads += kind == 1; memcpy(to, from, n); return 0; }

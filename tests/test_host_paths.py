@@ -165,3 +165,21 @@ def test_kept_memory_is_given_back_when_memory_runs_short(s):
         while tried[name] < 20 and fails_once_and_recovers(call, tried[name]):
             tried[name] += 1
     assert tried["create"] >= 1 and tried["verify"] >= 2 and tried["count"] >= 8 and tried["mask"] >= 1, tried
+
+
+@in_own_process
+def test_block_sets_beyond_32_bit_indices(s):
+    """few occurrences, but 2^32 words of block sets and more: cleared by the kernel that counts in 64 bits"""
+    V = 32768
+    for n_block, by_group in ((1 << 21, True), ((1 << 22) - 1, True), (1 << 22, False), ((1 << 22) + 5, False)):
+        ins = np.zeros(n_block + 1, np.uint32)
+        ins[1:] = 1   # the first block writes a value, the others are empty instructions
+        m = Mir(np.arange(n_block + 1), np.r_[np.arange(n_block), n_block - 1], np.arange(1, n_block), ins, [0], [1],
+                np.zeros(V, np.uint8), np.ones(V, np.uint8), np.ones(V, np.uint8), [64])
+        hm = s.vl.vl_mir_create(m)
+        s.launches.clear()
+        hl = s.vl.vl_liveness_multi([hm], stream=S1)
+        names = [x[0] for x in s.launches]
+        assert any("k_group" in x for x in names) == by_group and any("k_zero" in x for x in names) != by_group
+        s.vl.vl_live_destroy(hl[0])
+        s.vl.vl_mir_destroy(hm)
