@@ -106,7 +106,11 @@ struct LaneMaps {
 // The arrays that follow from the description (expansions of the CSR offsets, packed attributes and
 // records) are written by the device: an instruction and a vreg per thread.  They are three quarters
 // of a program's bytes, and putting them together and sending them from the host was most of what
-// vl_mir_create took (16 programs of 1,000-16,000 instructions: 1,900 us, 950 this way).
+// vl_mir_create took (16 programs of 1,000-16,000 instructions: 1,900 us, 950 this way).  For small programs the
+// launch costs more than that, and derive_on_host does the same.  (One program of 200, 1,000, 3,000, 4,000 and 8,000
+// instructions, created and destroyed: 17.5, 25.5, 30.0, 32.4 and 41 us with the launch, 15.7, 15.8, 27.7, 34.3 and 59 without;
+// 3,000 are 10,200 instructions, vregs and occurrences.)
+constexpr uint64_t kHostItems = 11500;
 __global__ __launch_bounds__(256) void k_derive(const vl::DevMir *__restrict__ prog, const uint8_t *__restrict__ vclass,
                                                 const uint8_t *__restrict__ vwidth, const uint8_t *__restrict__ valign,
                                                 uint32_t *__restrict__ occ_instr, uint32_t *__restrict__ instr_blk,
@@ -129,6 +133,22 @@ __global__ __launch_bounds__(256) void k_derive(const vl::DevMir *__restrict__ p
     occ_instr[o] = x;
     occ_rec[o] = (uint64_t)(m.occ_vreg[o] | keeps) | ((uint64_t)((x << 2) | (m.occ_flags[o] & 3u)) << 32);
   }
+}
+
+void derive_on_host(const vl_mir_desc &d, const vl::DevMir &h, uint32_t *occ_instr, uint32_t *instr_blk, uint32_t *vattr, uint64_t *occ_rec) {
+  for (uint32_t v = 0; v < d.n_vreg; ++v)
+    vattr[v] = vl::attr_pack(d.vreg_class[v], d.vreg_width[v], d.vreg_align[v]) | ((uint32_t)h.class_word[d.vreg_class[v]] << 16);
+  for (uint32_t b = 0; b < d.n_block; ++b)
+    for (uint32_t i = d.blk_start[b]; i < d.blk_start[b + 1]; ++i) {
+      instr_blk[i] = b;
+      uint32_t all = 0;
+      for (uint32_t o = d.instr_occ_off[i]; o < d.instr_occ_off[i + 1]; ++o) all |= d.occ_flags[o];
+      const uint32_t keeps = all & VL_OCC_EARLY ? vl::kRecKeeps : 0u;
+      for (uint32_t o = d.instr_occ_off[i]; o < d.instr_occ_off[i + 1]; ++o) {
+        occ_instr[o] = i;
+        occ_rec[o] = (uint64_t)(d.occ_vreg[o] | keeps) | ((uint64_t)((i << 2) | (d.occ_flags[o] & 3u)) << 32);
+      }
+    }
 }
 
 // What a program sends is put together here: kept by the thread for its next program, up to a bound.
@@ -174,9 +194,11 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
     o_vv = bump.take((size_t)(V ? V : 1) * 4); o_vl = bump.take((size_t)(V ? V : 1));
   }
   size_t o_dev = bump.take(sizeof(vl::DevMir));
-  const size_t sent = bump.off;
+  const bool on_host = (uint64_t)N + V + O <= kHostItems;
+  size_t sent = bump.off;
   size_t o_oi = bump.take((size_t)(O ? O : 1) * 4), o_ib = bump.take((size_t)N * 4);
   size_t o_va = bump.take((size_t)(V ? V : 1) * 4), o_rec = bump.take((size_t)(O ? O : 1) * 8);
+  if (on_host) sent = bump.off;
 
   vl_mir *m = new (std::nothrow) vl_mir;
   if (!m) return VL_E_SHAPE;
@@ -226,9 +248,12 @@ int32_t create_impl(const vl_mir_desc *d, const LaneMaps *maps, vl_mir **out) {
   }
   m->dev = (vl::DevMir *)(base + o_dev);
   up(o_dev, &h, sizeof(h));
+  if (on_host)
+    derive_on_host(*d, h, (uint32_t *)(image.data() + o_oi), (uint32_t *)(image.data() + o_ib), (uint32_t *)(image.data() + o_va),
+                   (uint64_t *)(image.data() + o_rec));
   e = hipMemcpyAsync(base, image.data(), sent, hipMemcpyHostToDevice, nullptr);
   if (e == hipSuccess) {
-    k_derive<<<(std::max(N, V) + 255) / 256, 256, 0, nullptr>>>(m->dev, (const uint8_t *)(base + o_vc), (const uint8_t *)(base + o_vw),
+    if (!on_host) k_derive<<<(std::max(N, V) + 255) / 256, 256, 0, nullptr>>>(m->dev, (const uint8_t *)(base + o_vc), (const uint8_t *)(base + o_vw),
                                                                 (const uint8_t *)(base + o_val), (uint32_t *)(base + o_oi),
                                                                 (uint32_t *)(base + o_ib), (uint32_t *)(base + o_va), (uint64_t *)(base + o_rec));
     e = hipGetLastError();

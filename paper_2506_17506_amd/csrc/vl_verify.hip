@@ -972,13 +972,19 @@ struct Launch {
   bool all_direct = true;   // every job can be staged with 32-bit offsets and without bounds (DevJob::direct)
 };
 
-// Validates one job, lays out its entry of the device job table and adds it to the launch.
-// results_only: for the kernels that read nothing but the jobs' results (cand and ld are
-// neither checked nor used).  span: analysis tiles taken at once, where the analysis allows it.
-int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool results_only, uint32_t span) {
+// results_only: for the kernels that read nothing but the jobs' results (cand and ld are neither checked nor used)
+inline int32_t check_job(const vl_job &u, bool transposed, bool results_only) {
   if (!u.mir || !u.live || !u.out || (!u.cand && !results_only)) return VL_E_NULL;
   if (u.mir->magic != kMirMagic || u.live->magic != kLiveMagic || u.live->mir != u.mir) return VL_E_ARG;
   if (u.K == 0 || (!results_only && u.ld < (transposed ? u.K : u.mir->h.O))) return VL_E_SHAPE;
+  return VL_OK;
+}
+
+// Validates one job, lays out its entry of the device job table and adds it to the launch.
+// span: analysis tiles taken at once, where the analysis allows it.
+int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, uint32_t span) {
+  const int32_t rc = check_job(u, transposed, false);
+  if (rc != VL_OK) return rc;
   memset(&d, 0, sizeof(d));
   d.mir = u.mir->dev; d.live = u.live->dev; d.cand = u.cand; d.out = u.out; d.ld = u.ld; d.K = u.K;
   const bool aligned = ((uintptr_t)u.cand & 15) == 0 && (u.ld & 7) == 0;
@@ -990,7 +996,7 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   // less than 4 GB, so that 32-bit offsets reach every register (a row alone needs less than 32 MB of it)
   constexpr uint64_t kReach = ((1ull << 32) - (1ull << 26)) / 2;
   uint32_t most = 64;
-  if (!transposed && !results_only && u.ld > kReach / 64) most = (uint32_t)std::max<uint64_t>(1, kReach / u.ld);
+  if (!transposed && u.ld > kReach / 64) most = (uint32_t)std::max<uint64_t>(1, kReach / u.ld);
   d.n_groups = (u.K + most - 1) / most;
   d.rows = (u.K + d.n_groups - 1) / d.n_groups;
   if (transposed) {
@@ -1007,7 +1013,7 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
   }
   const uint32_t last = u.K - (d.n_groups - 1) * d.rows;
   d.unit_base = out.units;
-  if (!results_only && out.total_rows + u.K > 0xFFFFFFFFull) return VL_E_SHAPE;   // (the board has an entry per row)
+  if (out.total_rows + u.K > 0xFFFFFFFFull) return VL_E_SHAPE;   // (the board has an entry per row)
   d.row_base = (uint32_t)out.total_rows;
   d.group_base = (uint32_t)out.groups;
   out.groups += d.n_groups;
@@ -1031,14 +1037,14 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, bool 
 // 2,000 x 1,000, 1,008 / 504 / 252: 29, 26, 30; 2,000 x 4,000, 3,969 / 1,984 / 992: 70, 54, 47;
 // 1,000 x 1,000, 512 / 256 / 128: 23, 24, 28; 400 straight x 4,000, 819 / 441 / 252: 23, 24, 30.)
 constexpr uint32_t kEnoughUnits = 900;
-int32_t fill_jobs(const vl_job *jobs, uint32_t n_jobs, bool transposed, DevJob *tab, Launch &out, bool results_only) {
+int32_t fill_jobs(const vl_job *jobs, uint32_t n_jobs, bool transposed, DevJob *tab, Launch &out) {
   for (uint32_t span = 1;; span *= 2) {
     out = Launch();
     for (uint32_t j = 0; j < n_jobs; ++j) {
-      const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, results_only, span);
+      const int32_t rc = fill_job(jobs[j], transposed, tab[j], out, span);
       if (rc != VL_OK) return rc;
     }
-    if (results_only || out.units <= kEnoughUnits || span >= out.most_span) return VL_OK;
+    if (out.units <= kEnoughUnits || span >= out.most_span) return VL_OK;
   }
 }
 
@@ -1075,26 +1081,35 @@ int32_t space_of(Scratch &sc, hipStream_t stream, WalkSpace *&out) {
 // caller's for the duration of the call, and its earlier kernels run on `stream` or have ended.
 int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &s, Launch &out, bool transposed = false,
                      bool results_only = false) {
-  std::vector<DevJob> tab(n_jobs);
-  const int32_t rc = fill_jobs(jobs, n_jobs, transposed, tab.data(), out, results_only);
-  if (rc != VL_OK) return rc;
-  if (results_only && n_jobs > 1 && s.n_valid == n_jobs && s.board) {
+  std::vector<DevJob> tab;
+  if (results_only) {
     // the table a verification call on this stream left behind serves, whatever its candidate
     // layout, when it names the same results
-    bool same = true;
-    for (uint32_t j = 0; j < n_jobs && same; ++j) same = s.host[j].out == jobs[j].out && s.host[j].K == jobs[j].K;
+    bool same = n_jobs > 1 && s.n_valid == n_jobs && s.board;
+    for (uint32_t j = 0; j < n_jobs; ++j) {
+      const int32_t rc = check_job(jobs[j], false, true);
+      if (rc != VL_OK) return rc;
+      same = same && s.host[j].out == jobs[j].out && s.host[j].K == jobs[j].K;
+      out.maxK = std::max(out.maxK, jobs[j].K);
+    }
     if (same) {
       out.dev = s.dev;
       out.finished = s.board;
       return VL_OK;
     }
+    tab.resize(n_jobs);
+    for (uint32_t j = 0; j < n_jobs; ++j) { tab[j].out = jobs[j].out; tab[j].K = jobs[j].K; }
+  } else {
+    tab.resize(n_jobs);
+    const int32_t rc = fill_jobs(jobs, n_jobs, transposed, tab.data(), out);
+    if (rc != VL_OK) return rc;
   }
   if (!s.board || (!results_only && (s.groups_cap < out.groups || s.rows_cap < out.total_rows))) {
     VL_HIP(hipStreamSynchronize(stream));   // earlier kernels of the stream may still use the old board
     if (s.board) (void)hipFree(s.board);
     s.board = nullptr; s.groups_cap = s.rows_cap = 0;
-    const uint64_t of_rows = results_only ? 0 : out.total_rows, of_groups = results_only ? 0 : out.groups;   // (reductions use the head alone)
-    const uint64_t rows = std::max<uint64_t>(65536, of_rows + of_rows / 2), groups = std::max<uint64_t>(4096, of_groups + of_groups / 2);
+    // (reductions use the head alone, and count no rows)
+    const uint64_t rows = std::max<uint64_t>(65536, out.total_rows + out.total_rows / 2), groups = std::max<uint64_t>(4096, out.groups + out.groups / 2);
     VL_HIP(device_alloc((void **)&s.board, (size_t)(kHeadWords + rows + groups) * 4));
     k_clear_board<<<256, 256, 0, stream>>>(s.board, kHeadWords + rows + groups);
     s.rows_cap = rows; s.groups_cap = groups;
@@ -1346,7 +1361,7 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
   const vl_job u = {mir, live, cand, K, ld, out};
   DevJob d;
   Launch L;
-  const int32_t rc = fill_jobs(&u, 1, false, &d, L, false);
+  const int32_t rc = fill_jobs(&u, 1, false, &d, L);
   if (rc != VL_OK) return rc;
   hipStream_t stream = (hipStream_t)stream_;
   int device = 0;

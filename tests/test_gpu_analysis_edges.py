@@ -127,3 +127,21 @@ def test_gaps_in_the_numbering_beside_a_program_of_many_blocks(n_block, step):
             assert_liveness_equal(m, an, g, m.name)
     finally:
         free(hm, hl)
+
+
+def test_programs_around_what_the_host_derives():
+    """arrays that follow from the description are written by the host for up to 11,500 instructions, vregs and
+    occurrences together, by the device beyond: the same program a little smaller and a little larger"""
+    from vlgen.mixed import mixed_mir
+    sides = set()
+    for seed, n in ((1, 200), (2, 1500), (3, 1900), (4, 2100), (5, 2300), (6, 2600), (7, 4000)):
+        m = mixed_mir(0xB700 + seed, n_instr=n, reserved=seed % 2 == 0)
+        V, O = m.n_vreg, m.n_occ
+        rng = np.random.default_rng(seed)
+        # early-clobber definitions here and there
+        m.occ_flags[(m.occ_flags & 1 == 1) & (rng.random(O) < 0.1)] |= 4
+        sides.add((n + V + O <= 11500))
+        check([m])
+    assert sides == {True, False}
+    last = [flow_program(8, 5, v, 300) for v in (500, 3000, 6000)]
+    check(last)
