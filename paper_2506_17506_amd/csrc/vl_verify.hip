@@ -30,17 +30,22 @@
 using namespace vl;
 
 namespace vl {
+// (Kernel arguments are fetched 64 bytes at a time: with 144 bytes of them for the pair search instead of 120, verification
+// of 8 to 64 samples took 0.1 to 0.3 us more.  Hence nothing here that the device does not need.)
 struct DevJob {
   const DevMir *mir;
   const DevLive *live;
   const uint16_t *cand;
   vl_result *out;
   uint64_t ld;
-  uint32_t K, rows, n_groups, unit_base, n_units, transposed, direct;   // transposed: cand is [occurrence][candidate]
+  uint32_t K, rows, n_groups, unit_base;
   uint32_t row_base, group_base;   // the job's first entry in Board::keys and Board::arrived
   uint32_t span, n_spans;          // analysis tiles that a workgroup takes at once, and how often that is
-  // direct: row-major, aligned, and every row has room for whole chunks up to its pitch
+  uint8_t transposed;              // cand is [occurrence][candidate]
+  uint8_t direct;                  // row-major, aligned, and every row has room for whole chunks up to its pitch
+  uint8_t unused[6];               // zero (tables are compared byte by byte)
 };
+static_assert(sizeof(DevJob) == 80, "no padding");
 }  // namespace vl
 
 namespace {
@@ -68,6 +73,7 @@ constexpr uint32_t kKeyCons = 0u << 28, kKeyReal = 1u << 28, kKeySafe = 2u << 28
 // those of the all-violations mode, writes the zeros again: calls that overlapped against the rules (their counts mixed)
 // spoil each other, and without it every later call too.  Of such calls, the one whose walk ends last clears
 // what it has in common with the others after all of them.
+constexpr uint32_t kHeadWords = 64;   // in front of Board::arrived; the first is Launch::finished
 struct Board {
   uint32_t *arrived;   // per group of candidate rows: tiles that have reported
   uint32_t *keys;      // per candidate row: ~(smallest violation key so far), 0 = none
@@ -838,12 +844,12 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
 // vregs instead of registers (flip_members_of_p); its members, some tens, are then listed so that
 // each gets a lane (a lane per vreg of the program took most of the kernel's time: 15,000 vregs
 // are 117 turns of 128 threads).  The workgroups of a group of rows share out the rows that
-// failed on safety; the first of them leaves the group's part of the board zero (Board).
+// failed on safety; the first workgroups of the launch leave the board zero (Board).
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
 constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
 template <bool kOne>
-__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group,
-                                                             const Board board, uint32_t *finished) {
+__global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group, uint32_t n_groups,
+                                                             const Board board) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
   __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], nd, members[kResolveMembers], n_members;
@@ -853,12 +859,17 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
   const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
   // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
-  const uint32_t status = out[min(lane, nrows - 1u)].status;   // (before the stores: reads wait for the stores before them)
-  if (mine_first == 0) {
+  const uint32_t status = out[min(lane, nrows - 1u)].status;
+  // The board of a group, by the workgroups that start first, since the launch ends with its last store, and
+  // behind the read above, since reads wait for the stores before them (60 instructions, us per
+  // call without / with this: 8 samples 11.2 / 11.2, 64 15.8 / 15.8, 4,000 19.1 / 20.1; by each group's own: 11.4, 16.4, 20.5).
+  if (blockIdx.x < n_groups) {
+    const DevJob C = kOne ? one : jobs[find_job(jobs, n_jobs, blockIdx.x, &DevJob::group_base)];
+    const uint32_t g = blockIdx.x - C.group_base, n = g + 1 == C.n_groups ? C.K - g * C.rows : C.rows;
     auto clear = [](uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    if (tid < nrows) clear(board.keys + J.row_base + row0 + tid);
-    if (tid == 64) clear(board.arrived + J.group_base + group);
-    if (tid == 65 && global_group == 0 && finished) clear(finished);
+    if (tid < n) clear(board.keys + C.row_base + g * C.rows + tid);
+    if (tid == 64) clear(board.arrived + blockIdx.x);
+    if (tid == 65 && blockIdx.x == 0) clear(board.arrived - kHeadWords);   // the counter of the stream's reductions
   }
   const uint64_t failed = __ballot(lane < nrows && status == VL_STATUS_SAFETY);
   uint32_t rank = 0;
@@ -940,7 +951,6 @@ struct Slot {
   uint64_t tick = 0;
 };
 constexpr int kSlots = 4;
-constexpr uint32_t kHeadWords = 64;   // of a board: the first is Launch::finished, then Board::arrived, Board::keys
 constexpr uint64_t kResolveGroups = 4096;   // workgroups that share out the clashes to resolve, about
 struct Scratch {
   std::mutex mu;
@@ -1019,9 +1029,8 @@ int32_t fill_job(const vl_job &u, bool transposed, DevJob &d, Launch &out, uint3
   out.groups += d.n_groups;
   d.span = std::min(span, u.live->span);
   d.n_spans = (u.live->h.T + d.span - 1) / d.span;
-  d.n_units = d.n_groups * d.n_spans;
   out.most_span = std::max(out.most_span, u.live->span);
-  out.units += d.n_units;
+  out.units += d.n_groups * d.n_spans;
   out.maxK = std::max(out.maxK, u.K);
   out.total_rows += u.K;
   out.max_rows = std::max(out.max_rows, std::max(d.rows, last));
@@ -1296,7 +1305,7 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   VL_HIP(hipGetLastError());
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
   (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
-      L.dev, n_jobs, L.one, per_group, L.board, L.finished);
+      L.dev, n_jobs, L.one, per_group, (uint32_t)L.groups, L.board);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
@@ -1345,6 +1354,7 @@ extern "C" int32_t vl_verify_batch(const vl_mir *mir, const vl_live *live, const
 namespace {
 constexpr uint32_t kStaticMaxK = VL_STATIC_MAX_K;
 struct StaticScratch {   // zero at load time, and between calls
+  uint32_t head[kHeadWords];
   uint32_t arrived[kStaticMaxK];   // (a group may be a single row)
   uint32_t keys[kStaticMaxK];
 };
