@@ -285,7 +285,9 @@ int32_t vl_summarize_multi(const vl_job *jobs, uint32_t n_jobs, vl_summary *summ
  * vl_mir handle; later calls are asynchronous on `stream` (rows are read
  * as vl_verify_batch reads them; the library has four
  * workspaces per device, used in turn: a call waits on the host until the kernels of the fourth
- * last call have finished with theirs).
+ * last call have finished with theirs, and its memory, 20 bytes per sample and what lists the
+ * failed ones, and for a program of more than 38,912 vregs 2 KB per vreg, grows on demand and
+ * is kept).
  * Errors: VL_E_NULL, VL_E_ARG (handles of different programs), VL_E_SHAPE (n_jobs == 0 or
  * above 65535, K == 0 or above 65535, ld < n_occ); nothing is launched on error. */
 typedef struct { uint32_t kinds, n_cons, n_real, n_safe, real_bits, reserved[3]; } vl_counts;

@@ -156,9 +156,7 @@ struct DevLive {
   uint8_t VL_GLOBAL *ent_sf;      // [O] where membership changes in the stretch, for the interval filling pass
   uint32_t VL_GLOBAL *hull;       // [V][2]
   uint32_t VL_GLOBAL *seed_off;   // [T+1]
-  uint32_t VL_GLOBAL *seed_cur;   // [T]
   uint32_t VL_GLOBAL *long_queue; // [V] vregs whose occurrence list needs the bitmap sort
-  uint32_t VL_GLOBAL *bitmap;     // [ceil(O/32)] scratch for the bitmap sort, one list at a time per block
   uint32_t VL_GLOBAL *counters;   // [kCounters]
   // --- sized after the counting pass ---
   u32x4 VL_GLOBAL *plan;          // [plan_len + 8] occupancy events (the last 8 are padding, never applied)

@@ -1896,8 +1896,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
 
   // ---- arena 1 layout: [zeroed zone | counters | rest | device tables] ----
   std::vector<DevLive> h(n);
-  struct Off1 { size_t last_live, vcnt, vcur, use, def, in, seed_off, seed_cur, out, tmp, vocc, ent, ent_info, first, prev,
-                role, kill, item, seg_off, hull, queue, bitmap, ent_seg, ent_sf, chk, evt_cut, tile_live, seg_base, item_base, bound_off; };
+  struct Off1 { size_t last_live, vcnt, vcur, use, def, in, seed_off, out, tmp, vocc, ent, ent_info, first, prev,
+                role, kill, item, seg_off, hull, queue, ent_seg, ent_sf, chk, evt_cut, tile_live, seg_base, item_base, bound_off; };
   std::vector<Off1> off(n);
   Bump bump;
   uint32_t maxO = 1, maxV = 1, maxN = 1, maxB = 1, maxW = 1, maxT = 1, maxE = 0;
@@ -1911,8 +1911,8 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     off[k].vcur = bump.take((size_t)(m.V + 1) * 4);
     off[k].last_live = bump.take((size_t)(m.V + 1) * 4);
     off[k].use = bump.take(bw); off[k].def = bump.take(bw); off[k].in = bump.take(bw);
-    off[k].seed_off = bump.take((size_t)(T + 1) * 4); off[k].seed_cur = bump.take((size_t)(T + 1) * 4);
-    off[k].item = bump.take((size_t)(m.N + m.B + 1) * 4);   // event counts are accumulated with atomics
+    off[k].seed_off = bump.take((size_t)(T + 1) * 4);
+    off[k].item = bump.take((size_t)(m.N + m.B + 1) * 4);
     maxO = std::max(maxO, m.O); maxV = std::max(maxV, m.V); maxN = std::max(maxN, m.N);
     maxB = std::max(maxB, m.B); maxW = std::max(maxW, m.W); maxT = std::max(maxT, T); maxE = std::max(maxE, m.E);
   }
@@ -1935,7 +1935,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     off[k].seg_base = bump.take(((size_t)stretches(m.O) + 1) * 4);
     off[k].item_base = bump.take(((size_t)stretches(m.N) + 1) * 4);
     off[k].bound_off = bump.take(((size_t)m.B + 1) * 4);
-    off[k].bitmap = 0;
   }
   const size_t o_mirs = bump.take((size_t)n * sizeof(DevMir *));
   const size_t o_lives = bump.take((size_t)n * sizeof(DevLive));
@@ -1953,7 +1952,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.last_live = (uint32_t VL_GLOBAL *)(a1 + off[k].last_live);
     L.use = (uint32_t VL_GLOBAL *)(a1 + off[k].use); L.def = (uint32_t VL_GLOBAL *)(a1 + off[k].def);
     L.live_in = (uint32_t VL_GLOBAL *)(a1 + off[k].in); L.live_out = (uint32_t VL_GLOBAL *)(a1 + off[k].out);
-    L.seed_off = (uint32_t VL_GLOBAL *)(a1 + off[k].seed_off); L.seed_cur = (uint32_t VL_GLOBAL *)(a1 + off[k].seed_cur);
+    L.seed_off = (uint32_t VL_GLOBAL *)(a1 + off[k].seed_off);
     L.vocc_tmp = (uint32_t VL_GLOBAL *)(a1 + off[k].tmp); L.vocc = (uint32_t VL_GLOBAL *)(a1 + off[k].vocc);
     L.ent = (u32x4 VL_GLOBAL *)(a1 + off[k].ent); L.ent_info = (uint8_t VL_GLOBAL *)(a1 + off[k].ent_info);
     L.first = (uint32_t VL_GLOBAL *)(a1 + off[k].first); L.prev_occ = (uint32_t VL_GLOBAL *)(a1 + off[k].prev);
@@ -1965,7 +1964,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.chk = (u32x4 VL_GLOBAL *)(a1 + off[k].chk); L.tile_live = (uint32_t VL_GLOBAL *)(a1 + off[k].tile_live); L.evt_cut = (uint32_t VL_GLOBAL *)(a1 + off[k].evt_cut);
     L.seg_base = (uint32_t VL_GLOBAL *)(a1 + off[k].seg_base); L.item_base = (uint32_t VL_GLOBAL *)(a1 + off[k].item_base);
     L.bound_off = (uint32_t VL_GLOBAL *)(a1 + off[k].bound_off);
-    L.bitmap = (uint32_t VL_GLOBAL *)nullptr;
     L.counters = (uint32_t VL_GLOBAL *)(a1 + o_counters) + (size_t)k * kCounters;
     mir_ptrs[k] = mirs[k]->dev;
   }

@@ -319,8 +319,7 @@ __device__ inline bool unrealizable(const DevMir VL_GLOBAL &m, uint32_t attr, ui
   return bad;
 }
 
-// Turns the winning key of a candidate row (one per lane, `in` for the lanes that have one) into
-// its result record.  Safety results get their pair from k_resolve.
+// Turns the winning key of a candidate row (one per lane) into its result record.  Safety results get their pair from k_resolve.
 __device__ inline void finish_row(const DevJob &J, uint32_t k, uint32_t key) {
   const DevMir VL_GLOBAL &m = *as_global(J.mir);
   const DevLive VL_GLOBAL &L = *as_global(J.live);
@@ -364,7 +363,6 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
   const auto g_occ_off = m.occ_off, g_occ_instr = m.occ_instr;
   const auto g_prev_occ = L.prev_occ, g_evt_cut = L.evt_cut;
   const auto g_seed_off = L.seed_off, g_tile_range = L.tile_range;
-  // 8-byte stream entries are read as one 64-bit word: x in the low half, y in the high half
   const u32x4 VL_GLOBAL *g_chk = L.chk, *g_seeds = L.seeds;
   const u32x4 VL_GLOBAL *g_plan = L.plan;
   const uint32_t local = unit - J.unit_base;
