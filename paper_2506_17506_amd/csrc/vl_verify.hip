@@ -858,15 +858,15 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
   // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
   const uint32_t status = out[min(lane, nrows - 1u)].status;
-  // The board of a group, by the workgroups that start first, since the launch ends with its last store, and
-  // behind the read above, since reads wait for the stores before them (60 instructions, us per
-  // call without / with this: 8 samples 11.2 / 11.2, 64 15.8 / 15.8, 4,000 19.1 / 20.1; by each group's own: 11.4, 16.4, 20.5).
-  if (blockIdx.x < n_groups) {
-    const DevJob C = kOne ? one : jobs[find_job(jobs, n_jobs, blockIdx.x, &DevJob::group_base)];
-    const uint32_t g = blockIdx.x - C.group_base, n = g + 1 == C.n_groups ? C.K - g * C.rows : C.rows;
+  // The board of a group, behind the read above, since reads wait for the stores before them.  One job: by the
+  // workgroups that start first, since the launch ends with its last store (60 instructions, us per call without /
+  // with this: 8 samples 11.2 / 11.2, 64 15.8 / 15.8, 4,000 19.1 / 20.1; by each group's own: 11.4, 16.4, 20.5).
+  // Several: by each group's first, which has found its job already.
+  if (kOne ? blockIdx.x < n_groups : mine_first == 0) {
+    const uint32_t g = kOne ? blockIdx.x : group, n = g + 1 == J.n_groups ? J.K - g * J.rows : J.rows;
     auto clear = [](uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    if (tid < n) clear(board.keys + C.row_base + g * C.rows + tid);
-    if (tid == 64) clear(board.arrived + blockIdx.x);
+    if (tid < n) clear(board.keys + J.row_base + g * J.rows + tid);
+    if (tid == 64) clear(board.arrived + J.group_base + g);
     if (tid == 65 && blockIdx.x == 0) clear(board.arrived - kHeadWords);   // the counter of the stream's reductions
   }
   const uint64_t failed = __ballot(lane < nrows && status == VL_STATUS_SAFETY);
