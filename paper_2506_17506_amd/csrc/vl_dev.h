@@ -303,6 +303,7 @@ struct WalkSpace {
   uint32_t cap = 0, n_valid = 0;
   uint32_t *board = nullptr;                 // zero between calls
   uint64_t groups_cap = 0, rows_cap = 0;     // what the board has room for
+  bool recorded = false;                     // a pass with this memory was recorded in a stream capture, and may be replayed at any time
 };
 // vl_verify_multi without the search for the pair of a safety violation (vl_verify.hip)
 int32_t verdicts_only(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, WalkSpace &space);

@@ -69,10 +69,11 @@ constexpr uint32_t kKeyOk = 0xFFFFFFFFu;
 constexpr uint32_t kKeyCons = 0u << 28, kKeyReal = 1u << 28, kKeySafe = 2u << 28, kKeyPos = (1u << 28) - 1;
 
 // What the workgroups of one verification share.  Everything is zero before the walk and left
-// zero by it, so that no launch is needed to clear it.  The pair search, which follows every walk but
-// those of the all-violations mode, writes the zeros again: calls that overlapped against the rules (their counts mixed)
-// spoil each other, and without it every later call too.  Of such calls, the one whose walk ends last clears
-// what it has in common with the others after all of them.
+// zero by it, so that no launch is needed to clear it.  Calls that overlap on one board against the rules (their
+// counts mix) spoil each other, and what they leave would spoil every later call too.  So where a board can be
+// shared at all (WalkSpace::recorded, and the entry point that allocates nothing) the pair search, which follows the
+// walk, writes the zeros again: of calls that overlapped, the one whose walk ends last clears what it has in
+// common with the others after all of them.
 constexpr uint32_t kHeadWords = 64;   // in front of Board::arrived; the first is Launch::finished
 struct Board {
   uint32_t *arrived;   // per group of candidate rows: tiles that have reported
@@ -842,10 +843,10 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
 // vregs instead of registers (flip_members_of_p); its members, some tens, are then listed so that
 // each gets a lane (a lane per vreg of the program took most of the kernel's time: 15,000 vregs
 // are 117 turns of 128 threads).  The workgroups of a group of rows share out the rows that
-// failed on safety; the first workgroups of the launch leave the board zero (Board).
+// failed on safety.  kShared: it leaves the board zero (Board).
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
 constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
-template <bool kOne>
+template <bool kOne, bool kShared>
 __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group, uint32_t n_groups,
                                                              const Board board) {
   extern __shared__ uint32_t in_p[];   // [W]
@@ -859,10 +860,10 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
   // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
   const uint32_t status = out[min(lane, nrows - 1u)].status;
   // The board of a group, behind the read above, since reads wait for the stores before them.  One job: by the
-  // workgroups that start first, since the launch ends with its last store (60 instructions, us per call without /
-  // with this: 8 samples 11.2 / 11.2, 64 15.8 / 15.8, 4,000 19.1 / 20.1; by each group's own: 11.4, 16.4, 20.5).
-  // Several: by each group's first, which has found its job already.
-  if (kOne ? blockIdx.x < n_groups : mine_first == 0) {
+  // workgroups that start first, since the launch ends with its last store.  Several: by each group's first.
+  // (60 instructions x 8, 64 and 4,000 samples, us per call without / with: 11.2 / 11.4, 15.8 / 16.1, 19.1 / 20.1;
+  // 256 programs x 100: 29.2 us for the launch, 33.6 with.)
+  if (kShared && (kOne ? blockIdx.x < n_groups : mine_first == 0)) {
     const uint32_t g = kOne ? blockIdx.x : group, n = g + 1 == J.n_groups ? J.K - g * J.rows : J.rows;
     auto clear = [](uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     if (tid < n) clear(board.keys + J.row_base + g * J.rows + tid);
@@ -877,7 +878,7 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
     const DevMir VL_GLOBAL &m = *as_global(J.mir);
     const DevLive VL_GLOBAL &L = *as_global(J.live);
     const uint32_t i = out[k - row0].where;
-    if (i >= m.N) continue;   // (not a result of this call: calls overlapped against the rules)
+    if (kShared && i >= m.N) continue;   // (not a result of this call: calls overlapped against the rules)
     for (uint32_t x = tid; x < m.W; x += kResolveThreads) in_p[x] = 0;
     // the vregs the instruction writes (each once) and their registers: one operand per lane
     const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo;
@@ -973,6 +974,7 @@ struct Launch {
   DevJob *dev = nullptr;   // the job table on the device; a single job travels as an argument instead
   DevJob one = {};
   Board board = {};
+  bool shared = false;     // other calls may find the board in use, against the rules
   uint32_t *finished = nullptr;   // counter of the stream's reductions, zero between calls
   uint64_t total_rows = 0, groups = 0;
   uint32_t most_span = 1;         // of the analyses
@@ -1076,6 +1078,12 @@ int32_t space_of(Scratch &sc, hipStream_t stream, WalkSpace *&out) {
     VL_HIP(hipDeviceSynchronize());
     found->space.n_valid = 0;
   }
+  // a recorded pass keeps the memory of its stream; threads that each pass their own default stream share one place
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (!found->space.recorded) {
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();   // (the null stream, while another is recorded)
+    found->space.recorded = capture != hipStreamCaptureStatusNone || stream == hipStreamPerThread;
+  }
   found->used = true;
   found->stream = stream;
   found->tick = ++sc.clock;
@@ -1155,6 +1163,7 @@ int32_t prepare_jobs(const vl_job *jobs, uint32_t n_jobs, hipStream_t stream, Wa
   out.dev = s.dev;
   out.finished = s.board;
   out.board = Board{s.board + kHeadWords, s.board + kHeadWords + s.groups_cap};
+  out.shared = s.recorded;
   return VL_OK;
 }
 
@@ -1302,8 +1311,8 @@ int32_t launch_all(const Launch &L, uint32_t n_jobs, hipStream_t stream, bool tr
   g_time_start = g_time_stop = nullptr;
   VL_HIP(hipGetLastError());
   const uint32_t per_group = (uint32_t)std::min<uint64_t>(L.max_rows, std::max<uint64_t>(1, kResolveGroups / L.groups));
-  (n_jobs == 1 ? k_resolve<true> : k_resolve<false>)<<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(
-      L.dev, n_jobs, L.one, per_group, (uint32_t)L.groups, L.board);
+  (n_jobs == 1 ? L.shared ? k_resolve<true, true> : k_resolve<true, false> : L.shared ? k_resolve<false, true> : k_resolve<false, false>)
+      <<<(uint32_t)L.groups * per_group, kResolveThreads, (size_t)L.max_w * 4, stream>>>(L.dev, n_jobs, L.one, per_group, (uint32_t)L.groups, L.board);
   VL_HIP(hipGetLastError());
   return VL_OK;
 }
@@ -1388,5 +1397,6 @@ extern "C" int32_t vl_verify_batch_static(const vl_mir *mir, const vl_live *live
   }
   L.one = d;
   L.board = Board{sc->arrived, sc->keys};
+  L.shared = true;
   return launch_all(L, 1, stream, false, true);
 }

@@ -77,6 +77,9 @@ int hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; *p = calloc
 int hipHostFree(void *p) { free(p); return 0; }
 int hipMemcpyAsync(void *to, const void *from, size_t n, int kind, void *stream) { (void)stream; g_uploads += kind == 1; memcpy(to, from, n); return 0; }
 int hipStreamSynchronize(void *s) { (void)s; ++g_stream_syncs; return 0; }
+static void *g_recorded;
+void stand_in_record(void *stream) { g_recorded = stream; }   /* the stream that is being recorded, or null */
+int hipStreamIsCapturing(void *stream, int *status) { *status = stream && stream == g_recorded; return 0; }
 int hipDeviceSynchronize(void) { ++g_device_syncs; return 0; }
 int hipEventCreateWithFlags(void **e, unsigned flags) { (void)flags; *e = malloc(1); return 0; }
 int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }

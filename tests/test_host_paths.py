@@ -183,3 +183,33 @@ def test_block_sets_beyond_32_bit_indices(s):
         assert any("k_group" in x for x in names) == by_group and any("k_zero" in x for x in names) != by_group
         s.vl.vl_live_destroy(hl[0])
         s.vl.vl_mir_destroy(hm)
+
+
+@in_own_process
+def test_boards_that_may_be_shared_are_left_zero(s):
+    """the pair search writes the board's zeros for the entry point that allocates nothing, and for a stream's
+    calls from the first that is recorded on: a pass of verification, or of reductions alone"""
+    hm, hl = analysed(s, 2)
+    jobs, keep = jobs_of(s, hm, hl, 8)
+    arr, one = s.vl.make_jobs(jobs), s.vl.make_jobs(jobs[:1])
+    sums, stats = Buffer(48), Buffer(48)
+    s.lib.stand_in_record.argtypes = [C.c_void_p]
+
+    def clears(call):
+        s.launches.clear()
+        call()
+        (name,) = [x[0] for x in s.launches if "k_resolve" in x[0]]
+        return "ELb1E" in name
+
+    def verify(jobs_, stream):
+        return clears(lambda: s.vl.vl_verify_multi(jobs_, stream=stream))
+    m, l, cand, K, ld, out = jobs[0]
+    assert clears(lambda: s.vl.vl_verify_batch_static(m, l, cand, K, ld, out, stream=S1))
+    assert not verify(arr, S1) and not verify(one, S1) and not verify(arr, S1 + 1)
+    s.lib.stand_in_record(S1)
+    assert verify(arr, S1) and not verify(arr, S1 + 1)
+    s.lib.stand_in_record(S1 + 1)
+    s.vl.vl_summarize_multi(arr, sums, stats, stream=S1 + 1)
+    s.lib.stand_in_record(None)
+    assert verify(arr, S1) and verify(one, S1) and verify(arr, S1 + 1)
+    assert verify(arr, 2) and not verify(arr, S1 + 2)   # 2: the thread's default stream
