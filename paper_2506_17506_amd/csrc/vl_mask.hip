@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
 // Runs of a query or two, a workgroup each: nothing to share out, so two wavefronts do everything
 // together.  The members of P(i) are first listed, which takes no reads from memory, and then looked up a lane
 // each.  (us per call, a workgroup of four wavefronts for each of them / this: 1,000 scattered queries of a program of
-// 8,000 instructions 31 / 25, 4,000 42 / 30, 16,000 121 / 53; of first mentions 31 / 25, 55 / 32, 153 / 66;
+// 8,000 instructions 31 / 25, 4,000 42 / 30, 16,000 121 / 56; of first mentions 31 / 25, 55 / 32, 153 / 66;
 // 29, 35, 63 and 30, 38, 81 with a workgroup of two that looked every vreg up.)
 constexpr uint32_t kAloneThreads = 128, kAloneMembers = 512;   // (members that are listed; with more, every vreg gets a turn)
 __global__ __launch_bounds__(kAloneThreads) void k_free_bases_alone(const Run *__restrict__ runs, uint32_t *__restrict__ masks) {
@@ -196,12 +196,12 @@ __global__ __launch_bounds__(kAloneThreads) void k_free_bases_alone(const Run *_
 
 // tables of runs on the device, one set per device, for calls with more runs than fit the kernel's
 // argument; used in turn, so that a call waits only for the one kTables calls ago
-constexpr uint32_t kTables = 4;
+constexpr uint32_t kTables = 4, kLeastRuns = 4096;
 struct Tables {
   std::mutex mu;
   struct One {
     Run *dev = nullptr, *host = nullptr;   // host: pinned
-    uint32_t cap = 0;
+    uint32_t cap = 0, dev_cap = 0;         // runs there is room for in host, in dev
     hipEvent_t consumed = nullptr;         // recorded after the kernel that reads the table
     bool in_flight = false;
   } one[kTables];
@@ -217,35 +217,51 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
   uint32_t max_w = 1;
   // neighbouring queries of one program at one occurrence whose rows lie at equal distances are one run
   RunArgs args;
-  Run *runs = args.run;
-  uint32_t n_runs = 0;
-  // the first run too many for the argument takes a table, and the runs are put together there
   std::unique_lock<std::mutex> lock;
   Tables::One *t = nullptr;
-  auto take_table = [&]() -> int32_t {
-    int device = 0;
-    VL_HIP(hipGetDevice(&device));
-    if (device < 0 || device >= 16) return VL_E_ARG;
-    Tables &all = g_tables[device];
-    lock = std::unique_lock<std::mutex>(all.mu);
-    t = &all.one[all.turn = (all.turn + 1) % kTables];
-    // the kernel that last read this table must be done with it before it is overwritten
-    if (t->in_flight) VL_HIP(hipEventSynchronize(t->consumed));
-    t->in_flight = false;
-    if (t->cap < n) {
-      if (t->dev) (void)hipFree(t->dev);
-      if (t->host) (void)hipHostFree(t->host);
-      t->dev = nullptr; t->host = nullptr; t->cap = 0;
-      const uint32_t cap = std::max(1024u, n);
-      VL_HIP(device_alloc((void **)&t->dev, (size_t)cap * sizeof(Run)));
-      VL_HIP(hipHostMalloc((void **)&t->host, (size_t)cap * sizeof(Run), hipHostMallocDefault));
-      if (!t->consumed) VL_HIP(hipEventCreateWithFlags(&t->consumed, hipEventDisableTiming));
-      t->cap = cap;
-    }
-    memcpy(t->host, args.run, sizeof(args.run));
-    runs = t->host;
-    return VL_OK;
+  // Room for more runs than there is now: the first too many for the argument takes a table, which grows with the
+  // runs, not with the queries, and the runs are put together there.  (Handed back by value: what the loop below
+  // works with stays in registers.)
+  struct Room {
+    Run *runs;
+    uint32_t most;
+    int32_t rc;
   };
+  auto more_room = [&]() -> Room {
+    auto fail = [](int32_t rc) { return Room{nullptr, 0, rc}; };
+    if (!t) {
+      int device = 0;
+      hipError_t e = hipGetDevice(&device);
+      if (e != hipSuccess) return fail(hip_fail(e));
+      if (device < 0 || device >= 16) return fail(VL_E_ARG);
+      Tables &all = g_tables[device];
+      lock = std::unique_lock<std::mutex>(all.mu);
+      t = &all.one[all.turn = (all.turn + 1) % kTables];
+      // the kernel that last read this table must be done with it before it is overwritten
+      if (t->in_flight) e = hipEventSynchronize(t->consumed);
+      if (e != hipSuccess) return fail(hip_fail(e));
+      t->in_flight = false;
+      if (!t->host) {
+        e = hipHostMalloc((void **)&t->host, (size_t)kLeastRuns * sizeof(Run), hipHostMallocDefault);
+        if (e != hipSuccess) return fail(hip_fail(e));
+        t->cap = kLeastRuns;
+      }
+      if (!t->consumed) e = hipEventCreateWithFlags(&t->consumed, hipEventDisableTiming);
+      if (e != hipSuccess) return fail(hip_fail(e));
+      memcpy(t->host, args.run, sizeof(args.run));
+      return Room{t->host, t->cap, VL_OK};
+    }
+    Run *larger = nullptr;
+    const hipError_t e = hipHostMalloc((void **)&larger, (size_t)t->cap * 4 * sizeof(Run), hipHostMallocDefault);
+    if (e != hipSuccess) return fail(hip_fail(e));
+    memcpy(larger, t->host, (size_t)t->cap * sizeof(Run));
+    (void)hipHostFree(t->host);
+    t->host = larger;
+    t->cap *= 4;
+    return Room{t->host, t->cap, VL_OK};
+  };
+  Run *runs = args.run;
+  uint32_t n_runs = 0, most_runs = kArgRuns;
   // a workgroup per four queries (one per wavefront) up to a thousand workgroups, then longer shares
   const uint32_t per_block = kMaskWaves * std::max(1u, std::min(16u, n / (kMaskWaves * 1024u)));
   uint32_t blocks = 0;
@@ -273,18 +289,21 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
       }
     }
     if (run.count) {   // the run before is complete
-      if (n_runs == kArgRuns) {
-        const int32_t rc = take_table();
-        if (rc != VL_OK) return rc;
+      if (n_runs == most_runs) {
+        const Room more = more_room();
+        if (more.rc != VL_OK) return more.rc;
+        runs = more.runs;
+        most_runs = more.most;
       }
       runs[n_runs++] = run;
       blocks += run.count <= per_block ? 1u : (run.count + per_block - 1) / per_block;
     }
     run = Run{mir->dev, live->dev, u.cand, 0, u.occ, 1, j, blocks};
   }
-  if (n_runs == kArgRuns) {
-    const int32_t rc = take_table();
-    if (rc != VL_OK) return rc;
+  if (n_runs == most_runs) {
+    const Room more = more_room();
+    if (more.rc != VL_OK) return more.rc;
+    runs = more.runs;
   }
   runs[n_runs++] = run;
   blocks += run.count <= per_block ? 1u : (run.count + per_block - 1) / per_block;
@@ -294,6 +313,12 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
     k_free_bases<true><<<blocks, kMaskThreads, lds, stream>>>(args, n_runs, per_block, masks);
     VL_HIP(hipGetLastError());
     return VL_OK;
+  }
+  if (t->dev_cap < n_runs) {
+    if (t->dev) (void)hipFree(t->dev);
+    t->dev = nullptr; t->dev_cap = 0;
+    VL_HIP(device_alloc((void **)&t->dev, (size_t)t->cap * sizeof(Run)));
+    t->dev_cap = t->cap;
   }
   VL_HIP(hipMemcpyAsync(t->dev, t->host, (size_t)n_runs * sizeof(Run), hipMemcpyHostToDevice, stream));
   if (blocks == n_runs && n <= 2ull * n_runs) k_free_bases_alone<<<blocks, kAloneThreads, lds, stream>>>(t->dev, masks);

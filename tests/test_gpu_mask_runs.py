@@ -126,3 +126,26 @@ def test_queries_that_stand_alone(n_live, together):
         assert (masks.cpu().numpy().view(np.uint32) == want).all()
     finally:
         free(hm, hl)
+
+
+def test_more_runs_than_the_table_starts_with():
+    """70,000 queries in no order, over and over from a few dozen different ones"""
+    m = mixed_mir(0xA203, n_instr=200, reserved=True)
+    rng = np.random.default_rng(8)
+    rows = rng.integers(0, 48, (6, m.n_occ)).astype(np.uint16)
+    an = vlo.analyze(m, interference=False, threads=8)
+    pairs = [(int(rng.integers(6)), int(o)) for o in rng.integers(0, m.n_occ, 60)]
+    want = np.stack([vlo.free_bases(m, an, rows[k], o) for k, o in pairs])
+    which = rng.integers(0, len(pairs), 70000)
+    hm, hl, _, _ = gpu_analyze([m], dense=False)
+    try:
+        dev, ld = vl.rows_to_device(rows)
+        at = [dev[k] for k in range(6)]
+        queries = vl.make_mask_queries([(hm[0], hl[0], at[pairs[w][0]], pairs[w][1]) for w in which])
+        for _ in range(2):
+            masks = torch.full((len(which), 16), -1, dtype=torch.int32, device="cuda")
+            vl.vl_free_bases_multi(queries, masks)
+            torch.cuda.synchronize()
+            assert (masks.cpu().numpy().view(np.uint32) == want[which]).all()
+    finally:
+        free(hm, hl)

@@ -213,3 +213,27 @@ def test_boards_that_may_be_shared_are_left_zero(s):
     s.lib.stand_in_record(None)
     assert verify(arr, S1) and verify(one, S1) and verify(arr, S1 + 1)
     assert verify(arr, 2) and not verify(arr, S1 + 2)   # 2: the thread's default stream
+
+
+@in_own_process
+def test_tables_of_runs_grow_with_the_runs(s):
+    """many queries that fold into few runs take little memory, many that do not fold find room"""
+    hm, hl = analysed(s, 2)
+    rows, masks = Buffer(1 << 20), Buffer(64)
+    base = rows.data_ptr()
+
+    def query(occs):
+        q = s.vl.make_mask_queries([(hm[0], hl[0], base + 128 * (j % 1000), int(o)) for j, o in enumerate(occs)])
+        s.launches.clear()
+        s.vl.vl_free_bases_multi(q, masks, stream=S1)
+        (launch,) = [x for x in s.launches if "k_free_bases" in x[0]]
+        return launch
+    before = s.counts()["largest"]
+    for _ in range(4):
+        query(np.repeat(np.arange(100) % 8, 1000))   # 100 runs of 1,000
+    assert s.counts()["largest"] <= max(before, 4096 * 48)
+    for n in (4096, 4097, 20000):
+        for _ in range(4):
+            launch = query(np.arange(n) % 8)
+            assert "alone" in launch[0] and launch[1][0] == n
+    assert s.counts()["largest"] <= 65536 * 48
