@@ -840,25 +840,31 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
 // with overlapping ranges.  At the first clashing instruction every clashing pair contains a
 // vreg that the instruction defines, so only pairs (definition, anything in P(i)) are
 // examined.  P(i) is rebuilt as a bitset in LDS the way the walk builds occupancy, but over
-// vregs instead of registers (flip_members_of_p); its members, some tens, are then listed so that
-// each gets a lane (a lane per vreg of the program took most of the kernel's time: 15,000 vregs
-// are 117 turns of 128 threads).  The workgroups of a group of rows share out the rows that
+// vregs instead of registers: the live-in list of i's tile, then every event up to those of i, flips one
+// bit each; the releases of values dead once i has executed are left out.  Every member has a record among these, which
+// names an occurrence of it, its width and its class; a candidate that got this far is consistent, so that
+// occurrence's register is the value's.  Records stay in registers between the flips and the comparison.
+// What bounds it is the chain of reads: result, offsets of i, events of i and its operands, records, registers.
+// (A list of members, with first occurrence, attributes and register of each looked up one after the other, and the
+// definitions' attributes read at every comparison, took three trips to memory more.)
+// The workgroups of a group of rows share out the rows that
 // failed on safety.  kShared: it leaves the board zero (Board).
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
-constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
 template <bool kOne, bool kShared>
 __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group, uint32_t n_groups,
                                                              const Board board) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
-  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], nd, members[kResolveMembers], n_members;
+  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], da[kMaxOperands], nd;
   const uint32_t global_group = blockIdx.x / per_group, mine_first = blockIdx.x % per_group;
   const DevJob J = kOne ? one : jobs[find_job(jobs, n_jobs, global_group, &DevJob::group_base)];
   const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
   const uint32_t nrows = group + 1 == J.n_groups ? J.K - row0 : J.rows, lane = tid & 63u;
   vl_result VL_GLOBAL *const out = as_global_rw(J.out) + row0;
+  const DevMir VL_GLOBAL &m = *as_global(J.mir);
+  const DevLive VL_GLOBAL &L = *as_global(J.live);
   // this workgroup's share of the group's rows (at most 64) that failed on safety, by rank
-  const uint32_t status = out[min(lane, nrows - 1u)].status;
+  const uint32_t my_row = min(lane, nrows - 1u), status = out[my_row].status, where = out[my_row].where;
   // The board of a group, behind the read above, since reads wait for the stores before them.  One job: by the
   // workgroups that start first, since the launch ends with its last store.  Several: by each group's first.
   // (60 instructions x 8, 64 and 4,000 samples, us per call without / with: 11.2 / 11.4, 15.8 / 16.1, 19.1 / 20.1;
@@ -870,71 +876,107 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
     if (tid == 64) clear(board.arrived + J.group_base + g);
     if (tid == 65 && blockIdx.x == 0) clear(board.arrived - kHeadWords);   // the counter of the stream's reductions
   }
-  const uint64_t failed = __ballot(lane < nrows && status == VL_STATUS_SAFETY);
-  uint32_t rank = 0;
-  for (uint64_t todo = failed; todo; todo &= todo - 1, ++rank) {
-    if (rank % per_group != mine_first) continue;
-    const uint32_t k = row0 + (uint32_t)__builtin_ctzll(todo);
-    const DevMir VL_GLOBAL &m = *as_global(J.mir);
-    const DevLive VL_GLOBAL &L = *as_global(J.live);
-    const uint32_t i = out[k - row0].where;
+  uint64_t todo = __ballot(lane < nrows && status == VL_STATUS_SAFETY);
+  for (uint32_t x = 0; x < mine_first; ++x) todo &= todo - 1;   // (zero stays zero)
+  while (todo) {
+    const uint32_t row = (uint32_t)__builtin_ctzll(todo), k = row0 + row, i = __builtin_amdgcn_readlane(where, row);
+    for (uint32_t x = 0; x < per_group && todo; ++x) todo &= todo - 1;
     if (kShared && i >= m.N) continue;   // (not a result of this call: calls overlapped against the rules)
+    const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo, item = i + m.instr_blk[i] + 1, tile = i / L.tile_len;
+    const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first, e_first = L.tile_range[2 * tile];
     for (uint32_t x = tid; x < m.W; x += kResolveThreads) in_p[x] = 0;
-    // the vregs the instruction writes (each once) and their registers: one operand per lane
-    const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo;
-    if (tid < 64) {
-      const uint32_t my_v = tid < n_ops && (m.occ_flags[o_lo + tid] & VL_OCC_DEF) ? m.occ_vreg[o_lo + tid] : kNone;
-      bool seen = my_v == kNone;
-      for (uint32_t t = 0; t < n_ops; ++t) {
-        const uint32_t other = __builtin_amdgcn_readlane(my_v, t);   // (every lane takes part)
-        seen |= (t < tid) & (other == my_v);
-      }
-      const uint64_t fresh = __ballot(!seen);
-      if (!seen) {
-        const uint32_t slot = (uint32_t)__popcll(fresh & ((1ull << tid) - 1ull));
-        dv[slot] = my_v;
-        dp[slot] = cand_at(J, k, L.first[my_v]);
-      }
-      if (tid == 0) { best = ~0ull; nd = (uint32_t)__popcll(fresh); n_members = 0; }
+    const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1];   // (boundary items come before their block's instructions)
+    // the vregs the instruction writes and their registers: one operand per lane
+    uint32_t my_v = kNone, my_p = 0;
+    if (tid < n_ops) {
+      const uint32_t flags = m.occ_flags[o_lo + tid], v = m.occ_vreg[o_lo + tid];
+      my_p = cand_at(J, k, o_lo + tid);
+      if (flags & VL_OCC_DEF) my_v = v;
     }
+    constexpr uint32_t kSeeds = 1, kEvents = 3;   // records that a thread keeps (256 programs x 100: 27 us with three or four, 34 with eight and the registers that takes)
+    u32x4 rec[kSeeds + kEvents];
+#pragma unroll
+    for (uint32_t u = 0; u < kSeeds; ++u) {
+      const uint32_t e = s_first + tid + u * kResolveThreads;
+      rec[u] = 0;
+      if (e < s_end) rec[u] = L.seeds[e];
+    }
+    auto counts = [&](uint32_t e, const u32x4 r) { return e < e_own || (e < e_end && !(r.w & kEvtPost)); };
+#pragma unroll
+    for (uint32_t u = 0; u < kEvents; ++u) {
+      const uint32_t e = e_first + tid + u * kResolveThreads;
+      rec[kSeeds + u] = 0;
+      if (e < e_end) rec[kSeeds + u] = L.plan[e];
+      if (!counts(e, rec[kSeeds + u])) rec[kSeeds + u] = 0;   // (a record that stands for something has a tuple mask)
+    }
+    if (tid < kMaxOperands) {   // one wavefront
+      const uint32_t attr = my_v != kNone ? m.vattr[my_v] : 0u;
+      const uint64_t defs = __ballot(my_v != kNone);
+      if (my_v != kNone) {
+        const uint32_t slot = (uint32_t)__popcll(defs & ((1ull << tid) - 1ull));
+        dv[slot] = my_v; dp[slot] = my_p; da[slot] = attr;
+      }
+      if (tid == 0) { best = ~0ull; nd = (uint32_t)__popcll(defs); }
+    }
+    static_assert(kMaxOperands == 64, "a wavefront");
     __syncthreads();
-    flip_members_of_p(m, L, i, in_p, tid, kResolveThreads);
-    __syncthreads();
-    for (uint32_t x = tid; x < m.W; x += kResolveThreads) {
-      uint32_t bits = in_p[x];
-      if (!bits) continue;
-      uint32_t at = atomicAdd(&n_members, (uint32_t)__popc(bits));
-      for (; bits && at < kResolveMembers; bits &= bits - 1) members[at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
+    auto flip = [&](const u32x4 r) {
+      const uint32_t v = r.x >> 8;
+      if (r.y) __hip_atomic_fetch_xor(&in_p[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < kSeeds + kEvents; ++u) flip(rec[u]);
+    // (long lists: the rest is read twice)
+    const uint32_t s_rest = s_first + tid + kSeeds * kResolveThreads, e_rest = e_first + tid + kEvents * kResolveThreads;
+    for (uint32_t e = s_rest; e < s_end; e += kResolveThreads) flip(L.seeds[e]);
+    for (uint32_t e = e_rest; e < e_end; e += kResolveThreads) {
+      const u32x4 r = L.plan[e];
+      if (counts(e, r)) flip(r);
     }
     __syncthreads();
     unsigned long long mine = ~0ull;
-    auto examine = [&](uint32_t x) {
-      const uint32_t ax = m.vattr[x], px = cand_at(J, k, L.first[x]), wx = attr_width(ax);
-      for (uint32_t t = 0; t < nd; ++t) {
-        const uint32_t d = dv[t];
-        if (d == x) continue;
-        const uint32_t ad = m.vattr[d];
-        if (attr_class(ad) != attr_class(ax)) continue;
+    const uint32_t n_defs = nd;
+    auto member = [&](const u32x4 r) {
+      const uint32_t v = r.x >> 8;
+      return r.y && ((in_p[v >> 5] >> (v & 31)) & 1u);
+    };
+    auto examine = [&](const u32x4 r, uint32_t px) {
+      const uint32_t x = r.x >> 8, wx = (uint32_t)__popc(r.y);
+      for (uint32_t t = 0; t < n_defs; ++t) {
+        const uint32_t d = dv[t], ad = da[t];
+        if (d == x || attr_word(ad) * 256u != r.z) continue;   // (classes begin at different mask words)
         const uint32_t pd = dp[t], wd = attr_width(ad);
         if (pd < px + wx && px < pd + wd) {
           // (a program with lanes as values reports the caller's vregs: the smallest pair of those)
-          const uint32_t da = m.val_vreg ? m.val_vreg[d] : d, xa = m.val_vreg ? m.val_vreg[x] : x;
-          const unsigned long long pr = ((unsigned long long)min(da, xa) << 32) | max(da, xa);
+          const uint32_t a = m.val_vreg ? m.val_vreg[d] : d, b = m.val_vreg ? m.val_vreg[x] : x;
+          const unsigned long long pr = ((unsigned long long)min(a, b) << 32) | max(a, b);
           mine = pr < mine ? pr : mine;
         }
       }
     };
-    if (n_members <= kResolveMembers) {
-      for (uint32_t x = tid; x < n_members; x += kResolveThreads) examine(members[x]);
-    } else {
-      for (uint32_t x = tid; x < m.V; x += kResolveThreads)
-        if ((in_p[x >> 5] >> (x & 31)) & 1u) examine(x);
+    uint32_t px[kSeeds + kEvents];
+#pragma unroll
+    for (uint32_t u = 0; u < kSeeds + kEvents; ++u) {   // (all in flight)
+      px[u] = 0;
+      if (member(rec[u])) px[u] = cand_at(J, k, rec[u].w & 0xFFFFFFu);
+      else rec[u].y = 0;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kSeeds + kEvents; ++u)
+      if (rec[u].y) examine(rec[u], px[u]);
+    for (uint32_t e = s_rest; e < s_end; e += kResolveThreads) {
+      const u32x4 r = L.seeds[e];
+      if (member(r)) examine(r, cand_at(J, k, r.w & 0xFFFFFFu));
+    }
+    for (uint32_t e = e_rest; e < e_end; e += kResolveThreads) {
+      const u32x4 r = L.plan[e];
+      if (counts(e, r) && member(r)) examine(r, cand_at(J, k, r.w & 0xFFFFFFu));
     }
     if (mine != ~0ull) atomicMin(&best, mine);
     __syncthreads();
     if (tid == 0) {
-      out[k - row0].a = (uint32_t)(best >> 32);
-      out[k - row0].b = (uint32_t)best;
+      out[row].a = (uint32_t)(best >> 32);
+      out[row].b = (uint32_t)best;
     }
     __syncthreads();   // the shared arrays are reused by the next row
   }

@@ -1,4 +1,4 @@
-"""The pair search of the verifier around the number of live values it lists (512) and with every
+"""The pair search of the verifier with many values live at once and with every
 row of a group failing, against the oracle, exactly."""
 import numpy as np
 import pytest
@@ -22,6 +22,17 @@ def _need_gpu():
 @pytest.mark.parametrize("n_live", [1, 64, 511, 512, 513, 800])
 @pytest.mark.parametrize("K", [1, 64, 129])
 def test_many_live_values(n_live, K):
+    check_many_live_values(n_live, K, 0)
+
+
+@pytest.mark.parametrize("n_live", [127, 128, 129, 383, 384, 385, 800])
+@pytest.mark.parametrize("tile_len", [100, 4096])
+def test_lists_longer_than_a_thread_keeps(n_live, tile_len):
+    """live-in lists around the 128 entries and tiles around the 384 events that the search keeps in registers"""
+    check_many_live_values(n_live, 64, tile_len)
+
+
+def check_many_live_values(n_live, K, tile_len):
     """n_live values of two files live together; the last one written clashes in almost every row"""
     rng = np.random.default_rng(n_live)
     V = n_live + 1
@@ -43,7 +54,7 @@ def test_many_live_values(n_live, K):
     if 64 <= n_live <= 800 and K > 1:
         assert (want["status"] == 3).sum() > K // 2
     hm = vl.vl_mir_create(m)
-    hl = vl.vl_liveness(hm)
+    hl = vl.vl_liveness_multi([hm], tile_len=tile_len)[0]
     try:
         dev, ld = vl.rows_to_device(rows)
         out = torch.full((K, 4), -1, dtype=torch.int32, device="cuda")
