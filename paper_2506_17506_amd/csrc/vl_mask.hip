@@ -7,8 +7,8 @@
 // The samples of one kernel reach an occurrence together, and their rows usually lie at equal
 // distances: the host folds such neighbouring queries into runs (program, occurrence, first row,
 // distance, count), and a workgroup rebuilds P(i) once for its share of a run; then a wavefront
-// answers a query at a time.  What bounds a call is waiting: some eight dependent reads to rebuild
-// P(i) (6 us), and on the host the pass over the queries.  A workgroup per query, each with a
+// answers a query at a time.  What bounds a call is waiting: some eight dependent reads
+// (one program x 100: 5.9 us; 12.2 when every lane looked up the members of its bitset words one after the other), and on the host the pass over the queries.  A workgroup per query, each with a
 // table entry to upload, took 28 us on the device and 51 us in all for 6,400 queries.
 #include <algorithm>
 #include <cstring>
@@ -62,26 +62,73 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
   const uint32_t F = m.class_size[cls];
   const uint32_t first_v = L.first[v];
   const bool fresh = first_v >= q;   // the first mention of v: everything in P(i) that already has a register is in the way
-  if (fresh) {
-    for (uint32_t x = threadIdx.x; x < m.W; x += kMaskThreads) in_p[x] = 0;
-    if (threadIdx.x == 0) n_members = 0;
-    __syncthreads();
-    flip_members_of_p(m, L, i, in_p, threadIdx.x, kMaskThreads);
-    __syncthreads();
-  }
   auto in_the_way = [&](uint32_t b, uint2 &out) {
     const uint32_t ab = m.vattr[b], fb = L.first[b];
     out = make_uint2(fb, attr_width(ab));
     return b != v && attr_class(ab) == cls && fb < q;
   };
   if (fresh) {
-    for (uint32_t x = threadIdx.x; x < m.W; x += kMaskThreads)
-      for (uint32_t bits = in_p[x]; bits; bits &= bits - 1) {
-        uint2 e;
-        if (!in_the_way(x * 32u + (uint32_t)__ffs(bits) - 1u, e)) continue;
-        const uint32_t slot = atomicAdd(&n_members, 1u);
-        if (slot < kMaskMembers) members[slot] = e;
-      }
+    for (uint32_t x = threadIdx.x; x < m.W; x += kMaskThreads) in_p[x] = 0;
+    if (threadIdx.x == 0) n_members = 0;
+    // Members of P(i): flip_members_of_p, with the records kept until the bits say which of them are members.  A record
+    // has its value's width and class, so that only the first occurrence is looked up, all of a thread's at once.
+    // (A value may have several records among them, and is then listed as often.)
+    const uint32_t item = i + m.instr_blk[i] + 1, tile = i / L.tile_len;
+    const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first, e_first = L.tile_range[2 * tile];
+    const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1];
+    constexpr uint32_t kKept = 4;   // live-ins, then events
+    u32x4 rec[kKept];
+    auto counts = [&](uint32_t e, const u32x4 r) { return e < e_own || (e < e_end && !(r.w & kEvtPost)); };
+    const uint32_t s_own = s_first + threadIdx.x, e_mine = e_first + threadIdx.x;
+    rec[0] = 0;
+    if (s_own < s_end) rec[0] = L.seeds[s_own];
+#pragma unroll
+    for (uint32_t u = 1; u < kKept; ++u) {
+      const uint32_t e = e_mine + (u - 1u) * kMaskThreads;
+      rec[u] = 0;
+      if (e < e_end) rec[u] = L.plan[e];
+      if (!counts(e, rec[u])) rec[u] = 0;   // (a record that stands for something has a tuple mask)
+    }
+    __syncthreads();
+    auto flip = [&](const u32x4 r) {
+      const uint32_t b = r.x >> 8;
+      if (r.y) __hip_atomic_fetch_xor(&in_p[b >> 5], 1u << (b & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < kKept; ++u) flip(rec[u]);
+    // (long lists: the rest is read twice)
+    const uint32_t s_rest = s_own + kMaskThreads, e_rest = e_mine + (kKept - 1u) * kMaskThreads;
+    for (uint32_t e = s_rest; e < s_end; e += kMaskThreads) flip(L.seeds[e]);
+    for (uint32_t e = e_rest; e < e_end; e += kMaskThreads) {
+      const u32x4 r = L.plan[e];
+      if (counts(e, r)) flip(r);
+    }
+    __syncthreads();
+    auto candidate = [&](const u32x4 r) {   // a member of v's class (classes begin at different mask words) other than v
+      const uint32_t b = r.x >> 8;
+      return r.y && b != v && r.z == attr_word(attr) * 256u && ((in_p[b >> 5] >> (b & 31)) & 1u);
+    };
+    auto list = [&](const u32x4 r, uint32_t fb) {
+      if (fb >= q) return;
+      const uint32_t slot = atomicAdd(&n_members, 1u);
+      if (slot < kMaskMembers) members[slot] = make_uint2(fb, (uint32_t)__popc(r.y));
+    };
+    uint32_t fb[kKept];
+#pragma unroll
+    for (uint32_t u = 0; u < kKept; ++u) {
+      fb[u] = kNone;
+      if (candidate(rec[u])) fb[u] = L.first[rec[u].x >> 8];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kKept; ++u) list(rec[u], fb[u]);
+    for (uint32_t e = s_rest; e < s_end; e += kMaskThreads) {
+      const u32x4 r = L.seeds[e];
+      if (candidate(r)) list(r, L.first[r.x >> 8]);
+    }
+    for (uint32_t e = e_rest; e < e_end; e += kMaskThreads) {
+      const u32x4 r = L.plan[e];
+      if (counts(e, r) && candidate(r)) list(r, L.first[r.x >> 8]);
+    }
     __syncthreads();
   }
   const uint32_t wm = width == 32 ? 0xFFFFFFFFu : ((1u << width) - 1u);
@@ -262,8 +309,9 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
   };
   Run *runs = args.run;
   uint32_t n_runs = 0, most_runs = kArgRuns;
-  // a workgroup per four queries (one per wavefront) up to a thousand workgroups, then longer shares
-  const uint32_t per_block = kMaskWaves * std::max(1u, std::min(16u, n / (kMaskWaves * 1024u)));
+  // a workgroup per four queries (one per wavefront) up to some five hundred workgroups, then longer shares, since each rebuilds P(i)
+  // (64 programs x 100, longer shares from 1,024 workgroups, from 512 and from 256 on: 11.0, 9.3 and 11.4 us)
+  const uint32_t per_block = kMaskWaves * std::max(1u, std::min(16u, n / (kMaskWaves * 512u)));
   uint32_t blocks = 0;
   Run run = {};
   const vl_mir *mir = nullptr;

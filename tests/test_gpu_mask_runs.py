@@ -149,3 +149,33 @@ def test_more_runs_than_the_table_starts_with():
             assert (masks.cpu().numpy().view(np.uint32) == want[which]).all()
     finally:
         free(hm, hl)
+
+
+@pytest.mark.parametrize("n_live", [255, 256, 257, 767, 768, 769, 1100])
+@pytest.mark.parametrize("tile_len", [100, 4096])
+def test_lists_longer_than_a_thread_keeps(n_live, tile_len):
+    """live-in lists around the 256 entries and tiles around the 768 events whose records stay in registers; half of
+    the values are of another file, some are written twice"""
+    rng = np.random.default_rng(n_live)
+    V = n_live + 1
+    vclass = (np.arange(V) % 2).astype(np.uint8)
+    width = rng.choice([1, 1, 2, 4], V).astype(np.uint8)
+    twice = [([int(v)], []) for v in rng.choice(n_live, 40)]
+    blocks = [[([v], []) for v in range(n_live)] + twice + [([n_live], [])] + [([], list(range(v, min(V, v + 40)))) for v in range(0, V, 40)]]
+    m = Mir.build(blocks, [[]], V, (512, 512), vclass, width, np.ones(V, np.uint8), None, name=f"live{n_live}")
+    rows = rng.integers(0, 512, (9, m.n_occ)).astype(np.uint16)
+    an = vlo.analyze(m, interference=False, threads=8)
+    hm = [vl.vl_mir_create(m)]
+    hl = vl.vl_liveness_multi(hm, tile_len=tile_len)
+    try:
+        dev, _ = vl.rows_to_device(rows)
+        first = int(np.nonzero(m.occ_vreg == n_live)[0][0])
+        qs = [(k, o) for o in (first, n_live // 2, first + 1) for k in range(len(rows))]
+        masks = torch.full((len(qs), 16), -1, dtype=torch.int32, device="cuda")
+        vl.vl_free_bases_multi([(hm[0], hl[0], dev[k], o) for k, o in qs], masks)
+        torch.cuda.synchronize()
+        got = masks.cpu().numpy().view(np.uint32)
+        want = np.stack([vlo.free_bases(m, an, rows[k], o) for k, o in qs])
+        assert (got == want).all()
+    finally:
+        free(hm, hl)
