@@ -9,6 +9,7 @@ torch = pytest.importorskip("torch")
 import paper_2506_17506_amd as vl  # noqa: E402
 from oracle import vlo  # noqa: E402
 from vlgen import gen  # noqa: E402
+from vlgen.mir import Mir  # noqa: E402
 from vlgen.mixed import mixed_mir  # noqa: E402
 
 
@@ -38,6 +39,20 @@ def test_mixed_shapes(n_banks):
     rows = rng.integers(0, 512, (70, m.n_occ)).astype(np.uint16)
     rows[5] = 65535
     rows[6] = 0
+    assert (gpu_scores(m, rows, n_banks) == vlo.bank_conflicts(m, rows, n_banks)).all()
+
+
+@pytest.mark.parametrize("n_banks", [1, 2, 4, 8])
+def test_every_width_at_every_base(n_banks):
+    """counts in bytes: instructions of up to four operands of widths 1 to 32, bases that cover every bank, all equal operands among them"""
+    V = 64
+    rng = np.random.default_rng(n_banks)
+    width = (np.arange(V) % 32 + 1).astype(np.uint8)
+    ins = [([v], []) for v in range(V)] + [([], [int(u) for u in rng.integers(0, V, rng.integers(0, 5))]) for _ in range(600)]
+    ins += [([], [31] * 4), ([], [31, 63, 31, 63]), ([], list(range(5)))]
+    m = Mir.build([ins], [[]], V, (512,), np.zeros(V, np.uint8), width, np.ones(V, np.uint8), None, name="widths")
+    rows = rng.integers(0, 65536, (37, m.n_occ)).astype(np.uint16)
+    rows[0], rows[1] = 0, 65535
     assert (gpu_scores(m, rows, n_banks) == vlo.bank_conflicts(m, rows, n_banks)).all()
 
 
