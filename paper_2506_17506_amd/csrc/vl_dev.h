@@ -22,8 +22,8 @@ constexpr uint32_t kMaxOperands = 64;      // per instruction
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kDefaultTile = 512;     // instructions per verification tile
 
-// Kernel (program) on the device.  All pointers are device memory.
-struct DevMir {
+// Kernel (program) on the device.  All pointers are device memory.  (What the analysis reads; the rest follows in DevMir.)
+struct DevProg {
   uint32_t N, V, B, O, C, E, W;
   uint32_t occ_words;              // occupancy words per candidate: every class may address 16 words from its
                                    // first one (classes are laid out smallest first, so this is rarely more
@@ -45,6 +45,8 @@ struct DevMir {
   uint32_t has_reserved;
   uint16_t class_size[kMaxClass];
   uint16_t class_word[kMaxClass];  // first occupancy word of the class
+};
+struct DevMir : DevProg {
   uint32_t reserved[kMaxClass][16];
 };
 
@@ -170,6 +172,9 @@ struct DevLive {
 
 template <class T> __host__ __device__ inline const T VL_GLOBAL *as_global(const T *p) {
   return (const T VL_GLOBAL *)p;
+}
+template <class T> __host__ __device__ inline const T VL_CONSTANT *as_constant(const T *p) {
+  return (const T VL_CONSTANT *)(uintptr_t)p;
 }
 template <class T> __host__ __device__ inline T VL_GLOBAL *as_global_rw(T *p) {
   return (T VL_GLOBAL *)p;

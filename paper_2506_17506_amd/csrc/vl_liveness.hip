@@ -22,14 +22,17 @@
 
 using namespace vl;
 
-#define MIRS const DevMir *const *__restrict__ mirs, DevLive *__restrict__ lives
+// The tables of a launch's programs hold the structures themselves: nothing but the kernel's arguments is
+// read before an array's address is known, and the loads are scalar ones wherever they stand.  (A launch
+// of few programs is a chain of some six trips to memory of 0.8 us, its table of pointers was one.)
+#define MIRS const DevProg *__restrict__ mirs, const DevLive *__restrict__ lives
 
 namespace {
 
 template <class P> __device__ inline bool bit_get(P row, uint32_t v) { return (row[v >> 5] >> (v & 31)) & 1u; }
 
 // first of the entries [lo, hi) of a vreg that is at instruction `at` or later
-__device__ inline uint32_t first_entry_at(const DevLive VL_GLOBAL &L, uint32_t lo, uint32_t hi, uint32_t at) {
+__device__ inline uint32_t first_entry_at(const DevLive VL_CONSTANT &L, uint32_t lo, uint32_t hi, uint32_t at) {
   while (lo < hi) {
     uint32_t mid = (lo + hi) >> 1;
     if ((L.ent[mid].y >> 2) < at) lo = mid + 1; else hi = mid;
@@ -45,8 +48,8 @@ constexpr uint32_t kSlice = 8192;   // occurrences per workgroup in the counting
 // then adds the non-zero bins to the global counters once.
 template <bool kLds>
 __global__ __launch_bounds__(1024) void k_count(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   extern __shared__ uint32_t sm[];
   const uint32_t o0 = blockIdx.x * kSlice;
   if (o0 >= m.O) return;
@@ -85,7 +88,7 @@ enum { kScanVreg = 0, kScanItems = 1, kScanSeg = 2, kScanSeed = 3, kScanBound = 
 // (The array is chosen at compile time: a run-time switch over the four arrays was
 // seen to pick the wrong pointer in its default branch.)
 template <int kWhich>
-__device__ inline void f_scan(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L) {
+__device__ inline void f_scan(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L) {
   uint32_t VL_GLOBAL *p = kWhich == kScanVreg ? L.vcnt : kWhich == kScanItems ? L.item_base : kWhich == kScanSeg ? L.seg_base :
                           kWhich == kScanBound ? L.bound_off : L.seed_off;
   const uint32_t n = kWhich == kScanVreg ? m.V : kWhich == kScanItems ? stretches(m.N) : kWhich == kScanSeg ? stretches(m.O) :
@@ -161,7 +164,7 @@ __device__ inline void f_scan(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L) {
 
 template <int kWhich>
 __global__ __launch_bounds__(1024) void k_scan(MIRS) {
-  f_scan<kWhich>(*as_global(mirs[blockIdx.x]), *as_global_rw(&lives[blockIdx.x]));
+  f_scan<kWhich>(as_constant(mirs)[blockIdx.x], as_constant(lives)[blockIdx.x]);
 }
 
 // Places each occurrence into its vreg's range (order inside a range is fixed later).
@@ -169,8 +172,8 @@ __global__ __launch_bounds__(1024) void k_scan(MIRS) {
 // then ranks its own occurrences in LDS.
 template <bool kLds>
 __global__ __launch_bounds__(1024) void k_place(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   extern __shared__ uint32_t sm[];
   const uint32_t o0 = blockIdx.x * kSlice;
   if (o0 >= m.O) return;
@@ -199,7 +202,7 @@ __global__ __launch_bounds__(1024) void k_place(MIRS) {
 
 // Lists of up to kShortList occurrences are rank-sorted by one lane (the longer ones were
 // queued by the scan of the list lengths).
-__device__ inline void f_sort_short(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx) {
+__device__ inline void f_sort_short(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx) {
   const uint32_t v = bx * 256 + tx;
   if (v >= m.V) return;
   const uint32_t lo = L.vcnt[v], len = L.vcnt[v + 1] - lo;
@@ -241,7 +244,7 @@ constexpr uint32_t kLongBlocks = 64;                 // workgroups per kernel th
 
 // Long lists: occurrence indices are distinct, so marking them in a bitmap and reading
 // the bitmap back in order sorts them, one window of kBitmapSpan occurrences at a time.
-__device__ inline void f_sort_long(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tid) {
+__device__ inline void f_sort_long(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tid) {
   __shared__ uint32_t bm[kBitmapWords];
   __shared__ uint32_t wave_total[4];
   const uint32_t n_long = L.counters[kCtrLong];
@@ -295,8 +298,8 @@ __device__ inline void f_sort_long(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL 
 
 // both sorts in one launch: the first kLongBlocks workgroups of each kernel take the long lists
 __global__ __launch_bounds__(256) void k_sort(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   if (blockIdx.x < kLongBlocks) f_sort_long(m, L, blockIdx.x, threadIdx.x);
   else f_sort_short(m, L, blockIdx.x - kLongBlocks, threadIdx.x);
 }
@@ -315,8 +318,8 @@ constexpr uint32_t kRound = 1024;
 constexpr uint32_t kGroupSlice = 16 * kRound;
 constexpr uint32_t kGroupMaxOcc = 1u << 17;   // with more in some program, counting it all in every workgroup costs too much
 __global__ __launch_bounds__(1024) void k_group(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   extern __shared__ uint32_t sm[];   // [V]
   __shared__ uint32_t part[16];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -428,8 +431,8 @@ static_assert(kOrdBack > kMaxOperands, "the look-back has to leave an instructio
 
 template <bool kSorted>
 __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_words) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   extern __shared__ uint32_t sm[];
   // by place in the window; s_o holds the occurrences as they stand, then in order with kRecKeeps
   __shared__ uint32_t s_o[kOrdWindow], s_v[kOrdWindow], s_ifl[kOrdWindow], s_blk[kOrdWindow];
@@ -605,8 +608,8 @@ __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_
 // block count allows, otherwise the sweep runs on global memory.
 template <bool kLds>
 __global__ __launch_bounds__(64) void k_fixpoint(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   extern __shared__ uint32_t sm[];
   const uint32_t lane = threadIdx.x, w = blockIdx.x * 64 + lane;
   if (blockIdx.x * 64 >= m.W) return;
@@ -743,8 +746,8 @@ __global__ __launch_bounds__(64) void k_fixpoint(MIRS) {
 // (8,000 instructions in 22 blocks: 21.6 us through LDS, 9.5 this way; 256 of 1,000-20,000: 34 and 19.)
 constexpr uint32_t kRegBlocks = 32;
 __global__ __launch_bounds__(64) void k_fixpoint_regs(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   const uint32_t lane = threadIdx.x, w = blockIdx.x * 64 + lane;
   const uint32_t B = m.B, W = m.W;
   if (blockIdx.x * 64 >= W) return;
@@ -857,9 +860,9 @@ constexpr uint32_t kEvtThreads = 256, kEvtHalo = 16, kEvtWindow = kEvtThreads + 
 // (One-dimensional grid: block_map names the kernel and the stretch of 256 entries of every
 // workgroup, so that no workgroup is launched for stretches a smaller kernel does not have.)
 __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__restrict__ block_map) {
-  const uint2 where = block_map[blockIdx.x];
-  const DevMir VL_GLOBAL &m = *as_global(mirs[where.x]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[where.x]);
+  const uint2 where = block_map ? block_map[blockIdx.x] : make_uint2(0, blockIdx.x);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[where.x];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[where.x];
   // The neighbours of an entry in the sorted order (its own mention group, the groups before
   // and after it) are looked at many times: the workgroup's stretch of entries plus a halo
   // on both sides is staged in LDS once, and only what lies beyond the halo is read from
@@ -1024,7 +1027,7 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
 constexpr uint32_t kStageReps = 4;
 
 // ---- 5a. event stream -----------------------------------------------------------------
-__device__ inline uint32_t item_of_instr(const DevMir VL_GLOBAL &m, uint32_t i) { return i + m.instr_blk[i] + 1; }
+__device__ inline uint32_t item_of_instr(const DevProg VL_CONSTANT &m, uint32_t i) { return i + m.instr_blk[i] + 1; }
 
 __device__ inline uint32_t wave_incl_scan(uint32_t x) {
   for (int d = 1; d < 64; d <<= 1) {
@@ -1035,7 +1038,7 @@ __device__ inline uint32_t wave_incl_scan(uint32_t x) {
 }
 
 // nearest occurrence of v before instruction `at`, else the first at or after it
-__device__ inline uint32_t source_occurrence(const DevLive VL_GLOBAL &L, uint32_t v, uint32_t at) {
+__device__ inline uint32_t source_occurrence(const DevLive VL_CONSTANT &L, uint32_t v, uint32_t at) {
   const uint32_t lo = L.vcnt[v], hi = L.vcnt[v + 1];
   const uint32_t x = first_entry_at(L, lo, hi, at);
   return x > lo ? L.ent[x - 1].x : (x < hi ? L.ent[x].x : 0u);
@@ -1053,7 +1056,7 @@ __device__ inline u32x4 event_record(uint32_t o, uint32_t v, uint32_t attr, bool
   r.w = o | (slow ? kEvtSlow : 0u) | (tested ? kEvtTested : 0u);
   return r;
 }
-__device__ inline u32x4 event_record(const DevMir VL_GLOBAL &m, uint32_t o, uint32_t v, bool tested, bool near) {
+__device__ inline u32x4 event_record(const DevProg VL_CONSTANT &m, uint32_t o, uint32_t v, bool tested, bool near) {
   return event_record(o, v, m.vattr[v], tested, near);
 }
 
@@ -1061,7 +1064,7 @@ __device__ inline u32x4 event_record(const DevMir VL_GLOBAL &m, uint32_t o, uint
 // earlier block's live-out to the later block's live-in: one wave per boundary lists the
 // values that leave (release) and those that enter (occupy without test).
 template <bool kFill>
-__device__ inline void f_boundary(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_boundary(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                   const uint32_t bdim) {
   const uint32_t b = bx, lane = tx;
   if (b >= m.B) return;
@@ -1125,7 +1128,7 @@ __device__ inline void f_boundary(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
 // Occupancy events of each instruction, in the order they take effect: releases of
 // operands that die here, then test-and-occupy of the values written, then releases of
 // values that are dead once the instruction has executed.
-__device__ inline void f_plan_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_plan_fill(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                    const uint32_t bdim) {
   uint32_t i = bx * bdim + tx;
   if (i >= m.N) return;
@@ -1196,7 +1199,7 @@ __device__ inline void f_plan_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL 
 
 // Number of events of each instruction (the roles of its operands, as the filling pass above has
 // them), prefixed over its stretch; kStageReps stretches at a time, side by side.
-__device__ inline void f_item_count(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx) {
+__device__ inline void f_item_count(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx) {
   const uint32_t s0 = bx * kStageReps, n_stretch = stretches(m.N);
   if (s0 >= n_stretch) return;
   uint32_t o0[kStageReps], n_op[kStageReps], blk[kStageReps], n_evt[kStageReps], role[kStageReps][4];
@@ -1234,7 +1237,7 @@ __device__ inline void f_item_count(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
 // end of the program) and finds the run starts and ends inside it; what holds just before
 // the stretch is known locally.  Groups are sorted by (vreg, instruction), so a prefix sum
 // of the start counts numbers the runs in CSR order; the j-th end belongs to the j-th start.
-__device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_seg_fill(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                   const uint32_t bdim) {
   const uint32_t e = bx * bdim + tx;
   if (e >= m.O) return;
@@ -1287,7 +1290,7 @@ __device__ inline void f_seg_fill(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &
 }
 
 // where each vreg's (ascending) runs begin, and its hull: [first start, last end), or [0,0) without runs
-__device__ inline void f_hull(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_hull(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                               const uint32_t bdim) {
   const uint32_t v = bx * bdim + tx;
   if (v > m.V) return;
@@ -1309,7 +1312,7 @@ __device__ inline void f_hull(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, c
 // of its instructions (an occurrence with an odd number of roles flips its vreg) and of
 // the block boundaries right after its instructions (live-out of the earlier block XOR
 // live-in of the later one).
-__device__ inline void f_tile_delta(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_tile_delta(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                     const uint32_t bdim) {
   extern __shared__ uint32_t row[];
   const uint32_t t = bx;
@@ -1347,7 +1350,7 @@ __device__ inline void f_tile_delta(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
 // (nothing is live into the first).
 constexpr uint32_t kTileWords = 1024;    // words of a workgroup
 constexpr uint32_t kTileCounts = 2048;   // most tiles whose members are counted
-__device__ inline void f_tile_prefix(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, uint32_t *members) {
+__device__ inline void f_tile_prefix(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, uint32_t *members) {
   __shared__ uint32_t run_xor[16][64];
   const uint32_t W = m.W, T = L.T, w0 = bx * kTileWords, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   if (w0 >= W) return;
@@ -1421,7 +1424,7 @@ __device__ inline void wave_scan(uint32_t VL_GLOBAL *p, const uint32_t n) {
 // One wavefront per tile lists the members of its seed row as occupy-without-test entries
 // whose register is taken from the nearest earlier occurrence of the vreg.
 template <bool kFill>
-__device__ inline void f_seed(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_seed(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                               const uint32_t bdim) {
   const uint32_t t = bx, lane = tx;
   if (t >= L.T) return;
@@ -1455,7 +1458,7 @@ __device__ inline void f_seed(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, c
 }
 
 // completes each seed entry: the register comes from the nearest earlier occurrence
-__device__ inline void f_seed_src(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_seed_src(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                   const uint32_t bdim) {
   const uint32_t k = bx * bdim + tx;
   if (k >= L.n_seed) return;
@@ -1489,14 +1492,14 @@ static inline void zero_async(void *p, size_t bytes, hipStream_t stream) {
 __global__ void k_collect(MIRS, uint32_t n) {
   uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
-  const DevMir VL_GLOBAL &m = *as_global(mirs[k]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[k]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[k];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[k];
   L.counters[kCtrPlanLen] = L.item_base[stretches(m.N)] + L.bound_off[m.B];
   L.counters[kCtrSeg] = L.seg_base[stretches(m.O)];
   L.counters[kCtrSeed] = L.seed_off[L.T];
 }
 
-__device__ inline void f_tile_range(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL &L, const uint32_t bx, const uint32_t tx,
+__device__ inline void f_tile_range(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t bx, const uint32_t tx,
                                     const uint32_t bdim) {
   uint32_t t = bx * bdim + tx;
   if (t >= L.T) return;
@@ -1527,8 +1530,8 @@ __device__ inline void f_tile_range(const DevMir VL_GLOBAL &m, DevLive VL_GLOBAL
 struct StageGrid { uint32_t a, b, c; };   // blocks of the three parts, in launch order
 
 __global__ __launch_bounds__(256) void k_stage_count(MIRS, StageGrid g) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   const uint32_t bx = blockIdx.x, tx = threadIdx.x;
   if (bx < g.a) f_tile_delta(m, L, bx, tx, 256);
   else if (bx < g.a + g.b) f_boundary<false>(m, L, (bx - g.a) * 4 + (tx >> 6), tx & 63u, 64);
@@ -1540,8 +1543,8 @@ __global__ __launch_bounds__(256) void k_stage_count(MIRS, StageGrid g) {
 constexpr uint32_t kWaveScan = 4096;   // longer arrays are scanned by the whole workgroup
 template <bool kCount>
 __global__ __launch_bounds__(1024) void k_stage_scan(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   if (!kCount && blockIdx.x > 0) {
     f_tile_prefix(m, L, blockIdx.x - 1, nullptr);
     return;
@@ -1578,7 +1581,7 @@ __global__ __launch_bounds__(1024) void k_stage_scan(MIRS) {
 
 // the counts of the tiles' live-ins where a row takes several workgroups of the launch above
 __global__ __launch_bounds__(256) void k_seed_count(MIRS) {
-  f_seed<false>(*as_global(mirs[blockIdx.y]), *as_global_rw(&lives[blockIdx.y]), blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63u, 64);
+  f_seed<false>(as_constant(mirs)[blockIdx.y], as_constant(lives)[blockIdx.y], blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63u, 64);
 }
 
 // One-dimensional grid.  Part a: per_a workgroups for every kernel; parts b and c: one
@@ -1588,18 +1591,18 @@ __global__ __launch_bounds__(256) void k_stage_fill(MIRS, StageGrid g, uint32_t 
   const uint32_t bx = blockIdx.x, tx = threadIdx.x;
   uint2 where;
   if (bx < g.a) where = make_uint2(bx / per_a, bx % per_a);
-  else if (bx < g.a + g.b) where = map_instr[bx - g.a];
-  else where = map_occ[bx - g.a - g.b];
-  const DevMir VL_GLOBAL &m = *as_global(mirs[where.x]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[where.x]);
+  else if (bx < g.a + g.b) where = map_instr ? map_instr[bx - g.a] : make_uint2(0, bx - g.a);
+  else where = map_occ ? map_occ[bx - g.a - g.b] : make_uint2(0, bx - g.a - g.b);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[where.x];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[where.x];
   if (bx < g.a) f_seed<true>(m, L, where.y * 4 + (tx >> 6), tx & 63u, 64);
   else if (bx < g.a + g.b) f_plan_fill(m, L, where.y, tx, 256);
   else f_seg_fill(m, L, where.y, tx, 256);
 }
 
 __global__ __launch_bounds__(256) void k_stage_finish(MIRS, StageGrid g) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.y]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.y]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
   const uint32_t bx = blockIdx.x, tx = threadIdx.x;
   if (bx < g.a) f_boundary<true>(m, L, bx * 4 + (tx >> 6), tx & 63u, 64);
   else if (bx < g.a + g.b) f_tile_range(m, L, bx - g.a, tx, 256);
@@ -1618,8 +1621,8 @@ __global__ __launch_bounds__(256) void k_stage_finish(MIRS, StageGrid g) {
 // one by one, and the prefix waited for memory at every row.)
 constexpr uint32_t kDenseRows = 64;
 __global__ __launch_bounds__(256) void k_dense(MIRS) {
-  const DevMir VL_GLOBAL &m = *as_global(mirs[blockIdx.z]);
-  DevLive VL_GLOBAL &L = *as_global_rw(&lives[blockIdx.z]);
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.z];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.z];
   const uint32_t t = blockIdx.y, w0 = blockIdx.x * 64, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, w = w0 + lane;
   if (t >= L.T || w0 >= m.W) return;
   __shared__ uint32_t rows[kDenseRows][64], start[kDenseRows + 1], total[4][64];
@@ -1686,11 +1689,11 @@ struct vl_batch {
   int device = 0;
   void *arena1 = nullptr, *arena2 = nullptr;
   size_t cap1 = 0, cap2 = 0;
-  const DevMir **dev_mirs = nullptr;  // device array [n]
+  DevProg *dev_mirs = nullptr;        // device array [n]
   DevLive *dev_lives = nullptr;       // device array [n]
   void *pinned = nullptr;             // one allocation that holds the five arrays below
   uint32_t *host_counters = nullptr;  // [n][kCounters]
-  const DevMir **stage_mirs = nullptr;  // [n]
+  DevProg *stage_mirs = nullptr;      // [n]
   DevLive *stage_a = nullptr, *stage_b = nullptr;  // [n] each: first and second upload
   uint2 *stage_map = nullptr;         // the block maps (kernel, stretch of 256) of the per-instruction and per-entry launches
   std::vector<vl_live *> lives;
@@ -1876,14 +1879,14 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     if (too_many) { delete batch; return VL_E_RANGE; }
     hipError_t e = hipGetDevice(&batch->device);
     Bump pin;
-    const size_t o_cnt = pin.take((size_t)n * kCounters * 4), o_mir = pin.take((size_t)n * sizeof(DevMir *));
+    const size_t o_cnt = pin.take((size_t)n * kCounters * 4), o_mir = pin.take((size_t)n * sizeof(DevProg));
     const size_t o_a = pin.take((size_t)n * sizeof(DevLive)), o_b = pin.take((size_t)n * sizeof(DevLive));
     const size_t o_map = pin.take((blocks_instr + blocks_occ + 1) * sizeof(uint2));
     if (e == hipSuccess) e = hipHostMalloc(&batch->pinned, pin.off, hipHostMallocDefault);
     if (e == hipSuccess) {
       char *at = (char *)batch->pinned;
       batch->host_counters = (uint32_t *)(at + o_cnt);
-      batch->stage_mirs = (const DevMir **)(at + o_mir);
+      batch->stage_mirs = (DevProg *)(at + o_mir);
       batch->stage_a = (DevLive *)(at + o_a); batch->stage_b = (DevLive *)(at + o_b);
       batch->stage_map = (uint2 *)(at + o_map);
     }
@@ -1936,7 +1939,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     off[k].item_base = bump.take(((size_t)stretches(m.N) + 1) * 4);
     off[k].bound_off = bump.take(((size_t)m.B + 1) * 4);
   }
-  const size_t o_mirs = bump.take((size_t)n * sizeof(DevMir *));
+  const size_t o_mirs = bump.take((size_t)n * sizeof(DevProg));
   const size_t o_lives = bump.take((size_t)n * sizeof(DevLive));
   const size_t o_map = bump.take((blocks_instr + blocks_occ + 1) * sizeof(uint2));
   if (bump.off > batch->cap1) {
@@ -1945,7 +1948,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     if (e != hipSuccess) return fail(hip_fail(e));
   }
   char *a1 = (char *)batch->arena1;
-  const DevMir **mir_ptrs = batch->stage_mirs;
+  DevProg *const progs = batch->stage_mirs;
   for (uint32_t k = 0; k < n; ++k) {
     DevLive &L = h[k];
     L.vcnt = (uint32_t VL_GLOBAL *)(a1 + off[k].vcnt); L.vcur = (uint32_t VL_GLOBAL *)(a1 + off[k].vcur);
@@ -1965,9 +1968,9 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.seg_base = (uint32_t VL_GLOBAL *)(a1 + off[k].seg_base); L.item_base = (uint32_t VL_GLOBAL *)(a1 + off[k].item_base);
     L.bound_off = (uint32_t VL_GLOBAL *)(a1 + off[k].bound_off);
     L.counters = (uint32_t VL_GLOBAL *)(a1 + o_counters) + (size_t)k * kCounters;
-    mir_ptrs[k] = mirs[k]->dev;
+    progs[k] = mirs[k]->h;
   }
-  batch->dev_mirs = (const DevMir **)(a1 + o_mirs);
+  batch->dev_mirs = (DevProg *)(a1 + o_mirs);
   batch->dev_lives = (DevLive *)(a1 + o_lives);
   // Recycled handles of a call with the same options: the result sizes and the absence of
   // contract violations are known from it (the analysis of the same kernels is
@@ -2026,9 +2029,9 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   if (!tables_current) {
     batch->uploaded.clear();
     memcpy(batch->stage_a, h.data(), (size_t)n * sizeof(DevLive));
-    if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_mirs, mir_ptrs, (size_t)n * sizeof(DevMir *), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_mirs, progs, (size_t)n * sizeof(DevProg), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_lives, batch->stage_a, (size_t)n * sizeof(DevLive), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) {
+    if (e == hipSuccess && n > 1) {
       uint2 *at = batch->stage_map;
       for (uint32_t k = 0; k < n; ++k)
         for (uint32_t x = 0; x < (mirs[k]->h.N + 255u) / 256u; ++x) *at++ = make_uint2(k, x);
@@ -2038,10 +2041,11 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     }
   }
   if (e != hipSuccess) return fail(hip_fail(e));
-  const uint2 *map_instr = (const uint2 *)(a1 + o_map), *map_occ = map_instr + blocks_instr;
+  // (one program's blocks are its stretches in order: no map, a trip to memory less)
+  const uint2 *map_instr = n > 1 ? (const uint2 *)(a1 + o_map) : nullptr, *map_occ = n > 1 ? map_instr + blocks_instr : nullptr;
 
-  const DevMir *const *dm = batch->dev_mirs;
-  DevLive *dl = batch->dev_lives;
+  const DevProg *dm = batch->dev_mirs;
+  const DevLive *dl = batch->dev_lives;
   const uint32_t TB = 256;
   // LDS histograms over the vregs when they fit
   static const bool lds_ok = [] {
