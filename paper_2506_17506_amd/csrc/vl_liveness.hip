@@ -29,6 +29,14 @@ using namespace vl;
 
 namespace {
 
+// Which program and which of its blocks a workgroup of a two-dimensional launch has.  Consecutive
+// workgroups go to the eight dies in turn, each with an L2 of its own; where a batch deals its programs out
+// to the dies (`deal`), program p stays on die p % 8 through every launch, so that what its workgroups
+// gather and scatter meets in one L2: row y of the grid then holds programs 8 y to 8 y + 7 side by side.
+struct Grid { uint32_t n, dealt; };   // programs; 3 where they are dealt out, else 0
+__device__ inline uint32_t grid_prog(Grid g) { return g.dealt ? blockIdx.y * 8u + (blockIdx.x & 7u) : blockIdx.y; }
+__device__ inline uint32_t grid_block(Grid g) { return blockIdx.x >> g.dealt; }
+
 template <class P> __device__ inline bool bit_get(P row, uint32_t v) { return (row[v >> 5] >> (v & 31)) & 1u; }
 
 // first of the entries [lo, hi) of a vreg that is at instruction `at` or later
@@ -317,14 +325,16 @@ __global__ __launch_bounds__(256) void k_sort(MIRS) {
 constexpr uint32_t kRound = 1024;
 constexpr uint32_t kGroupSlice = 16 * kRound;
 constexpr uint32_t kGroupMaxOcc = 1u << 17;   // with more in some program, counting it all in every workgroup costs too much
-__global__ __launch_bounds__(1024) void k_group(MIRS) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
+__global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
   extern __shared__ uint32_t sm[];   // [V]
   __shared__ uint32_t part[16];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t s0 = blockIdx.x * kGroupSlice, n_slices = max(1u, (m.O + kGroupSlice - 1) / kGroupSlice), s1 = min(m.O, s0 + kGroupSlice);
-  if (blockIdx.x >= n_slices) return;
+  const uint32_t s0 = bx * kGroupSlice, n_slices = max(1u, (m.O + kGroupSlice - 1) / kGroupSlice), s1 = min(m.O, s0 + kGroupSlice);
+  if (bx >= n_slices) return;
   auto add_all = [&](uint32_t end) {   // sm[v] += mentions among the occurrences [0, end)
     for (uint32_t o = tid * 4; o < end; o += 4 * 4 * 1024) {
       u32x4 v[4];
@@ -352,12 +362,12 @@ __global__ __launch_bounds__(1024) void k_group(MIRS) {
   // (the regions are whole vectors long)
   const uint32_t vecs = (m.B * m.W + 3u) / 4u;
   const u32x4 none = {0, 0, 0, 0};
-  for (uint32_t x = blockIdx.x * 1024 + tid; x < vecs; x += n_slices * 1024) {
+  for (uint32_t x = bx * 1024 + tid; x < vecs; x += n_slices * 1024) {
     reinterpret_cast<u32x4 VL_GLOBAL *>(L.use)[x] = none;
     reinterpret_cast<u32x4 VL_GLOBAL *>(L.def)[x] = none;
     reinterpret_cast<u32x4 VL_GLOBAL *>(L.live_in)[x] = none;
   }
-  if (blockIdx.x == 0 && tid < kCounters) L.counters[tid] = 0;
+  if (bx == 0 && tid < kCounters) L.counters[tid] = 0;
   __syncthreads();
   // exclusive prefix: a contiguous run of vregs per thread
   const uint32_t per = (m.V + 1023u) / 1024u, lo = min(m.V, tid * per), hi = min(m.V, lo + per);
@@ -380,13 +390,13 @@ __global__ __launch_bounds__(1024) void k_group(MIRS) {
     run += c;
   }
   __syncthreads();
-  for (uint32_t v = blockIdx.x * 1024 + tid; v < m.V; v += n_slices * 1024) {
+  for (uint32_t v = bx * 1024 + tid; v < m.V; v += n_slices * 1024) {
     const uint32_t at = sm[v], next = v + 1 < m.V ? sm[v + 1] : m.O;
     L.vcnt[v] = at;
     L.last_live[v] = 0;
     if (at == next) L.first[v] = kNone;
   }
-  if (blockIdx.x == 0 && tid == 0) L.vcnt[m.V] = m.O;
+  if (bx == 0 && tid == 0) L.vcnt[m.V] = m.O;
   __syncthreads();
   add_all(min(s0, m.O));
   __syncthreads();
@@ -430,15 +440,17 @@ constexpr uint32_t kOrdWords = kOrdStretch / 32 + 1;   // most words a stretch t
 static_assert(kOrdBack > kMaxOperands, "the look-back has to leave an instruction");
 
 template <bool kSorted>
-__global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_words) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
+__global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const Grid grid, const uint32_t lds_words) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
   extern __shared__ uint32_t sm[];
   // by place in the window; s_o holds the occurrences as they stand, then in order with kRecKeeps
   __shared__ uint32_t s_o[kOrdWindow], s_v[kOrdWindow], s_ifl[kOrdWindow], s_blk[kOrdWindow];
   __shared__ uint32_t heads[kOrdPer * kOrdThreads / 32 + 1];   // a bit per place: a group begins here
   __shared__ uint32_t bits[kRound / 32], n_edge, crossing;
-  const uint32_t s0 = blockIdx.x * kOrdStretch, tid = threadIdx.x;
+  const uint32_t s0 = bx * kOrdStretch, tid = threadIdx.x;
   if (s0 >= m.O) return;
   const uint32_t s1 = min(m.O, s0 + kOrdStretch);
   const uint32_t x_lo = s0 - min(s0, kOrdBack);                                           // first entry put in order
@@ -607,12 +619,14 @@ __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const uint32_t lds_
 // swept in reverse linear order.  LDS holds in/use/def of the wave's 64 words when the
 // block count allows, otherwise the sweep runs on global memory.
 template <bool kLds>
-__global__ __launch_bounds__(64) void k_fixpoint(MIRS) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
+__global__ __launch_bounds__(64) void k_fixpoint(MIRS, const Grid grid) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
   extern __shared__ uint32_t sm[];
-  const uint32_t lane = threadIdx.x, w = blockIdx.x * 64 + lane;
-  if (blockIdx.x * 64 >= m.W) return;
+  const uint32_t lane = threadIdx.x, w = bx * 64 + lane;
+  if (bx * 64 >= m.W) return;
   const bool act = w < m.W;
   const uint32_t B = m.B, W = m.W;
   // in_l has one row more than there are blocks: row B stays empty and stands for "no successor"
@@ -745,12 +759,14 @@ __global__ __launch_bounds__(64) void k_fixpoint(MIRS) {
 // a vector of four at a time, where a loop over the set bits of every block's row stored them one by one.
 // (8,000 instructions in 22 blocks: 21.6 us through LDS, 9.5 this way; 256 of 1,000-20,000: 34 and 19.)
 constexpr uint32_t kRegBlocks = 32;
-__global__ __launch_bounds__(64) void k_fixpoint_regs(MIRS) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
-  const uint32_t lane = threadIdx.x, w = blockIdx.x * 64 + lane;
+__global__ __launch_bounds__(64) void k_fixpoint_regs(MIRS, const Grid grid) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
+  const uint32_t lane = threadIdx.x, w = bx * 64 + lane;
   const uint32_t B = m.B, W = m.W;
-  if (blockIdx.x * 64 >= W) return;
+  if (bx * 64 >= W) return;
   const bool act = w < W;
   const uint32_t col = min(w, W - 1);
   typedef uint32_t rows_t __attribute__((ext_vector_type(kRegBlocks)));   // (a vector, so that a scalar index stays in registers)
@@ -861,6 +877,7 @@ constexpr uint32_t kEvtThreads = 256, kEvtHalo = 16, kEvtWindow = kEvtThreads + 
 // workgroup, so that no workgroup is launched for stretches a smaller kernel does not have.)
 __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__restrict__ block_map) {
   const uint2 where = block_map ? block_map[blockIdx.x] : make_uint2(0, blockIdx.x);
+  if (where.x == kNone) return;   // (a die with fewer blocks than the others)
   const DevProg VL_CONSTANT &m = as_constant(mirs)[where.x];
   const DevLive VL_CONSTANT &L = as_constant(lives)[where.x];
   // The neighbours of an entry in the sorted order (its own mention group, the groups before
@@ -1529,10 +1546,12 @@ __device__ inline void f_tile_range(const DevProg VL_CONSTANT &m, const DevLive 
 // instructions and 22 for one of 8,000, where the one launch takes 11.5 and 7.5.)
 struct StageGrid { uint32_t a, b, c; };   // blocks of the three parts, in launch order
 
-__global__ __launch_bounds__(256) void k_stage_count(MIRS, StageGrid g) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
-  const uint32_t bx = blockIdx.x, tx = threadIdx.x;
+__global__ __launch_bounds__(256) void k_stage_count(MIRS, const Grid grid, StageGrid g) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
+  const uint32_t tx = threadIdx.x;
   if (bx < g.a) f_tile_delta(m, L, bx, tx, 256);
   else if (bx < g.a + g.b) f_boundary<false>(m, L, (bx - g.a) * 4 + (tx >> 6), tx & 63u, 64);
   else f_item_count(m, L, bx - g.a - g.b, tx);
@@ -1586,13 +1605,18 @@ __global__ __launch_bounds__(256) void k_seed_count(MIRS) {
 
 // One-dimensional grid.  Part a: per_a workgroups for every kernel; parts b and c: one
 // workgroup per stretch of 256 instructions / entries that exists, named by the block maps.
-__global__ __launch_bounds__(256) void k_stage_fill(MIRS, StageGrid g, uint32_t per_a, const uint2 *__restrict__ map_instr,
+// (Where programs are dealt out to the dies, each part begins at a multiple of eight.)
+__global__ __launch_bounds__(256) void k_stage_fill(MIRS, const Grid grid, StageGrid g, uint32_t per_a, const uint2 *__restrict__ map_instr,
                                                     const uint2 *__restrict__ map_occ) {
   const uint32_t bx = blockIdx.x, tx = threadIdx.x;
   uint2 where;
-  if (bx < g.a) where = make_uint2(bx / per_a, bx % per_a);
+  if (bx < g.a) {
+    const uint32_t per_row = per_a << grid.dealt, y = bx / per_row, x = bx - y * per_row;
+    where = make_uint2((y << grid.dealt) + (x & ((1u << grid.dealt) - 1u)), x >> grid.dealt);
+  }
   else if (bx < g.a + g.b) where = map_instr ? map_instr[bx - g.a] : make_uint2(0, bx - g.a);
   else where = map_occ ? map_occ[bx - g.a - g.b] : make_uint2(0, bx - g.a - g.b);
+  if (where.x >= grid.n) return;
   const DevProg VL_CONSTANT &m = as_constant(mirs)[where.x];
   const DevLive VL_CONSTANT &L = as_constant(lives)[where.x];
   if (bx < g.a) f_seed<true>(m, L, where.y * 4 + (tx >> 6), tx & 63u, 64);
@@ -1600,10 +1624,12 @@ __global__ __launch_bounds__(256) void k_stage_fill(MIRS, StageGrid g, uint32_t 
   else f_seg_fill(m, L, where.y, tx, 256);
 }
 
-__global__ __launch_bounds__(256) void k_stage_finish(MIRS, StageGrid g) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.y];
-  const uint32_t bx = blockIdx.x, tx = threadIdx.x;
+__global__ __launch_bounds__(256) void k_stage_finish(MIRS, const Grid grid, StageGrid g) {
+  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+  if (prog >= grid.n) return;
+  const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
+  const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
+  const uint32_t tx = threadIdx.x;
   if (bx < g.a) f_boundary<true>(m, L, bx * 4 + (tx >> 6), tx & 63u, 64);
   else if (bx < g.a + g.b) f_tile_range(m, L, bx - g.a, tx, 256);
   else if (bx < g.a + g.b + g.c) f_seed_src(m, L, bx - g.a - g.b, tx, 256);
@@ -1696,6 +1722,11 @@ struct vl_batch {
   DevProg *stage_mirs = nullptr;      // [n]
   DevLive *stage_a = nullptr, *stage_b = nullptr;  // [n] each: first and second upload
   uint2 *stage_map = nullptr;         // the block maps (kernel, stretch of 256) of the per-instruction and per-entry launches
+  // The order of the batch's programs in the device tables, and the sizes of the block maps.  dealt:
+  // program k stays on die place[k] % 8 (see Grid).
+  std::vector<uint32_t> place;   // [n]
+  bool dealt = false;
+  size_t blocks_instr = 0, blocks_occ = 0;
   std::vector<vl_live *> lives;
   // result sizes of the last successful call (the analysis of the same kernels with the same
   // options is deterministic, so a recycling call need not read them back)
@@ -1821,8 +1852,33 @@ extern "C" void vl_live_destroy(vl_live *l) {
   if (--b->refs == 0) batch_free(b);
 }
 
-static inline dim3 grid1(uint32_t items, uint32_t threads, uint32_t n) {
-  return dim3(std::max(1u, (items + threads - 1) / threads), n, 1);
+// Deals the programs out to the eight dies where that leaves the dies equally busy: by size, to and fro.
+// A batch of few or very unequal programs, one of whose dies would get a sixteenth more than the
+// mean, stays in the caller's order, every program spread over all dies.
+static void deal(vl_batch *batch, const vl_mir *const *mirs) {
+  const uint32_t n = batch->n;
+  std::vector<uint32_t> by_size(n);
+  for (uint32_t k = 0; k < n; ++k) by_size[k] = k;
+  batch->place = by_size;
+  uint64_t instr[8] = {}, occ[8] = {}, sum_instr = 0, sum_occ = 0, max_instr = 0, max_occ = 0;
+  std::stable_sort(by_size.begin(), by_size.end(), [&](uint32_t a, uint32_t b) { return mirs[a]->h.O > mirs[b]->h.O; });
+  auto place_of = [&](uint32_t r) { return (r & 8u) && (r | 7u) < n ? r ^ 7u : r; };   // every second row of eight backwards
+  for (uint32_t r = 0; r < n; ++r) {
+    const DevMir &m = mirs[by_size[r]]->h;
+    instr[place_of(r) % 8] += stretches(m.N);
+    occ[place_of(r) % 8] += stretches(m.O);
+  }
+  for (uint32_t d = 0; d < 8; ++d) {
+    sum_instr += instr[d];
+    sum_occ += occ[d];
+    max_instr = std::max(max_instr, instr[d]);
+    max_occ = std::max(max_occ, occ[d]);
+  }
+  batch->dealt = n >= 8 && 8 * max_occ <= sum_occ + sum_occ / 16 && 8 * max_instr <= sum_instr + sum_instr / 16;
+  if (batch->dealt)
+    for (uint32_t r = 0; r < n; ++r) batch->place[by_size[r]] = place_of(r);
+  batch->blocks_instr = batch->dealt ? 8 * max_instr : sum_instr;
+  batch->blocks_occ = batch->dealt ? 8 * max_occ : sum_occ;
 }
 
 extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint32_t flags, uint32_t tile_len,
@@ -1851,14 +1907,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   }
   const bool dense = (flags & VL_DENSE_POINTS) != 0;
 
-  // block maps: one entry per stretch of 256 instructions, then one per stretch of 256 entries
-  size_t blocks_instr = 0, blocks_occ = 0;
-  for (uint32_t k = 0; k < n; ++k) {
-    blocks_instr += stretches(mirs[k]->h.N);
-    blocks_occ += stretches(mirs[k]->h.O);
-  }
-  const bool too_many = blocks_instr + blocks_occ > 0x7FFFFFFFull;
-
   // recycle or create the batch
   vl_batch *batch = nullptr;
   bool fresh = false;
@@ -1876,6 +1924,10 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     if (!batch) return VL_E_SHAPE;
     batch->n = n;
     fresh = true;
+    deal(batch, mirs);
+    // block maps: one entry per stretch of 256 instructions, then one per stretch of 256 entries
+    const size_t blocks_instr = batch->blocks_instr, blocks_occ = batch->blocks_occ;
+    const bool too_many = blocks_instr + blocks_occ > 0x7FFFFFFFull;
     if (too_many) { delete batch; return VL_E_RANGE; }
     hipError_t e = hipGetDevice(&batch->device);
     Bump pin;
@@ -1895,6 +1947,13 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   auto fail = [&](int32_t rc) {
     if (fresh) batch_free(batch);
     return rc;
+  };
+
+  const size_t blocks_instr = batch->blocks_instr, blocks_occ = batch->blocks_occ;
+  const std::vector<uint32_t> &place = batch->place;
+  // the tables in the order they have on the device
+  auto placed = [&](const std::vector<DevLive> &from, DevLive *to) {
+    for (uint32_t k = 0; k < n; ++k) to[place[k]] = from[k];
   };
 
   // ---- arena 1 layout: [zeroed zone | counters | rest | device tables] ----
@@ -1968,7 +2027,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     L.seg_base = (uint32_t VL_GLOBAL *)(a1 + off[k].seg_base); L.item_base = (uint32_t VL_GLOBAL *)(a1 + off[k].item_base);
     L.bound_off = (uint32_t VL_GLOBAL *)(a1 + off[k].bound_off);
     L.counters = (uint32_t VL_GLOBAL *)(a1 + o_counters) + (size_t)k * kCounters;
-    progs[k] = mirs[k]->h;
+    progs[place[k]] = mirs[k]->h;
   }
   batch->dev_mirs = (DevProg *)(a1 + o_mirs);
   batch->dev_lives = (DevLive *)(a1 + o_lives);
@@ -2028,15 +2087,27 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
                               memcmp(batch->uploaded.data(), h.data(), batch->uploaded.size()) == 0;
   if (!tables_current) {
     batch->uploaded.clear();
-    memcpy(batch->stage_a, h.data(), (size_t)n * sizeof(DevLive));
+    placed(h, batch->stage_a);
     if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_mirs, progs, (size_t)n * sizeof(DevProg), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(a1 + o_lives, batch->stage_a, (size_t)n * sizeof(DevLive), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess && n > 1) {
-      uint2 *at = batch->stage_map;
-      for (uint32_t k = 0; k < n; ++k)
-        for (uint32_t x = 0; x < (mirs[k]->h.N + 255u) / 256u; ++x) *at++ = make_uint2(k, x);
-      for (uint32_t k = 0; k < n; ++k)
-        for (uint32_t x = 0; x < (mirs[k]->h.O + 255u) / 256u; ++x) *at++ = make_uint2(k, x);
+      uint2 *const at = batch->stage_map;
+      std::vector<uint32_t> prog(n);
+      for (uint32_t k = 0; k < n; ++k) prog[place[k]] = k;
+      // die d's blocks are the entries d, d + 8, ...; `step` 1: all in a row
+      auto map_of = [&](uint2 *map, size_t len, bool occ) {
+        const uint32_t step = batch->dealt ? 8u : 1u;
+        for (uint32_t d = 0; d < step; ++d) {
+          size_t x = d;
+          for (uint32_t p = d; p < n; p += step) {
+            const uint32_t all = stretches(occ ? mirs[prog[p]]->h.O : mirs[prog[p]]->h.N);
+            for (uint32_t y = 0; y < all; ++y, x += step) map[x] = make_uint2(p, y);
+          }
+          for (; x < len; x += step) map[x] = make_uint2(kNone, 0);
+        }
+      };
+      map_of(at, blocks_instr, false);
+      map_of(at + blocks_instr, blocks_occ, true);
       e = hipMemcpyAsync(a1 + o_map, batch->stage_map, (blocks_instr + blocks_occ) * sizeof(uint2), hipMemcpyHostToDevice, stream);
     }
   }
@@ -2056,9 +2127,17 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   }();
   const bool hist_lds = lds_ok && (size_t)maxV * 4 <= 128 * 1024;
   // (k_group clears block sets by 32-bit indices)
+  auto blocks = [](uint32_t items, uint32_t per) { return std::max(1u, (items + per - 1) / per); };
+  // a launch of so many blocks for every program
+  struct Launch { dim3 dim; Grid grid; };
+  auto all_progs = [&](uint32_t per) {
+    // (threads in a row of the grid stay below 2^32)
+    return batch->dealt && per < (1u << 18) ? Launch{dim3(8 * per, (n + 7) / 8), {n, 3}} : Launch{dim3(per, n), {n, 0}};
+  };
   const bool small = hist_lds && maxO <= kGroupMaxOcc && (uint64_t)maxB * maxW < (1ull << 32) - 4;
   if (small) {
-    k_group<<<dim3((maxO + kGroupSlice - 1) / kGroupSlice, n), 1024, (size_t)maxV * 4, stream>>>(dm, dl);
+    const Launch l = all_progs(blocks(maxO, kGroupSlice));
+    k_group<<<l.dim, 1024, (size_t)maxV * 4, stream>>>(dm, dl, l.grid);
   } else {
     zero_async(a1, zero_bytes, stream);
     const dim3 slices((maxO + kSlice - 1) / kSlice, n);
@@ -2071,19 +2150,21 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   }
   {
     const size_t lds = std::min<size_t>((size_t)maxB * std::min(maxW, kOrdWords) * 8, 40 * 1024);
-    (small ? k_order<false> : k_order<true>)<<<grid1(maxO, kOrdStretch, n), kOrdThreads, lds, stream>>>(dm, dl, (uint32_t)(lds / 4));
+    const Launch l = all_progs(blocks(maxO, kOrdStretch));
+    (small ? k_order<false> : k_order<true>)<<<l.dim, kOrdThreads, lds, stream>>>(dm, dl, l.grid, (uint32_t)(lds / 4));
   }
   {
     const size_t lds = ((size_t)maxB * 3 + 1) * 64 * 4 + ((size_t)maxB * 3 + 1 + maxE) * 4;
-    if (maxB <= kRegBlocks) k_fixpoint_regs<<<grid1(maxW, 64, n), 64, 0, stream>>>(dm, dl);
-    else if (lds <= 64 * 1024) k_fixpoint<true><<<grid1(maxW, 64, n), 64, lds, stream>>>(dm, dl);
-    else k_fixpoint<false><<<grid1(maxW, 64, n), 64, 0, stream>>>(dm, dl);
+    const Launch l = all_progs(blocks(maxW, 64));
+    if (maxB <= kRegBlocks) k_fixpoint_regs<<<l.dim, 64, 0, stream>>>(dm, dl, l.grid);
+    else if (lds <= 64 * 1024) k_fixpoint<true><<<l.dim, 64, lds, stream>>>(dm, dl, l.grid);
+    else k_fixpoint<false><<<l.dim, 64, 0, stream>>>(dm, dl, l.grid);
   }
   static_assert(kEvtThreads == kStretch && kStretch == 256, "the block map counts stretches of 256 entries");
   if (blocks_occ) k_events<<<(uint32_t)blocks_occ, kEvtThreads, 0, stream>>>(dm, dl, map_occ);
-  auto blocks = [](uint32_t items, uint32_t per) { return std::max(1u, (items + per - 1) / per); };
   const StageGrid g_count = {maxT, blocks(maxB, 4), blocks(maxN, TB * kStageReps)};
-  k_stage_count<<<dim3(g_count.a + g_count.b + g_count.c, n), 256, (size_t)maxW * 4, stream>>>(dm, dl, g_count);
+  const Launch l_count = all_progs(g_count.a + g_count.b + g_count.c);
+  k_stage_count<<<l_count.dim, 256, (size_t)maxW * 4, stream>>>(dm, dl, l_count.grid, g_count);
   if (maxW <= kTileWords && maxT <= kTileCounts) {
     k_stage_scan<true><<<dim3(1, n), 1024, 0, stream>>>(dm, dl);
   } else {
@@ -2107,15 +2188,17 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     }
     const int32_t rc2 = layout2();
     if (rc2 != VL_OK) return fail(rc2);
-    memcpy(batch->stage_b, h.data(), (size_t)n * sizeof(DevLive));
+    placed(h, batch->stage_b);
     e = hipMemcpyAsync(a1 + o_lives, batch->stage_b, (size_t)n * sizeof(DevLive), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return fail(hip_fail(e));
   }
   const uint32_t per_a = blocks(maxT, 4);
-  const StageGrid g_fill = {per_a * n, (uint32_t)blocks_instr, (uint32_t)blocks_occ};
+  const Grid in_dies = {n, batch->dealt ? 3u : 0u};
+  const StageGrid g_fill = {per_a * (batch->dealt ? (n + 7) / 8 * 8 : n), (uint32_t)blocks_instr, (uint32_t)blocks_occ};
   const StageGrid g_fin = {blocks(maxB, 4), blocks(maxT, TB), blocks(max_seed, TB)};
-  k_stage_fill<<<g_fill.a + g_fill.b + g_fill.c, 256, 0, stream>>>(dm, dl, g_fill, per_a, map_instr, map_occ);
-  k_stage_finish<<<dim3(g_fin.a + g_fin.b + g_fin.c + blocks(maxV + 1, TB), n), 256, 0, stream>>>(dm, dl, g_fin);
+  k_stage_fill<<<g_fill.a + g_fill.b + g_fill.c, 256, 0, stream>>>(dm, dl, in_dies, g_fill, per_a, map_instr, map_occ);
+  const Launch l_fin = all_progs(g_fin.a + g_fin.b + g_fin.c + blocks(maxV + 1, TB));
+  k_stage_finish<<<l_fin.dim, 256, 0, stream>>>(dm, dl, l_fin.grid, g_fin);
   if (dense) {
     k_dense<<<dim3((maxW + 63) / 64, maxT, n), 256, 0, stream>>>(dm, dl);
   }
@@ -2140,7 +2223,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   for (uint32_t k = 0; k < n; ++k) {
     vl_live *l = batch->lives[k];
     l->h = h[k];
-    l->dev = batch->dev_lives + k;
+    l->dev = batch->dev_lives + place[k];
     l->span = span;
     live[k] = l;
   }

@@ -145,3 +145,12 @@ def test_programs_around_what_the_host_derives():
     assert sides == {True, False}
     last = [flow_program(8, 5, v, 300) for v in (500, 3000, 6000)]
     check(last)
+
+
+@pytest.mark.parametrize("n, n_block", [(8, 5), (9, 5), (16, 5), (48, 3), (48, 40), (163, 2)])
+@pytest.mark.parametrize("alike", [True, False])
+def test_batches_dealt_out_to_the_dies(n, n_block, alike):
+    """programs alike (eight and multiples: dealt out evenly; 163: rows of eight, the last of three) and of mixed
+    sizes (dealt out where to and fro leaves the dies equally busy)"""
+    rng = np.random.default_rng(n)
+    check([flow_program(k, n_block, 40 if alike else int(rng.integers(20, 400)), 8 if alike else 3 + k % 7) for k in range(n)], dense=n % 16 == 0)
