@@ -312,9 +312,10 @@ __global__ __launch_bounds__(256) void k_sort(MIRS) {
   else f_sort_short(m, L, blockIdx.x - kLongBlocks, threadIdx.x);
 }
 
-// The usual way: a workgroup per 16,384 occurrences of a program, all of which count the whole
+// The usual way: a workgroup per `slice` occurrences of a program (2,048 to 16,384), all of which count the whole
 // program: the LDS of each then holds, a word per vreg, first the list lengths, then the lists'
-// starts, then the places its own occurrences go to (the starts plus what earlier workgroups place),
+// starts, then the places its own occurrences go to (the starts plus what earlier workgroups place;
+// kPacked: up to 65,535 occurrences, whose count and whose count in earlier slices share a word, otherwise those are counted anew),
 // and nothing is cleared, reserved or prefixed in memory, nor in a launch of its own.  Occurrences
 // are placed 1,024 at a time, with a barrier in between: what is out of order in a list
 // afterwards lies within one such round, and the next kernel puts it right.  It also clears what
@@ -323,9 +324,13 @@ __global__ __launch_bounds__(256) void k_sort(MIRS) {
 // programs (256 programs of 1,000-20,000 instructions: 50 us; a workgroup per program 58 us;
 // clearing, counting, scanning and placing in launches of their own 86 us).
 constexpr uint32_t kRound = 1024;
-constexpr uint32_t kGroupSlice = 16 * kRound;
+constexpr uint32_t kGroupRounds = 16;         // most rounds of a workgroup, one after the other
+// Few programs are cut into more slices, of fewer rounds, while there are compute units for them; up to eight of a
+// program, since each reads and counts the whole of it.
+constexpr uint32_t kGroupFew = 256, kGroupSlices = 8;
 constexpr uint32_t kGroupMaxOcc = 1u << 17;   // with more in some program, counting it all in every workgroup costs too much
-__global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
+template <bool kPacked>
+__global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid, const uint32_t slice) {
   const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
   if (prog >= grid.n) return;
   const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
@@ -333,9 +338,9 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
   extern __shared__ uint32_t sm[];   // [V]
   __shared__ uint32_t part[16];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t s0 = bx * kGroupSlice, n_slices = max(1u, (m.O + kGroupSlice - 1) / kGroupSlice), s1 = min(m.O, s0 + kGroupSlice);
+  const uint32_t s0 = bx * slice, n_slices = max(1u, (m.O + slice - 1) / slice), s1 = min(m.O, s0 + slice);
   if (bx >= n_slices) return;
-  auto add_all = [&](uint32_t end) {   // sm[v] += mentions among the occurrences [0, end)
+  auto add_all = [&](uint32_t end) {   // sm[v] += mentions among the occurrences [0, end); kPacked: high half, those before the slice
     for (uint32_t o = tid * 4; o < end; o += 4 * 4 * 1024) {
       u32x4 v[4];
 #pragma unroll
@@ -352,8 +357,8 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
 #pragma unroll
       for (uint32_t u = 0; u < 4; ++u)
 #pragma unroll
-        for (uint32_t t = 0; t < 4; ++t)
-          if (v[u][t] != kNone) atomicAdd(&sm[v[u][t]], 1u);
+        for (uint32_t t = 0; t < 4; ++t)   // (a slice begins at a multiple of four)
+          if (v[u][t] != kNone) atomicAdd(&sm[v[u][t]], kPacked && o + u * 4 * 1024 < s0 ? 0x10001u : 1u);
     }
   };
   for (uint32_t v = tid; v < m.V; v += 1024) sm[v] = 0;
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
   const uint32_t per = (m.V + 1023u) / 1024u, lo = min(m.V, tid * per), hi = min(m.V, lo + per);
   uint32_t sum = 0;
 #pragma unroll 4
-  for (uint32_t v = lo; v < hi; ++v) sum += sm[v];
+  for (uint32_t v = lo; v < hi; ++v) sum += kPacked ? sm[v] & 0xFFFFu : sm[v];
   uint32_t incl = sum;
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
@@ -386,19 +391,24 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
 #pragma unroll 4
   for (uint32_t v = lo; v < hi; ++v) {
     const uint32_t c = sm[v];
-    sm[v] = run;
-    run += c;
+    sm[v] = kPacked ? run | (c & 0xFFFF0000u) : run;
+    run += kPacked ? c & 0xFFFFu : c;
   }
   __syncthreads();
   for (uint32_t v = bx * 1024 + tid; v < m.V; v += n_slices * 1024) {
-    const uint32_t at = sm[v], next = v + 1 < m.V ? sm[v + 1] : m.O;
+    const uint32_t start = sm[v], after = v + 1 < m.V ? sm[v + 1] : m.O;
+    const uint32_t at = kPacked ? start & 0xFFFFu : start, next = kPacked ? after & 0xFFFFu : after;
     L.vcnt[v] = at;
     L.last_live[v] = 0;
     if (at == next) L.first[v] = kNone;
   }
   if (bx == 0 && tid == 0) L.vcnt[m.V] = m.O;
   __syncthreads();
-  add_all(min(s0, m.O));
+  if (kPacked) {
+    for (uint32_t v = tid; v < m.V; v += 1024) sm[v] = (sm[v] & 0xFFFFu) + (sm[v] >> 16);
+  } else {
+    add_all(min(s0, m.O));
+  }
   __syncthreads();
   // the vregs of the next two rounds are in flight
   auto vreg_of = [&](uint32_t o) { return o < s1 ? m.occ_vreg[o] : 0u; };
@@ -431,21 +441,26 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid) {
 //
 // (A launch that sorted each list in the registers of a lane and one that summarised the sorted
 // entries took 38 and 45 us where this takes 70, but this needs no sorted list and no cleared counters.)
-constexpr uint32_t kOrdStretch = 1024, kOrdThreads = 256;
+constexpr uint32_t kOrdStretch = 1024;
 constexpr uint32_t kOrdBack = 72;        // entries before the stretch that are put in order too: one more than an instruction has
 constexpr uint32_t kOrdMargin = 128;
 constexpr uint32_t kOrdWindow = kOrdBack + kOrdStretch + 2 * kOrdMargin;
-constexpr uint32_t kOrdPer = (kOrdWindow + kOrdThreads - 1) / kOrdThreads;
 constexpr uint32_t kOrdWords = kOrdStretch / 32 + 1;   // most words a stretch touches when every vreg is mentioned
 static_assert(kOrdBack > kMaxOperands, "the look-back has to leave an instruction");
 
-template <bool kSorted>
+// Threads of a workgroup: 512 (the sweep of 256 programs: 60 us a launch; 66 with 256, 81 with 1,024, of which
+// a compute unit holds two workgroups); 1,024 where the launch has no more workgroups than the device
+// holds at once and a workgroup's chain is what it takes (8,000 instructions: 8.2 us, 9.7 with 512, 14.2 with
+// 256; 2,000: 6.6, 8.4, 11.9).
+constexpr uint32_t kOrdFew = 512;   // workgroups of 1,024 threads that the device holds
+template <bool kSorted, uint32_t kOrdThreads>
 __global__ __launch_bounds__(kOrdThreads) void k_order(MIRS, const Grid grid, const uint32_t lds_words) {
   const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
   if (prog >= grid.n) return;
   const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
   const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
   extern __shared__ uint32_t sm[];
+  constexpr uint32_t kOrdPer = (kOrdWindow + kOrdThreads - 1) / kOrdThreads;
   // by place in the window; s_o holds the occurrences as they stand, then in order with kRecKeeps
   __shared__ uint32_t s_o[kOrdWindow], s_v[kOrdWindow], s_ifl[kOrdWindow], s_blk[kOrdWindow];
   __shared__ uint32_t heads[kOrdPer * kOrdThreads / 32 + 1];   // a bit per place: a group begins here
@@ -2121,7 +2136,7 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   // LDS histograms over the vregs when they fit
   static const bool lds_ok = [] {
     bool ok = true;
-    for (const void *f : {(const void *)k_group, (const void *)k_count<true>, (const void *)k_place<true>})
+    for (const void *f : {(const void *)k_group<true>, (const void *)k_group<false>, (const void *)k_count<true>, (const void *)k_place<true>})
       ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) == hipSuccess;
     return ok;
   }();
@@ -2136,8 +2151,10 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   };
   const bool small = hist_lds && maxO <= kGroupMaxOcc && (uint64_t)maxB * maxW < (1ull << 32) - 4;
   if (small) {
-    const Launch l = all_progs(blocks(maxO, kGroupSlice));
-    k_group<<<l.dim, 1024, (size_t)maxV * 4, stream>>>(dm, dl, l.grid);
+    uint32_t rounds = kGroupRounds;
+    while (rounds > 2 && blocks_occ * kStretch / (rounds / 2 * kRound) + n <= kGroupFew && maxO / (rounds / 2 * kRound) < kGroupSlices) rounds /= 2;
+    const Launch l = all_progs(blocks(maxO, rounds * kRound));
+    (rounds < kGroupRounds && maxO < (1u << 16) ? k_group<true> : k_group<false>)<<<l.dim, 1024, (size_t)maxV * 4, stream>>>(dm, dl, l.grid, rounds * kRound);
   } else {
     zero_async(a1, zero_bytes, stream);
     const dim3 slices((maxO + kSlice - 1) / kSlice, n);
@@ -2151,7 +2168,10 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   {
     const size_t lds = std::min<size_t>((size_t)maxB * std::min(maxW, kOrdWords) * 8, 40 * 1024);
     const Launch l = all_progs(blocks(maxO, kOrdStretch));
-    (small ? k_order<false> : k_order<true>)<<<l.dim, kOrdThreads, lds, stream>>>(dm, dl, l.grid, (uint32_t)(lds / 4));
+    const uint32_t words = (uint32_t)(lds / 4);
+    const bool few = blocks_occ / (kOrdStretch / kStretch) <= kOrdFew;
+    if (few) (small ? k_order<false, 1024> : k_order<true, 1024>)<<<l.dim, 1024, lds, stream>>>(dm, dl, l.grid, words);
+    else (small ? k_order<false, 512> : k_order<true, 512>)<<<l.dim, 512, lds, stream>>>(dm, dl, l.grid, words);
   }
   {
     const size_t lds = ((size_t)maxB * 3 + 1) * 64 * 4 + ((size_t)maxB * 3 + 1 + maxE) * 4;

@@ -1,5 +1,5 @@
 """Occurrences grouped by vreg and put in order, at the sizes where the work is cut: rounds of 1,024
-and slices of 16,384 occurrences, values mentioned hundreds of times in a round (their group reaches
+and slices of 2,048 to 16,384 occurrences, values mentioned hundreds of times in a round (their group reaches
 beyond what a workgroup has at hand), more than 2^17 occurrences or more vregs than LDS counts
 (the large-program sort); the whole analysis and some verdicts against the oracle, exactly."""
 import numpy as np
@@ -60,6 +60,13 @@ def test_rounds_and_slices(n_occ, V, heavy, share):
         assert_results_equal(vlo.verify(m, an, rows, threads=8), gpu_verify(hm, hl, [rows])[0], m.name)
     finally:
         free(hm, hl)
+
+
+@pytest.mark.parametrize("n_occ,V,heavy,share", [(2048, 60, 2, 0.5), (2049, 700, 1, 0.9), (4097, 64, 3, 0.5), (16385, 300, 1, 1.0),
+                                                 (65535, 6, 1, 1.0), (65536, 6, 1, 1.0), (65535, 9000, 5, 0.4)])
+def test_slices_of_few_programs(n_occ, V, heavy, share):
+    """slices of 2,048 and more, counts in half a word up to 65,535 occurrences (nearly all of one value)"""
+    test_rounds_and_slices(n_occ, V, heavy, share)
 
 
 @pytest.mark.parametrize("n_occ,V", [(140000, 200), (60000, 33000)])
