@@ -1548,6 +1548,76 @@ __device__ inline void f_tile_range(const DevProg VL_CONSTANT &m, const DevLive 
   L.tile_range[2 * t + 1] = end;
 }
 
+// ---- 5d. dense per-point bitsets (optional) ---------------------------------------------
+// Every occupy / release event flips one bit of the occupied set.  A workgroup takes 64 bitset
+// words of one tile: 64 instructions at a time, it XORs each event into the LDS row of the
+// instruction at which it takes effect (an event per thread, its row found by bisection in the
+// rows' first events), then prefix-XORs the rows downwards from the tile's live-in row, four
+// wavefronts with 16 rows each, and writes every row once.  What changes at a block boundary comes from
+// the two blocks' sets, not from the boundary's events, so that nothing here waits for those and a call of
+// few programs needs no launch for it (2,000 instructions: 47.6 -> 43.6 us a call).
+// (A pass of global atomics over cleared rows, an instruction per lane, and a second pass that prefixed
+// them in place took 33 and 48 us for 2,000 instructions and 1,500 vregs: a lane with a block boundary's events walked them
+// one by one, and the prefix waited for memory at every row.)
+constexpr uint32_t kDenseRows = 64;
+__device__ inline void f_dense(const DevProg VL_CONSTANT &m, const DevLive VL_CONSTANT &L, const uint32_t t, const uint32_t w0) {
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, w = w0 + lane;
+  if (t >= L.T || w0 >= m.W) return;
+  // per row: its events [start, stop), and the block that begins there (0: none, or the tile does too)
+  __shared__ uint32_t rows[kDenseRows][64], start[kDenseRows], stop[kDenseRows], begins[kDenseRows], total[4][64];
+  constexpr uint32_t kPer = kDenseRows / 4;
+  const uint32_t i0 = t * L.tile_len, i1 = min(m.N, i0 + L.tile_len);
+  uint32_t cur = t && w < m.W ? L.tile_live[(size_t)t * m.W + w] : 0u;
+  for (uint32_t c0 = i0; c0 < i1; c0 += kDenseRows) {
+    const uint32_t n = min(kDenseRows, i1 - c0);
+    if (threadIdx.x < kDenseRows) {
+      const uint32_t i = min(c0 + threadIdx.x, i1 - 1), b = m.instr_blk[i], item = i + b + 1;
+      start[threadIdx.x] = L.item_off[item];
+      stop[threadIdx.x] = L.item_off[item + 1];
+      begins[threadIdx.x] = threadIdx.x < n && i != i0 && m.blk_start[b] == i ? b : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) rows[wave * kPer + k][lane] = 0;
+    __syncthreads();
+    for (uint32_t e = start[0] + threadIdx.x; e < stop[n - 1]; e += 256) {
+      uint32_t lo = 0, hi = n;   // the last row whose first event is e or earlier
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (start[mid] <= e) lo = mid; else hi = mid;
+      }
+      if (e >= stop[lo]) continue;   // a boundary's
+      const uint32_t v = L.plan[e].x >> 8, col = (v >> 5) - w0;
+      if (col < 64) atomicXor(&rows[lo][col], 1u << (v & 31));
+    }
+    __syncthreads();
+    uint32_t x = 0, down[kPer];
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      const uint32_t b = __builtin_amdgcn_readfirstlane(begins[wave * kPer + k]);
+      if (b && w < m.W) x ^= L.live_out[(size_t)(b - 1) * m.W + w] ^ L.live_in[(size_t)b * m.W + w];
+      down[k] = x ^= rows[wave * kPer + k][lane];
+    }
+    total[wave][lane] = x;
+    __syncthreads();
+    uint32_t above = cur;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      above ^= k < wave ? total[k][lane] : 0u;
+      cur ^= total[k][lane];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      const uint32_t r = wave * kPer + k;
+      if (r < n && w < m.W) L.live_after[(size_t)(c0 + r) * m.W + w] = above ^ down[k];
+    }
+    __syncthreads();   // the shared rows are cleared for the next ones
+  }
+}
+
+__global__ __launch_bounds__(256) void k_dense(MIRS) {
+  f_dense(as_constant(mirs)[blockIdx.z], as_constant(lives)[blockIdx.z], blockIdx.y, blockIdx.x * 64);
+}
+
 // ---- stages ---------------------------------------------------------------------------
 // After the per-occurrence pass three chains are independent: the event stream (counts, prefix,
 // fill, chunk cuts), the intervals (counts, prefix, fill, offsets) and the tile live-ins (flips,
@@ -1639,78 +1709,26 @@ __global__ __launch_bounds__(256) void k_stage_fill(MIRS, const Grid grid, Stage
   else f_seg_fill(m, L, where.y, tx, 256);
 }
 
-__global__ __launch_bounds__(256) void k_stage_finish(MIRS, const Grid grid, StageGrid g) {
-  const uint32_t prog = grid_prog(grid), bx = grid_block(grid);
+// kDense: the first n_dense workgroups of a program write its dense points, across words 64 at a time, then tiles
+template <bool kDense>
+__global__ __launch_bounds__(256) void k_stage_finish(MIRS, const Grid grid, StageGrid g, uint32_t n_dense, uint32_t across) {
+  const uint32_t prog = grid_prog(grid);
+  uint32_t bx = grid_block(grid);
   if (prog >= grid.n) return;
   const DevProg VL_CONSTANT &m = as_constant(mirs)[prog];
   const DevLive VL_CONSTANT &L = as_constant(lives)[prog];
   const uint32_t tx = threadIdx.x;
+  if (kDense) {
+    if (bx < n_dense) {
+      f_dense(m, L, bx / across, bx % across * 64);
+      return;
+    }
+    bx -= n_dense;
+  }
   if (bx < g.a) f_boundary<true>(m, L, bx * 4 + (tx >> 6), tx & 63u, 64);
   else if (bx < g.a + g.b) f_tile_range(m, L, bx - g.a, tx, 256);
   else if (bx < g.a + g.b + g.c) f_seed_src(m, L, bx - g.a - g.b, tx, 256);
   else f_hull(m, L, bx - g.a - g.b - g.c, tx, 256);
-}
-
-// ---- 5d. dense per-point bitsets (optional) ---------------------------------------------
-// Every occupy / release event flips one bit of the occupied set.  A workgroup takes 64 bitset
-// words of one tile: 64 instructions at a time, it XORs each event into the LDS row of the
-// instruction at which it takes effect (an event per thread, its row found by bisection in the
-// rows' first events), then prefix-XORs the rows downwards from the tile's live-in row, four
-// wavefronts with 16 rows each, and writes every row once.  (A pass of global atomics over
-// cleared rows, an instruction per lane, and a second pass that prefixed them in place took 33 and
-// 48 us for 2,000 instructions and 1,500 vregs: a lane with a block boundary's events walked them
-// one by one, and the prefix waited for memory at every row.)
-constexpr uint32_t kDenseRows = 64;
-__global__ __launch_bounds__(256) void k_dense(MIRS) {
-  const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.z];
-  const DevLive VL_CONSTANT &L = as_constant(lives)[blockIdx.z];
-  const uint32_t t = blockIdx.y, w0 = blockIdx.x * 64, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, w = w0 + lane;
-  if (t >= L.T || w0 >= m.W) return;
-  __shared__ uint32_t rows[kDenseRows][64], start[kDenseRows + 1], total[4][64];
-  constexpr uint32_t kPer = kDenseRows / 4;
-  const uint32_t i0 = t * L.tile_len, i1 = min(m.N, i0 + L.tile_len);
-  uint32_t cur = t && w < m.W ? L.tile_live[(size_t)t * m.W + w] : 0u;
-  for (uint32_t c0 = i0; c0 < i1; c0 += kDenseRows) {
-    const uint32_t n = min(kDenseRows, i1 - c0);
-    if (threadIdx.x < n) {
-      // the events of a block boundary go with the block's first instruction; a tile that starts
-      // there takes its row from the seed instead
-      const uint32_t i = c0 + threadIdx.x, b = m.instr_blk[i], item = i + b + 1;
-      start[threadIdx.x] = L.item_off[i != i0 && m.blk_start[b] == i ? item - 1 : item];
-      if (threadIdx.x == n - 1) start[n] = L.item_off[item + 1];
-    }
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) rows[wave * kPer + k][lane] = 0;
-    __syncthreads();
-    for (uint32_t e = start[0] + threadIdx.x; e < start[n]; e += 256) {
-      const uint32_t v = L.plan[e].x >> 8, col = (v >> 5) - w0;
-      if (col >= 64) continue;
-      uint32_t lo = 0, hi = n;   // the last row whose first event is e or earlier
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (start[mid] <= e) lo = mid; else hi = mid;
-      }
-      atomicXor(&rows[lo][col], 1u << (v & 31));
-    }
-    __syncthreads();
-    uint32_t x = 0, down[kPer];
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) down[k] = x ^= rows[wave * kPer + k][lane];
-    total[wave][lane] = x;
-    __syncthreads();
-    uint32_t above = cur;
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      above ^= k < wave ? total[k][lane] : 0u;
-      cur ^= total[k][lane];
-    }
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-      const uint32_t r = wave * kPer + k;
-      if (r < n && w < m.W) L.live_after[(size_t)(c0 + r) * m.W + w] = above ^ down[k];
-    }
-    __syncthreads();   // the shared rows are cleared for the next ones
-  }
 }
 
 struct Bump {
@@ -2217,9 +2235,14 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
   const StageGrid g_fill = {per_a * (batch->dealt ? (n + 7) / 8 * 8 : n), (uint32_t)blocks_instr, (uint32_t)blocks_occ};
   const StageGrid g_fin = {blocks(maxB, 4), blocks(maxT, TB), blocks(max_seed, TB)};
   k_stage_fill<<<g_fill.a + g_fill.b + g_fill.c, 256, 0, stream>>>(dm, dl, in_dies, g_fill, per_a, map_instr, map_occ);
-  const Launch l_fin = all_progs(g_fin.a + g_fin.b + g_fin.c + blocks(maxV + 1, TB));
-  k_stage_finish<<<l_fin.dim, 256, 0, stream>>>(dm, dl, l_fin.grid, g_fin);
-  if (dense) {
+  // dense points go along where they are few workgroups, as many as the device takes at once; where they are
+  // many, a launch more is nothing beside them
+  const uint32_t across = (maxW + 63) / 64;
+  const bool dense_along = dense && (uint64_t)across * maxT * n <= 1024;
+  const uint32_t n_dense = dense_along ? across * maxT : 0u;
+  const Launch l_fin = all_progs(n_dense + g_fin.a + g_fin.b + g_fin.c + blocks(maxV + 1, TB));
+  (dense_along ? k_stage_finish<true> : k_stage_finish<false>)<<<l_fin.dim, 256, 0, stream>>>(dm, dl, l_fin.grid, g_fin, n_dense, across);
+  if (dense && !dense_along) {
     k_dense<<<dim3((maxW + 63) / 64, maxT, n), 256, 0, stream>>>(dm, dl);
   }
   e = hipGetLastError();

@@ -20,7 +20,7 @@ def _need_gpu():
     vl.load()
 
 
-@pytest.mark.parametrize("tile_len", [0, 63, 64, 65, 128, 200, 5000])
+@pytest.mark.parametrize("tile_len", [0, 16, 63, 64, 65, 128, 200, 5000])   # (16: a launch of its own)
 def test_tile_and_row_edges(tile_len):
     # 47 words; 64 and 65 words; mixed shapes; a chain of 60 blocks
     mirs = [gen.Kernel(gen.LOOP3, 0x2D0, 2000, 1500).mir, gen.Kernel(gen.STRAIGHT, 0x2D1, 64 * 32, 64 * 32).mir,
