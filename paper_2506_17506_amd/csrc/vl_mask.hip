@@ -256,6 +256,26 @@ struct Tables {
 };
 Tables g_tables[16];
 
+// How many of the queries at q, n at most, go on with the run that `u` (checked) belongs to: the same but for the
+// row, which is `next` and so on.  A run of many queries is what a decoding step of many samples makes, and the
+// host's pass over them took longer than the kernel (64 programs x 100: 16.6 us a call, 8.9 of them the kernel;
+// 13.8 this way).  Eight queries to a branch.
+inline uint32_t same_run(const vl_mask_query *q, uint32_t n, const vl_mask_query &u, const uint16_t *next, int64_t stride) {
+  const uintptr_t mir = (uintptr_t)u.mir, live = (uintptr_t)u.live, step = (uintptr_t)(stride * 2);
+  uintptr_t at = (uintptr_t)next;
+  auto other = [&](const vl_mask_query &x, uintptr_t cand) {
+    return ((uintptr_t)x.mir ^ mir) | ((uintptr_t)x.live ^ live) | ((uintptr_t)x.cand ^ cand) | (uintptr_t)((x.occ ^ u.occ) | x.reserved0) | (uintptr_t)!cand;
+  };
+  uint32_t k = 0;
+  for (; k + 8 <= n; k += 8, at += 8 * step) {
+    uintptr_t any = 0;
+    for (uint32_t t = 0; t < 8; ++t) any |= other(q[k + t], at + t * step);
+    if (any) break;
+  }
+  while (k < n && !other(q[k], at)) { ++k; at += step; }
+  return k;
+}
+
 }  // namespace
 
 extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n, uint32_t *masks, vl_stream stream_) {
@@ -333,6 +353,10 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
       if (u.cand == run.cand + (int64_t)run.count * run.stride) {   // (an odd distance in bytes is no multiple of an element)
         ++run.count;
         next = u.cand + run.stride;
+        const uint32_t more = same_run(queries + j + 1, n - j - 1, u, next, run.stride);
+        run.count += more;
+        next += (int64_t)more * run.stride;
+        j += more;
         continue;
       }
     }
