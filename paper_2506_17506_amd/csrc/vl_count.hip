@@ -323,8 +323,14 @@ __device__ __attribute__((always_inline)) inline void count_unit(const Unit &W, 
       const u16x2 x = __builtin_elementwise_sub_sat(ra, rb), y = __builtin_elementwise_sub_sat(rb, ra);
       return __builtin_elementwise_min(__builtin_elementwise_min(__builtin_elementwise_sub_sat(wb, x), __builtin_elementwise_sub_sat(wa, y)), one);
     };
+    // The next record is in flight while one is looked at, since a compute unit has few wavefronts to look at others
+    // meanwhile (64 programs x 100, half failing: 298 -> 292 us a call).  (Attributes read ahead beside it: 200 small programs
+    // 235 -> 261.)
+    u32x4 next_lo = 0, next_hi = 0;
+    if (tid < n) { next_lo = records[2 * tid]; next_hi = records[2 * tid + 1]; }
     for (uint32_t x = tid; x < n; x += 1024) {
-      const u32x4 lo = records[2 * x], hi = records[2 * x + 1];
+      const u32x4 lo = next_lo, hi = next_hi;
+      if (x + 1024 < n) { next_lo = records[2 * (x + 1024)]; next_hi = records[2 * (x + 1024) + 1]; }
       const uint32_t b[kPartners] = {lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
       const Regs ta = at(lo.x);
       Regs tb[kPartners];
