@@ -33,6 +33,8 @@ namespace {
 // workgroups go to the eight dies in turn, each with an L2 of its own; where a batch deals its programs out
 // to the dies (`deal`), program p stays on die p % 8 through every launch, so that what its workgroups
 // gather and scatter meets in one L2: row y of the grid then holds programs 8 y to 8 y + 7 side by side.
+// (256 programs of 1,000-20,000 instructions, us per launch, spread over all dies and dealt out: k_group 50 and 31,
+// k_events 98 and 78, k_stage_count 35 and 29, k_stage_finish 30 and 21.)
 struct Grid { uint32_t n, dealt; };   // programs; 3 where they are dealt out, else 0
 __device__ inline uint32_t grid_prog(Grid g) { return g.dealt ? blockIdx.y * 8u + (blockIdx.x & 7u) : blockIdx.y; }
 __device__ inline uint32_t grid_block(Grid g) { return blockIdx.x >> g.dealt; }
@@ -321,8 +323,8 @@ __global__ __launch_bounds__(256) void k_sort(MIRS) {
 // afterwards lies within one such round, and the next kernel puts it right.  It also clears what
 // the later kernels add to.
 // What bounds it: LDS atomics and the placing stores, 64 lines per wavefront, of the largest
-// programs (256 programs of 1,000-20,000 instructions: 50 us; a workgroup per program 58 us;
-// clearing, counting, scanning and placing in launches of their own 86 us).
+// programs (256 programs of 1,000-20,000 instructions: 31 us, 50 before programs were dealt out to the dies; a
+// workgroup per program 58 us then; clearing, counting, scanning and placing in launches of their own 86 us).
 constexpr uint32_t kRound = 1024;
 constexpr uint32_t kGroupRounds = 16;         // most rounds of a workgroup, one after the other
 // Few programs are cut into more slices, of fewer rounds, while there are compute units for them; up to eight of a
