@@ -101,6 +101,19 @@ constexpr uint32_t kWalkChunk = 64, kWalkRing = 192;
 constexpr uint32_t kWalkReach = 2 * kWalkChunk;
 constexpr uint32_t kKeepMaxGap = 4096;   // longer gaps are not worth a slot
 
+// Whether occurrence `prev` is still in the ring, and not being written over, when chunk o / kWalkChunk is checked.
+__host__ __device__ inline bool check_reaches(uint32_t o, uint32_t prev) { return prev + kWalkReach >= (o / kWalkChunk + 1u) * kWalkChunk; }
+
+// What stands for the check record of an occurrence of chunk c outside the tile: nothing to test.  It reads the ring
+// all the same, and twice, so it names the occurrence's own slot: chunk c stays as it is while it is checked, where any fixed
+// slot is at some time one of chunk c + 1, which other wavefronts write meanwhile.  (Slot 0 served here
+// once; a store that fell between its two reads passed for a broken rule of the row, in a tile's first chunk.  256
+// programs x 100 samples, a step: 699 us then, 697 with the own slot.)
+__host__ __device__ inline u32x4 nothing_to_check(uint32_t c, uint32_t lane) {
+  u32x4 r = {(c % (kWalkRing / kWalkChunk) * kWalkChunk + lane) << 8, 0u, 0u, 0xFFFFFFFFu};
+  return r;
+}
+
 // An occupancy event in the form the verifier's occupancy wavefront consumes it, four
 // scalar registers that need no further decoding:
 //   x  ring slot (index % kWalkRing) of the occurrence that carries the register | vreg << 8

@@ -974,7 +974,7 @@ __global__ __launch_bounds__(kEvtThreads) void k_events(MIRS, const uint2 *__res
     const uint32_t next = e + 1 < hi ? occ_at(e + 1) : o;
     const bool keep = o + kWalkReach < (next / kWalkChunk + 1u) * kWalkChunk && next - o <= kKeepMaxGap;
     const uint32_t delta = prev == kNone ? 0u : min(o - prev, 0xFFFFu);
-    const bool near = prev != kNone && delta != 0xFFFFu && prev + kWalkReach >= (o / kWalkChunk + 1u) * kWalkChunk;
+    const bool near = prev != kNone && delta != 0xFFFFu && check_reaches(o, prev);
     const uint32_t width = attr_width(attr), align = attr_align(attr);
     const bool is_first = (role & kRoleFirst) != 0;
     const bool generic = is_first && ((align & (align - 1u)) != 0 || m.has_reserved || width > F);

@@ -602,7 +602,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
   // two reads and three compares, identical for every lane.
   auto load_chk = [&](uint32_t c) __attribute__((always_inline)) {
     const uint32_t o = c * kChunk + w.lane;
-    u32x4 r = {0u, 0u, 0u, 0xFFFFFFFFu};   // outside the tile: nothing to test
+    u32x4 r = nothing_to_check(c, w.lane);
     if (o >= oa && o < ob) r = g_chk[o];
     return r;
   };
