@@ -226,20 +226,61 @@ __device__ inline uint32_t bad_bits(const DevMir VL_GLOBAL &m, uint32_t attr, ui
 
 // P(i) = live_after(i) + defs(i) as a vreg bitset: the live-in list of i's tile, then every
 // event up to those of i, flips one bit each (in any order); the releases of values dead once
-// i has executed are left out, since such values still belong to P(i).  in_p: [W] words in
-// LDS, cleared by the caller (with a barrier in between); the caller also adds the barrier
-// after this call.
-__device__ inline void flip_members_of_p(const DevMir VL_GLOBAL &m, const DevLive VL_GLOBAL &L, const uint32_t i, uint32_t *in_p,
-                                         const uint32_t tid, const uint32_t n_threads) {
-  const uint32_t tile = i / L.tile_len;
-  auto flip_vreg = [&](uint32_t v) {   // records carry their vreg in x (above the ring slot)
-    __hip_atomic_fetch_xor(&in_p[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  };
-  const uint32_t item = i + m.instr_blk[i] + 1;   // boundary items come before their block's instructions
-  const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1], e_first = L.tile_range[2 * tile];
-  const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first;
-  // the first word of a record holds the vreg; eight reads in flight per thread (a tile of 512
-  // instructions has some 800 events, which 128 threads then fetch in one round of waiting)
+// i has executed are left out, since such values still belong to P(i).  Every member has a record
+// among these, which names an occurrence of it, its width and its class.
+// in_p: [W] words in LDS, cleared by the caller (with a barrier in between); the caller also adds
+// the barrier after the flips.
+struct RecordsOfP {
+  uint32_t s_first, s_end;            // in the live-in lists
+  uint32_t e_first, e_own, e_end;     // in the event stream; those of i from e_own on
+  __device__ bool counts(uint32_t e, const u32x4 r) const { return e < e_own || (e < e_end && !(r.w & kEvtPost)); }
+};
+__device__ inline RecordsOfP records_of_p(const DevMir VL_GLOBAL &m, const DevLive VL_GLOBAL &L, const uint32_t i) {
+  const uint32_t tile = i / L.tile_len, item = i + m.instr_blk[i] + 1;   // boundary items come before their block's instructions
+  RecordsOfP r;
+  r.s_first = L.seed_off[tile];
+  r.s_end = tile > 0 ? L.seed_off[tile + 1] : r.s_first;
+  r.e_first = L.tile_range[2 * tile];
+  r.e_own = L.item_off[item];
+  r.e_end = L.item_off[item + 1];
+  return r;
+}
+__device__ inline void flip_vreg(uint32_t *in_p, uint32_t v) {
+  __hip_atomic_fetch_xor(&in_p[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ inline bool is_member(const uint32_t *in_p, uint32_t v) { return (in_p[v >> 5] >> (v & 31)) & 1u; }
+
+// Lists of up to kSeeds live-ins and kEvents events for every thread: the records stay in registers, so that
+// whoever flips them knows the members' occurrences, widths and classes without another trip to memory.
+template <uint32_t kSeeds, uint32_t kEvents, uint32_t kThreads> struct KeptRecords {
+  static constexpr uint32_t kAll = kSeeds + kEvents;
+  u32x4 rec[kAll];   // (a record that stands for something has a tuple mask)
+  __device__ static bool fit(const RecordsOfP &p) { return p.s_end - p.s_first <= kSeeds * kThreads && p.e_end - p.e_first <= kEvents * kThreads; }
+  __device__ void load(const DevLive VL_GLOBAL &L, const RecordsOfP &p, const uint32_t tid) {
+#pragma unroll
+    for (uint32_t u = 0; u < kSeeds; ++u) {
+      const uint32_t e = p.s_first + tid + u * kThreads;
+      rec[u] = 0;
+      if (e < p.s_end) rec[u] = L.seeds[e];
+    }
+#pragma unroll
+    for (uint32_t u = kSeeds; u < kAll; ++u) {
+      const uint32_t e = p.e_first + tid + (u - kSeeds) * kThreads;
+      rec[u] = 0;
+      if (e < p.e_end) rec[u] = L.plan[e];
+      if (!p.counts(e, rec[u])) rec[u] = 0;
+    }
+  }
+  __device__ void flip(uint32_t *in_p) const {
+#pragma unroll
+    for (uint32_t u = 0; u < kAll; ++u)
+      if (rec[u].y) flip_vreg(in_p, rec[u].x >> 8);
+  }
+};
+
+// Lists of any length: only the word of a record that holds the vreg is read, eight at a time per thread
+// (a tile of 512 instructions has some 800 events, which 128 threads then fetch in one round of waiting).
+__device__ inline void flip_members_of_p(const DevLive VL_GLOBAL &L, const RecordsOfP &p, uint32_t *in_p, const uint32_t tid, const uint32_t n_threads) {
   auto flip_all = [&](const u32x4 VL_GLOBAL *records, uint32_t from, uint32_t to) {
     for (uint32_t e0 = from + tid; e0 < to; e0 += 8 * n_threads) {
       uint32_t x[8];
@@ -250,14 +291,24 @@ __device__ inline void flip_members_of_p(const DevMir VL_GLOBAL &m, const DevLiv
       }
 #pragma unroll
       for (uint32_t u = 0; u < 8; ++u)
-        if (e0 + u * n_threads < to) flip_vreg(x[u] >> 8);
+        if (e0 + u * n_threads < to) flip_vreg(in_p, x[u] >> 8);
     }
   };
-  flip_all(L.seeds, s_first, s_end);
-  flip_all(L.plan, e_first, e_own);
-  for (uint32_t e = e_own + tid; e < e_end; e += n_threads) {
+  flip_all(L.seeds, p.s_first, p.s_end);
+  flip_all(L.plan, p.e_first, p.e_own);
+  for (uint32_t e = p.e_own + tid; e < p.e_end; e += n_threads) {
     const u32x4 r = L.plan[e];
-    if (!(r.w & kEvtPost)) flip_vreg(r.x >> 8);
+    if (!(r.w & kEvtPost)) flip_vreg(in_p, r.x >> 8);
+  }
+}
+// the bits that are set, in any order; *n (zero before) ends as their number, of which `room` at most are listed
+__device__ inline void list_members(const uint32_t *in_p, const uint32_t W, uint32_t *members, const uint32_t room, uint32_t *n, const uint32_t tid,
+                                    const uint32_t n_threads) {
+  for (uint32_t x = tid; x < W; x += n_threads) {
+    uint32_t bits = in_p[x];
+    if (!bits) continue;
+    uint32_t at = __hip_atomic_fetch_add(n, (uint32_t)__popc(bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (; bits && at < room; bits &= bits - 1) members[at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
   }
 }
 }  // namespace vl

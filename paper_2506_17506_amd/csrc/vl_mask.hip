@@ -32,7 +32,9 @@ constexpr uint32_t kArgRuns = 64;   // runs that travel as a kernel argument (3 
                                    // (runs of 20 queries: 64 take 12.3 us, 65 19.2)
 struct RunArgs { Run run[kArgRuns]; };
 constexpr uint32_t kMaskThreads = 256, kMaskWaves = kMaskThreads / 64;
-constexpr uint32_t kMaskMembers = 256;   // members of P(i) that are listed; with more, every vreg gets a turn
+// members of P(i) that are listed: those in the way, and all where they are found by their bits (in the same memory,
+// before that); with more, every vreg gets a turn
+constexpr uint32_t kMaskMembers = 256, kMaskListed = 2 * kMaskMembers;
 
 template <bool kByArgument>
 __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditional_t<kByArgument, RunArgs, const Run *> args, uint32_t n_runs,
@@ -55,6 +57,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
   extern __shared__ uint32_t in_p[];                  // [W] members of P(i)
   __shared__ uint2 members[kMaskMembers];             // (first occurrence, width) of those in the way
   __shared__ uint32_t n_members;
+  __shared__ uint32_t n_listed;
   __shared__ uint32_t blocked_all[kMaskWaves][17];    // registers that are taken or reserved (word 16: always zero)
   uint32_t *const blocked = blocked_all[wave];
   const uint32_t q = R.occ, v = m.occ_vreg[q], i = m.occ_instr[q];
@@ -69,65 +72,52 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
   };
   if (fresh) {
     for (uint32_t x = threadIdx.x; x < m.W; x += kMaskThreads) in_p[x] = 0;
-    if (threadIdx.x == 0) n_members = 0;
-    // Members of P(i): flip_members_of_p, with the records kept until the bits say which of them are members.  A record
+    if (threadIdx.x == 0) n_members = n_listed = 0;
+    // Short lists: the records are kept until the bits say which of them are members.  A record
     // has its value's width and class, so that only the first occurrence is looked up, all of a thread's at once.
-    // (A value may have several records among them, and is then listed as often.)
-    const uint32_t item = i + m.instr_blk[i] + 1, tile = i / L.tile_len;
-    const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first, e_first = L.tile_range[2 * tile];
-    const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1];
-    constexpr uint32_t kKept = 4;   // live-ins, then events
-    u32x4 rec[kKept];
-    auto counts = [&](uint32_t e, const u32x4 r) { return e < e_own || (e < e_end && !(r.w & kEvtPost)); };
-    const uint32_t s_own = s_first + threadIdx.x, e_mine = e_first + threadIdx.x;
-    rec[0] = 0;
-    if (s_own < s_end) rec[0] = L.seeds[s_own];
-#pragma unroll
-    for (uint32_t u = 1; u < kKept; ++u) {
-      const uint32_t e = e_mine + (u - 1u) * kMaskThreads;
-      rec[u] = 0;
-      if (e < e_end) rec[u] = L.plan[e];
-      if (!counts(e, rec[u])) rec[u] = 0;   // (a record that stands for something has a tuple mask)
-    }
+    // Longer ones: the members are listed from the bits, and looked up a lane each.  (4,000 instructions in one tile, one
+    // program x 100 and 64 x 100: 9.6 and 23 us; 14.5 and 30 when the records beyond those kept were read one at a time, twice.)
+    const RecordsOfP p = records_of_p(m, L, i);
+    KeptRecords<1, 3, kMaskThreads> kept;
+    const bool fit = kept.fit(p);
+    if (fit) kept.load(L, p, threadIdx.x);
     __syncthreads();
-    auto flip = [&](const u32x4 r) {
-      const uint32_t b = r.x >> 8;
-      if (r.y) __hip_atomic_fetch_xor(&in_p[b >> 5], 1u << (b & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-#pragma unroll
-    for (uint32_t u = 0; u < kKept; ++u) flip(rec[u]);
-    // (long lists: the rest is read twice)
-    const uint32_t s_rest = s_own + kMaskThreads, e_rest = e_mine + (kKept - 1u) * kMaskThreads;
-    for (uint32_t e = s_rest; e < s_end; e += kMaskThreads) flip(L.seeds[e]);
-    for (uint32_t e = e_rest; e < e_end; e += kMaskThreads) {
-      const u32x4 r = L.plan[e];
-      if (counts(e, r)) flip(r);
-    }
+    if (fit) kept.flip(in_p);
+    else flip_members_of_p(L, p, in_p, threadIdx.x, kMaskThreads);
     __syncthreads();
-    auto candidate = [&](const u32x4 r) {   // a member of v's class (classes begin at different mask words) other than v
-      const uint32_t b = r.x >> 8;
-      return r.y && b != v && r.z == attr_word(attr) * 256u && ((in_p[b >> 5] >> (b & 31)) & 1u);
-    };
-    auto list = [&](const u32x4 r, uint32_t fb) {
-      if (fb >= q) return;
+    auto list = [&](uint2 e) {
       const uint32_t slot = atomicAdd(&n_members, 1u);
-      if (slot < kMaskMembers) members[slot] = make_uint2(fb, (uint32_t)__popc(r.y));
+      if (slot < kMaskMembers) members[slot] = e;
     };
-    uint32_t fb[kKept];
+    if (fit) {
+      uint32_t fb[kept.kAll];
 #pragma unroll
-    for (uint32_t u = 0; u < kKept; ++u) {
-      fb[u] = kNone;
-      if (candidate(rec[u])) fb[u] = L.first[rec[u].x >> 8];
-    }
+      for (uint32_t u = 0; u < kept.kAll; ++u) {   // members of v's class (classes begin at different mask words) other than v
+        const u32x4 r = kept.rec[u];
+        const uint32_t b = r.x >> 8;
+        fb[u] = kNone;
+        if (r.y && b != v && r.z == attr_word(attr) * 256u && is_member(in_p, b)) fb[u] = L.first[b];
+      }
 #pragma unroll
-    for (uint32_t u = 0; u < kKept; ++u) list(rec[u], fb[u]);
-    for (uint32_t e = s_rest; e < s_end; e += kMaskThreads) {
-      const u32x4 r = L.seeds[e];
-      if (candidate(r)) list(r, L.first[r.x >> 8]);
-    }
-    for (uint32_t e = e_rest; e < e_end; e += kMaskThreads) {
-      const u32x4 r = L.plan[e];
-      if (counts(e, r) && candidate(r)) list(r, L.first[r.x >> 8]);
+      for (uint32_t u = 0; u < kept.kAll; ++u)
+        if (fb[u] < q) list(make_uint2(fb[u], (uint32_t)__popc(kept.rec[u].y)));
+    } else {
+      uint32_t *const listed = &members[0].x;
+      list_members(in_p, m.W, listed, kMaskListed, &n_listed, threadIdx.x, kMaskThreads);
+      __syncthreads();
+      constexpr uint32_t kEach = kMaskListed / kMaskThreads;
+      uint2 mine[kEach];
+      bool taken[kEach];
+#pragma unroll
+      for (uint32_t u = 0; u < kEach; ++u) {
+        const uint32_t y = threadIdx.x + u * kMaskThreads;
+        taken[u] = y < n_listed && in_the_way(listed[y], mine[u]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (uint32_t u = 0; u < kEach; ++u)
+        if (taken[u]) list(mine[u]);
+      if (threadIdx.x == 0 && n_listed > kMaskListed) atomicAdd(&n_members, kMaskMembers + 1u);   // every vreg gets a turn
     }
     __syncthreads();
   }
@@ -151,7 +141,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
       } else {
         for (uint32_t b = lane; b < m.V; b += 64) {
           uint2 e;
-          if (((in_p[b >> 5] >> (b & 31)) & 1u) && in_the_way(b, e)) take(e);
+          if (is_member(in_p, b) && in_the_way(b, e)) take(e);
         }
       }
     }
@@ -195,14 +185,9 @@ __global__ __launch_bounds__(kAloneThreads) void k_free_bases_alone(const Run *_
     for (uint32_t x = tid; x < m.W; x += kAloneThreads) in_p[x] = 0;
     if (tid == 0) n_members = 0;
     __syncthreads();
-    flip_members_of_p(m, L, i, in_p, tid, kAloneThreads);
+    flip_members_of_p(L, records_of_p(m, L, i), in_p, tid, kAloneThreads);
     __syncthreads();
-    for (uint32_t x = tid; x < m.W; x += kAloneThreads) {
-      uint32_t bits = in_p[x];
-      if (!bits) continue;
-      uint32_t at = atomicAdd(&n_members, (uint32_t)__popc(bits));
-      for (; bits && at < kAloneMembers; bits &= bits - 1) members[at++] = x * 32u + (uint32_t)__ffs(bits) - 1u;
-    }
+    list_members(in_p, m.W, members, kAloneMembers, &n_members, tid, kAloneThreads);
   }
   const uint32_t wm = width == 32 ? 0xFFFFFFFFu : ((1u << width) - 1u);
   for (uint32_t x = 0; x < R.count; ++x) {
@@ -223,7 +208,7 @@ __global__ __launch_bounds__(kAloneThreads) void k_free_bases_alone(const Run *_
         for (uint32_t y = tid; y < n_members; y += kAloneThreads) take(members[y]);
       } else {
         for (uint32_t b = tid; b < m.V; b += kAloneThreads)
-          if ((in_p[b >> 5] >> (b & 31)) & 1u) take(b);
+          if (is_member(in_p, b)) take(b);
       }
       __syncthreads();
     }

@@ -840,22 +840,24 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(kT
 // with overlapping ranges.  At the first clashing instruction every clashing pair contains a
 // vreg that the instruction defines, so only pairs (definition, anything in P(i)) are
 // examined.  P(i) is rebuilt as a bitset in LDS the way the walk builds occupancy, but over
-// vregs instead of registers: the live-in list of i's tile, then every event up to those of i, flips one
-// bit each; the releases of values dead once i has executed are left out.  Every member has a record among these, which
-// names an occurrence of it, its width and its class; a candidate that got this far is consistent, so that
-// occurrence's register is the value's.  Records stay in registers between the flips and the comparison.
+// vregs instead of registers (RecordsOfP); a candidate that got this far is consistent, so any occurrence
+// of a member has the value's register.
 // What bounds it is the chain of reads: result, offsets of i, events of i and its operands, records, registers.
-// (A list of members, with first occurrence, attributes and register of each looked up one after the other, and the
-// definitions' attributes read at every comparison, took three trips to memory more.)
+// Short lists are kept as records between the flips and the comparison; of longer ones one word is read of each record, and
+// the members are listed from the bitset and looked up a lane each, two trips more.  (Reading the rest of a long list a
+// record at a time, before and after the flips: 4,000 instructions in one tile, 50 rows to resolve 21.6 us, 10.2 this way,
+// 11.3 with lists for all; 256 programs in tiles of 512, 27.7 and 25.3.  Five events kept instead of three, and the
+// registers that takes: 28.8, packed into two words each 25.1, but 4.6 instead of 4.4 for 200 instructions x 64.)
 // The workgroups of a group of rows share out the rows that
 // failed on safety.  kShared: it leaves the board zero (Board).
 constexpr uint32_t kResolveThreads = 128;   // at least kMaxOperands; 64 and 256 were measured slower
+constexpr uint32_t kResolveMembers = 512;   // members of P(i) that are listed; with more, every vreg gets a turn
 template <bool kOne, bool kShared>
 __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__restrict__ jobs, uint32_t n_jobs, const DevJob one, uint32_t per_group, uint32_t n_groups,
                                                              const Board board) {
   extern __shared__ uint32_t in_p[];   // [W]
   __shared__ unsigned long long best;
-  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], da[kMaxOperands], nd;
+  __shared__ uint32_t dv[kMaxOperands], dp[kMaxOperands], da[kMaxOperands], nd, members[kResolveMembers], n_members;
   const uint32_t global_group = blockIdx.x / per_group, mine_first = blockIdx.x % per_group;
   const DevJob J = kOne ? one : jobs[find_job(jobs, n_jobs, global_group, &DevJob::group_base)];
   const uint32_t group = global_group - J.group_base, row0 = group * J.rows, tid = threadIdx.x;
@@ -882,10 +884,9 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
     const uint32_t row = (uint32_t)__builtin_ctzll(todo), k = row0 + row, i = __builtin_amdgcn_readlane(where, row);
     for (uint32_t x = 0; x < per_group && todo; ++x) todo &= todo - 1;
     if (kShared && i >= m.N) continue;   // (not a result of this call: calls overlapped against the rules)
-    const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo, item = i + m.instr_blk[i] + 1, tile = i / L.tile_len;
-    const uint32_t s_first = L.seed_off[tile], s_end = tile > 0 ? L.seed_off[tile + 1] : s_first, e_first = L.tile_range[2 * tile];
+    const uint32_t o_lo = m.occ_off[i], n_ops = m.occ_off[i + 1] - o_lo;
+    const RecordsOfP p = records_of_p(m, L, i);
     for (uint32_t x = tid; x < m.W; x += kResolveThreads) in_p[x] = 0;
-    const uint32_t e_own = L.item_off[item], e_end = L.item_off[item + 1];   // (boundary items come before their block's instructions)
     // the vregs the instruction writes and their registers: one operand per lane
     uint32_t my_v = kNone, my_p = 0;
     if (tid < n_ops) {
@@ -893,22 +894,9 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
       my_p = cand_at(J, k, o_lo + tid);
       if (flags & VL_OCC_DEF) my_v = v;
     }
-    constexpr uint32_t kSeeds = 1, kEvents = 3;   // records that a thread keeps (256 programs x 100: 27 us with three or four, 34 with eight and the registers that takes)
-    u32x4 rec[kSeeds + kEvents];
-#pragma unroll
-    for (uint32_t u = 0; u < kSeeds; ++u) {
-      const uint32_t e = s_first + tid + u * kResolveThreads;
-      rec[u] = 0;
-      if (e < s_end) rec[u] = L.seeds[e];
-    }
-    auto counts = [&](uint32_t e, const u32x4 r) { return e < e_own || (e < e_end && !(r.w & kEvtPost)); };
-#pragma unroll
-    for (uint32_t u = 0; u < kEvents; ++u) {
-      const uint32_t e = e_first + tid + u * kResolveThreads;
-      rec[kSeeds + u] = 0;
-      if (e < e_end) rec[kSeeds + u] = L.plan[e];
-      if (!counts(e, rec[kSeeds + u])) rec[kSeeds + u] = 0;   // (a record that stands for something has a tuple mask)
-    }
+    KeptRecords<1, 3, kResolveThreads> kept;
+    const bool fit = kept.fit(p);
+    if (fit) kept.load(L, p, tid);
     if (tid < kMaxOperands) {   // one wavefront
       const uint32_t attr = my_v != kNone ? m.vattr[my_v] : 0u;
       const uint64_t defs = __ballot(my_v != kNone);
@@ -916,35 +904,19 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
         const uint32_t slot = (uint32_t)__popcll(defs & ((1ull << tid) - 1ull));
         dv[slot] = my_v; dp[slot] = my_p; da[slot] = attr;
       }
-      if (tid == 0) { best = ~0ull; nd = (uint32_t)__popcll(defs); }
+      if (tid == 0) { best = ~0ull; nd = (uint32_t)__popcll(defs); n_members = 0; }
     }
     static_assert(kMaxOperands == 64, "a wavefront");
     __syncthreads();
-    auto flip = [&](const u32x4 r) {
-      const uint32_t v = r.x >> 8;
-      if (r.y) __hip_atomic_fetch_xor(&in_p[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-#pragma unroll
-    for (uint32_t u = 0; u < kSeeds + kEvents; ++u) flip(rec[u]);
-    // (long lists: the rest is read twice)
-    const uint32_t s_rest = s_first + tid + kSeeds * kResolveThreads, e_rest = e_first + tid + kEvents * kResolveThreads;
-    for (uint32_t e = s_rest; e < s_end; e += kResolveThreads) flip(L.seeds[e]);
-    for (uint32_t e = e_rest; e < e_end; e += kResolveThreads) {
-      const u32x4 r = L.plan[e];
-      if (counts(e, r)) flip(r);
-    }
+    if (fit) kept.flip(in_p);
+    else flip_members_of_p(L, p, in_p, tid, kResolveThreads);
     __syncthreads();
     unsigned long long mine = ~0ull;
     const uint32_t n_defs = nd;
-    auto member = [&](const u32x4 r) {
-      const uint32_t v = r.x >> 8;
-      return r.y && ((in_p[v >> 5] >> (v & 31)) & 1u);
-    };
-    auto examine = [&](const u32x4 r, uint32_t px) {
-      const uint32_t x = r.x >> 8, wx = (uint32_t)__popc(r.y);
+    auto examine = [&](uint32_t x, uint32_t wx, uint32_t cls_word, uint32_t px) {
       for (uint32_t t = 0; t < n_defs; ++t) {
         const uint32_t d = dv[t], ad = da[t];
-        if (d == x || attr_word(ad) * 256u != r.z) continue;   // (classes begin at different mask words)
+        if (d == x || attr_word(ad) != cls_word) continue;   // (classes begin at different mask words)
         const uint32_t pd = dp[t], wd = attr_width(ad);
         if (pd < px + wx && px < pd + wd) {
           // (a program with lanes as values reports the caller's vregs: the smallest pair of those)
@@ -954,23 +926,33 @@ __global__ __launch_bounds__(kResolveThreads) void k_resolve(const DevJob *__res
         }
       }
     };
-    uint32_t px[kSeeds + kEvents];
+    if (fit) {
+      uint32_t px[kept.kAll];
 #pragma unroll
-    for (uint32_t u = 0; u < kSeeds + kEvents; ++u) {   // (all in flight)
-      px[u] = 0;
-      if (member(rec[u])) px[u] = cand_at(J, k, rec[u].w & 0xFFFFFFu);
-      else rec[u].y = 0;
-    }
+      for (uint32_t u = 0; u < kept.kAll; ++u) {   // (all in flight)
+        u32x4 &r = kept.rec[u];
+        px[u] = 0;
+        if (r.y && is_member(in_p, r.x >> 8)) px[u] = cand_at(J, k, r.w & 0xFFFFFFu);
+        else r.y = 0;
+      }
 #pragma unroll
-    for (uint32_t u = 0; u < kSeeds + kEvents; ++u)
-      if (rec[u].y) examine(rec[u], px[u]);
-    for (uint32_t e = s_rest; e < s_end; e += kResolveThreads) {
-      const u32x4 r = L.seeds[e];
-      if (member(r)) examine(r, cand_at(J, k, r.w & 0xFFFFFFu));
-    }
-    for (uint32_t e = e_rest; e < e_end; e += kResolveThreads) {
-      const u32x4 r = L.plan[e];
-      if (counts(e, r) && member(r)) examine(r, cand_at(J, k, r.w & 0xFFFFFFu));
+      for (uint32_t u = 0; u < kept.kAll; ++u) {
+        const u32x4 r = kept.rec[u];
+        if (r.y) examine(r.x >> 8, (uint32_t)__popc(r.y), r.z / 256u, px[u]);
+      }
+    } else {
+      auto look_up = [&](uint32_t x) {
+        const uint32_t ax = m.vattr[x], o = L.first[x];
+        examine(x, attr_width(ax), attr_word(ax), cand_at(J, k, o));
+      };
+      list_members(in_p, m.W, members, kResolveMembers, &n_members, tid, kResolveThreads);
+      __syncthreads();
+      if (n_members <= kResolveMembers) {
+        for (uint32_t x = tid; x < n_members; x += kResolveThreads) look_up(members[x]);
+      } else {
+        for (uint32_t x = tid; x < m.V; x += kResolveThreads)
+          if (is_member(in_p, x)) look_up(x);
+      }
     }
     if (mine != ~0ull) atomicMin(&best, mine);
     __syncthreads();

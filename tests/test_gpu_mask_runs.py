@@ -151,11 +151,11 @@ def test_more_runs_than_the_table_starts_with():
         free(hm, hl)
 
 
-@pytest.mark.parametrize("n_live", [255, 256, 257, 767, 768, 769, 1100])
+@pytest.mark.parametrize("n_live", [255, 256, 257, 510, 511, 512, 513, 767, 768, 769, 1100])
 @pytest.mark.parametrize("tile_len", [100, 4096])
 def test_lists_longer_than_a_thread_keeps(n_live, tile_len):
-    """live-in lists around the 256 entries and tiles around the 768 events whose records stay in registers; half of
-    the values are of another file, some are written twice"""
+    """live-in lists around the 256 entries and tiles around the 768 events whose records stay in registers, and around the
+    512 values that are listed from longer ones; half of the values are of another file, some are written twice"""
     rng = np.random.default_rng(n_live)
     V = n_live + 1
     vclass = (np.arange(V) % 2).astype(np.uint8)

@@ -25,10 +25,11 @@ def test_many_live_values(n_live, K):
     check_many_live_values(n_live, K, 0)
 
 
-@pytest.mark.parametrize("n_live", [127, 128, 129, 383, 384, 385, 800])
+@pytest.mark.parametrize("n_live", [127, 128, 129, 383, 384, 385, 510, 511, 512, 800])
 @pytest.mark.parametrize("tile_len", [100, 4096])
 def test_lists_longer_than_a_thread_keeps(n_live, tile_len):
-    """live-in lists around the 128 entries and tiles around the 384 events that the search keeps in registers"""
+    """live-in lists around the 128 entries and tiles around the 384 events that the search keeps in registers,
+    and around the 512 values that it lists of longer ones"""
     check_many_live_values(n_live, 64, tile_len)
 
 
