@@ -70,6 +70,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
     out = make_uint2(fb, attr_width(ab));
     return b != v && attr_class(ab) == cls && fb < q;
   };
+  bool listed_once = false;   // what is in `members` has no bit any more
   if (fresh) {
     for (uint32_t x = threadIdx.x; x < m.W; x += kMaskThreads) in_p[x] = 0;
     if (threadIdx.x == 0) n_members = n_listed = 0;
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
     // program x 100 and 64 x 100: 9.6 and 23 us; 14.5 and 30 when the records beyond those kept were read one at a time, twice.)
     const RecordsOfP p = records_of_p(m, L, i);
     KeptRecords<1, 3, kMaskThreads> kept;
-    const bool fit = kept.fit(p);
+    const bool fit = listed_once = kept.fit(p);
     if (fit) kept.load(L, p, threadIdx.x);
     __syncthreads();
     if (fit) kept.flip(in_p);
@@ -88,6 +89,7 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
     auto list = [&](uint2 e) {
       const uint32_t slot = atomicAdd(&n_members, 1u);
       if (slot < kMaskMembers) members[slot] = e;
+      return slot < kMaskMembers;
     };
     if (fit) {
       uint32_t fb[kept.kAll];
@@ -99,8 +101,15 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
         if (r.y && b != v && r.z == attr_word(attr) * 256u && is_member(in_p, b)) fb[u] = L.first[b];
       }
 #pragma unroll
-      for (uint32_t u = 0; u < kept.kAll; ++u)
-        if (fb[u] < q) list(make_uint2(fb[u], (uint32_t)__popc(kept.rec[u].y)));
+      for (uint32_t u = 0; u < kept.kAll; ++u) {
+        if (fb[u] >= q) continue;
+        // A value may have several records: the one that finds its bit lists it, and takes the bit.  (As many entries as
+        // records: 30 values written four times in a tile of 512, one program x 100:
+        // 19.7 us a launch, since every vreg then has its turn; 5.5 this way.)
+        const uint32_t b = kept.rec[u].x >> 8, bit = 1u << (b & 31);
+        if (!(__hip_atomic_fetch_and(&in_p[b >> 5], ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit)) continue;
+        if (!list(make_uint2(fb[u], (uint32_t)__popc(kept.rec[u].y)))) atomicOr(&in_p[b >> 5], bit);   // no room: found by its bit
+      }
     } else {
       uint32_t *const listed = &members[0].x;
       list_members(in_p, m.W, listed, kMaskListed, &n_listed, threadIdx.x, kMaskThreads);
@@ -136,9 +145,10 @@ __global__ __launch_bounds__(kMaskThreads) void k_free_bases(const std::conditio
       }
     };
     if (fresh) {
-      if (n_members <= kMaskMembers) {
-        for (uint32_t y = lane; y < n_members; y += 64) take(members[y]);
-      } else {
+      const bool all = n_members <= kMaskMembers;
+      if (all || listed_once)
+        for (uint32_t y = lane; y < min(n_members, kMaskMembers); y += 64) take(members[y]);
+      if (!all) {
         for (uint32_t b = lane; b < m.V; b += 64) {
           uint2 e;
           if (is_member(in_p, b) && in_the_way(b, e)) take(e);

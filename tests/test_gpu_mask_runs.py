@@ -179,3 +179,33 @@ def test_lists_longer_than_a_thread_keeps(n_live, tile_len):
         assert (got == want).all()
     finally:
         free(hm, hl)
+
+
+@pytest.mark.parametrize("n_values,times", [(30, 4), (60, 4), (255, 1), (256, 1), (257, 1), (300, 1)])
+def test_values_with_many_records(n_values, times):
+    """values that end and are written again within one tile: several records each, listed once; more of them than there is room
+    for are found by their bits"""
+    V = n_values + 1
+    rng = np.random.default_rng(n_values + times)
+    ins = [([v], []) for v in range(n_values)]
+    for _ in range(times):
+        for v in range(n_values):
+            ins += [([], [v]), ([v], [])]
+    ins += [([n_values], [])] + [([], list(range(v, min(V, v + 40)))) for v in range(0, V, 40)]
+    m = Mir.build([ins], [[]], V, (512,), np.zeros(V, np.uint8), rng.choice([1, 1, 2], V), np.ones(V, np.uint8), None, name=f"again{n_values}")
+    rows = rng.integers(0, 512, (9, m.n_occ)).astype(np.uint16)
+    an = vlo.analyze(m, interference=False, threads=8)
+    first = int(np.nonzero(m.occ_vreg == n_values)[0][0])
+    want = np.stack([vlo.free_bases(m, an, rows[k], first) for k in range(len(rows))])
+    hm = [vl.vl_mir_create(m)]
+    try:
+        dev, _ = vl.rows_to_device(rows)
+        for tile_len in (512, 1024):   # at most 768 events, and more
+            hl = vl.vl_liveness_multi(hm, tile_len=tile_len)
+            masks = torch.full((len(rows), 16), -1, dtype=torch.int32, device="cuda")
+            vl.vl_free_bases_multi([(hm[0], hl[0], dev[k], first) for k in range(len(rows))], masks)
+            torch.cuda.synchronize()
+            vl.vl_live_destroy(hl[0])
+            assert (masks.cpu().numpy().view(np.uint32) == want).all(), tile_len
+    finally:
+        vl.vl_mir_destroy(hm[0])
