@@ -1889,7 +1889,9 @@ extern "C" void vl_live_destroy(vl_live *l) {
 
 // Deals the programs out to the eight dies where that leaves the dies equally busy: by size, to and fro.
 // A batch of few or very unequal programs, one of whose dies would get a sixteenth more than the
-// mean, stays in the caller's order, every program spread over all dies.
+// mean, stays in the caller's order, every program spread over all dies; so does one so large that the
+// empty blocks which fill up a die could make a launch larger than a grid can be (2^24 blocks of 256).
+constexpr uint64_t kDealtBlocks = 1u << 22;
 static void deal(vl_batch *batch, const vl_mir *const *mirs) {
   const uint32_t n = batch->n;
   std::vector<uint32_t> by_size(n);
@@ -1909,7 +1911,7 @@ static void deal(vl_batch *batch, const vl_mir *const *mirs) {
     max_instr = std::max(max_instr, instr[d]);
     max_occ = std::max(max_occ, occ[d]);
   }
-  batch->dealt = n >= 8 && 8 * max_occ <= sum_occ + sum_occ / 16 && 8 * max_instr <= sum_instr + sum_instr / 16;
+  batch->dealt = n >= 8 && 8 * max_occ <= sum_occ + sum_occ / 16 && 8 * max_instr <= sum_instr + sum_instr / 16 && 8 * (max_instr + max_occ) <= kDealtBlocks;
   if (batch->dealt)
     for (uint32_t r = 0; r < n; ++r) batch->place[by_size[r]] = place_of(r);
   batch->blocks_instr = batch->dealt ? 8 * max_instr : sum_instr;
@@ -2233,8 +2235,9 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     if (e != hipSuccess) return fail(hip_fail(e));
   }
   const uint32_t per_a = blocks(maxT, 4);
-  const Grid in_dies = {n, batch->dealt ? 3u : 0u};
-  const StageGrid g_fill = {per_a * (batch->dealt ? (n + 7) / 8 * 8 : n), (uint32_t)blocks_instr, (uint32_t)blocks_occ};
+  const uint32_t in_rows = (n + 7) / 8 * 8;   // programs with those that fill up the last row of eight
+  const Grid in_dies = {n, batch->dealt && (uint64_t)per_a * in_rows <= kDealtBlocks ? 3u : 0u};
+  const StageGrid g_fill = {per_a * (in_dies.dealt ? in_rows : n), (uint32_t)blocks_instr, (uint32_t)blocks_occ};
   const StageGrid g_fin = {blocks(maxB, 4), blocks(maxT, TB), blocks(max_seed, TB)};
   k_stage_fill<<<g_fill.a + g_fill.b + g_fill.c, 256, 0, stream>>>(dm, dl, in_dies, g_fill, per_a, map_instr, map_occ);
   // dense points go along where they are few workgroups, as many as the device takes at once; where they are

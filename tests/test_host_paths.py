@@ -237,3 +237,21 @@ def test_tables_of_runs_grow_with_the_runs(s):
             launch = query(np.arange(n) % 8)
             assert "alone" in launch[0] and launch[1][0] == n
     assert s.counts()["largest"] <= 65536 * 48
+
+
+@in_own_process
+def test_launches_of_many_tiles_stay_within_a_grid(s):
+    """eight programs of four million instructions and a small one, tiles of one instruction: no launch has 2^32 threads in a row,
+    dealt out to the dies or not"""
+    n = 1 << 22
+    off = np.zeros(n + 1, np.uint32)
+    large = Mir([0, n], [0, 0], [], off, np.zeros(0, np.uint32), np.zeros(0, np.uint8), np.zeros(1, np.uint8), np.ones(1, np.uint8),
+                np.ones(1, np.uint8), np.array([64], np.uint16))
+    small = Mir([0, 1], [0, 0], [], off[:2], np.zeros(0, np.uint32), np.zeros(0, np.uint8), np.zeros(1, np.uint8), np.ones(1, np.uint8),
+                np.ones(1, np.uint8), np.array([64], np.uint16))
+    hm = [s.vl.vl_mir_create(large) for _ in range(8)] + [s.vl.vl_mir_create(small)]
+    s.launches.clear()
+    s.vl.vl_liveness_multi(hm, tile_len=1, stream=S1)
+    assert any("k_stage_fill" in x[0] for x in s.launches)
+    for name, grid, block, *_ in s.launches:
+        assert grid[0] * block < 1 << 32 and grid[1] < 1 << 16, (name, grid, block)
