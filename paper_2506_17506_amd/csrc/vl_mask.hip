@@ -254,7 +254,10 @@ Tables g_tables[16];
 // How many of the queries at q, n at most, go on with the run that `u` (checked) belongs to: the same but for the
 // row, which is `next` and so on.  A run of many queries is what a decoding step of many samples makes, and the
 // host's pass over them took longer than the kernel (64 programs x 100: 16.6 us a call, 8.9 of them the kernel;
-// 13.8 this way).  Eight queries to a branch.
+// 13.8 this way).  Eight queries to a branch, once a run has a dozen: looking eight ahead from a run's second query on cost
+// more than it saved where runs are short (16,000 queries in runs of 2, 4, 8 and 16: 121, 72, 48 and 36 us a call; 43, 44, 37
+// and 38 one by one; 42, 38, 37 and 35 this way).  The last of the eight is looked at first.
+constexpr uint32_t kLongRun = 12;
 inline uint32_t same_run(const vl_mask_query *q, uint32_t n, const vl_mask_query &u, const uint16_t *next, int64_t stride) {
   const uintptr_t mir = (uintptr_t)u.mir, live = (uintptr_t)u.live, step = (uintptr_t)(stride * 2);
   uintptr_t at = (uintptr_t)next;
@@ -262,9 +265,9 @@ inline uint32_t same_run(const vl_mask_query *q, uint32_t n, const vl_mask_query
     return ((uintptr_t)x.mir ^ mir) | ((uintptr_t)x.live ^ live) | ((uintptr_t)x.cand ^ cand) | (uintptr_t)((x.occ ^ u.occ) | x.reserved0) | (uintptr_t)!cand;
   };
   uint32_t k = 0;
-  for (; k + 8 <= n; k += 8, at += 8 * step) {
+  for (; k + 8 <= n && !other(q[k + 7], at + 7 * step); k += 8, at += 8 * step) {
     uintptr_t any = 0;
-    for (uint32_t t = 0; t < 8; ++t) any |= other(q[k + t], at + t * step);
+    for (uint32_t t = 0; t < 7; ++t) any |= other(q[k + t], at + t * step);
     if (any) break;
   }
   while (k < n && !other(q[k], at)) { ++k; at += step; }
@@ -348,10 +351,12 @@ extern "C" int32_t vl_free_bases_multi(const vl_mask_query *queries, uint32_t n,
       if (u.cand == run.cand + (int64_t)run.count * run.stride) {   // (an odd distance in bytes is no multiple of an element)
         ++run.count;
         next = u.cand + run.stride;
-        const uint32_t more = same_run(queries + j + 1, n - j - 1, u, next, run.stride);
-        run.count += more;
-        next += (int64_t)more * run.stride;
-        j += more;
+        if (run.count == kLongRun) {
+          const uint32_t more = same_run(queries + j + 1, n - j - 1, u, next, run.stride);
+          run.count += more;
+          next += (int64_t)more * run.stride;
+          j += more;
+        }
         continue;
       }
     }

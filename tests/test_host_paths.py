@@ -255,3 +255,35 @@ def test_launches_of_many_tiles_stay_within_a_grid(s):
     assert any("k_stage_fill" in x[0] for x in s.launches)
     for name, grid, block, *_ in s.launches:
         assert grid[0] * block < 1 << 32 and grid[1] < 1 << 16, (name, grid, block)
+
+
+@in_own_process
+def test_queries_fold_into_runs_of_any_length(s):
+    """the runs that travel with the launch, against a plain fold; lengths around those at which the queries are looked at eight at a time"""
+    hm, hl = analysed(s, 2)
+    masks = Buffer(64)
+    seen = []
+    plain = s.on_launch
+
+    def on_launch(name, grid, block, lds, stream, args):
+        if "k_free_bases" in name:
+            n_runs = C.cast(args[1], C.POINTER(C.c_uint32))[0]
+            seen.append(np.frombuffer(C.string_at(args[0], 48 * n_runs), np.int64).reshape(-1, 6).copy())
+        plain(name, grid, block, lds, stream, args)
+    s.on_launch = on_launch
+    rng = np.random.default_rng(4)
+    for length in [1, 2, 3, 8, 11, 12, 13, 14, 19, 20, 21, 22, 27, 28, 29, 30, 40]:
+        queries, want = [], []   # (program, row, occurrence); (row, stride, occurrence, count)
+        for j in range(12):
+            which, row, step, occ = j % 2, 0x10000 + 0x1000 * j, [256, -512, 0][int(rng.integers(3))], int(rng.integers(8))
+            queries += [(which, row + t * step, occ) for t in range(length)]
+            want.append((row, step // 2 if length > 1 else 0, occ, length))
+        if length > 1:   # ends that go on in all but one thing: the row, the occurrence, the program
+            which, row, occ = queries[-1]
+            step = queries[-1][1] - queries[-2][1]
+            for q in ((which, row + step + 2, occ), (which, row + step + 4, (occ + 1) % 8), (1 - which, row + step + 6, (occ + 1) % 8)):
+                queries.append(q)
+                want.append((q[1], 0, q[2], 1))
+        s.vl.vl_free_bases_multi(s.vl.make_mask_queries([(hm[w], hl[w], r, o) for w, r, o in queries]), masks, stream=S1)
+        got = [(int(x[2]), int(x[3]), int(x[4] & 0xFFFFFFFF), int(x[4] >> 32)) for x in seen.pop()]
+        assert got == want, (length, got, want)
