@@ -154,3 +154,18 @@ def test_batches_dealt_out_to_the_dies(n, n_block, alike):
     sizes (dealt out where to and fro leaves the dies equally busy)"""
     rng = np.random.default_rng(n)
     check([flow_program(k, n_block, 40 if alike else int(rng.integers(20, 400)), 8 if alike else 3 + k % 7) for k in range(n)], dense=n % 16 == 0)
+
+
+def test_many_entries_beside_the_sort_for_large_programs():
+    """a batch of more than half a million occurrences (entries put in order by workgroups of 512 threads) with programs of more
+    vregs than are counted in LDS, whose lists are sorted in launches of their own"""
+    large, small = flow_program(21, 4, 33000, 900), flow_program(22, 5, 60, 40)
+    mirs = [large, small] + [large] * 15
+    assert sum(-(-m.n_occ // 256) for m in mirs) // 4 > 512 and large.n_vreg > 32768
+    ans = {id(m): vlo.analyze(m, interference=False, threads=8) for m in (large, small)}
+    hm, hl, got, _ = gpu_analyze(mirs, dense=False)
+    try:
+        for m, g in zip(mirs, got):
+            assert_liveness_equal(m, ans[id(m)], g, m.name)
+    finally:
+        free(hm, hl)

@@ -44,12 +44,13 @@ def test_mixed_shapes(n_banks):
 
 @pytest.mark.parametrize("n_banks", [1, 2, 4, 8])
 def test_every_width_at_every_base(n_banks):
-    """counts in bytes: instructions of up to four operands of widths 1 to 32, bases that cover every bank, all equal operands among them"""
-    V = 64
+    """counts in bytes: instructions of up to four operands of widths 1 to 32, bases that cover every bank, all equal operands among
+    them, and four different ones of width 32, the most that a count has to hold (128 for one bank)"""
+    V = 128
     rng = np.random.default_rng(n_banks)
     width = (np.arange(V) % 32 + 1).astype(np.uint8)
     ins = [([v], []) for v in range(V)] + [([], [int(u) for u in rng.integers(0, V, rng.integers(0, 5))]) for _ in range(600)]
-    ins += [([], [31] * 4), ([], [31, 63, 31, 63]), ([], list(range(5)))]
+    ins += [([], [31] * 4), ([], [31, 63, 31, 63]), ([], list(range(5))), ([], [31, 63, 95, 127]), ([], [127, 31, 63])]
     m = Mir.build([ins], [[]], V, (512,), np.zeros(V, np.uint8), width, np.ones(V, np.uint8), None, name="widths")
     rows = rng.integers(0, 65536, (37, m.n_occ)).astype(np.uint16)
     rows[0], rows[1] = 0, 65535
@@ -81,7 +82,7 @@ def test_argument_errors():
 @pytest.mark.parametrize("n_ops", [0, 1, 3, 4, 5, 16, 64])
 @pytest.mark.parametrize("n_banks", [2, 4, 7])
 def test_operand_counts(n_ops, n_banks):
-    """instructions of n_ops operands among short ones, repeated operands, K around a slab of eight"""
+    """instructions of n_ops operands among short ones, repeated operands, K around slabs of four"""
     rng = np.random.default_rng(n_ops)
     from vlgen.mir import Mir
     V = 90
@@ -91,6 +92,6 @@ def test_operand_counts(n_ops, n_banks):
         n = n_ops if i % 3 == 0 else int(rng.integers(0, 5))
         instrs.append(([], [int(x) for x in rng.integers(0, V if n < 10 else 20, n)]))
     m = Mir.build([instrs], [[]], V, (512,), np.zeros(V, np.uint8), width, np.ones(V, np.uint8), None)
-    for K in (1, 7, 8, 9):
+    for K in (1, 3, 4, 5, 7, 8, 9):
         rows = rng.integers(0, 512, (K, m.n_occ)).astype(np.uint16)
         assert (gpu_scores(m, rows, n_banks) == vlo.bank_conflicts(m, rows, n_banks)).all(), K
