@@ -442,7 +442,7 @@ __global__ __launch_bounds__(1024) void k_group(MIRS, const Grid grid, const uin
 // goes to memory once; when the table would not fit, every entry issues its own atomics.
 //
 // (A launch that sorted each list in the registers of a lane and one that summarised the sorted
-// entries took 38 and 45 us where this takes 70, but this needs no sorted list and no cleared counters.)
+// entries took 38 and 45 us, this 70 then and 59 now, but this needs no sorted list and no cleared counters.)
 constexpr uint32_t kOrdStretch = 1024;
 constexpr uint32_t kOrdBack = 72;        // entries before the stretch that are put in order too: one more than an instruction has
 constexpr uint32_t kOrdMargin = 128;
@@ -2163,7 +2163,6 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     return ok;
   }();
   const bool hist_lds = lds_ok && (size_t)maxV * 4 <= 128 * 1024;
-  // (k_group clears block sets by 32-bit indices)
   auto blocks = [](uint32_t items, uint32_t per) { return std::max(1u, (items + per - 1) / per); };
   // a launch of so many blocks for every program
   struct Launch { dim3 dim; Grid grid; };
@@ -2171,12 +2170,14 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     // (threads in a row of the grid stay below 2^32)
     return batch->dealt && per < (1u << 18) ? Launch{dim3(8 * per, (n + 7) / 8), {n, 3}} : Launch{dim3(per, n), {n, 0}};
   };
+  // (k_group clears block sets by 32-bit indices)
   const bool small = hist_lds && maxO <= kGroupMaxOcc && (uint64_t)maxB * maxW < (1ull << 32) - 4;
   if (small) {
     uint32_t rounds = kGroupRounds;
     while (rounds > 2 && blocks_occ * kStretch / (rounds / 2 * kRound) + n <= kGroupFew && maxO / (rounds / 2 * kRound) < kGroupSlices) rounds /= 2;
     const Launch l = all_progs(blocks(maxO, rounds * kRound));
-    (rounds < kGroupRounds && maxO < (1u << 16) ? k_group<true> : k_group<false>)<<<l.dim, 1024, (size_t)maxV * 4, stream>>>(dm, dl, l.grid, rounds * kRound);
+    static_assert(kGroupSlices * (kGroupRounds / 2) * kRound <= 1u << 16, "more slices than usual: counts of 16 bits");
+    (rounds < kGroupRounds ? k_group<true> : k_group<false>)<<<l.dim, 1024, (size_t)maxV * 4, stream>>>(dm, dl, l.grid, rounds * kRound);
   } else {
     zero_async(a1, zero_bytes, stream);
     const dim3 slices((maxO + kSlice - 1) / kSlice, n);
