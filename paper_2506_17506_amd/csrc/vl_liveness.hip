@@ -53,9 +53,31 @@ __device__ inline uint32_t first_entry_at(const DevLive VL_CONSTANT &L, uint32_t
 // ---- 1. occurrences grouped by vreg -------------------------------------------------
 constexpr uint32_t kSlice = 8192;   // occurrences per workgroup in the counting kernels
 
+// A slice's counts where a word for every vreg would not fit LDS: a table with a place per vreg modulo its size, which
+// belongs to the first vreg of the slice that asks for it.  Others that fall on the place go to memory one by one, but the vregs
+// that are mentioned again and again nearly always get a place.  (What bounds these launches is atomics on those few counters,
+// of all workgroups at a time: with every occurrence counted and placed in memory, 8 programs of 112,000 instructions took 783 us an
+// analysis, and 824 once workgroups had their addresses without a trip to memory and met at the counters sooner; 318 this way.
+// One program of 50,000: 353 and 188.  Where no vreg is mentioned more than others, it costs what it saves: 8 programs of
+// 200,000 occurrences, both launches 139 and 140.)
+constexpr uint32_t kPlaces = 8192;
+struct CountTable {
+  uint32_t *const vreg, *const count;
+  __device__ explicit CountTable(uint32_t *lds) : vreg(lds), count(lds + kPlaces) {}
+  __device__ void clear(uint32_t tid) {
+    for (uint32_t x = tid; x < kPlaces; x += 1024) { vreg[x] = kNone; count[x] = 0; }
+  }
+  __device__ bool claim(uint32_t v) {
+    const uint32_t owner = atomicCAS(&vreg[v % kPlaces], kNone, v);
+    return owner == kNone || owner == v;
+  }
+  __device__ bool has(uint32_t v) const { return vreg[v % kPlaces] == v; }
+  __device__ uint32_t &of(uint32_t v) { return count[v % kPlaces]; }
+};
+
 // Occurrences per vreg.  A few vregs (base addresses, accumulators) are mentioned
-// thousands of times, so each workgroup first counts its slice in an LDS histogram and
-// then adds the non-zero bins to the global counters once.
+// thousands of times, so each workgroup first counts its slice in LDS, in a histogram over all vregs or in a
+// CountTable, and then adds the non-zero bins to the global counters once.
 template <bool kLds>
 __global__ __launch_bounds__(1024) void k_count(MIRS) {
   const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
@@ -65,7 +87,17 @@ __global__ __launch_bounds__(1024) void k_count(MIRS) {
   if (o0 >= m.O) return;
   const uint32_t o1 = min(m.O, o0 + kSlice);
   if (!kLds) {
-    for (uint32_t o = o0 + threadIdx.x; o < o1; o += 1024) atomicAdd(&L.vcnt[m.occ_vreg[o]], 1u);
+    CountTable table(sm);
+    table.clear(threadIdx.x);
+    __syncthreads();
+    for (uint32_t o = o0 + threadIdx.x; o < o1; o += 1024) {
+      const uint32_t v = m.occ_vreg[o];
+      if (table.claim(v)) atomicAdd(&table.of(v), 1u);
+      else atomicAdd(&L.vcnt[v], 1u);
+    }
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < kPlaces; x += 1024)
+      if (table.count[x]) atomicAdd(&L.vcnt[table.vreg[x]], table.count[x]);
     return;
   }
   for (uint32_t v = threadIdx.x; v < m.V; v += 1024) sm[v] = 0;
@@ -179,7 +211,7 @@ __global__ __launch_bounds__(1024) void k_scan(MIRS) {
 
 // Places each occurrence into its vreg's range (order inside a range is fixed later).
 // Same privatisation: the slice reserves a sub-range per vreg with one global atomic,
-// then ranks its own occurrences in LDS.
+// then ranks its own occurrences in LDS; those without a place in the table reserve one by one.
 template <bool kLds>
 __global__ __launch_bounds__(1024) void k_place(MIRS) {
   const DevProg VL_CONSTANT &m = as_constant(mirs)[blockIdx.y];
@@ -189,9 +221,22 @@ __global__ __launch_bounds__(1024) void k_place(MIRS) {
   if (o0 >= m.O) return;
   const uint32_t o1 = min(m.O, o0 + kSlice);
   if (!kLds) {
+    CountTable table(sm);
+    table.clear(threadIdx.x);
+    __syncthreads();
     for (uint32_t o = o0 + threadIdx.x; o < o1; o += 1024) {
       const uint32_t v = m.occ_vreg[o];
-      L.vocc_tmp[L.vcnt[v] + atomicAdd(&L.vcur[v], 1u)] = o;
+      if (table.claim(v)) atomicAdd(&table.of(v), 1u);
+    }
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < kPlaces; x += 1024) {
+      const uint32_t c = table.count[x], v = table.vreg[x];
+      if (c) table.count[x] = L.vcnt[v] + atomicAdd(&L.vcur[v], c);
+    }
+    __syncthreads();
+    for (uint32_t o = o0 + threadIdx.x; o < o1; o += 1024) {
+      const uint32_t v = m.occ_vreg[o];
+      L.vocc_tmp[table.has(v) ? atomicAdd(&table.of(v), 1u) : L.vcnt[v] + atomicAdd(&L.vcur[v], 1u)] = o;
     }
     return;
   }
@@ -2182,10 +2227,10 @@ extern "C" int32_t vl_liveness_multi(const vl_mir *const *mirs, uint32_t n, uint
     zero_async(a1, zero_bytes, stream);
     const dim3 slices((maxO + kSlice - 1) / kSlice, n);
     if (hist_lds) k_count<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
-    else k_count<false><<<slices, 1024, 0, stream>>>(dm, dl);
+    else k_count<false><<<slices, 1024, 2 * kPlaces * 4, stream>>>(dm, dl);
     k_scan<kScanVreg><<<n, 1024, 0, stream>>>(dm, dl);
     if (hist_lds) k_place<true><<<slices, 1024, (size_t)maxV * 4, stream>>>(dm, dl);
-    else k_place<false><<<slices, 1024, 0, stream>>>(dm, dl);
+    else k_place<false><<<slices, 1024, 2 * kPlaces * 4, stream>>>(dm, dl);
     k_sort<<<dim3(kLongBlocks + (maxV + 255) / 256, n), 256, 0, stream>>>(dm, dl);
   }
   {

@@ -71,7 +71,23 @@ def test_slices_of_few_programs(n_occ, V, heavy, share):
 
 @pytest.mark.parametrize("n_occ,V", [(140000, 200), (60000, 33000)])
 def test_large_programs(n_occ, V):
-    m = program(n_occ, n_occ, V, 3, 0.3)
+    check_large_program(program(n_occ, n_occ, V, 3, 0.3))
+
+
+@pytest.mark.parametrize("n_occ,V,share", [(40000, 32769, 0.5), (70000, 45000, 0.9), (150000, 100000, 1.0)])
+def test_values_that_share_a_place(n_occ, V, share):
+    """more vregs than LDS has counters for: the values mentioned again and again fall on one place of the slices' tables of
+    8,192, and only one of them has it"""
+    m = program(n_occ, n_occ, V, 4, share)
+    name = np.arange(V, dtype=np.uint32)
+    for k in range(4):
+        name[[k, 7 + 8192 * k]] = name[[7 + 8192 * k, k]]
+    m.occ_vreg = name[m.occ_vreg]
+    check_large_program(m)
+
+
+def check_large_program(m):
+    V = m.n_vreg
     an = vlo.analyze(m, interference=False, threads=8) if V < 1000 else None
     hm, hl, got, _ = gpu_analyze([m], dense=V < 1000)
     try:
