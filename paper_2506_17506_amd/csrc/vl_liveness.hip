@@ -31,7 +31,8 @@ namespace {
 
 // Which program and which of its blocks a workgroup of a two-dimensional launch has.  Consecutive
 // workgroups go to the eight dies in turn, each with an L2 of its own; where a batch deals its programs out
-// to the dies (`deal`), program p stays on die p % 8 through every launch, so that what its workgroups
+// to the dies (`deal`), program p stays on die p % 8 through the launches from k_order on and k_group (not the scans, nor
+// those that only very large programs have), so that what its workgroups
 // gather and scatter meets in one L2: row y of the grid then holds programs 8 y to 8 y + 7 side by side.
 // (256 programs of 1,000-20,000 instructions, us per launch, spread over all dies and dealt out: k_group 50 and 31,
 // k_events 98 and 78, k_stage_count 35 and 29, k_stage_finish 30 and 21.)
